@@ -817,11 +817,13 @@ __global__ __launch_bounds__(256) void assign_finalize_kernel(int P, TableDesc t
     }
 }
 
+// For callers of the single steps; a tree call clears the counters of all its heights at its start.
+void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height) { assign_reset_kernel<<<1, 1, 0, s>>>(w, height); }
+
 void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const HeightDesc &h,
                    int height, double thr, double band, int rule)
 {
     const int64_t cols = (int64_t)w.G * h.total_r_cap;
-    assign_reset_kernel<<<1, 1, 0, s>>>(w, height);
     if (cols > 0) {
         // 1: the listed values are upper bounds only (prefix screen); 2: cosines within a per-pair radius (fp8 screen);
         // 3: both screens: upper bounds that assign_q8_fill_kernel turns into the values of 2

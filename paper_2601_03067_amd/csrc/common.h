@@ -90,11 +90,19 @@ struct WorkDesc {
     int32_t *n_active;   // [max_heights]
     int32_t *refine;     // [G * r_stride][2] columns that need the fp64 re-check: (g * r_stride + c, node)
     int32_t *n_refine;   // [max_heights]
+    int32_t *n_pairs_all;// [max_heights] pairs that early rejection left open (early.hip)
+    int32_t *early_nk_mem;   // [G]
     int32_t *counters;   // [G][8]: 0 fused, 1 near-threshold, 2 refined, 3 candidate overflow, 4 invalid ids, 5 entries of shared blocks
     const uint8_t *group_enable;   // [G] or null: groups with 0 are skipped by the similarity step (nothing fuses)
     int32_t *leaf_src;   // [n] position in a set_ids row -> logical entry the leaf step fills it from, -1 = none
     float *rem_k;        // [G][P] prefix screen: share of each key block's norm that lies beyond the prefix, rounded up
     int32_t screen_prefix;   // elements of every block the similarity screen multiplies; 0 = the whole block
+    // early rejection in the full-length screen (early.hip); all null unless a tree call uses it, when rem_k is set as well
+    const int32_t *early_nk; // [G] 64-byte slices after which a tile is tested
+    int4 *pairs;             // [pair_cap] pairs that passed the test: (column, row, physical ids of left and right block) ...
+    float *pair_head;        // [pair_cap] ... and their product so far
+    int32_t *n_pairs;        // counter of the current height
+    int32_t pair_cap;
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
     int4 *dyn_items;     // [G][item_cap of the height] node, first column, first row, rows
     int32_t *dyn_base;   // [G][dyn_stride] first item of every node, and the total
@@ -150,13 +158,21 @@ template <typename K> static int resident_workgroups(K kernel, int threads = 256
 }
 
 // launchers, one per source file
-void launch_block_norms(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, float *rem = nullptr, int prefix = 0,
-                        const Q8Desc *q8 = nullptr);
+void launch_block_norms(hipStream_t s, const PoolDesc &pool, const TableDesc &tab);
+// the same norms and table for a tree call, with everything its heights expect cleared, the leaf sets and the checks of
+// the table, in the order clear -> entries -> norms -> table (w.rem_k, w.screen_prefix, w.early_nk, w.q8 are honoured)
+void launch_tree_entries(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, const int32_t *slot_init,
+                         int n_heights);
+void launch_tree_norms(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab);
 // fp8 screen: the direction of every group that its key blocks are centred on (no-op unless one is asked for)
 void launch_centre_direction(hipStream_t s, const PoolDesc &pool, const WorkDesc &w);
 void launch_leaf_sets(hipStream_t s, const WorkDesc &w, const TableDesc &tab, int P, const int32_t *slot_init, const double *norm_k);
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
                        float *dense_s);
+// early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
+void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
+void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
+void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height);
 void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const HeightDesc &h,
                    int height, double thr, double band, int rule);
 void launch_merge(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height);
@@ -395,6 +411,48 @@ __device__ __forceinline__ float quantise_error(double se, const Q8Block &p, dou
     if (p.wide)
         return nrm > 0.0 ? 2.0f : 0.0f;
     return nrm > 0.0 ? __double2float_ru(sqrt(se) * p.scale * (1.0 + 1e-5) + 3e-6) : 0.0f;
+}
+
+// Early rejection: this lane's part of <a, b> over the 16-byte chunks [c0, c1) of two blocks, `lanes` lanes sharing a pair.
+// Four chunks of each block are on their way at a time.
+template <typename T>
+__device__ __forceinline__ float product_from(const T *__restrict__ a, const T *__restrict__ b, int c0, int c1, int lane, int lanes)
+{
+    constexpr int PER = Elem<T>::PER16;
+    const uint4 *pa = reinterpret_cast<const uint4 *>(a), *pb = reinterpret_cast<const uint4 *>(b);
+    float dot = 0.0f;
+    for (int c = c0 + lane; c < c1; c += 4 * lanes) {
+        uint4 xa[4], xb[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ck = min(c + k * lanes, c1 - 1);
+            xa[k] = pa[ck];
+            xb[k] = pb[ck];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float u[PER], v[PER];
+            widen_f32<T>(xa[k], u);
+            widen_f32<T>(xb[k], v);
+            float part = 0.0f;
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                part = fmaf(u[e], v[e], part);
+            dot += c + k * lanes < c1 ? part : 0.0f;
+        }
+    }
+    return dot;
+}
+
+// Append (row, cosine) to the candidate list of a column; the count is exact even when the list is full.
+__device__ __forceinline__ void emit_candidate(int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand_idx,
+                                               float *__restrict__ cand_val, int64_t column, int cap, int row, float s)
+{
+    const int slot = atomicAdd(&cand_cnt[column], 1);
+    if (slot < cap) {
+        cand_idx[column * cap + slot] = row;
+        cand_val[column * cap + slot] = s;
+    }
 }
 
 // Nearest-even rounding of a finite double straight to bfloat16 bits (no intermediate binary32 rounding).

@@ -1,0 +1,195 @@
+// Early rejection in the full-length similarity screen of a tree call (Algorithm 1: sim <- k_l k_r^T; only the entries
+// above the threshold matter).
+//
+// After the product has run over the first p elements of two key blocks, cos(a, b) <= <a[0:p], b[0:p]> / (|a| |b|) +
+// tail(a) tail(b) with tail(x) = |x[p:]| / |x| (Cauchy-Schwarz).  The similarity kernel tests every tile of the product
+// once, after the p of its group: a tile in which no pair's bound reaches the candidate floor is done there; the few pairs
+// of a tile that do reach it are written to a list, from which finish_pairs_kernel completes their products one by one;
+// and a tile with too many of them simply goes on to its full length.  Either way a candidate list receives exactly the
+// pairs whose whole screened cosine clears the floor, so nothing downstream knows the difference, whatever the data; what
+// depends on the data is how much of the product is spared.
+//
+// p is chosen per group and per call from a sample of the group's own blocks (sample_bounds_kernel): unrelated blocks of
+// white-noise-like keys at thr 0.9 are ruled out after a sixth of their length, keys that share a direction need more, and
+// where even three quarters of a block would not do, the group's product runs at full length (its tests cost nothing then).
+#include <algorithm>
+
+#include "common.h"
+
+namespace kvfuse {
+
+constexpr int kSamples = 64;      // sampled pairs per group: one per lane of a wavefront
+constexpr int kSteps = 32;        // lengths considered: (k / 32) of the block's slices
+static_assert(kSteps * kSamples * sizeof(float) <= 256 * 2 * sizeof(int4), "the bounds of a group fit its share of the merge work list");
+
+// Fixed pseudo-random logical entries: the sample depends on the sizes alone.
+__device__ __forceinline__ uint32_t mix32(uint32_t x)
+{
+    x ^= x >> 16;
+    x *= 0x7feb352du;
+    x ^= x >> 15;
+    x *= 0x846ca68bu;
+    return x ^ (x >> 16);
+}
+
+// One wavefront per (group, sampled pair): the pair's bound after every length considered, in binary32 (the result only
+// steers how much work the product does).  Reads half a megabyte per group, HBM-bound for many groups (134 MB for 256 groups
+// of 4 KiB blocks, 33 us) and a few microseconds for few.  (One workgroup per group, the first form of this, took 95 us for
+// 256 groups and 174 us for 16 groups of 8 KiB blocks.)
+template <typename T>
+__global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict__ kpool, const int32_t *__restrict__ bt, int G, int P, int n,
+                                                            int r, float *__restrict__ bounds)
+{
+    constexpr int PER = Elem<T>::PER16, BATCH = 4;
+    __shared__ float seg[4][3][kSteps];               // <a, b>, <a, a>, <b, b> of every segment
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int id = blockIdx.x * 4 + wave, g = id / kSamples, s = id % kSamples;      // (the grid is exactly G * kSamples / 4)
+    const int chunks = r / PER, nk = chunks / 4;
+    const int per_seg = chunks / kSteps;
+    const int lanes_per_seg = chunks % (64 * kSteps) == 0 || (chunks % kSteps == 0 && (per_seg & (per_seg - 1)) == 0) ? min(per_seg, 64) : 1;
+    for (int i = lane; i < 3 * kSteps; i += 64)
+        (&seg[wave][0][0])[i] = 0.0f;
+    __builtin_amdgcn_wave_barrier();
+    const int x = (int)(((uint64_t)mix32(2u * s + 1u) * (uint32_t)n) >> 32);
+    const int y = (int)(((uint64_t)mix32(2u * s + 2u) * (uint32_t)(n - 1)) >> 32);
+    const int pa = min(max(bt[(int64_t)g * n + x], 0), P - 1);
+    const int pb = min(max(bt[(int64_t)g * n + (x + 1 + y) % n], 0), P - 1);
+    const uint4 *a = reinterpret_cast<const uint4 *>(kpool + ((int64_t)g * P + pa) * r);
+    const uint4 *b = reinterpret_cast<const uint4 *>(kpool + ((int64_t)g * P + pb) * r);
+    for (int c0 = lane; c0 < chunks; c0 += 64 * BATCH) {
+        uint4 ra[BATCH], rb[BATCH];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int c = min(c0 + 64 * q, chunks - 1);
+            ra[q] = a[c];
+            rb[q] = b[c];
+        }
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int c = c0 + 64 * q;
+            float u[PER], v[PER], ab = 0.0f, aa = 0.0f, bb = 0.0f;
+            widen_f32<T>(ra[q], u);
+            widen_f32<T>(rb[q], v);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                ab = fmaf(u[e], v[e], ab);
+                aa = fmaf(u[e], u[e], aa);
+                bb = fmaf(v[e], v[e], bb);
+            }
+            // where a segment is a power of two of neighbouring lanes (the usual block sizes) these are summed first: eight
+            // lanes adding to one LDS word took twice as long as everything else here
+            for (int off = 1; off < lanes_per_seg; off <<= 1) {
+                ab += __shfl_xor(ab, off, 64);
+                aa += __shfl_xor(aa, off, 64);
+                bb += __shfl_xor(bb, off, 64);
+            }
+            if (c < chunks && (lane & (lanes_per_seg - 1)) == 0) {
+                const int k = (kSteps * ((c >> 2) + 1) - 1) / nk;       // segment k: slices [k nk / 32, (k + 1) nk / 32)
+                atomicAdd(&seg[wave][0][k], ab);
+                atomicAdd(&seg[wave][1][k], aa);
+                atomicAdd(&seg[wave][2][k], bb);
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int len = lane & (kSteps - 1);              // lane = length of `len` segments
+    float head = 0.0f, ha = 0.0f, hb = 0.0f, A = 0.0f, B = 0.0f;
+#pragma unroll 4
+    for (int k = 0; k < kSteps; ++k) {
+        const float sa = seg[wave][1][k], sb = seg[wave][2][k];
+        head += k < len ? seg[wave][0][k] : 0.0f;
+        ha += k < len ? 0.0f : sa;                    // (tails)
+        hb += k < len ? 0.0f : sb;
+        A += sa;
+        B += sb;
+    }
+    float bound = (head + sqrtf(ha * hb)) / sqrtf(A * B);
+    if (A == 0.0f || B == 0.0f)
+        bound = 0.0f;                                 // a zero block has cosine 0 with everything
+    if (!(bound < 1e30f))
+        bound = 1e30f;                                // blocks beyond binary32's range: no early test
+    if (lane < kSteps)
+        bounds[((int64_t)g * kSteps + len) * kSamples + s] = bound;
+}
+
+// One workgroup per group: for every length the bounds of all pairs are ranked; with their median m and the 84th
+// percentile q, m + 4 (q - m) estimates what one unrelated pair in 30 000 reaches, about two of a 256 x 256 tile.  The
+// shortest length for which that stays below the candidate floor is taken.  Ranks instead of moments because a few per cent
+// of the pairs may be related ones.
+__global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
+                                                            int32_t *__restrict__ early_nk)
+{
+    __shared__ int enough[kSteps];
+    const int g = blockIdx.x, lane = threadIdx.x & 63;
+    for (int len = threadIdx.x >> 6; len < kSteps; len += 16) {
+        const float bound = bounds[((int64_t)g * kSteps + len) * kSamples + lane];
+        int rank = 0;
+#pragma unroll 8
+        for (int k = 0; k < kSamples; ++k) {
+            const float other = __shfl(bound, k, 64);
+            rank += other < bound || (other == bound && k < lane);
+        }
+        const float med = __shfl(bound, __ffsll((long long)__ballot(rank == kSamples / 2)) - 1, 64);
+        const float q84 = __shfl(bound, __ffsll((long long)__ballot(rank == 54)) - 1, 64);
+        const int slices = (nk * len) / kSteps;
+        if (lane == 0)
+            enough[len] = med + 4.0f * (q84 - med) < thr_floor - 1e-3f && slices >= 2 && 4 * slices <= 3 * nk;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int best = nk;
+        for (int len = kSteps - 1; len >= 1; --len)
+            if (enough[len])
+                best = (nk * len) / kSteps;
+        early_nk[g] = best;
+    }
+}
+
+void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor)
+{
+    float *bounds = reinterpret_cast<float *>(w.active);      // (free until the first assignment step; l_stride >= 256 is room enough)
+    const unsigned grid = (unsigned)pool.G * kSamples / 4;
+    if (pool.dtype == KVFUSE_BF16)
+        sample_bounds_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, bounds);
+    else
+        sample_bounds_kernel<float><<<grid, 256, 0, s>>>((const float *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, bounds);
+    choose_early_kernel<<<pool.G, 1024, 0, s>>>(bounds, pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64, thr_floor, w.early_nk_mem);
+}
+
+// The pairs that the tests left open, 16 lanes per pair: the rest of the product, and the pair's entry in its column's
+// candidate list if the whole cosine clears the floor.  HBM-bound: what is left of two blocks per pair (their heads
+// were read by the product); a sixteenth of a wavefront's lanes each hold 16 bytes of one row, so a load instruction
+// covers 256 consecutive bytes of each of four rows.
+template <typename T>
+__global__ __launch_bounds__(256) void finish_pairs_kernel(PoolDesc pool, WorkDesc w, float thr_floor)
+{
+    const int n = min(w.n_pairs[0], w.pair_cap);
+    const int sub = threadIdx.x & 15;
+    for (int q = (blockIdx.x * 256 + threadIdx.x) >> 4; q < n; q += gridDim.x * 16) {
+        const int4 rec = w.pairs[q];
+        const int g = rec.x / w.r_stride;
+        const int64_t pa = (int64_t)g * pool.P + rec.z, pb = (int64_t)g * pool.P + rec.w;
+        const float ia = pool.inv_norm_k[pa], ib = pool.inv_norm_k[pb];
+        float dot = product_from<T>((const T *)pool.k + pa * pool.r, (const T *)pool.k + pb * pool.r, 4 * w.early_nk[g],
+                                    pool.r / Elem<T>::PER16, sub, 16);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1)
+            dot += __shfl_xor(dot, off, 64);
+        const float cs = (w.pair_head[q] + dot) * ia * ib;
+        if (sub == 0 && cs > thr_floor)
+            emit_candidate(w.cand_cnt, w.cand_idx, w.cand_val, rec.x, w.cand_cap, rec.y, cs);
+    }
+}
+
+void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor)
+{
+    const unsigned grid = (unsigned)std::min<int64_t>(((int64_t)w.pair_cap + 15) / 16, 256 * 8);
+    if (grid == 0)
+        return;
+    if (pool.dtype == KVFUSE_BF16)
+        finish_pairs_kernel<bf16_t><<<grid, 256, 0, s>>>(pool, w, thr_floor);
+    else
+        finish_pairs_kernel<float><<<grid, 256, 0, s>>>(pool, w, thr_floor);
+}
+
+}  // namespace kvfuse

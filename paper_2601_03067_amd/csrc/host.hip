@@ -37,6 +37,12 @@ struct HostHeight {
     HeightDesc dev;
 };
 
+// Early rejection costs a launch that samples every group (about 30 us) and one small launch per height, and saves up to
+// three quarters of the product: it is used when the product alone is some 60 us (binary32 products run at a sixteenth of
+// the rate).  Rows shorter than 2 KiB have too few 64-byte slices to stop early in.
+constexpr double kEarlyMinFlops = 5e10;
+constexpr int kEarlyMinRowBytes = 2048;
+
 struct Plan {
     Ctx *ctx = nullptr;
     PoolDesc pool;
@@ -49,6 +55,17 @@ struct Plan {
     std::vector<uint8_t> group_enable_host;   // copy of the group mask for the statistics; empty = all groups
     int assign_rule = KVFUSE_RULE_ARGMAX;
     float *q8_dir_mem = nullptr;    // fp8 screen with centring asked for: the caller's [G][r] floats for the directions
+
+    // Early rejection in a tree call (early.hip), by a rule on sizes: see kEarlyMinFlops.
+    bool early_pays(float thr_floor) const
+    {
+        double flops = 0.0;
+        for (const HostHeight &h : heights)
+            flops += 2.0 * (double)h.dev.total_s * pool.r * work.G;
+        const int row_bytes = pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4);
+        return !work.q8.k && work.screen_prefix == 0 && row_bytes >= kEarlyMinRowBytes && work.n >= 64 && work.l_stride >= 256 && thr_floor > 0.25f &&
+               flops >= (pool.dtype == KVFUSE_BF16 ? kEarlyMinFlops : kEarlyMinFlops / 16);
+    }
 
     // The copies are centred only where that pays and fits: not together with the prefix screen (a block's share of the
     // common direction differs between prefix and tail) and not for blocks whose direction kernel would need more than
@@ -252,6 +269,13 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.n_active = cv.take<int32_t>(kMaxHeights);
     w.refine = cv.take<int32_t>(2 * R);
     w.n_refine = cv.take<int32_t>(kMaxHeights);
+    w.n_pairs_all = cv.take<int32_t>(kMaxHeights);
+    w.early_nk_mem = cv.take<int32_t>((size_t)G);
+    w.early_nk = nullptr;
+    w.pairs = nullptr;
+    w.pair_head = nullptr;
+    w.n_pairs = nullptr;
+    w.pair_cap = 0;
     w.counters = cv.take<int32_t>((size_t)G * 8);
     w.group_enable = nullptr;
     w.leaf_src = cv.take<int32_t>((size_t)std::max(n, 1));
@@ -556,6 +580,7 @@ int kvfuse_assign(kvfuse_ctx *ctx, kvfuse_plan *plan, int32_t height, double thr
     const int rc = check_step(ctx, plan, height, thr, band, true);
     if (rc)
         return rc;
+    launch_assign_reset(ctx->c.stream, plan->p.work, height);
     launch_assign(ctx->c.stream, plan->p.pool, plan->p.tab, plan->p.work, plan->p.heights[height].dev, height, thr, band,
                   plan->p.assign_rule);
     KVF_HIP(&ctx->c, hipGetLastError());
@@ -622,19 +647,34 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     } while (0)
 
     const float floor_f = std::nextafterf((float)(thr - 2.0 * band), -INFINITY);
+    WorkDesc w = p.work;
+    const bool early = p.early_pays(floor_f);
+    if (early) {
+        // Until the rewrite counts references anew, tab.refcount holds the tail shares; the merge work list, which the
+        // assignment step fills, holds the open pairs of the similarity step before it.
+        w.rem_k = reinterpret_cast<float *>(p.tab.refcount);
+        w.early_nk = w.early_nk_mem;
+        w.pair_cap = (int32_t)((size_t)w.G * w.l_stride * 2 * sizeof(int4) / (sizeof(int4) + sizeof(float)));
+        w.pairs = w.active;
+        w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
+    }
     KVF_TRY(mark());
-    launch_centre_direction(c->stream, p.pool, p.work);                      // no-op unless the fp8 copies are centred
-    launch_block_norms(c->stream, p.pool, p.tab, p.work.screen_prefix > 0 ? p.work.rem_k : nullptr, p.work.screen_prefix,
-                       p.work.q8.k ? &p.work.q8 : nullptr);
-    launch_leaf_sets(c->stream, p.work, p.tab, p.pool.P, p.slot_init, p.pool.norm_k);
+    launch_centre_direction(c->stream, p.pool, w);                      // no-op unless the fp8 copies are centred
+    launch_tree_entries(c->stream, p.pool, w, p.tab, p.slot_init, nh);
+    if (early)
+        launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
+    launch_tree_norms(c->stream, p.pool, w, p.tab);
     KVF_TRY(mark());
     for (int hgt = 0; hgt < nh; ++hgt) {
         const HeightDesc &d = p.heights[hgt].dev;
-        launch_similarity(c->stream, p.pool, p.work, d, floor_f, nullptr);
+        w.n_pairs = w.n_pairs_all + hgt;
+        launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr);
+        if (early)
+            launch_finish_pairs(c->stream, p.pool, w, floor_f);
         KVF_TRY(mark());
-        launch_assign(c->stream, p.pool, p.tab, p.work, d, hgt, thr, band, p.assign_rule);
+        launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule);
         KVF_TRY(mark());
-        launch_merge(c->stream, p.pool, p.work, d, hgt);
+        launch_merge(c->stream, p.pool, w, d, hgt);
         KVF_TRY(mark());
     }
     launch_rewrite(c->stream, p.pool, p.tab, free_list, n_free, n_phys);
@@ -664,7 +704,6 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     cleanup();
     evs.clear();
     // counters and set sizes (small) come back to the host; the similarity flop count uses the actual set sizes
-    const WorkDesc &w = p.work;
     std::vector<int32_t> counters((size_t)w.G * 8), cnt((size_t)w.G * w.n_slots);
     KVF_TRY(hipMemcpy(counters.data(), w.counters, counters.size() * 4, hipMemcpyDeviceToHost));
     KVF_TRY(hipMemcpy(cnt.data(), w.set_cnt, cnt.size() * 4, hipMemcpyDeviceToHost));

@@ -183,8 +183,8 @@ __global__ __launch_bounds__(256, 3) void merge_group_kernel(PoolDesc pool, Work
         const double il = len == 0.0 ? 0.0 : 1.0 / len;
         uint4 *dst = reinterpret_cast<uint4 *>(pool_g + (int64_t)a * pool.r);
         // ss2t: the squares of the new key block beyond the prefix of the prefix screen, for its tail share
-        const bool want_tail = w.rem_k != nullptr && w.screen_prefix > 0;     // uniform over the launch
-        const int prefix_chunks = w.screen_prefix / PER;
+        const bool want_tail = w.rem_k != nullptr && (w.early_nk || w.screen_prefix > 0);     // uniform over the launch
+        const int prefix_chunks = w.early_nk ? 4 * w.early_nk[g] : w.screen_prefix / PER;
         double ss2 = 0.0, ss2t = 0.0;
         uint4 outp[Q8 ? CPT : 1];
 #pragma unroll
@@ -344,8 +344,8 @@ __global__ __launch_bounds__(256) void merge_kernel(PoolDesc pool, WorkDesc w, H
                     ss = fma(acc[c][e], acc[c][e], ss);
             const double len = sqrt(block_sum_256(ss, red));
             uint4 *dst = reinterpret_cast<uint4 *>(pool_g + (int64_t)a * pool.r);
-            const bool want_tail = w.rem_k != nullptr && w.screen_prefix > 0 && kv == 0;     // uniform over the workgroup
-            const int prefix_chunks = w.screen_prefix / PER;
+            const bool want_tail = w.rem_k != nullptr && (w.early_nk || w.screen_prefix > 0) && kv == 0;     // uniform over the workgroup
+            const int prefix_chunks = w.early_nk ? 4 * w.early_nk[g] : w.screen_prefix / PER;
             double ss2 = 0.0, ss2t = 0.0;
 #pragma unroll
             for (int c = 0; c < MAXC; ++c) {

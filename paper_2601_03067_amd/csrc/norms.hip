@@ -49,7 +49,8 @@ template <typename T, int KEEP>
 __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ kpool, const T *__restrict__ vpool,
                                                           int64_t n_blocks, int r, double *__restrict__ norm_k,
                                                           double *__restrict__ norm_v, float *__restrict__ inv_norm_k,
-                                                          float *__restrict__ rem, int prefix_chunks, Q8Desc q8, int P)
+                                                          float *__restrict__ rem, int prefix_chunks,
+                                                          const int32_t *__restrict__ early_nk, Q8Desc q8, int P)
 {
     constexpr int PER = Elem<T>::PER16;
     const int lane = threadIdx.x & 63;
@@ -60,9 +61,11 @@ __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ 
     const int64_t b = is_v ? w - n_blocks : w;
     const uint4 *src = reinterpret_cast<const uint4 *>((is_v ? vpool : kpool) + b * (int64_t)r);
     const int chunks = r / PER;
-    // st: the squares beyond the prefix of the prefix screen, summed on their own (rem = |tail| / |block|, see
-    // prefix_tails_kernel); the norm's own sum keeps its order
+    // st: the squares beyond the prefix of the prefix screen or of early rejection, summed on their own (rem = |tail| /
+    // |block|, see prefix_tails_kernel)
     const bool want_tail = rem != nullptr && !is_v;
+    if (want_tail && early_nk)
+        prefix_chunks = 4 * early_nk[b / P];       // early rejection: one prefix per group, in 64-byte slices
     double ss = 0.0, st = 0.0, sm = 0.0;
     const float *dir_g = (KEEP > 0 && !is_v && q8.dir) ? q8.dir + (b / P) * (int64_t)r : nullptr;
     uint4 keep[KEEP > 0 ? KEEP : 1];
@@ -89,23 +92,32 @@ __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ 
             }
         }
     } else {
-        for (int c = lane; c < chunks; c += 64) {
-            const uint4 raw = src[c];
-            double x[PER];
-            Elem<T>::widen(raw, x);
-#pragma unroll
-            for (int i = 0; i < PER; ++i)
-                ss = fma(x[i], x[i], ss);
-            if (want_tail && c >= prefix_chunks) {
+        if (!want_tail) {
+            for (int c = lane; c < chunks; c += 64) {
+                double x[PER];
+                Elem<T>::widen(src[c], x);
 #pragma unroll
                 for (int i = 0; i < PER; ++i)
-                    st = fma(x[i], x[i], st);
+                    ss = fma(x[i], x[i], ss);
+            }
+        } else {                       // ss: the squares of the prefix only; the tail's are added below
+            for (int c = lane; c < chunks; c += 64) {
+                double x[PER], part = 0.0;
+                Elem<T>::widen(src[c], x);
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    part = fma(x[i], x[i], part);
+                ss += c < prefix_chunks ? part : 0.0;
+                st += c < prefix_chunks ? 0.0 : part;
             }
         }
     }
     ss = wave_sum(ss);
-    if (want_tail)
+    if (want_tail) {
         st = wave_sum(st);
+        if (KEEP == 0)
+            ss += st;
+    }
     const double nrm = sqrt(ss);
     if (lane == 0) {
         if (is_v) {
@@ -175,35 +187,124 @@ __global__ void table_init_kernel(TableDesc tab, int G, int P, const double *__r
     atomicAdd(&tab.refcount[(int64_t)g * P + p], 1);
 }
 
-void launch_block_norms(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, float *rem, int prefix, const Q8Desc *q8p)
+static void launch_norms_kernel(hipStream_t s, const PoolDesc &pool, float *rem, int prefix, const int32_t *early_nk, const Q8Desc &q8)
 {
-    Q8Desc q8 = {};
-    if (q8p)
-        q8 = *q8p;
     const int pchunks = prefix / (pool.dtype == KVFUSE_BF16 ? 8 : 4);
     const int64_t nb = (int64_t)pool.G * pool.P;
     const unsigned grid = (unsigned)((2 * nb + 3) / 4);
-    if (nb > 0) {
-        const int chunks = pool.r / (pool.dtype == KVFUSE_BF16 ? 8 : 4);
-        const int keep = !q8.k ? 0 : (chunks <= 256 ? 4 : (chunks <= 512 ? 8 : 0));
+    if (nb <= 0)
+        return;
+    const int chunks = pool.r / (pool.dtype == KVFUSE_BF16 ? 8 : 4);
+    const int keep = !q8.k ? 0 : (chunks <= 256 ? 4 : (chunks <= 512 ? 8 : 0));
 #define KVF_NORMS(T, KEEP)                                                                                              \
     block_norms_kernel<T, KEEP><<<grid, 256, 0, s>>>((const T *)pool.k, (const T *)pool.v, nb, pool.r, pool.norm_k, pool.norm_v, \
-                                                     pool.inv_norm_k, rem, pchunks, q8, pool.P)
-        if (pool.dtype == KVFUSE_BF16) {
-            if (keep == 4) KVF_NORMS(bf16_t, 4);
-            else if (keep == 8) KVF_NORMS(bf16_t, 8);
-            else KVF_NORMS(bf16_t, 0);
-        } else {
-            if (keep == 4) KVF_NORMS(float, 4);
-            else if (keep == 8) KVF_NORMS(float, 8);
-            else KVF_NORMS(float, 0);
-        }
-#undef KVF_NORMS
-        table_clear_kernel<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(tab.refcount, tab.remap, nb);
+                                                     pool.inv_norm_k, rem, pchunks, early_nk, q8, pool.P)
+    if (pool.dtype == KVFUSE_BF16) {
+        if (keep == 4) KVF_NORMS(bf16_t, 4);
+        else if (keep == 8) KVF_NORMS(bf16_t, 8);
+        else KVF_NORMS(bf16_t, 0);
+    } else {
+        if (keep == 4) KVF_NORMS(float, 4);
+        else if (keep == 8) KVF_NORMS(float, 8);
+        else KVF_NORMS(float, 0);
     }
+#undef KVF_NORMS
+}
+
+void launch_block_norms(hipStream_t s, const PoolDesc &pool, const TableDesc &tab)
+{
+    const int64_t nb = (int64_t)pool.G * pool.P;
+    launch_norms_kernel(s, pool, nullptr, 0, nullptr, Q8Desc{});
+    if (nb > 0)
+        table_clear_kernel<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(tab.refcount, tab.remap, nb);
     const int64_t ne = (int64_t)pool.G * tab.n;
     if (ne > 0)
         table_init_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v);
+}
+
+// ---- the start of a tree call ----------------------------------------------------------------------------------
+//
+// The same work in an order that leaves tab.refcount free while the tree runs (the table rewrite at its end counts
+// anew): references are counted and the checks that need the counts are made before the norm pass, which then writes the
+// blocks' tail shares there when early rejection is on.  Four launches instead of the six of the single steps, and the
+// counters of all heights are cleared here, so that the assignment steps of a tree need no launch for that.
+__global__ __launch_bounds__(256) void tree_clear_kernel(TableDesc tab, WorkDesc w, int64_t n_blocks, const int32_t *__restrict__ slot_init,
+                                                         int n_heights)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n_blocks) {
+        tab.refcount[i] = 0;
+        tab.remap[i] = -1;
+    }
+    if (i < (int64_t)w.G * 8)
+        w.counters[i] = 0;
+    if (i < (int64_t)w.G * w.n_slots)
+        w.set_cnt[i] = slot_init[i % w.n_slots];
+    if (i < n_heights) {
+        w.n_active[i] = 0;
+        w.n_refine[i] = 0;
+        w.n_pairs_all[i] = 0;
+    }
+}
+
+// Thread i: reference count of table entry i and the leaf-set position i (leaf_sets_kernel).  Caller errors are counted
+// as check_ids_kernel counts them: the second entry that finds a block taken reports both (counters[g][5]).
+__global__ __launch_bounds__(256) void tree_entries_kernel(TableDesc tab, WorkDesc w, int P)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)w.G * w.n)
+        return;
+    const int64_t g = i / w.n;
+    const int p = tab.bt[i];
+    if (p < 0 || p >= P) {
+        atomicAdd(&w.counters[g * 8 + 4], 1);
+    } else {
+        const int before = atomicAdd(&tab.refcount[g * P + p], 1);
+        if (before > 0)
+            atomicAdd(&w.counters[g * 8 + 5], before == 1 ? 2 : 1);
+    }
+    const int src = w.leaf_src[i - g * w.n];
+    int q = src >= 0 ? tab.bt[g * w.n + src] : 0;
+    if (q < 0 || q >= P)
+        q = q < 0 ? 0 : P - 1;
+    w.set_ids[i] = q;
+}
+
+__global__ __launch_bounds__(256) void tree_table_kernel(TableDesc tab, WorkDesc w, int P, const double *__restrict__ norm_k,
+                                                         const double *__restrict__ norm_v)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)w.G * w.n)
+        return;
+    const int64_t g = i / w.n;
+    const int p = tab.bt[i];
+    const bool ok = p >= 0 && p < P;             // an invalid id leaves a poisoned entry
+    const double nk = ok ? norm_k[g * P + p] : 0.0;
+    tab.orig_norm_k[i] = nk;
+    tab.orig_norm_v[i] = ok ? norm_v[g * P + p] : 0.0;
+    tab.scale_k[i] = ok ? 1.0f : 0.0f;
+    tab.scale_v[i] = ok ? 1.0f : 0.0f;
+    if (nk != 0.0 && !(nk >= 0x1p-40 && nk <= 0x1p40))
+        atomicAdd(&w.counters[g * 8 + 6], 1);
+}
+
+void launch_tree_entries(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, const int32_t *slot_init,
+                         int n_heights)
+{
+    const int64_t nb = (int64_t)pool.G * pool.P, ne = (int64_t)w.G * w.n;
+    const int64_t total = std::max({nb, (int64_t)w.G * w.n_slots, (int64_t)w.G * 8, (int64_t)n_heights});
+    tree_clear_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(tab, w, nb, slot_init, n_heights);
+    if (ne > 0)
+        tree_entries_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, w, pool.P);
+}
+
+void launch_tree_norms(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab)
+{
+    const bool tails = w.early_nk || w.screen_prefix > 0;
+    launch_norms_kernel(s, pool, tails ? w.rem_k : nullptr, w.screen_prefix, w.early_nk, w.q8);
+    const int64_t ne = (int64_t)w.G * w.n;
+    if (ne > 0)
+        tree_table_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, w, pool.P, pool.norm_k, pool.norm_v);
 }
 
 // Leaf sets = physical ids of the leaves' logical entries, each leaf at the region the plan gave it (leaf_src maps

@@ -58,24 +58,20 @@ __device__ __forceinline__ unsigned long long pack_best(float s, int row)
     return ((unsigned long long)ord << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)row);
 }
 
-// Rare path of the epilogue: append (row, cosine) to the
-// candidate list of a column; the count is exact even when the list is full.
-__device__ __forceinline__ void emit_candidate(int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand_idx,
-                                                         float *__restrict__ cand_val, int64_t column, int cap, int row, float s)
-{
-    const int slot = atomicAdd(&cand_cnt[column], 1);
-    if (slot < cap) {
-        cand_idx[column * cap + slot] = row;
-        cand_val[column * cap + slot] = s;
-    }
-}
-
 struct SimArgs {
     int32_t G, n, n_slots, r_stride, cand_cap, P, n_items;
     int32_t row_bytes;             // bytes of one block row
     int32_t nk_screen;             // 64-byte slices of a row that are multiplied: all of them, or a prefix (see PREFIX)
     float thr_floor;
     int64_t total_s;
+};
+
+struct EarlyArgs {
+    const int32_t *nk;      // [G] slices after which a tile is tested
+    int4 *pairs;            // see WorkDesc
+    float *pair_head;
+    int32_t *n_pairs;
+    int32_t pair_cap;
 };
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -123,7 +119,14 @@ constexpr int kRingRowTiles = 4;   // most row tiles of one work item (the host'
 // err_a + err_b + err_a err_b of their cosine, so the value plus that is an upper bound of the cosine, listed when it
 // clears the floor and evaluated in full by the assignment step like a prefix-screen candidate.  The two bounds add up
 // when both shortcuts are on.
-template <typename T, bool BIG, bool DENSE, bool PREFIX>
+// EARLY (early rejection, early.hip): the same bound, used to stop.  Measured (ms, all similarity launches of a tree; full
+// length -> early): 64 requests x 128 blocks of 2048 elements, 256 groups, 20.3 -> 6.2; 512 ragged requests, 8 groups of
+// 141 355 blocks, 154.8 -> 37.4; 256 requests of Zipf-drawn 4096-element blocks, 16 groups, whose low heights hold 500 related
+// pairs per tile, 8.0 -> 5.5.  Every row tile is tested after the early.nk[g] slices
+// of its group.  Pairs that pass go to the pair list with their product so far (`rem` holds the tail shares); a tile
+// with more than LIMIT of them, or more than the workgroup's list holds, is not worth finishing pair by pair and runs on
+// to its full length instead, whose epilogue lists real candidates.
+template <typename T, bool BIG, bool DENSE, bool PREFIX, bool EARLY>
 __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_kernel(
     SimArgs A, const char *__restrict__ kpool, const float *__restrict__ inv_norm, const int32_t *__restrict__ set_ids,
     const int32_t *__restrict__ set_cnt, const int4 *__restrict__ dyn_items, const int32_t *__restrict__ dyn_count,
@@ -132,9 +135,11 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     const int32_t *__restrict__ r_base, const int32_t *__restrict__ r_cap, const int64_t *__restrict__ s_base,
     unsigned long long *__restrict__ best_packed, int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand_idx,
     float *__restrict__ cand_val, float *__restrict__ dense_s, const uint8_t *__restrict__ group_enable,
-    const float *__restrict__ rem, const Q8Desc q8)
+    const float *__restrict__ rem, const Q8Desc q8, const EarlyArgs early)
 {
-    static_assert(!(DENSE && PREFIX), "the dense matrix is the full-length product");
+    static_assert(!(DENSE && (PREFIX || EARLY)) && !(PREFIX && EARLY), "the dense matrix is the full-length product");
+    static_assert(!EARLY || !std::is_same<T, fp8_t>::value, "early rejection tests the pool's own values");
+    constexpr bool TAILS = PREFIX || EARLY;
     constexpr bool Q8 = std::is_same<T, fp8_t>::value;
     constexpr int WN = 2, TM = 2, TN = BIG ? 4 : 2, NT = BIG ? 512 : 256, BM = BIG ? 256 : 128, BN = BM;
     constexpr int WM = NT / 64 / WN;          // wavefronts along the rows
@@ -150,10 +155,11 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
 
     __shared__ __attribute__((aligned(1024))) char ring[4 * STAGE];
     __shared__ float lds_invl[RT * BM];      // inverse norms of all left rows of the item; NaN past the end
+    __shared__ int lds_lid[EARLY ? RT * BM : 1];         // EARLY: physical ids of the left rows
     __shared__ float lds_invr[BN];
     __shared__ float lds_tcol[BN];
-    __shared__ __attribute__((aligned(16))) float lds_reml[PREFIX ? RT * BM : 1];     // PREFIX: tail share of the left rows
-    __shared__ float lds_tcolb[PREFIX ? BN : 1];         // PREFIX: tail share of the right blocks / their inverse norm
+    __shared__ __attribute__((aligned(16))) float lds_reml[TAILS ? RT * BM : 1];     // PREFIX, EARLY: tail share of the left rows
+    __shared__ float lds_tcolb[TAILS ? BN : 1];         // PREFIX, EARLY: tail share of the right blocks / their inverse norm
     __shared__ __attribute__((aligned(16))) float lds_errl[Q8 ? RT * BM : 1];        // Q8: copy error of the left rows
     __shared__ float lds_c1[Q8 ? BN : 1];                // Q8: (1 + copy error of the right block) / its scale
     __shared__ __attribute__((aligned(16))) float lds_all[Q8 ? RT * BM : 1];         // Q8: alpha of the left rows
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     __shared__ float lds_g_inv[RT * BM / 32];
     __shared__ float lds_g_err[Q8 ? RT * BM / 32 : 1];
     __shared__ float lds_g_al[Q8 ? RT * BM / 32 : 1];
-    __shared__ float lds_g_rem[PREFIX ? RT * BM / 32 : 1];
+    __shared__ float lds_g_rem[TAILS ? RT * BM / 32 : 1];
     // The column maximum (best_packed) is a diagnostic: the assignment step works from the candidate lists alone.  It
     // is kept only in the instantiation that also writes the dense matrix; in the production one it cost four of
     // the six vector instructions per accumulator in the epilogue, during which the MFMA units of the CU idle.
@@ -173,12 +179,21 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     __shared__ int lds_brt[BEST ? TN : 1][BEST ? NT : 1];
     constexpr int MAXC = (BIG || !Q8) ? 512 : 256;      // (two small fp8 workgroups must fit one compute unit's LDS)
     __shared__ int lds_ncand;
+    __shared__ int lds_npairs, lds_pair0;       // EARLY: open pairs of the item, their place in the pair list
+    constexpr int OPEN = (int)0x80000000;       // EARLY: mark of an open pair in lds_cand_row
+    constexpr int LIMIT = BM / 2;               // EARLY: open pairs a tile may leave (see early.hip)
+    int n_kept = 0;                             // EARLY: entries of the list that belong to earlier row tiles
     __shared__ int lds_cand_row[MAXC];
     __shared__ int lds_cand_col[MAXC];
     __shared__ float lds_cand_val[MAXC];
 
+    // Each XCD walks a contiguous range of items.  Within it the four items of every quad are rotated by a number that
+    // changes from quad to quad: the workgroups of an XCD are handed to its four shader engines in turn, in order, and items
+    // come in patterns of four and eight (the tiles of a node), so without this the long tiles of every node land on the same
+    // engine while the others wait (nodes of 2 x 2 tiles, one of them run to its full length: 1236 us, rotated 654 us).
     const int per_xcd = gridDim.x >> 3;
-    const long long v = (long long)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int seat = blockIdx.x >> 3, quad = seat >> 2;
+    const long long v = (long long)(blockIdx.x & 7) * per_xcd + (quad << 2) + ((seat + quad + (quad >> 2) + (quad >> 4)) & 3);
     if (v >= (long long)A.G * A.n_items)
         return;
     const int g = (int)(v / A.n_items);
@@ -206,7 +221,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     const int wm = wave / WN, wn = wave % WN;
     const int half = lane >> 5;
     const int64_t row_bytes = A.row_bytes;
-    const int nk = A.nk_screen;                               // 64-byte slices walked per row
+    const int nk_full = A.nk_screen;                          // 64-byte slices walked per row ...
+    const int nk = EARLY ? early.nk[g] : nk_full;             // ... before a tile is looked at
     const int n_rt = (row_end - row0 + BM - 1) / BM;
     const char *__restrict__ kg = kpool + (int64_t)g * A.P * row_bytes;
     const float *__restrict__ inv_g = inv_norm + (int64_t)g * A.P;
@@ -214,12 +230,26 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     // ---- global -> LDS loaders: this lane's row within a half tile and its (swizzled) chunk
     const int ld_row = wave * 16 + (lane >> 2);
     const int ld_chunk = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
+    // ids of the rows this lane loads, row tile by row tile: in registers, or (EARLY, whose registers are full) in LDS
 #define KVF_LID(t, i) l_ids[min(row0 + (t) * BM + (i) * HALF + ld_row, row_end - 1)]
     const int ia00 = KVF_LID(0, 0), ia01 = KVF_LID(0, 1);
-    const int ia10 = KVF_LID(1, 0), ia11 = KVF_LID(1, 1);
-    const int ia20 = KVF_LID(2, 0), ia21 = KVF_LID(2, 1);
-    const int ia30 = KVF_LID(3, 0), ia31 = KVF_LID(3, 1);
+    int ia10 = 0, ia11 = 0, ia20 = 0, ia21 = 0, ia30 = 0, ia31 = 0;
+    if constexpr (!EARLY) {
+        ia10 = KVF_LID(1, 0), ia11 = KVF_LID(1, 1);
+        ia20 = KVF_LID(2, 0), ia21 = KVF_LID(2, 1);
+        ia30 = KVF_LID(3, 0), ia31 = KVF_LID(3, 1);
+    }
 #undef KVF_LID
+    auto row_id = [&](int t, int i) __attribute__((always_inline)) {
+        if constexpr (EARLY) {      // (in assembly for the reason given for the fragment reads)
+            int id;
+            const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int *)lds_lid + (min(t, RT - 1) * BM + i * HALF + ld_row) * 4;
+            asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(id) : "v"(at) : "memory");
+            return id;
+        } else {
+            return i == 0 ? (t == 1 ? ia10 : (t == 2 ? ia20 : ia30)) : (t == 1 ? ia11 : (t == 2 ? ia21 : ia31));
+        }
+    };
     const char *pa0 = kg + (int64_t)ia00 * row_bytes + ld_chunk;
     const char *pa1 = kg + (int64_t)ia01 * row_bytes + ld_chunk;
     const char *pb0 = kg + (int64_t)r_ids[min(col0 + ld_row, mr - 1)] * row_bytes + ld_chunk;
@@ -336,13 +366,15 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
             const float ir = col < mr ? inv_g[r_ids[col]] : 0.0f;
             lds_invr[x] = ir;
             lds_tcol[x] = col >= mr ? INFINITY : (ir > 0.0f ? A.thr_floor / ir : (A.thr_floor < 0.0f ? -INFINITY : INFINITY));
-            if constexpr (PREFIX)
+            if constexpr (TAILS)
                 lds_tcolb[x] = (col < mr && ir > 0.0f) ? rem[(int64_t)g * A.P + r_ids[col]] / ir : 0.0f;
         }
     }
     static_assert((RT * BM) % NT == 0, "every wavefront takes whole groups of 32 rows");
     for (int x = tid; x < RT * BM; x += NT) {
         const int row = row0 + x;
+        if constexpr (EARLY)
+            lds_lid[x] = l_ids[min(row, row_end - 1)];
         float g_inv = 0.0f, g_err = 0.0f, g_al = 0.0f, g_rem = 0.0f;
         if constexpr (Q8) {
             const int64_t id = (int64_t)g * A.P + l_ids[min(row, row_end - 1)];
@@ -360,7 +392,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 g_inv = inv_g[l_ids[row]];
             lds_invl[x] = row < row_end ? g_inv : __uint_as_float(0x7FC00000u);
         }
-        if constexpr (PREFIX) {
+        if constexpr (TAILS) {
             if (row < row_end)
                 g_rem = rem[(int64_t)g * A.P + l_ids[row]];
             lds_reml[x] = g_rem;
@@ -373,7 +405,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 g_err = fmaxf(g_err, __shfl_xor(g_err, off, 64));
                 g_al = fmaxf(g_al, __shfl_xor(g_al, off, 64));
             }
-            if constexpr (PREFIX)
+            if constexpr (TAILS)
                 g_rem = fmaxf(g_rem, __shfl_xor(g_rem, off, 64));
         }
         if ((x & 31) == 0) {
@@ -382,7 +414,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 lds_g_err[x >> 5] = g_err;
                 lds_g_al[x >> 5] = g_al;
             }
-            if constexpr (PREFIX)
+            if constexpr (TAILS)
                 lds_g_rem[x >> 5] = g_rem;
         }
     }
@@ -393,8 +425,10 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
             lds_brt[nt][tid] = 0;
         }
     }
-    if (tid == 0)
+    if (tid == 0) {
         lds_ncand = 0;
+        lds_npairs = 0;
+    }
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -410,14 +444,15 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     // slices with its own counters.  Past the last slice of the last row tile both keep loading rows that exist (the
     // ids of the last row tile, the panel from its start), and those loads are only waited for, never read.
     int pf_kt_a = 0, pf_rt_a = 0, pf_kt_b = 0;
+    int lim_a = nk, lim_b = nk;          // (a tile that runs on to its full length moves these while it does)
 #define KVF_DMA_ADVANCE_A()                                                                                        \
     do {                                                                                                           \
         pa0 += 64; pa1 += 64;                                                                                      \
-        if (++pf_kt_a == nk) {                                                                                     \
+        if (++pf_kt_a == lim_a) {                                                                                  \
             pf_kt_a = 0;                                                                                           \
+            lim_a = nk;                                                                                            \
             ++pf_rt_a;                                                                                             \
-            const int na0 = pf_rt_a == 1 ? ia10 : (pf_rt_a == 2 ? ia20 : ia30);                                    \
-            const int na1 = pf_rt_a == 1 ? ia11 : (pf_rt_a == 2 ? ia21 : ia31);                                    \
+            const int na0 = row_id(pf_rt_a, 0), na1 = row_id(pf_rt_a, 1);                                          \
             pa0 = kg + (int64_t)na0 * row_bytes + ld_chunk;                                                        \
             pa1 = kg + (int64_t)na1 * row_bytes + ld_chunk;                                                        \
         }                                                                                                          \
@@ -425,27 +460,35 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
 #define KVF_DMA_ADVANCE_B()                                                                                        \
     do {                                                                                                           \
         pb0 += 64; pb1 += 64;                                                                                      \
-        if (++pf_kt_b == nk) {                                                                                     \
+        if (++pf_kt_b == lim_b) {                                                                                  \
             pf_kt_b = 0;                                                                                           \
-            pb0 -= (int64_t)nk * 64;                                                                               \
-            pb1 -= (int64_t)nk * 64;                                                                               \
+            pb0 -= (int64_t)lim_b * 64;                                                                            \
+            pb1 -= (int64_t)lim_b * 64;                                                                            \
+            lim_b = nk;                                                                                            \
         }                                                                                                          \
     } while (0)
-#pragma unroll 1
-    for (int p = 0; p < 3; ++p) {
-        const int so = p * STAGE;
-        KVF_DMA(pa0, so + dma_a0);
-        KVF_DMA(pa1, so + dma_a1);
-        KVF_DMA(pb0, so + dma_b0);
-        KVF_DMA(pb1, so + dma_b1);
-        KVF_DMA_ADVANCE_A();
-        KVF_DMA_ADVANCE_B();
-    }
-    KVF_DMA(pa0, 3 * STAGE + dma_a0);       // the A part of slice 3; its B part follows in the first iteration
-    KVF_DMA(pa1, 3 * STAGE + dma_a1);
-    KVF_DMA_ADVANCE_A();
-    asm volatile("s_waitcnt vmcnt(10)" ::: "memory");     // slice 0 has landed
-    __syncthreads();
+#define KVF_PROLOGUE(IT)                                                                                           \
+    do {                                                                                                           \
+        _Pragma("unroll 1") for (int p = 0; p < 3; ++p)                                                            \
+        {                                                                                                          \
+            const int so = (((IT) + p) & 3) * STAGE;                                                               \
+            KVF_DMA(pa0, so + dma_a0);                                                                             \
+            KVF_DMA(pa1, so + dma_a1);                                                                             \
+            KVF_DMA(pb0, so + dma_b0);                                                                             \
+            KVF_DMA(pb1, so + dma_b1);                                                                             \
+            KVF_DMA_ADVANCE_A();                                                                                   \
+            KVF_DMA_ADVANCE_B();                                                                                   \
+        }                                                                                                          \
+        const int s3 = (((IT) + 3) & 3) * STAGE;                                                                   \
+        KVF_DMA(pa0, s3 + dma_a0); /* the A part of slice 3; its B part follows in the first iteration */          \
+        KVF_DMA(pa1, s3 + dma_a1);                                                                                 \
+        KVF_DMA_ADVANCE_A();                                                                                       \
+        asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); /* the first slice has landed */                         \
+        __syncthreads();                                                                                           \
+    } while (0)
+    if constexpr (EARLY)
+        __syncthreads();     // lds_lid
+    KVF_PROLOGUE(0);
     if constexpr (Q8) {
         KVF_Q8_READ_SET0(0u)
         KVF_Q8_WAIT_SET0();
@@ -545,28 +588,33 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
         KVF_DMA_ADVANCE_A();                                                                                       \
     } while (0)
 
-    int it = 0;
-    for (int rt = 0; rt < n_rt; ++rt) {
+    // One pass of this loop walks the K slices of a row tile and looks at its products.  EARLY: the slices up to the
+    // group's test, and for a tile that the test does not settle a second pass over all of them.  (Going on from the
+    // accumulators of the first pass would save a sixth of such a tile, but makes them live across the look and the two
+    // K loops, which the register allocator answers with a second copy: 420 spilled registers.)
+    int it = 0, rt = 0, n_slices = nk;
+    bool whole = !EARLY || nk == nk_full;       // this pass ends with whole products
+    for (;;) {
         const bool act_m1 = row_end - (row0 + rt * BM) > MT_STRIDE;
         if constexpr (Q8) {
             if (act_m1 && act_n[TN - 1]) {
 #pragma unroll 1
-                for (int kt = 0; kt < nk; ++kt, ++it)
+                for (int kt = 0; kt < n_slices; ++kt, ++it)
                     KVF_Q8_SLICE(KVF_Q8_MMA, KVF_Q8_MMA_HI);
             } else {
 #pragma unroll 1
-                for (int kt = 0; kt < nk; ++kt, ++it)
+                for (int kt = 0; kt < n_slices; ++kt, ++it)
                     KVF_Q8_SLICE(KVF_Q8_MMA_IF, KVF_Q8_MMA_HI_IF);
             }
             KVF_Q8_WAIT_SET0();
         } else {
             if (act_m1 && act_n[TN - 1]) {
 #pragma unroll 1
-                for (int kt = 0; kt < nk; ++kt, ++it)
+                for (int kt = 0; kt < n_slices; ++kt, ++it)
                     KVF_SLICE(KVF_MMA, KVF_MMA_HI);
             } else {
 #pragma unroll 1
-                for (int kt = 0; kt < nk; ++kt, ++it)
+                for (int kt = 0; kt < n_slices; ++kt, ++it)
                     KVF_SLICE(KVF_MMA_IF, KVF_MMA_HI_IF);
             }
             // the prefetched fragments of the next row tile's first slice must be in their registers before anything
@@ -582,7 +630,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
             for (int nt = 0; nt < TN; ++nt) {
                 kmax[nt] = 0u;
                 tcol[nt] = lds_tcol[nt * NT_STRIDE + wn * 32 + (lane & 31)];
-                tcolb[nt] = PREFIX ? lds_tcolb[nt * NT_STRIDE + wn * 32 + (lane & 31)] : 0.0f;
+                tcolb[nt] = PREFIX || (EARLY && !whole) ? lds_tcolb[nt * NT_STRIDE + wn * 32 + (lane & 31)] : 0.0f;
                 c1[nt] = Q8 ? lds_c1[nt * NT_STRIDE + wn * 32 + (lane & 31)] : 0.0f;
                 alrs[nt] = Q8 ? lds_alrs[nt * NT_STRIDE + wn * 32 + (lane & 31)] : 0.0f;
             }
@@ -597,7 +645,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     const int grp = (rt * BM + mt * MT_STRIDE + wm * 32) >> 5;
                     const float gi = lds_g_inv[grp];
                     const float ge = Q8 ? lds_g_err[grp] : 0.0f, ga = Q8 ? lds_g_al[grp] : 0.0f;
-                    const float gr = PREFIX ? lds_g_rem[grp] : 0.0f;
+                    const float gr = TAILS ? lds_g_rem[grp] : 0.0f;
 #pragma unroll
                     for (int nt = 0; nt < TN; ++nt) {
                         float mx = 0.0f;
@@ -609,7 +657,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                             low = fmaf(-ge, c1[nt], low);
                             low = fmaf(-ga, fabsf(alrs[nt]), low);
                         }
-                        if constexpr (PREFIX)
+                        if constexpr (TAILS)
                             low = fmaf(-gr, tcolb[nt], low);
                         // (the binary32 roundings of this line and of the exact test differ by parts in 10^7; the factor
                         // covers them, and the floor sits a whole band below anything that has to be listed)
@@ -624,7 +672,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     const float4 il4 = *reinterpret_cast<const float4 *>(&lds_invl[rt * BM + rl0]);
                     const float il[4] = {il4.x, il4.y, il4.z, il4.w};
                     float rl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if constexpr (PREFIX) {
+                    if constexpr (TAILS) {
                         const float4 rl4 = *reinterpret_cast<const float4 *>(&lds_reml[rt * BM + rl0]);
                         rl[0] = rl4.x; rl[1] = rl4.y; rl[2] = rl4.z; rl[3] = rl4.w;
                     }
@@ -651,7 +699,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                                 lim[q] = fmaf(-el[q], c1[nt], lim[q]);      // and the part of the cosine that lies along
                                 lim[q] = fmaf(-al[q], alrs[nt], lim[q]);    // the common direction moves over to this side
                             }
-                            if constexpr (PREFIX)
+                            if constexpr (TAILS)
                                 lim[q] = fmaf(-rl[q], tcolb[nt], lim[q]);
                             hit |= t[q] > lim[q];
                             if constexpr (BEST) {
@@ -670,11 +718,12 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                                     if constexpr (Q8)
                                         sv = fmaf(al[q], lds_alr[cl], sv);
                                     const int k = atomicAdd(&lds_ncand, 1);
+                                    const bool open = EARLY && !whole;         // a pair still to be finished: its product so far
                                     if (k < MAXC) {
-                                        lds_cand_row[k] = row;
+                                        lds_cand_row[k] = open ? row | OPEN : row;
                                         lds_cand_col[k] = cl;
-                                        lds_cand_val[k] = sv;
-                                    } else {
+                                        lds_cand_val[k] = open ? acc[mt][nt][eg * 4 + q] : sv;
+                                    } else if (!open) {
                                         emit_candidate(cand_cnt, cand_idx, cand_val, cbase + col0 + cl, A.cand_cap, row, sv);
                                     }
                                 }
@@ -702,21 +751,65 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                             }
                         }
             }
+            if constexpr (BEST) {
 #pragma unroll
-            for (int nt = 0; nt < TN; ++nt) {
-                if constexpr (BEST) {
+                for (int nt = 0; nt < TN; ++nt) {
                     if (kmax[nt] > lds_bkey[nt][tid]) {
                         lds_bkey[nt][tid] = kmax[nt];
                         lds_brt[nt][tid] = rt;
                     }
                 }
-#pragma unroll
-                for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        acc[mt][nt][e] = 0.0f;
             }
         }
+        if constexpr (EARLY) {
+            if (nk != nk_full) {
+                // every wavefront's pairs are counted (a plain barrier: the loads into the ring stay on their way)
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                const int n_now = lds_ncand;
+                if (whole) {                         // the list may have run over: the surplus went out directly
+                    __syncthreads();
+                    n_kept = min(n_now, MAXC);
+                    if (tid == 0)
+                        lds_ncand = n_kept;
+                    whole = false;
+                    n_slices = nk;
+                } else if (n_now <= MAXC && n_now - n_kept <= LIMIT) {
+                    n_kept = n_now;                  // (nothing is appended before the barriers of the next slices)
+                } else {
+                    // Drop this tile's pairs, drain the ring (it holds the next row tile's first slices) and start over; the
+                    // loads then run ahead into the next row tile as they always do.
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    if (tid == 0)
+                        lds_ncand = n_kept;
+                    whole = true;
+                    n_slices = nk_full;
+                    --rt;
+                    const int ra0 = row_id(rt + 1, 0), ra1 = row_id(rt + 1, 1);
+                    pa0 = kg + (int64_t)ra0 * row_bytes + ld_chunk;
+                    pa1 = kg + (int64_t)ra1 * row_bytes + ld_chunk;
+                    pb0 -= (int64_t)pf_kt_b * 64;
+                    pb1 -= (int64_t)pf_kt_b * 64;
+                    pf_rt_a = rt + 1;
+                    pf_kt_a = pf_kt_b = 0;
+                    lim_a = lim_b = nk_full;
+                    KVF_PROLOGUE(it);
+                    const uint32_t cur = (uint32_t)(it & 3) * STAGE;
+                    const uint32_t ra = fa_lo + cur, rb = fb_lo + cur;
+                    KVF_READ_SET(0, ra, rb)
+                    KVF_WAIT_SET(0);
+                }
+            }
+        }
+        if (++rt == n_rt)
+            break;
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < TN; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    acc[mt][nt][e] = 0.0f;
     }
     // loads past the last slice are still on their way into the ring; nothing may leave before they land
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -724,9 +817,45 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
 
     {
         const int nc = min(lds_ncand, MAXC);
-        for (int k = tid; k < nc; k += NT)
-            emit_candidate(cand_cnt, cand_idx, cand_val, cbase + col0 + lds_cand_col[k], A.cand_cap, lds_cand_row[k],
-                           lds_cand_val[k]);
+        for (int k = tid; k < nc; k += NT) {
+            if (EARLY && lds_cand_row[k] < 0)       // BN <= 256: the column takes 8 bits, the pair's number the rest
+                lds_cand_col[k] |= atomicAdd(&lds_npairs, 1) << 8;
+            else
+                emit_candidate(cand_cnt, cand_idx, cand_val, cbase + col0 + lds_cand_col[k], A.cand_cap, lds_cand_row[k],
+                               lds_cand_val[k]);
+        }
+        if constexpr (EARLY) {
+            __syncthreads();
+            if (tid == 0 && lds_npairs > 0)
+                lds_pair0 = atomicAdd(early.n_pairs, lds_npairs);
+            __syncthreads();
+            if (lds_npairs > 0) {
+                const int first = lds_pair0;
+                for (int k = tid; k < nc; k += NT) {
+                    const int slot = first + (lds_cand_col[k] >> 8);
+                    if (lds_cand_row[k] < 0 && slot < early.pair_cap) {
+                        const int row = lds_cand_row[k] & ~OPEN, col = col0 + (lds_cand_col[k] & 255);
+                        early.pairs[slot] = make_int4((int)(cbase + col), row, l_ids[row], r_ids[col]);
+                        early.pair_head[slot] = lds_cand_val[k];
+                    }
+                }
+                // a full list: this workgroup finishes its own pairs, a wavefront per pair
+                for (int k = wave; k < nc && first + lds_npairs > early.pair_cap; k += NT / 64) {
+                    if (lds_cand_row[k] < 0 && first + (lds_cand_col[k] >> 8) >= early.pair_cap) {
+                        const int row = lds_cand_row[k] & ~OPEN, cl = lds_cand_col[k] & 255, col = col0 + cl;
+                        using E = typename std::conditional<Q8, bf16_t, T>::type;
+                        float dot = product_from<E>((const E *)(kg + (int64_t)l_ids[row] * row_bytes),
+                                                    (const E *)(kg + (int64_t)r_ids[col] * row_bytes), 4 * nk, 4 * nk_full, lane, 64);
+#pragma unroll
+                        for (int off = 32; off >= 1; off >>= 1)
+                            dot += __shfl_xor(dot, off, 64);
+                        const float cs = (lds_cand_val[k] + dot) * lds_invl[row - row0] * lds_invr[cl];
+                        if (lane == 0 && cs > A.thr_floor)
+                            emit_candidate(cand_cnt, cand_idx, cand_val, cbase + col, A.cand_cap, row, cs);
+                    }
+                }
+            }
+        }
     }
     if constexpr (BEST) {
 #pragma unroll
@@ -743,6 +872,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
         }
     }
 #undef KVF_DMA
+#undef KVF_PROLOGUE
 #undef KVF_DS_READ
 #undef KVF_READ_SET
 #undef KVF_WAIT_SET
@@ -871,18 +1001,26 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     A.nk_screen = (prefix ? w.screen_prefix * (int)sizeof(T) : A.row_bytes) >> 6;
     A.thr_floor = thr_floor;
     A.total_s = h.total_s;
-    const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
-#define KVF_SIM_LAUNCH(D, PF)                                                                                          \
-    similarity_ring_kernel<T, BIG, D, PF><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
+    const unsigned grid = (unsigned)(((total + 31) / 32) * 32);      // whole quads on every XCD
+    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap};
+#define KVF_SIM_LAUNCH(D, PF, EA)                                                                                          \
+    similarity_ring_kernel<T, BIG, D, PF, EA><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
         A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_count, h.l_off, h.r_off, \
         h.l_slot, h.r_slot, h.r_base, h.r_cap, h.s_base, w.best_packed, w.cand_cnt, w.cand_idx, w.cand_val, dense_s,           \
-        w.group_enable, w.rem_k, w.q8)
-    if (dense_s)
-        KVF_SIM_LAUNCH(true, false);
-    else if (prefix)
-        KVF_SIM_LAUNCH(false, true);
-    else
-        KVF_SIM_LAUNCH(false, false);
+        w.group_enable, w.rem_k, w.q8, early)
+    if (dense_s) {
+        KVF_SIM_LAUNCH(true, false, false);
+    } else if (prefix) {
+        KVF_SIM_LAUNCH(false, true, false);
+    } else {
+        if constexpr (!std::is_same<T, fp8_t>::value) {
+            if (w.early_nk) {
+                KVF_SIM_LAUNCH(false, false, true);
+                return;
+            }
+        }
+        KVF_SIM_LAUNCH(false, false, false);
+    }
 #undef KVF_SIM_LAUNCH
 }
 

@@ -1,0 +1,59 @@
+"""Early rejection in the similarity step of a tree call (csrc/early.hip) against the oracle.  It is used from a product of
+5e10 operations (binary32: a sixteenth of that) and rows of 2 KiB on, which takes more groups than the oracle has time for:
+groups are independent, so two of them are compared exactly (tables, pools, counts, scales, norms)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_03067_amd import workloads as wl
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _case(which):
+    """-> (recipe, offset that every key block of a group shares, candidate slots)"""
+    bff = dict(t=16, d=64)                                   # 2 KiB rows: 32 slices
+    if which == "white":                                     # a few pairs per tile stay open, sets ragged against the tiles
+        return wl.llama8b_bff(n_req=9, tokens=16 * 150, layers=12, kv_heads=2, prefix_tokens=16 * 9, near_pool=60, **bff), 0.0, 16
+    if which == "shared_direction":                          # unrelated cosines around 0.5: a longer part before the test
+        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=12, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 1.0, 16
+    if which == "no_test":                                   # unrelated cosines around 0.85 against thr 0.9: full length
+        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=12, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 2.35, 64
+    if which == "dense":                                     # most tiles hold more related pairs than are finished one by one
+        return wl.zipf_bff(n_req=8, tokens=32 * 150, layers=8, kv_heads=2, pool=150, t=32, d=64, thr=0.9), 0.0, 64
+    if which == "pair_list_full":                            # 2.4 open pairs per left block; the list holds 1.6
+        return wl.llama8b_bff(n_req=2, tokens=16 * 1300, layers=8, kv_heads=2, prefix_tokens=0, near_pool=560, near_frac=1.0, **bff), 0.0, 64
+    if which == "f32":
+        return wl.mixed(n_req=9, min_tokens=600, max_tokens=3000, chunk_tokens=512, layers=2, kv_heads=2, pool=64, dtype=torch.float32, seed=78, **bff), 0.0, 16
+    raise AssertionError(which)
+
+
+@pytest.mark.parametrize("rule", ["argmax", "first_row"])
+@pytest.mark.parametrize("which", ["white", "shared_direction", "no_test", "dense", "pair_list_full", "f32"])
+def test_tree_with_early_rejection_matches_oracle(oracle, which, rule):
+    kb = gu.load_binding()
+    rec, common, cap = _case(which)
+    print("early", which, rule, "G", rec.G, "n", rec.n, "r", rec.r, flush=True)
+    mat = wl.materialise(rec, DEV, phys_perm=True)
+    if common:
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(5)
+        for g in range(rec.G):
+            mat["K"][g] = (mat["K"][g].float() + common * torch.randn(rec.r, generator=gen, device=DEV)).to(rec.dtype)
+    pick = [0, rec.G - 1]
+    host = ([wl.to_numpy_pool(mat["K"][g]) for g in pick], [wl.to_numpy_pool(mat["V"][g]) for g in pick],
+            [mat["bt"][g].cpu().numpy().copy() for g in pick])
+    cache, plan, stats, ctx = gu.gpu_fuse(rec, mat, cand_cap=cap, rule=rule)
+    res = gu.oracle_fuse(oracle, rec, host, rule=rule)
+    gu.check_ambiguity(res, which)
+    for r, g in zip(res, pick):
+        gu.compare_group(r, cache, g, rec.dtype == torch.float32, which)
+    per_group = kb.group_counters(ctx, plan)
+    assert per_group[pick, 0].tolist() == [int(r.stats[1]) for r in res]
+    assert per_group[pick, 1].tolist() == [int(r.stats[2]) for r in res]
+    assert stats.fused > 0 and int(cache.refcount.sum()) == rec.G * rec.n and bool((cache.remap >= -1).all())
+    if which != "no_test":
+        assert np.all(per_group[:, 3] == 0)
