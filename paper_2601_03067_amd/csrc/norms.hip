@@ -61,8 +61,8 @@ __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ 
     const int64_t b = is_v ? w - n_blocks : w;
     const uint4 *src = reinterpret_cast<const uint4 *>((is_v ? vpool : kpool) + b * (int64_t)r);
     const int chunks = r / PER;
-    // st: the squares beyond the prefix of the prefix screen or of early rejection, summed on their own (rem = |tail| /
-    // |block|, see prefix_tails_kernel)
+    // st: the squares beyond the prefix of the prefix screen or of early rejection (rem = |tail| / |block|, see
+    // prefix_tails_kernel)
     const bool want_tail = rem != nullptr && !is_v;
     if (want_tail && early_nk)
         prefix_chunks = 4 * early_nk[b / P];       // early rejection: one prefix per group, in 64-byte slices
@@ -92,31 +92,27 @@ __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ 
             }
         }
     } else {
-        if (!want_tail) {
-            for (int c = lane; c < chunks; c += 64) {
-                double x[PER];
-                Elem<T>::widen(src[c], x);
+        // One sum in one order, with or without a tail, so that the norm's bits do not depend on the screens: a lane walks its
+        // chunks upwards, and its tail is what the sum gains after the prefix.  The 2^-44 pays for the roundings of both
+        // (fewer than 2^9 additions of at most half a unit of 2^-52), upwards, as the bound needs it.
+        double sp = 0.0;
+        for (int c = lane; c < chunks; c += 64) {
+            double x[PER];
+            Elem<T>::widen(src[c], x);
 #pragma unroll
-                for (int i = 0; i < PER; ++i)
-                    ss = fma(x[i], x[i], ss);
-            }
-        } else {                       // ss: the squares of the prefix only; the tail's are added below
-            for (int c = lane; c < chunks; c += 64) {
-                double x[PER], part = 0.0;
-                Elem<T>::widen(src[c], x);
-#pragma unroll
-                for (int i = 0; i < PER; ++i)
-                    part = fma(x[i], x[i], part);
-                ss += c < prefix_chunks ? part : 0.0;
-                st += c < prefix_chunks ? 0.0 : part;
-            }
+            for (int i = 0; i < PER; ++i)
+                ss = fma(x[i], x[i], ss);
+            if (want_tail)
+                sp = c < prefix_chunks ? ss : sp;
         }
+        if (want_tail)
+            st = ss - sp + ss * 0x1p-44;
     }
     ss = wave_sum(ss);
     if (want_tail) {
         st = wave_sum(st);
-        if (KEEP == 0)
-            ss += st;
+        if (!(st < INFINITY))          // inf - inf: everything is tail
+            st = ss;
     }
     const double nrm = sqrt(ss);
     if (lane == 0) {

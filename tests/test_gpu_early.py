@@ -46,7 +46,11 @@ def test_tree_with_early_rejection_matches_oracle(oracle, which, rule):
     pick = [0, rec.G - 1]
     host = ([wl.to_numpy_pool(mat["K"][g]) for g in pick], [wl.to_numpy_pool(mat["V"][g]) for g in pick],
             [mat["bt"][g].cpu().numpy().copy() for g in pick])
+    alone = kb.Cache(mat["K"], mat["V"], mat["bt"], rec.t, rec.d)
+    kb.block_norms(kb.Context(DEV), alone)
+    torch.cuda.synchronize()
     cache, plan, stats, ctx = gu.gpu_fuse(rec, mat, cand_cap=cap, rule=rule)
+    assert torch.equal(cache.orig_norm_k, alone.orig_norm_k)          # bit for bit: tails written or not
     res = gu.oracle_fuse(oracle, rec, host, rule=rule)
     gu.check_ambiguity(res, which)
     for r, g in zip(res, pick):
