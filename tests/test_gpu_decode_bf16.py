@@ -1,0 +1,96 @@
+"""Paged decode over bfloat16 pools, both products on the matrix cores: edges of the 16-token pieces, of the pairs a
+wavefront takes and of the splits, every head count, both pool layouts, against attention in binary64."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# every way a request can end inside, at and just past a piece, a pair of pieces, a round of four wavefronts, a split
+CONTEXTS = [0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 127, 128, 129, 255, 300, 1000]
+
+
+def _setup(t, d, heads, seed, layers=2, all_heads=False):
+    from paper_2601_03067_amd import binding as kb
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    blocks = [(c + t - 1) // t for c in CONTEXTS]
+    n, groups, width = sum(blocks), layers * (1 if all_heads else heads), d * (heads if all_heads else 1)
+    P = n + 3
+    K = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(torch.bfloat16)
+    V = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(torch.bfloat16)
+    bt = torch.randint(0, P, (groups, n), generator=gen, device=DEV, dtype=torch.int32)       # shared blocks among them
+    cache = kb.Cache(K, V, bt, t, width)
+    cache.scale_k.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
+    cache.scale_v.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
+    start = np.concatenate([[0], np.cumsum(blocks)[:-1]]).astype(np.int32)
+    return kb, cache, start, max(blocks), gen
+
+
+def _call(kb, cache, heads, q, start, max_blocks, all_heads):
+    ctx = kb.Context(DEV)
+    rs = torch.from_numpy(start).to(DEV)
+    cl = torch.tensor(CONTEXTS, dtype=torch.int32, device=DEV)
+    step = kb.paged_decode_attn_all_heads if all_heads else kb.paged_decode_attn
+    out = step(ctx, cache, heads, q, rs, cl, max_blocks)
+    torch.cuda.synchronize()
+    return out.cpu().double()
+
+
+def _reference(cache, t, d, heads, q, start, all_heads):
+    layers, B, Hq, _ = q.shape
+    rep = Hq // heads
+    out = torch.zeros(q.shape, dtype=torch.float64)
+    qc, K, V, bt = q.cpu().double(), cache.K.cpu().double(), cache.V.cpu().double(), cache.bt.cpu().long()
+    sk, sv = cache.scale_k.cpu().double(), cache.scale_v.cpu().double()
+    for li in range(layers):
+        for h in range(heads):
+            g, w, s = (li, heads, h) if all_heads else (li * heads + h, 1, 0)
+            for b, c in enumerate(CONTEXTS):
+                if c == 0:
+                    continue
+                x = slice(int(start[b]), int(start[b]) + (c + t - 1) // t)
+                k = (K[g, bt[g, x]].view(-1, t, w, d)[:, :, s] * sk[g, x, None, None]).reshape(-1, d)[:c]
+                v = (V[g, bt[g, x]].view(-1, t, w, d)[:, :, s] * sv[g, x, None, None]).reshape(-1, d)[:c]
+                p = torch.softmax(qc[li, b, h * rep:(h + 1) * rep] @ k.T / d ** 0.5, -1)
+                out[li, b, h * rep:(h + 1) * rep] = p @ v
+    return out
+
+
+@pytest.mark.parametrize("t,d,heads,rep,all_heads", [(16, 128, 2, 4, False), (16, 64, 3, 1, False), (32, 128, 2, 8, False),
+                                                     (48, 64, 1, 3, False), (16, 128, 1, 16, False), (64, 128, 2, 7, False),
+                                                     (16, 128, 2, 4, True), (32, 64, 4, 2, True), (48, 128, 2, 16, True)])
+def test_against_binary64(t, d, heads, rep, all_heads):
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 7 * t + d + rep, all_heads=all_heads)
+    q = torch.randn(2, len(CONTEXTS), heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
+    ref = _reference(cache, t, d, heads, q, start, all_heads)
+    out = _call(kb, cache, heads, q, start, max_blocks, all_heads)
+    # A logit of this input is at most 10 (|q| |k| / sqrt(d) = sqrt(d), times a scale below 1.5, and the largest of a thousand
+    # normal draws at 4 of 1.5 standard deviations): its binary32 roundings move a weight by 10 * 3 * 2^-24 = 2e-6, and
+    # outputs, sums of values below 6 with weights that add to one, by 1.2e-5 at most.
+    assert float((out - ref).abs().max()) < 1.2e-5
+    assert float(out[:, CONTEXTS.index(0)].abs().max()) == 0.0
+
+
+def test_rows_past_the_context_and_infinite_values():
+    t, d, heads, rep = 32, 128, 2, 4
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 5)
+    n = cache.bt.shape[1]
+    cache.bt.copy_(torch.arange(n, dtype=torch.int32, device=DEV))         # one block each, so that tails can be spoilt
+    q = torch.randn(2, len(CONTEXTS), heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
+    clean = _call(kb, cache, heads, q, start, max_blocks, False)
+    K, V = cache.K.view(4, -1, t, d), cache.V.view(4, -1, t, d)
+    for b, c in enumerate(CONTEXTS):
+        if c % t:
+            K[:, int(start[b]) + c // t, c % t:] = float("nan")
+            V[:, int(start[b]) + c // t, c % t:] = float("nan")
+    assert torch.equal(_call(kb, cache, heads, q, start, max_blocks, False), clean)
+    # one infinite value inside a context: that column of that request is infinite for every head, all else is finite
+    b = CONTEXTS.index(300)
+    V[:, int(start[b]) + 3, 5, 77] = float("-inf")
+    out = _call(kb, cache, heads, q, start, max_blocks, False)
+    assert bool((out[:, b, :, 77] == float("-inf")).all())
+    keep = torch.ones_like(out, dtype=torch.bool)
+    keep[:, b, :, 77] = False
+    assert float((out[keep] - clean[keep]).abs().max()) < 1.2e-5           # the same bound as above
