@@ -72,60 +72,34 @@ struct PPiece {
     int tok_base;
 };
 
+// The context of a run of queries, piece by piece: the part before the chunk (distinct stored blocks with their instances),
+// then the chunk's own blocks up to pos_last.
 template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
-{
-    typedef bf16_t T;
-    constexpr int KS = D / 16;                 // MFMA steps along the head dimension for the logits
-    constexpr int DT = D / 32;                 // 32-row tiles of out^T
-    constexpr int KSTR = D * 2 + 16;           // bytes per token row of the K tile (pad: conflict-free 16-byte row reads)
-    constexpr int VSTR = D * 2 + 64;           // bytes per token row of the V tile (pad: conflict-free transpose reads)
-    constexpr int RCH = D / 8;                 // 16-byte chunks per token row
-    constexpr int LPT = 32 * RCH / 256;        // chunks per thread, per tensor and tile (2 for D = 128, 1 for D = 64)
+struct PWalk {
+    const bf16_t *kg, *vg;
+    const int32_t *btg;
+    const float *skg, *svg;
+    int64_t r;
+    int ppb, e0, n_pre, n_pieces;
 
-    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KSTR];
-    __shared__ __attribute__((aligned(16))) char v_lds[2][32 * VSTR];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kvh = blockIdx.y, li = blockIdx.z;
-    const int gi = li * A.kv_heads + kvh;                        // group index within the plan
-    const int g = (A.layer_begin + li) * A.kv_heads + kvh;
-    const int64_t r = (int64_t)A.t * D;
-    const T *kg = (const T *)A.kpool + (int64_t)g * A.P * r;
-    const T *vg = (const T *)A.vpool + (int64_t)g * A.P * r;
-    const int32_t *btg = A.bt + (int64_t)g * A.n;
-    const float *skg = A.scale_k + (int64_t)g * A.n;
-    const float *svg = A.scale_v + (int64_t)g * A.n;
-
-    // rows of this wavefront: lane & 31 = query row, lane >> 5 = which half of the tokens / head elements it holds
-    const int qrow = lane & 31, h2 = lane >> 5;
-    const int wg_first = A.q_begin + (int)blockIdx.x * 4 * A.npw;
-    const int pos_last_wg = min(A.q_end - 1, wg_first + 4 * A.npw - 1);
-    const int pos_first = wg_first + wave * A.npw;                // may lie past the end: such a wavefront only helps loading
-    const bool wave_live = pos_first < A.q_end;
-    const int pos_last = min(A.q_end - 1, pos_first + A.npw - 1);
-    const int rs = qrow / A.rep_pad, hh = qrow - rs * A.rep_pad;
-    const bool row_used = wave_live && pos_first + rs <= pos_last && hh < A.rep;
-    const int my_pos = wave_live ? min(pos_first + rs, pos_last) : A.q_end - 1;   // unused rows mask like a real one
-
-    uint4 qf[KS];                                     // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row
+    __device__ __forceinline__ PWalk(const PrefillArgs &A, int kvh, int li, int pos_last)
     {
-        const int64_t qi = (int64_t)li * (A.q_end - A.q_begin) + (my_pos - A.q_begin);
-        const T *qp = (const T *)A.q + (qi * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + 8 * h2;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            qf[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+        const int gi = li * A.kv_heads + kvh;                    // group index within the plan
+        const int g = (A.layer_begin + li) * A.kv_heads + kvh;
+        r = (int64_t)A.t * D;
+        kg = (const bf16_t *)A.kpool + (int64_t)g * A.P * r;
+        vg = (const bf16_t *)A.vpool + (int64_t)g * A.P * r;
+        btg = A.bt + (int64_t)g * A.n;
+        skg = A.scale_k + (int64_t)g * A.n;
+        svg = A.scale_v + (int64_t)g * A.n;
+        ppb = A.t / 16;                                          // pieces per block
+        e0 = A.entry_begin[gi];
+        n_pre = (A.entry_begin[gi + 1] - e0) * ppb;
+        n_pieces = n_pre + (pos_last - A.chunk_begin) / 16 + 1;
     }
 
-    // ---- the walk: pieces of the part before the chunk (distinct stored blocks with their instances), then the
-    //      chunk's own blocks up to the last position of this workgroup
-    const int ppb = A.t / 16;                                     // pieces per block
-    const int e0 = A.entry_begin[gi], e1 = A.entry_begin[gi + 1];
-    const int n_pre = (e1 - e0) * ppb;
-    const int n_pieces = n_pre + (pos_last_wg - A.chunk_begin) / 16 + 1;
-    const int n_tiles = (n_pieces + 1) / 2;
-    auto piece_at = [&](int p) __attribute__((always_inline)) {
+    __device__ __forceinline__ PPiece at(const PrefillArgs &A, int p) const
+    {
         PPiece pc;
         pc.k = kg; pc.v = vg; pc.ip = nullptr; pc.single = make_float2(0.0f, 0.0f); pc.n_inst = 0; pc.tok_base = 0;
         if (p < n_pre) {
@@ -149,7 +123,176 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
             pc.tok_base = tok;
         }
         return pc;
-    };
+    }
+};
+
+// Online softmax of one tile for this lane's query row: z = the logits of 16 of the tile's 32 tokens (the other 16 are with
+// lane ^ 32), pw = their weights summed over the instances of each piece, times the value scales.  Returns the factor that
+// the sums so far are rescaled by.
+__device__ static __forceinline__ float tile_weights(const PPiece &pc0, const PPiece &pc1, const floatx16 &z, float sm_scale, int h2,
+                                                     int my_pos, float &m_run, float &l_run, float (&pw)[16])
+{
+    // accumulator i of this lane: token 8 (i / 4) + 4 h2 + i % 4 of the tile, i.e. piece i / 8
+    // everything below works in base 2: exp(x) = exp2(x * log2(e)), and v_exp_f32 is an exp2
+    const float base = sm_scale * 1.4426950408889634f;
+    float bmax, m_new, corr, psum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        pw[i] = 0.0f;
+    // The common tile: both pieces lie before the chunk (visible to every query) and stand for one logical
+    // block each.  No masks and no instance loops: the kernel is bound by instruction issue, and this is
+    // where most of its instructions went.
+    const bool plain = pc0.tok_base < 0 && pc1.tok_base < 0 && pc0.n_inst == 1 && pc1.n_inst == 1;
+    if (__builtin_amdgcn_readfirstlane((int)plain)) {
+        const float2 s0 = pc0.ip[0], s1 = pc1.ip[0];
+        const float zs0 = base * s0.x, zs1 = base * s1.x;
+        float t[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            t[i] = z[i] * (i < 8 ? zs0 : zs1);
+        bmax = fmaxf(fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7]))),
+                     fmaxf(fmaxf(fmaxf(t[8], t[9]), fmaxf(t[10], t[11])), fmaxf(fmaxf(t[12], t[13]), fmaxf(t[14], t[15]))));
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        m_new = fmaxf(m_run, bmax);
+        corr = __builtin_amdgcn_exp2f(m_run - m_new);          // m_new is finite here; 0 on the very first tile
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float pr = __builtin_amdgcn_exp2f(t[i] - m_new);
+            psum += pr;
+            pw[i] = pr * (i < 8 ? s0.y : s1.y);
+        }
+    } else if (__builtin_amdgcn_readfirstlane((int)(pc0.tok_base < 0 && pc1.tok_base < 0 && pc1.n_inst > 0))) {
+        // both pieces before the chunk, several logical blocks behind at least one of them: instance loops, no masks
+        bmax = -INFINITY;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const PPiece &pc = half ? pc1 : pc0;
+            const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
+            for (int q = 0; q < ni; ++q) {
+                const float zs = base * pc.ip[q].x;
+#pragma unroll
+                for (int i = 8 * half; i < 8 * half + 8; ++i)
+                    bmax = fmaxf(bmax, z[i] * zs);
+            }
+        }
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        m_new = fmaxf(m_run, bmax);
+        corr = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const PPiece &pc = half ? pc1 : pc0;
+            const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
+            for (int q = 0; q < ni; ++q) {
+                const float2 sc = pc.ip[q];
+                const float zs = base * sc.x;
+#pragma unroll
+                for (int i = 8 * half; i < 8 * half + 8; ++i) {
+                    const float pr = __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new));
+                    psum += pr;
+                    pw[i] = fmaf(pr, sc.y, pw[i]);
+                }
+            }
+        }
+    } else {
+        // pieces before the chunk are visible to every query: no masks in that (common) case
+        const bool masked = pc0.tok_base >= 0 || pc1.tok_base >= 0 || pc1.n_inst == 0;
+        bool vis[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int tp = 8 * ((i >> 2) & 1) + 4 * h2 + (i & 3);
+            const PPiece &pc = i < 8 ? pc0 : pc1;
+            vis[i] = !masked || (pc.n_inst > 0 && pc.tok_base + tp <= my_pos);
+        }
+        bmax = -INFINITY;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const PPiece &pc = half ? pc1 : pc0;
+            for (int q = 0; q < pc.n_inst; ++q) {
+                const float zs = base * (pc.ip ? pc.ip[q].x : pc.single.x);
+#pragma unroll
+                for (int i = 8 * half; i < 8 * half + 8; ++i)
+                    bmax = fmaxf(bmax, vis[i] ? z[i] * zs : -INFINITY);
+            }
+        }
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        m_new = fmaxf(m_run, bmax);
+        corr = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first visible tile
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const PPiece &pc = half ? pc1 : pc0;
+            for (int q = 0; q < pc.n_inst; ++q) {
+                const float2 sc = pc.ip ? pc.ip[q] : pc.single;
+                const float zs = base * sc.x;
+#pragma unroll
+                for (int i = 8 * half; i < 8 * half + 8; ++i) {
+                    const float pr = vis[i] ? __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new)) : 0.0f;
+                    psum += pr;
+                    pw[i] = fmaf(pr, sc.y, pw[i]);
+                }
+            }
+        }
+    }
+    psum += __shfl_xor(psum, 32, 64);
+    l_run = l_run * corr + psum;
+    m_run = m_new;
+    return corr;
+}
+
+// The weights as B operands: the 8 values of MFMA jj are accumulators 8 jj .. 8 jj + 7, as a bfloat16 head (nearest) plus
+// the bfloat16 of what is left.
+__device__ static __forceinline__ void split_weights(const float (&pw)[16], bf16x8 (&p_hi)[2], bf16x8 (&p_lo)[2])
+{
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float w = pw[8 * jj + e];
+            const __bf16 hb = (__bf16)w;
+            p_hi[jj][e] = hb;
+            p_lo[jj][e] = (__bf16)(w - (float)hb);
+        }
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
+{
+    typedef bf16_t T;
+    constexpr int KS = D / 16;                 // MFMA steps along the head dimension for the logits
+    constexpr int DT = D / 32;                 // 32-row tiles of out^T
+    constexpr int KSTR = D * 2 + 16;           // bytes per token row of the K tile (pad: conflict-free 16-byte row reads)
+    constexpr int VSTR = D * 2 + 64;           // bytes per token row of the V tile (pad: conflict-free transpose reads)
+    constexpr int RCH = D / 8;                 // 16-byte chunks per token row
+    constexpr int LPT = 32 * RCH / 256;        // chunks per thread, per tensor and tile (2 for D = 128, 1 for D = 64)
+
+    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KSTR];
+    __shared__ __attribute__((aligned(16))) char v_lds[2][32 * VSTR];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kvh = blockIdx.y, li = blockIdx.z;
+
+    // rows of this wavefront: lane & 31 = query row, lane >> 5 = which half of the tokens / head elements it holds
+    const int qrow = lane & 31, h2 = lane >> 5;
+    const int wg_first = A.q_begin + (int)blockIdx.x * 4 * A.npw;
+    const int pos_last_wg = min(A.q_end - 1, wg_first + 4 * A.npw - 1);
+    const int pos_first = wg_first + wave * A.npw;                // may lie past the end: such a wavefront only helps loading
+    const bool wave_live = pos_first < A.q_end;
+    const int pos_last = min(A.q_end - 1, pos_first + A.npw - 1);
+    const int rs = qrow / A.rep_pad, hh = qrow - rs * A.rep_pad;
+    const bool row_used = wave_live && pos_first + rs <= pos_last && hh < A.rep;
+    const int my_pos = wave_live ? min(pos_first + rs, pos_last) : A.q_end - 1;   // unused rows mask like a real one
+
+    uint4 qf[KS];                                     // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row
+    {
+        const int64_t qi = (int64_t)li * (A.q_end - A.q_begin) + (my_pos - A.q_begin);
+        const T *qp = (const T *)A.q + (qi * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + 8 * h2;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            qf[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+    }
+
+    const PWalk<D> walk(A, kvh, li, pos_last_wg);
+    const int n_tiles = (walk.n_pieces + 1) / 2;
 
     // global -> registers -> LDS, LPT chunks per thread and tensor: chunk c of a tile = token c / RCH, row chunk c % RCH
     // two register sets: the tile after next is already on its way while the next one waits to be written to LDS
@@ -159,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
         for (int u = 0; u < LPT; ++u) {
             const int c = tid + 256 * u;
             const int tok = c / RCH, rc = c % RCH;                // token 0 .. 31 of the tile
-            const PPiece pc = piece_at(2 * ti + (tok >> 4));
+            const PPiece pc = walk.at(A, 2 * ti + (tok >> 4));
             const bool ok = pc.n_inst > 0;
             // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
             const bool v_ok = ok && pc.tok_base + (tok & 15) <= pos_last_wg;
@@ -203,111 +346,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
                 const uint4 ka = *reinterpret_cast<const uint4 *>(&k_lds[buf][k_off + ks * 32]);
                 z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
             }
-            // accumulator i of this lane: token 8 (i / 4) + 4 h2 + i % 4 of the tile, i.e. piece i / 8
-            const PPiece pc0 = piece_at(2 * ti), pc1 = piece_at(2 * ti + 1);
-            // everything below works in base 2: exp(x) = exp2(x * log2(e)), and v_exp_f32 is an exp2
-            constexpr float LOG2E = 1.4426950408889634f;
-            float bmax, m_new, corr, psum = 0.0f;
             float pw[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                pw[i] = 0.0f;
-            // The common tile: both pieces lie before the chunk (visible to every query) and stand for one logical
-            // block each.  No masks and no instance loops: the kernel is bound by instruction issue, and this is
-            // where most of its instructions went.
-            const bool plain = pc0.tok_base < 0 && pc1.tok_base < 0 && pc0.n_inst == 1 && pc1.n_inst == 1;
-            if (__builtin_amdgcn_readfirstlane((int)plain)) {
-                const float2 s0 = pc0.ip[0], s1 = pc1.ip[0];
-                const float zs0 = A.sm_scale * LOG2E * s0.x, zs1 = A.sm_scale * LOG2E * s1.x;
-                float t[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    t[i] = z[i] * (i < 8 ? zs0 : zs1);
-                bmax = fmaxf(fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7]))),
-                             fmaxf(fmaxf(fmaxf(t[8], t[9]), fmaxf(t[10], t[11])), fmaxf(fmaxf(t[12], t[13]), fmaxf(t[14], t[15]))));
-                bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-                m_new = fmaxf(m_run, bmax);
-                corr = __builtin_amdgcn_exp2f(m_run - m_new);          // m_new is finite here; 0 on the very first tile
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float pr = __builtin_amdgcn_exp2f(t[i] - m_new);
-                    psum += pr;
-                    pw[i] = pr * (i < 8 ? s0.y : s1.y);
-                }
-            } else if (__builtin_amdgcn_readfirstlane((int)(pc0.tok_base < 0 && pc1.tok_base < 0 && pc1.n_inst > 0))) {
-                // both pieces before the chunk, several logical blocks behind at least one of them: instance loops, no masks
-                bmax = -INFINITY;
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const PPiece &pc = half ? pc1 : pc0;
-                    const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
-                    for (int q = 0; q < ni; ++q) {
-                        const float zs = A.sm_scale * LOG2E * pc.ip[q].x;
-#pragma unroll
-                        for (int i = 8 * half; i < 8 * half + 8; ++i)
-                            bmax = fmaxf(bmax, z[i] * zs);
-                    }
-                }
-                bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-                m_new = fmaxf(m_run, bmax);
-                corr = __builtin_amdgcn_exp2f(m_run - m_new);
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const PPiece &pc = half ? pc1 : pc0;
-                    const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
-                    for (int q = 0; q < ni; ++q) {
-                        const float2 sc = pc.ip[q];
-                        const float zs = A.sm_scale * LOG2E * sc.x;
-#pragma unroll
-                        for (int i = 8 * half; i < 8 * half + 8; ++i) {
-                            const float pr = __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new));
-                            psum += pr;
-                            pw[i] = fmaf(pr, sc.y, pw[i]);
-                        }
-                    }
-                }
-            } else {
-                // pieces before the chunk are visible to every query: no masks in that (common) case
-                const bool masked = pc0.tok_base >= 0 || pc1.tok_base >= 0 || pc1.n_inst == 0;
-                bool vis[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int tp = 8 * ((i >> 2) & 1) + 4 * h2 + (i & 3);
-                    const PPiece &pc = i < 8 ? pc0 : pc1;
-                    vis[i] = !masked || (pc.n_inst > 0 && pc.tok_base + tp <= my_pos);
-                }
-                bmax = -INFINITY;
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const PPiece &pc = half ? pc1 : pc0;
-                    for (int q = 0; q < pc.n_inst; ++q) {
-                        const float zs = A.sm_scale * LOG2E * (pc.ip ? pc.ip[q].x : pc.single.x);
-#pragma unroll
-                        for (int i = 8 * half; i < 8 * half + 8; ++i)
-                            bmax = fmaxf(bmax, vis[i] ? z[i] * zs : -INFINITY);
-                    }
-                }
-                bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-                m_new = fmaxf(m_run, bmax);
-                corr = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first visible tile
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const PPiece &pc = half ? pc1 : pc0;
-                    for (int q = 0; q < pc.n_inst; ++q) {
-                        const float2 sc = pc.ip ? pc.ip[q] : pc.single;
-                        const float zs = A.sm_scale * LOG2E * sc.x;
-#pragma unroll
-                        for (int i = 8 * half; i < 8 * half + 8; ++i) {
-                            const float pr = vis[i] ? __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new)) : 0.0f;
-                            psum += pr;
-                            pw[i] = fmaf(pr, sc.y, pw[i]);
-                        }
-                    }
-                }
-            }
-            psum += __shfl_xor(psum, 32, 64);
-            l_run = l_run * corr + psum;
-            m_run = m_new;
+            const float corr = tile_weights(walk.at(A, 2 * ti), walk.at(A, 2 * ti + 1), z, A.sm_scale, h2, my_pos, m_run, l_run, pw);
             if (__builtin_amdgcn_ballot_w64(corr != 1.0f)) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
@@ -315,18 +355,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
                     for (int i = 0; i < 16; ++i)
                         o[dt][i] *= corr;
             }
-            // weights as B operands: the 8 values of MFMA jj are accumulators 8 jj .. 8 jj + 7, as a bfloat16 head
-            // (nearest) plus the bfloat16 of what is left
             bf16x8 p_hi[2], p_lo[2];
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float w = pw[8 * jj + e];
-                    const __bf16 hb = (__bf16)w;
-                    p_hi[jj][e] = hb;
-                    p_lo[jj][e] = (__bf16)(w - (float)hb);
-                }
+            split_weights(pw, p_hi, p_lo);
             // ---- out^T += V^T P^T
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
@@ -380,6 +410,161 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
             for (int g4 = 0; g4 < 4; ++g4)
                 *reinterpret_cast<float4 *>(dst + 32 * dt + 8 * g4) =
                     make_float4(o[dt][4 * g4] * inv, o[dt][4 * g4 + 1] * inv, o[dt][4 * g4 + 2] * inv, o[dt][4 * g4 + 3] * inv);
+    }
+}
+
+// The same attention for few queries: one set of 32 query rows per workgroup, the context dealt out to its 8 wavefronts tile
+// by tile.  Every wavefront fetches its own tiles straight into registers and needs no one else until the sums are merged
+// through LDS at the end: no barriers, no staging, so eight tiles are in flight per workgroup.  The staged kernel shares
+// every tile among 4 x 32 rows instead, which is the better trade once its own grid fills the chip.  Bound: latency of a tile
+// (table words, rows, two products, one after the other); 200 queries of 4296 tokens, 8 KV heads: 252 -> 47 us.
+//   V^T fragment dt of a lane (m = lane & 31): element dt of the DT consecutive head elements DT m .. that it loads of its 8
+//   tokens, one v_perm per two values; the tokens are those whose weights the lane already holds.
+constexpr int kSplitWaves = 8;
+// Grids of the staged kernel up to this many workgroups take the split kernel.  Both measured, staged / split, one layer of 8
+// KV heads and 4 query heads each over 4096 tokens: 8 workgroups (16 queries) 203 / 42 us, 64: 241 / 52, 128: 248 / 100, 192:
+// 258 / 153; over 512 tokens 128: 41 / 32.  From 256 on it depends on the length (4096 tokens: 269 / 204, 512 tokens: 46 / 56).
+constexpr int64_t kSplitBelow = 192;
+
+template <int D>
+__global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(PrefillArgs A)
+{
+    constexpr int KS = D / 16;                 // MFMA steps along the head dimension for the logits
+    constexpr int DT = D / 32;                 // 32-row tiles of out^T = head elements of a V row per lane
+    typedef uint32_t vrow_t __attribute__((ext_vector_type(DT / 2)));
+
+    __shared__ __attribute__((aligned(16))) float4 s_o[kSplitWaves / 2][4 * DT][64];
+    __shared__ float2 s_ml[kSplitWaves / 2][64];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kvh = blockIdx.y, li = blockIdx.z;
+    const int qrow = lane & 31, h2 = lane >> 5;
+    const int pos_first = A.q_begin + (int)blockIdx.x * A.npw;
+    const int pos_last = min(A.q_end - 1, pos_first + A.npw - 1);
+    const int rs = qrow / A.rep_pad, hh = qrow - rs * A.rep_pad;
+    const bool row_used = pos_first + rs <= pos_last && hh < A.rep;
+    const int my_pos = min(pos_first + rs, pos_last);             // unused rows mask like a real one
+    const int64_t qi = (int64_t)li * (A.q_end - A.q_begin) + (my_pos - A.q_begin);
+
+    uint4 qf[KS];                                     // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row
+    {
+        const bf16_t *qp = (const bf16_t *)A.q + (qi * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + 8 * h2;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            qf[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+    }
+    const PWalk<D> walk(A, kvh, li, pos_last);
+    const int n_tiles = (walk.n_pieces + 1) / 2;
+
+    float m_run = -INFINITY, l_run = 0.0f;
+    floatx16 o[DT];                            // o[dt][i]: head element DT (8 (i / 4) + 4 h2 + i % 4) + dt of this lane's row
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            o[dt][i] = 0.0f;
+
+    for (int ti = wave; ti < n_tiles; ti += kSplitWaves) {
+        const PPiece pc0 = walk.at(A, 2 * ti), pc1 = walk.at(A, 2 * ti + 1);
+        uint4 ka[KS];
+        vrow_t vr[2][8];                       // [piece][token slot e]: token 8 (e / 4) + 4 h2 + e % 4 of the piece
+        const bf16_t *kp = ((qrow & 16) ? pc1.k : pc0.k) + (int64_t)(qrow & 15) * D + 8 * h2;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            ka[ks] = *reinterpret_cast<const uint4 *>(kp + 16 * ks);
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                vr[jj][e] = *reinterpret_cast<const vrow_t *>((jj ? pc1.v : pc0.v) + (8 * (e >> 2) + 4 * h2 + (e & 3)) * D + DT * qrow);
+        floatx16 z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            z[i] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
+        float pw[16];
+        const float corr = tile_weights(pc0, pc1, z, A.sm_scale, h2, my_pos, m_run, l_run, pw);
+        if (pc0.tok_base >= 0 || pc1.tok_base >= 0) {
+            // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const PPiece &pc = jj ? pc1 : pc0;
+                    if (pc.n_inst == 0 || pc.tok_base + 8 * (e >> 2) + 4 * h2 + (e & 3) > pos_last)
+                        vr[jj][e] = (vrow_t)(0u);
+                }
+        }
+        if (__builtin_amdgcn_ballot_w64(corr != 1.0f)) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    o[dt][i] *= corr;
+        }
+        bf16x8 p_hi[2], p_lo[2];
+        split_weights(pw, p_hi, p_lo);
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const uint32_t sel = (dt & 1) ? 0x07060302u : 0x05040100u;
+                uint4 va;
+                va.x = __builtin_amdgcn_perm(vr[jj][1][dt / 2], vr[jj][0][dt / 2], sel);
+                va.y = __builtin_amdgcn_perm(vr[jj][3][dt / 2], vr[jj][2][dt / 2], sel);
+                va.z = __builtin_amdgcn_perm(vr[jj][5][dt / 2], vr[jj][4][dt / 2], sel);
+                va.w = __builtin_amdgcn_perm(vr[jj][7][dt / 2], vr[jj][6][dt / 2], sel);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), p_hi[jj], o[dt], 0, 0, 0);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), p_lo[jj], o[dt], 0, 0, 0);
+            }
+    }
+
+    // ---- merge: the upper half of the wavefronts hands its state to the lower half, lane by lane, until one is left
+    for (int half = kSplitWaves / 2; half > 0; half >>= 1) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    s_o[wave - half][4 * dt + v][lane] = make_float4(o[dt][4 * v], o[dt][4 * v + 1], o[dt][4 * v + 2], o[dt][4 * v + 3]);
+            s_ml[wave - half][lane] = make_float2(m_run, l_run);
+        }
+        __syncthreads();
+        if (wave < half) {
+            const float2 ml = s_ml[wave][lane];
+            const float m_new = fmaxf(m_run, ml.x);
+            const float fa = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+            const float fb = ml.x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml.x - m_new);
+            l_run = l_run * fa + ml.y * fb;
+            m_run = m_new;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float4 b = s_o[wave][4 * dt + v][lane];
+                    o[dt][4 * v] = o[dt][4 * v] * fa + b.x * fb;
+                    o[dt][4 * v + 1] = o[dt][4 * v + 1] * fa + b.y * fb;
+                    o[dt][4 * v + 2] = o[dt][4 * v + 2] * fa + b.z * fb;
+                    o[dt][4 * v + 3] = o[dt][4 * v + 3] * fa + b.w * fb;
+                }
+        }
+        __syncthreads();
+    }
+    if (wave == 0 && row_used) {
+        const float inv = l_run > 0.0f ? 1.0f / l_run : 0.0f;
+        float *dst = A.out + (qi * A.Hq + (int64_t)kvh * A.rep + hh) * D;
+        typedef float orow_t __attribute__((ext_vector_type(DT)));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            orow_t w;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+                w[dt] = o[dt][i] * inv;
+            *reinterpret_cast<orow_t *>(dst + DT * (8 * (i >> 2) + 4 * h2 + (i & 3))) = w;
+        }
     }
 }
 
@@ -577,8 +762,15 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
     A.req_start = plan->req_start; A.q_begin = plan->q_begin; A.q_end = plan->q_end; A.chunk_begin = plan->chunk_begin;
     A.sm_scale = sm_scale;
     const int per_wg = 4 * plan->npw;
-    const dim3 grid((unsigned)((nq + per_wg - 1) / per_wg), (unsigned)plan->kv_heads, (unsigned)plan->n_layers);
-    if (pool->d == 128)
+    const unsigned heads = (unsigned)plan->kv_heads, layers = (unsigned)plan->n_layers;
+    const dim3 grid((unsigned)((nq + per_wg - 1) / per_wg), heads, layers);
+    if ((int64_t)grid.x * heads * layers <= kSplitBelow) {
+        const dim3 sgrid((unsigned)((nq + plan->npw - 1) / plan->npw), heads, layers);
+        if (pool->d == 128)
+            prefill_split_kernel<128><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
+        else
+            prefill_split_kernel<64><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
+    } else if (pool->d == 128)
         prefill_attn_kernel<128><<<grid, 256, 0, c->stream>>>(A);
     else
         prefill_attn_kernel<64><<<grid, 256, 0, c->stream>>>(A);
