@@ -41,8 +41,13 @@ namespace kvfuse {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-struct PEntry {          // 16 bytes
+// A distinct stored block of the part before the chunk.  Its first two scale pairs stand beside it, so that most tiles need
+// one read of the table; the others are at inst_off + 2 ...
+struct PEntry {          // 48 bytes
     int32_t phys, inst_off, inst_cnt, pad;
+    float2 first, second;
+    float sk_max, sk_min;            // over the instances
+    float pad2[2];
 };
 
 struct PrefillArgs {
@@ -56,186 +61,190 @@ struct PrefillArgs {
     float *out;                      // [n_layers][Nq][Hq][D]
     int32_t P, n, t, kv_heads, layer_begin, Hq, rep, rep_pad, npw;
     int32_t req_start, q_begin, q_end, chunk_begin;
+    uint64_t ppb_inv;                // 2^40 / pieces per block, rounded up
     float sm_scale;
 };
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// One 16-token piece of the context: where its K and V rows are, whose scale pairs apply, and the absolute
-// position of its first token for the causal test (very negative = visible to every query).
-struct PPiece {
-    const bf16_t *k, *v;
-    const float2 *ip;       // instance list, or null: the single pair below
-    float2 single;
-    int n_inst;             // 0 = no such piece (past the end of the walk)
-    int tok_base;
+// One 16-token piece of the context: the words that tables hold of it, as they come from memory.  Nothing is computed from
+// them until they are used, a tile later, so that no wait stands between their loads; where they come from is a choice of
+// addresses and not a branch.
+struct PRows {              // where its rows are
+    int32_t phys, sub;      // stored block, piece of that block
+    int32_t tok_base;       // position of its first token for the causal test (very negative = visible to every query)
 };
+struct PScales {            // whose scale pairs apply
+    int32_t inst_cnt, inst_off;
+    float2 first, second;
+    float sk_max, sk_min;   // of a stored block before the chunk
+    int32_t tok_base;       // as above; kNowhere past the end of the walk
+};
+constexpr int32_t kBefore = -(1 << 30), kNowhere = 1 << 30;
 
 // The context of a run of queries, piece by piece: the part before the chunk (distinct stored blocks with their instances),
-// then the chunk's own blocks up to pos_last.
+// then the chunk's own blocks up to pos_last.  The piece's index is uniform over the wavefront, so its words are scalar loads.
 template <int D>
 struct PWalk {
     const bf16_t *kg, *vg;
     const int32_t *btg;
     const float *skg, *svg;
-    int64_t r;
-    int ppb, e0, n_pre, n_pieces;
+    const PEntry *eg;
+    int ppb, last_block, n_pre, n_pieces;
+    uint32_t inv_hi, inv_lo;                                     // 2^40 / ppb, rounded up
 
     __device__ __forceinline__ PWalk(const PrefillArgs &A, int kvh, int li, int pos_last)
     {
         const int gi = li * A.kv_heads + kvh;                    // group index within the plan
         const int g = (A.layer_begin + li) * A.kv_heads + kvh;
-        r = (int64_t)A.t * D;
+        const int64_t r = (int64_t)A.t * D;
+        const int64_t x = (int64_t)g * A.n + A.req_start + A.chunk_begin / A.t;
         kg = (const bf16_t *)A.kpool + (int64_t)g * A.P * r;
         vg = (const bf16_t *)A.vpool + (int64_t)g * A.P * r;
-        btg = A.bt + (int64_t)g * A.n;
-        skg = A.scale_k + (int64_t)g * A.n;
-        svg = A.scale_v + (int64_t)g * A.n;
+        btg = A.bt + x;                                          // the chunk's first block
+        skg = A.scale_k + x;
+        svg = A.scale_v + x;
         ppb = A.t / 16;                                          // pieces per block
-        e0 = A.entry_begin[gi];
-        n_pre = (A.entry_begin[gi + 1] - e0) * ppb;
+        inv_hi = (uint32_t)(A.ppb_inv >> 32);
+        inv_lo = (uint32_t)A.ppb_inv;
+        eg = A.entries + A.entry_begin[gi];
+        last_block = A.entry_begin[gi + 1] - A.entry_begin[gi] - 1;
+        n_pre = (last_block + 1) * ppb;
         n_pieces = n_pre + (pos_last - A.chunk_begin) / 16 + 1;
     }
 
-    __device__ __forceinline__ PPiece at(const PrefillArgs &A, int p) const
+    // p / ppb, exact for p * ppb < 2^40
+    __device__ __forceinline__ int block_of(int p) const
     {
-        PPiece pc;
-        pc.k = kg; pc.v = vg; pc.ip = nullptr; pc.single = make_float2(0.0f, 0.0f); pc.n_inst = 0; pc.tok_base = 0;
-        if (p < n_pre) {
-            const PEntry en = A.entries[e0 + p / ppb];
-            const int sub = (p % ppb) * 16;
-            pc.k = kg + (int64_t)en.phys * r + (int64_t)sub * D;
-            pc.v = vg + (int64_t)en.phys * r + (int64_t)sub * D;
-            pc.ip = A.inst + en.inst_off;
-            pc.n_inst = en.inst_cnt;
-            pc.tok_base = -(1 << 30);
-        } else if (p < n_pieces) {
-            const int cp = p - n_pre;
-            const int tok = A.chunk_begin + cp * 16;
-            const int x = A.req_start + tok / A.t;
-            const int phys = min(max(btg[x], 0), A.P - 1);      // a bad id in the table must not leave the pool
-            const int sub = tok % A.t;
-            pc.k = kg + (int64_t)phys * r + (int64_t)sub * D;
-            pc.v = vg + (int64_t)phys * r + (int64_t)sub * D;
-            pc.single = make_float2(skg[x], svg[x]);
-            pc.n_inst = 1;
-            pc.tok_base = tok;
-        }
-        return pc;
+        return (int)(((uint64_t)(uint32_t)p * inv_hi + __umulhi((uint32_t)p, inv_lo)) >> 8);
+    }
+
+    // past the end of the walk: the rows of the last piece (its values are not used, but they are there to be read)
+    __device__ __forceinline__ PRows rows(const PrefillArgs &A, int p) const
+    {
+        p = min(p, n_pieces - 1);
+        const bool pre = p < n_pre;
+        const int q = pre ? p : p - n_pre, b = block_of(q);
+        PRows rw;
+        rw.phys = *(pre ? &eg[b].phys : &btg[b]);
+        rw.sub = q - b * ppb;
+        rw.tok_base = pre ? kBefore : A.chunk_begin + q * 16;
+        return rw;
+    }
+    // first element of a piece's rows in the group's pool; a bad id in the table must not leave the pool
+    __device__ __forceinline__ int64_t first_row(const PrefillArgs &A, const PRows &rw) const
+    {
+        return ((int64_t)min(max(rw.phys, 0), A.P - 1) * ppb + rw.sub) * (16 * D);
+    }
+
+    __device__ __forceinline__ PScales scales(const PrefillArgs &A, int p) const
+    {
+        const bool pre = p < n_pre;
+        const int q = max(min(p, n_pieces - 1) - n_pre, 0);
+        // no entries at all: unused words of the plan's own memory
+        const PEntry *en = &eg[max(min(block_of(p), last_block), 0)];
+        PScales sc;
+        sc.inst_cnt = en->inst_cnt; sc.inst_off = en->inst_off;
+        sc.first.x = *(pre ? &en->first.x : &skg[block_of(q)]);
+        sc.first.y = *(pre ? &en->first.y : &svg[block_of(q)]);
+        sc.second = en->second;
+        sc.sk_max = en->sk_max; sc.sk_min = en->sk_min;
+        sc.tok_base = pre ? kBefore : p < n_pieces ? A.chunk_begin + q * 16 : kNowhere;
+        return sc;
     }
 };
 
-// Online softmax of one tile for this lane's query row: z = the logits of 16 of the tile's 32 tokens (the other 16 are with
-// lane ^ 32), pw = their weights summed over the instances of each piece, times the value scales.  Returns the factor that
-// the sums so far are rescaled by.
-__device__ static __forceinline__ float tile_weights(const PPiece &pc0, const PPiece &pc1, const floatx16 &z, float sm_scale, int h2,
-                                                     int my_pos, float &m_run, float &l_run, float (&pw)[16])
+// max or sum over the two lanes that share a query row (lane, lane ^ 32)
+__device__ static __forceinline__ float halves_max(float x)
 {
-    // accumulator i of this lane: token 8 (i / 4) + 4 h2 + i % 4 of the tile, i.e. piece i / 8
-    // everything below works in base 2: exp(x) = exp2(x * log2(e)), and v_exp_f32 is an exp2
-    const float base = sm_scale * 1.4426950408889634f;
-    float bmax, m_new, corr, psum = 0.0f;
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ static __forceinline__ float halves_sum(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Online softmax of one tile for this lane's query row: z = the logits of 16 of the tile's 32 tokens (the other 16 are with
+// lane ^ 32): accumulator i is token 8 (i / 4) + 4 h2 + i % 4 of the tile, i.e. piece i / 8.  pw = their weights summed over
+// the instances of each piece, times the value scales; l_run sums the weights of this lane's tokens only.  Everything works
+// in base 2: exp(x) = exp2(x * log2(e)), and v_exp_f32 is an exp2.
+// Returns the factor that the sums so far are rescaled by.  (Letting the maximum lag by up to 2^8 would save most rescalings,
+// but a row that sees a single token then loses the exact weight of one: error 1.9e-6 -> 2.4e-6 on short contexts.)
+template <bool MASKED>
+__device__ static __forceinline__ float tile_weights_as(const PrefillArgs &A, const PScales &s0, const PScales &s1, const floatx16 &z,
+                                                        int h2, int my_pos, float &m_run, float &l_run, float (&pw)[16])
+{
+    const float base = A.sm_scale * 1.4426950408889634f;
+    // tokens of a piece that this row sees: those whose offset from the lane's first one (i % 4, + 8) is at most `last`
+    const int last0 = my_pos - s0.tok_base - 4 * h2, last1 = my_pos - s1.tok_base - 4 * h2;
+    auto seen = [&](int i) __attribute__((always_inline)) {
+        return !MASKED || 8 * ((i >> 2) & 1) + (i & 3) <= (i < 8 ? last0 : last1);
+    };
+    // ---- the largest scaled logit of each piece: a product's extremes lie at the extremes of its factors
+    float bmax = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-        pw[i] = 0.0f;
-    // The common tile: both pieces lie before the chunk (visible to every query) and stand for one logical
-    // block each.  No masks and no instance loops: the kernel is bound by instruction issue, and this is
-    // where most of its instructions went.
-    const bool plain = pc0.tok_base < 0 && pc1.tok_base < 0 && pc0.n_inst == 1 && pc1.n_inst == 1;
-    if (__builtin_amdgcn_readfirstlane((int)plain)) {
-        const float2 s0 = pc0.ip[0], s1 = pc1.ip[0];
-        const float zs0 = base * s0.x, zs1 = base * s1.x;
-        float t[16];
+    for (int half = 0; half < 2; ++half) {
+        const PScales &sc = half ? s1 : s0;
+        const bool own = MASKED && sc.tok_base >= 0;
+        const float big = own ? sc.first.x : sc.sk_max, small = own ? sc.first.x : sc.sk_min;
+        float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            t[i] = z[i] * (i < 8 ? zs0 : zs1);
-        bmax = fmaxf(fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7]))),
-                     fmaxf(fmaxf(fmaxf(t[8], t[9]), fmaxf(t[10], t[11])), fmaxf(fmaxf(t[12], t[13]), fmaxf(t[14], t[15]))));
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        m_new = fmaxf(m_run, bmax);
-        corr = __builtin_amdgcn_exp2f(m_run - m_new);          // m_new is finite here; 0 on the very first tile
+        for (int i = 8 * half; i < 8 * half + 8; ++i)
+            hi = fmaxf(hi, seen(i) ? z[i] : -INFINITY);
+        if (hi > -INFINITY)
+            bmax = fmaxf(bmax, fmaxf(hi * big, hi * small));
+        if (small < 0.0f) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float pr = __builtin_amdgcn_exp2f(t[i] - m_new);
+            for (int i = 8 * half; i < 8 * half + 8; ++i)
+                lo = fminf(lo, seen(i) ? z[i] : INFINITY);
+            if (lo < INFINITY)
+                bmax = fmaxf(bmax, fmaxf(lo * big, lo * small));
+        }
+    }
+    const float m_new = fmaxf(m_run, halves_max(bmax) * base);
+    const float corr = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);      // 0 on the first visible tile
+    m_run = m_new;
+    float psum = 0.0f;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const PScales &sc = half ? s1 : s0;
+        const float zs = base * sc.first.x, sv = sc.first.y;
+#pragma unroll
+        for (int i = 8 * half; i < 8 * half + 8; ++i) {
+            const float e = __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new));
+            const float pr = seen(i) ? e : 0.0f;
             psum += pr;
-            pw[i] = pr * (i < 8 ? s0.y : s1.y);
+            pw[i] = pr * sv;
         }
-    } else if (__builtin_amdgcn_readfirstlane((int)(pc0.tok_base < 0 && pc1.tok_base < 0 && pc1.n_inst > 0))) {
-        // both pieces before the chunk, several logical blocks behind at least one of them: instance loops, no masks
-        bmax = -INFINITY;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const PPiece &pc = half ? pc1 : pc0;
-            const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
-            for (int q = 0; q < ni; ++q) {
-                const float zs = base * pc.ip[q].x;
-#pragma unroll
-                for (int i = 8 * half; i < 8 * half + 8; ++i)
-                    bmax = fmaxf(bmax, z[i] * zs);
-            }
-        }
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        m_new = fmaxf(m_run, bmax);
-        corr = __builtin_amdgcn_exp2f(m_run - m_new);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const PPiece &pc = half ? pc1 : pc0;
-            const int ni = __builtin_amdgcn_readfirstlane(pc.n_inst);
-            for (int q = 0; q < ni; ++q) {
-                const float2 sc = pc.ip[q];
-                const float zs = base * sc.x;
+        const int n_inst = MASKED && sc.tok_base >= 0 ? 1 : sc.inst_cnt;
+        if (n_inst > 1) {                // before the chunk, and visible to every query
+            float2 next = sc.second;
+            for (int q = 1; q < n_inst; ++q) {
+                const float zq = base * next.x, vq = next.y;
+                if (q + 1 < n_inst)
+                    next = A.inst[sc.inst_off + q + 1];
 #pragma unroll
                 for (int i = 8 * half; i < 8 * half + 8; ++i) {
-                    const float pr = __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new));
+                    const float pr = __builtin_amdgcn_exp2f(fmaf(z[i], zq, -m_new));
                     psum += pr;
-                    pw[i] = fmaf(pr, sc.y, pw[i]);
-                }
-            }
-        }
-    } else {
-        // pieces before the chunk are visible to every query: no masks in that (common) case
-        const bool masked = pc0.tok_base >= 0 || pc1.tok_base >= 0 || pc1.n_inst == 0;
-        bool vis[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int tp = 8 * ((i >> 2) & 1) + 4 * h2 + (i & 3);
-            const PPiece &pc = i < 8 ? pc0 : pc1;
-            vis[i] = !masked || (pc.n_inst > 0 && pc.tok_base + tp <= my_pos);
-        }
-        bmax = -INFINITY;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const PPiece &pc = half ? pc1 : pc0;
-            for (int q = 0; q < pc.n_inst; ++q) {
-                const float zs = base * (pc.ip ? pc.ip[q].x : pc.single.x);
-#pragma unroll
-                for (int i = 8 * half; i < 8 * half + 8; ++i)
-                    bmax = fmaxf(bmax, vis[i] ? z[i] * zs : -INFINITY);
-            }
-        }
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        m_new = fmaxf(m_run, bmax);
-        corr = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first visible tile
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const PPiece &pc = half ? pc1 : pc0;
-            for (int q = 0; q < pc.n_inst; ++q) {
-                const float2 sc = pc.ip ? pc.ip[q] : pc.single;
-                const float zs = base * sc.x;
-#pragma unroll
-                for (int i = 8 * half; i < 8 * half + 8; ++i) {
-                    const float pr = vis[i] ? __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new)) : 0.0f;
-                    psum += pr;
-                    pw[i] = fmaf(pr, sc.y, pw[i]);
+                    pw[i] = fmaf(pr, vq, pw[i]);
                 }
             }
         }
     }
-    psum += __shfl_xor(psum, 32, 64);
     l_run = l_run * corr + psum;
-    m_run = m_new;
     return corr;
+}
+
+__device__ static __forceinline__ float tile_weights(const PrefillArgs &A, const PScales &s0, const PScales &s1, const floatx16 &z,
+                                                     int h2, int my_pos, float &m_run, float &l_run, float (&pw)[16])
+{
+    if (s0.tok_base >= 0 || s1.tok_base >= 0)
+        return tile_weights_as<true>(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+    return tile_weights_as<false>(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
 }
 
 // The weights as B operands: the 8 values of MFMA jj are accumulators 8 jj .. 8 jj + 7, as a bfloat16 head (nearest) plus
@@ -296,28 +305,36 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
 
     // global -> registers -> LDS, LPT chunks per thread and tensor: chunk c of a tile = token c / RCH, row chunk c % RCH
     // two register sets: the tile after next is already on its way while the next one waits to be written to LDS
-    uint4 kr0[LPT], vr0[LPT], kr1[LPT], vr1[LPT];
-    auto fetch = [&](int ti, uint4 (&kreg)[LPT], uint4 (&vreg)[LPT]) __attribute__((always_inline)) {
+    typedef uint32_t chunk_t __attribute__((ext_vector_type(4)));
+    chunk_t kr0[LPT], vr0[LPT], kr1[LPT], vr1[LPT];
+    auto fetch = [&](PRows r0, PRows r1, chunk_t (&kreg)[LPT], chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
+        const int64_t u0 = walk.first_row(A, r0), u1 = walk.first_row(A, r1);
 #pragma unroll
         for (int u = 0; u < LPT; ++u) {
             const int c = tid + 256 * u;
-            const int tok = c / RCH, rc = c % RCH;                // token 0 .. 31 of the tile
-            const PPiece pc = walk.at(A, 2 * ti + (tok >> 4));
-            const bool ok = pc.n_inst > 0;
-            // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
-            const bool v_ok = ok && pc.tok_base + (tok & 15) <= pos_last_wg;
-            const int64_t off = (int64_t)(tok & 15) * D + rc * 8;
-            kreg[u] = ok ? *reinterpret_cast<const uint4 *>(pc.k + off) : make_uint4(0, 0, 0, 0);
-            vreg[u] = v_ok ? *reinterpret_cast<const uint4 *>(pc.v + off) : make_uint4(0, 0, 0, 0);
+            const bool second = RCH == 16 ? u == 1 : (wave & 2) != 0;          // the chunks of a wavefront lie in one piece
+            const int64_t off = (second ? u1 : u0) + (c % (16 * RCH)) * 8;
+            kreg[u] = *reinterpret_cast<const chunk_t *>(walk.kg + off);
+            vreg[u] = *reinterpret_cast<const chunk_t *>(walk.vg + off);
         }
     };
-    auto stash = [&](int buf, const uint4 (&kreg)[LPT], const uint4 (&vreg)[LPT]) __attribute__((always_inline)) {
+    // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
+    auto hide = [&](PRows r0, PRows r1, chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const bool second = RCH == 16 ? u == 1 : (wave & 2) != 0;
+            const int tok_base = second ? r1.tok_base : r0.tok_base;
+            const bool hidden = tok_base + ((tid + 256 * u) / RCH & 15) > pos_last_wg;
+            vreg[u] = hidden ? (chunk_t)(0u) : vreg[u];
+        }
+    };
+    auto stash = [&](int buf, const chunk_t (&kreg)[LPT], const chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < LPT; ++u) {
             const int c = tid + 256 * u;
             const int tok = c / RCH, rc = c % RCH;
-            *reinterpret_cast<uint4 *>(&k_lds[buf][tok * KSTR + rc * 16]) = kreg[u];
-            *reinterpret_cast<uint4 *>(&v_lds[buf][tok * VSTR + rc * 16]) = vreg[u];
+            *reinterpret_cast<chunk_t *>(&k_lds[buf][tok * KSTR + rc * 16]) = kreg[u];
+            *reinterpret_cast<chunk_t *>(&v_lds[buf][tok * VSTR + rc * 16]) = vreg[u];
         }
     };
 
@@ -334,70 +351,104 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
     const int l16 = lane & 15;
     const int v_off = (4 * h2 + (l16 >> 2)) * VSTR + (16 * ((lane >> 4) & 1) + 4 * (l16 & 3)) * 2;
 
-    auto compute = [&](int ti, int buf) __attribute__((always_inline)) {
-        if (wave_live) {
-            // ---- logits^T of the tile: 32 tokens x 32 query rows
-            floatx16 z;
+    // Bound: the softmax's vector instructions and the matrix instructions of a SIMD's two wavefronts hardly overlap (per tile
+    // 270 of the former, 24 of the latter: 51 and 30 % of the cycles).  2048 queries of a 32768-token prompt, 4 layers of 8 KV
+    // heads, a third of the blocks fused: 7.15 -> 5.70 ms since table words and fragments come ahead of their use and the
+    // maximum is taken before the scales are applied.
+    // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
+    // before the first product, the V fragments and the next tiles' table words (which wait on the same counter) before the
+    // softmax.  The compiler left to itself reads one fragment, waits, multiplies.
+    auto compute = [&](const PScales &s0, const PScales &s1, int buf, auto &&tables) __attribute__((always_inline)) {
+        uint4 ka[KS];
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                z[i] = 0.0f;
+        for (int ks = 0; ks < KS; ++ks)
+            ka[ks] = *reinterpret_cast<const uint4 *>(&k_lds[buf][k_off + ks * 32]);
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- logits^T of the tile: 32 tokens x 32 query rows
+        floatx16 z;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const uint4 ka = *reinterpret_cast<const uint4 *>(&k_lds[buf][k_off + ks * 32]);
-                z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
+        for (int i = 0; i < 16; ++i)
+            z[i] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x4 vt[2][DT][2];
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const char *vp = &v_lds[buf][v_off + (16 * jj) * VSTR + dt * 64];
+                vt[jj][dt][0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp));
+                vt[jj][dt][1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp + 8 * VSTR));
             }
-            float pw[16];
-            const float corr = tile_weights(walk.at(A, 2 * ti), walk.at(A, 2 * ti + 1), z, A.sm_scale, h2, my_pos, m_run, l_run, pw);
-            if (__builtin_amdgcn_ballot_w64(corr != 1.0f)) {
+        tables();
+        __builtin_amdgcn_sched_barrier(0);
+        float pw[16];
+        const float corr = tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+        if (__builtin_amdgcn_ballot_w64(corr != 1.0f)) {
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+            for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        o[dt][i] *= corr;
-            }
-            bf16x8 p_hi[2], p_lo[2];
-            split_weights(pw, p_hi, p_lo);
-            // ---- out^T += V^T P^T
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    const char *vp = &v_lds[buf][v_off + (16 * jj) * VSTR + dt * 64];
-                    const bf16x4 t0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                        (__attribute__((address_space(3))) bf16x4 *)(vp));
-                    const bf16x4 t1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                        (__attribute__((address_space(3))) bf16x4 *)(vp + 8 * VSTR));
-                    const bf16x8 va = __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7);
-                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, p_hi[jj], o[dt], 0, 0, 0);
-                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, p_lo[jj], o[dt], 0, 0, 0);
-                }
-            }
+                for (int i = 0; i < 16; ++i)
+                    o[dt][i] *= corr;
         }
+        bf16x8 p_hi[2], p_lo[2];
+        split_weights(pw, p_hi, p_lo);
+        // ---- out^T += V^T P^T
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const bf16x8 va = __builtin_shufflevector(vt[jj][dt][0], vt[jj][dt][1], 0, 1, 2, 3, 4, 5, 6, 7);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, p_hi[jj], o[dt], 0, 0, 0);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, p_lo[jj], o[dt], 0, 0, 0);
+            }
     };
 
-    fetch(0, kr0, vr0);
-    if (n_tiles > 1)
-        fetch(1, kr1, vr1);
+    // The rows of the tiles whose values wait in register set 0 (a), in set 1 (b), of the next fetch (c).
+    PRows a0 = walk.rows(A, 0), a1 = walk.rows(A, 1), b0 = walk.rows(A, 2), b1 = walk.rows(A, 3), c0 = walk.rows(A, 4), c1 = walk.rows(A, 5);
+    PScales sa0 = walk.scales(A, 0), sa1 = walk.scales(A, 1), sb0, sb1;
+    fetch(a0, a1, kr0, vr0);
+    fetch(b0, b1, kr1, vr1);
+    hide(a0, a1, vr0);
     stash(0, kr0, vr0);
     __syncthreads();
     for (int ti = 0; ti < n_tiles; ti += 2) {
         // tile ti is in buffer 0, tile ti + 1 in register set 1
+        a0 = c0;
+        a1 = c1;
         if (ti + 2 < n_tiles)
-            fetch(ti + 2, kr0, vr0);
-        compute(ti, 0);
-        if (ti + 1 < n_tiles)
-            stash(1, kr1, vr1);
-        __syncthreads();
+            fetch(a0, a1, kr0, vr0);
+        compute(sa0, sa1, 0, [&]() __attribute__((always_inline)) {
+            c0 = walk.rows(A, 2 * (ti + 3));
+            c1 = walk.rows(A, 2 * (ti + 3) + 1);
+            sb0 = walk.scales(A, 2 * (ti + 1));
+            sb1 = walk.scales(A, 2 * (ti + 1) + 1);
+        });
         if (ti + 1 >= n_tiles)
             break;
+        hide(b0, b1, vr1);
+        stash(1, kr1, vr1);
+        __syncthreads();
         // tile ti + 1 is in buffer 1, tile ti + 2 in register set 0
+        b0 = c0;
+        b1 = c1;
         if (ti + 3 < n_tiles)
-            fetch(ti + 3, kr1, vr1);
-        compute(ti + 1, 1);
-        if (ti + 2 < n_tiles)
+            fetch(b0, b1, kr1, vr1);
+        compute(sb0, sb1, 1, [&]() __attribute__((always_inline)) {
+            c0 = walk.rows(A, 2 * (ti + 4));
+            c1 = walk.rows(A, 2 * (ti + 4) + 1);
+            sa0 = walk.scales(A, 2 * (ti + 2));
+            sa1 = walk.scales(A, 2 * (ti + 2) + 1);
+        });
+        if (ti + 2 < n_tiles) {
+            hide(a0, a1, vr0);
             stash(0, kr0, vr0);
+        }
         __syncthreads();
     }
+    l_run = halves_sum(l_run);
 
     // ---- normalise and store: this lane holds out[row qrow][head element 32 dt + 8 (i / 4) + 4 h2 + i % 4]
     if (row_used) {
@@ -422,8 +473,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
 //   tokens, one v_perm per two values; the tokens are those whose weights the lane already holds.
 constexpr int kSplitWaves = 8;
 // Grids of the staged kernel up to this many workgroups take the split kernel.  Both measured, staged / split, one layer of 8
-// KV heads and 4 query heads each over 4096 tokens: 8 workgroups (16 queries) 203 / 42 us, 64: 241 / 52, 128: 248 / 100, 192:
-// 258 / 153; over 512 tokens 128: 41 / 32.  From 256 on it depends on the length (4096 tokens: 269 / 204, 512 tokens: 46 / 56).
+// KV heads and 4 query heads each over 4096 tokens: 8 workgroups (16 queries) 151 / 43 us, 64: 181 / 50, 128: 187 / 99, 192:
+// 188 / 149; over 512 tokens 128: 31 / 31.  At 256 they are level (195 / 198), over 512 tokens the split kernel loses (36 / 54).
 constexpr int64_t kSplitBelow = 192;
 
 template <int D>
@@ -465,11 +516,14 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
         for (int i = 0; i < 16; ++i)
             o[dt][i] = 0.0f;
 
+    PRows r0 = walk.rows(A, 2 * wave), r1 = walk.rows(A, 2 * wave + 1);       // a tile ahead of their use
+    PScales n0 = walk.scales(A, 2 * wave), n1 = walk.scales(A, 2 * wave + 1);
     for (int ti = wave; ti < n_tiles; ti += kSplitWaves) {
-        const PPiece pc0 = walk.at(A, 2 * ti), pc1 = walk.at(A, 2 * ti + 1);
+        const int64_t u0 = walk.first_row(A, r0), u1 = walk.first_row(A, r1);
+        const PScales s0 = n0, s1 = n1;
         uint4 ka[KS];
         vrow_t vr[2][8];                       // [piece][token slot e]: token 8 (e / 4) + 4 h2 + e % 4 of the piece
-        const bf16_t *kp = ((qrow & 16) ? pc1.k : pc0.k) + (int64_t)(qrow & 15) * D + 8 * h2;
+        const bf16_t *kp = walk.kg + ((qrow & 16) ? u1 : u0) + (qrow & 15) * D + 8 * h2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             ka[ks] = *reinterpret_cast<const uint4 *>(kp + 16 * ks);
@@ -477,7 +531,12 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                vr[jj][e] = *reinterpret_cast<const vrow_t *>((jj ? pc1.v : pc0.v) + (8 * (e >> 2) + 4 * h2 + (e & 3)) * D + DT * qrow);
+                vr[jj][e] = *reinterpret_cast<const vrow_t *>(walk.vg + (jj ? u1 : u0) + (8 * (e >> 2) + 4 * h2 + (e & 3)) * D + DT * qrow);
+        r0 = walk.rows(A, 2 * (ti + kSplitWaves));
+        r1 = walk.rows(A, 2 * (ti + kSplitWaves) + 1);
+        n0 = walk.scales(A, 2 * (ti + kSplitWaves));
+        n1 = walk.scales(A, 2 * (ti + kSplitWaves) + 1);
+        __builtin_amdgcn_sched_barrier(0);     // all loads of the tile are on their way before the first wait
         floatx16 z;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
@@ -486,15 +545,15 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
         for (int ks = 0; ks < KS; ++ks)
             z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
         float pw[16];
-        const float corr = tile_weights(pc0, pc1, z, A.sm_scale, h2, my_pos, m_run, l_run, pw);
-        if (pc0.tok_base >= 0 || pc1.tok_base >= 0) {
+        const float corr = tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+        if (s0.tok_base >= 0 || s1.tok_base >= 0) {
             // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const PPiece &pc = jj ? pc1 : pc0;
-                    if (pc.n_inst == 0 || pc.tok_base + 8 * (e >> 2) + 4 * h2 + (e & 3) > pos_last)
+                    const PScales &sc = jj ? s1 : s0;
+                    if (sc.tok_base + 8 * (e >> 2) + 4 * h2 + (e & 3) > pos_last)
                         vr[jj][e] = (vrow_t)(0u);
                 }
         }
@@ -522,6 +581,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
             }
     }
 
+    l_run = halves_sum(l_run);
     // ---- merge: the upper half of the wavefronts hands its state to the lower half, lane by lane, until one is left
     for (int half = kSplitWaves / 2; half > 0; half >>= 1) {
         if (wave >= half && wave < 2 * half) {
@@ -676,8 +736,19 @@ int kvfuse_prefill_plan_build(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kv
             en.inst_off = (int32_t)pl->inst.size();
             en.inst_cnt = (int32_t)(e - s);
             en.pad = 0;
-            for (size_t k = s; k < e; ++k)
-                pl->inst.push_back(make_float2(sk[(size_t)gi * nb_pre + order[k].second], sv[(size_t)gi * nb_pre + order[k].second]));
+            en.pad2[0] = en.pad2[1] = 0.0f;
+            for (size_t k = s; k < e; ++k) {
+                const float2 pair = make_float2(sk[(size_t)gi * nb_pre + order[k].second], sv[(size_t)gi * nb_pre + order[k].second]);
+                pl->inst.push_back(pair);
+                if (k == s) {
+                    en.first = en.second = pair;
+                    en.sk_max = en.sk_min = pair.x;
+                }
+                if (k == s + 1)
+                    en.second = pair;
+                en.sk_max = std::max(en.sk_max, pair.x);
+                en.sk_min = std::min(en.sk_min, pair.x);
+            }
             pl->entries.push_back(en);
             s = e;
         }
@@ -760,6 +831,7 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
     A.P = pool->P; A.n = table->n; A.t = pool->t; A.kv_heads = plan->kv_heads; A.layer_begin = plan->layer_begin;
     A.Hq = plan->Hq; A.rep = plan->rep; A.rep_pad = plan->rep_pad; A.npw = plan->npw;
     A.req_start = plan->req_start; A.q_begin = plan->q_begin; A.q_end = plan->q_end; A.chunk_begin = plan->chunk_begin;
+    A.ppb_inv = ((1ull << 40) + (uint64_t)(pool->t / 16) - 1) / (uint64_t)(pool->t / 16);
     A.sm_scale = sm_scale;
     const int per_wg = 4 * plan->npw;
     const unsigned heads = (unsigned)plan->kv_heads, layers = (unsigned)plan->n_layers;
