@@ -52,6 +52,7 @@ struct HeightDesc {
     const int32_t *l_base, *r_base;   // [n_nodes + 1] prefix sums of the capacities
     const int64_t *s_base;            // [n_nodes + 1] prefix sums of l_cap * r_cap
     int32_t item_cap;                 // most similarity work items one group can have at this height (see similarity.hip)
+    int32_t small_tiles;              // most 32 x 32 tiles one node can have
     bool use_big_tiles;
     int64_t total_s;
 };

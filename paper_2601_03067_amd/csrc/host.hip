@@ -32,6 +32,7 @@ struct Node {
 struct HostHeight {
     std::vector<int32_t> l_off, r_off, l_slot, r_slot, out_slot, l_cap, r_cap, l_base, r_base;
     int item_cap = 0;                                          // most similarity work items of one group
+    int small_tiles = 1;
     bool big = false;
     std::vector<int64_t> s_base;
     HeightDesc dev;
@@ -229,6 +230,8 @@ static void build_heights(const std::vector<Node> &nodes, std::vector<HostHeight
             const int n_cp = (h.r_cap[k] + bn - 1) / bn;
             const int n_rtile = (h.l_cap[k] + bm - 1) / bm;
             cap += (int64_t)n_cp * (n_rtile < 4 ? n_rtile : std::max(4, (n_rtile + 3) / 4));
+            const int64_t small = (int64_t)((h.l_cap[k] + 31) / 32) * ((h.r_cap[k] + 31) / 32);
+            h.small_tiles = (int)std::min<int64_t>(std::max<int64_t>(h.small_tiles, small), INT32_MAX);
         }
         h.item_cap = (int)std::min<int64_t>(cap, INT32_MAX);
     }
@@ -301,6 +304,7 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
         d.total_l_cap = h.l_base[nn];
         d.total_r_cap = h.r_base[nn];
         d.total_s = h.s_base[nn];
+        d.small_tiles = h.small_tiles;
         d.use_big_tiles = h.big;
         d.item_cap = h.item_cap;
         d.l_off = cv.take<int32_t>(nn);

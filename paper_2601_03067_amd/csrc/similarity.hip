@@ -1024,6 +1024,105 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
 #undef KVF_SIM_LAUNCH
 }
 
+// ---- small heights -----------------------------------------------------------------------------------------------
+//
+// When the tiles of a height cannot fill the chip, what it costs is one workgroup's walk along K: 64 slices of a 2048-element
+// row, each behind a barrier (4 sets of 8 binary32 blocks of 1024 elements: 32 us).  Here a workgroup takes one 32 x 32 tile and
+// its 8 wavefronts an eighth of the row each, straight from memory into fragments, with no barrier until the eight partial
+// products are added up in LDS.  The tiles follow from the sets' sizes, so no work items are laid out.  Nodes of at most 32 x
+// 32 blocks always come here (one tile each, where the 128 x 128 kernel computes one MFMA tile of sixteen); larger ones while
+// all tiles run at once: up to 512 of them, two per compute unit.  Both measured (us, similarity of a whole tree, ring / small):
+// 4 x 8 blocks, 8 groups 66 / 29; 8 x 64 blocks, 8 groups 127 / 65; 32 x 16 blocks, 256 groups 787 / 386; with the line at 4096
+// tiles 8 x 28 blocks, 256 groups take 286 instead of 167.
+constexpr int kSmallWaves = 8;
+constexpr int64_t kSmallTiles = 512;
+
+template <typename T>
+__global__ __launch_bounds__(64 * kSmallWaves, 2) void similarity_small_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, float thr_floor)
+{
+    constexpr int BATCH = 4;                     // 64-byte slices of both rows that are on their way at a time
+    __shared__ float red[kSmallWaves][16][64];
+    const int v = blockIdx.x;
+    const int tile = v % h.small_tiles;
+    const int node = (v / h.small_tiles) % h.n_nodes;
+    const int g = v / h.small_tiles / h.n_nodes;
+    if (w.group_enable && !w.group_enable[g])
+        return;
+    const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[node]];
+    const int mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[node]];
+    const int n_ct = (mr + 31) >> 5;
+    if (tile >= n_ct * ((ml + 31) >> 5))
+        return;
+    const int row0 = (tile / n_ct) * 32, col0 = (tile % n_ct) * 32;
+    const int32_t *l_ids = w.set_ids + (int64_t)g * w.n + h.l_off[node];
+    const int32_t *r_ids = w.set_ids + (int64_t)g * w.n + h.r_off[node];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l31 = lane & 31, half = lane >> 5;
+    const int64_t row_bytes = (int64_t)pool.r * (int)sizeof(T);
+    const char *kg = (const char *)pool.k + (int64_t)g * pool.P * row_bytes;
+    const char *pa = kg + (int64_t)l_ids[min(row0 + l31, ml - 1)] * row_bytes + half * 16;
+    const char *pb = kg + (int64_t)r_ids[min(col0 + l31, mr - 1)] * row_bytes + half * 16;
+    const int nk = (int)(row_bytes >> 6);
+    const int first = wave * nk / kSmallWaves, last = (wave + 1) * nk / kSmallWaves;
+
+    floatx16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        acc[i] = 0.0f;
+    for (int s0 = first; s0 < last; s0 += BATCH) {
+        u32x4 fa[2 * BATCH], fb[2 * BATCH];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int64_t off = (int64_t)min(s0 + q, last - 1) * 64;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                fa[2 * q + f] = *reinterpret_cast<const u32x4 *>(pa + off + 32 * f);
+                fb[2 * q + f] = *reinterpret_cast<const u32x4 *>(pb + off + 32 * f);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q)
+            if (s0 + q < last) {
+                acc = MmaV<T>::run(fa[2 * q], fb[2 * q], acc);
+                acc = MmaV<T>::run(fa[2 * q + 1], fb[2 * q + 1], acc);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        red[wave][i][lane] = acc[i];
+    __syncthreads();
+    // accumulator i of lane x: left row 8 (i / 4) + 4 (x / 32) + i % 4, right column x % 32
+#pragma unroll
+    for (int rep = 0; rep < 16 / kSmallWaves; ++rep) {
+        const int i = wave + kSmallWaves * rep;
+        float dot = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kSmallWaves; ++k)
+            dot += red[k][i][lane];
+        const int row = row0 + 8 * (i >> 2) + 4 * half + (i & 3), col = col0 + l31;
+        if (row < ml && col < mr) {
+            const int64_t gp = (int64_t)g * pool.P;
+            const float cs = dot * pool.inv_norm_k[gp + l_ids[row]] * pool.inv_norm_k[gp + r_ids[col]];
+            if (cs > thr_floor)
+                emit_candidate(w.cand_cnt, w.cand_idx, w.cand_val, (int64_t)g * w.r_stride + h.r_base[node] + col, w.cand_cap, row, cs);
+        }
+    }
+}
+
+// One tile per node, or few enough tiles to run side by side (two workgroups per compute unit).
+static bool small_height(const WorkDesc &w, const HeightDesc &h)
+{
+    return h.small_tiles == 1 || (int64_t)w.G * h.n_nodes * h.small_tiles <= kSmallTiles;
+}
+
+template <typename T>
+static void launch_small(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor)
+{
+    const int64_t total = (int64_t)w.G * h.n_nodes * h.small_tiles;
+    if (total > 0)
+        similarity_small_kernel<T><<<(unsigned)total, 64 * kSmallWaves, 0, s>>>(pool, w, h, thr_floor);
+}
 
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
                        float *dense_s)
@@ -1032,7 +1131,13 @@ void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
     if (cols > 0)
         similarity_clear_kernel<<<(unsigned)((cols + 255) / 256), 256, 0, s>>>(w.best_packed, w.cand_cnt, cols);
     const bool big = h.use_big_tiles;
-    if (w.q8.k) {
+    const bool full = !dense_s && !w.q8.k && !w.early_nk && w.screen_prefix == 0;
+    if (full && small_height(w, h)) {
+        if (pool.dtype == KVFUSE_BF16)
+            launch_small<bf16_t>(s, pool, w, h, thr_floor);
+        else
+            launch_small<float>(s, pool, w, h, thr_floor);
+    } else if (w.q8.k) {
         if (big)
             launch_ring<fp8_t, true>(s, pool, w, h, thr_floor, dense_s);
         else
