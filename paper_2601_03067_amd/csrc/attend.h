@@ -1,0 +1,144 @@
+// One step of decode attention over bfloat16 blocks, shared by the paged and the shared-block kernels: 32 tokens (two
+// 16-token pieces) against 16 query rows, both products on the matrix cores and no LDS.
+//   logits  two 16 tokens x 16 rows groups: lane (row = lane & 15, kg = lane >> 4) ends up with the tokens 4 kg .. + 3 of
+//           both pieces, which are the 8 summation indices of the same lane in the second product.
+//   P.V     out^T (16 head elements x 16 rows) += V^T P^T, once per column c of the lane's slice: lane (n = lane & 15, kg)
+//           loads the rows of its own 8 tokens at the head elements NC n .. NC n + NC - 1 (16 lanes read a row end to end)
+//           and V^T's fragment c is element c of its 8 rows, one v_perm per two values.  The order of the summation
+//           indices is free as long as both operands agree, so the weights never leave their lane.
+// The weights are split exactly: three truncated bfloat16 parts hold all 24 bits of a binary32, so every product is exact
+// and the sums are binary32, smallest parts first.  The exponent's argument is rounded once (scale carried in two words).
+#ifndef KVFUSE_ATTEND_H
+#define KVFUSE_ATTEND_H
+
+#include "common.h"
+
+namespace kvfuse {
+
+typedef float attend_f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 attend_bf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ void attend_mma(const uint4 &a, const uint4 &b, attend_f32x4 &c)
+{
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(attend_bf16x8, a), __builtin_bit_cast(attend_bf16x8, b), c, 0, 0, 0);
+}
+
+// The scales of a piece's logical block.  Logits are in base 2, exp(x) = exp2(x log2(e)): sk + sk_rest = scale of the keys *
+// softmax scale * log2(e).
+struct AttendScale {
+    float sk, sk_rest, sv;
+    // base = softmax scale * log2(e)
+    __device__ __forceinline__ AttendScale(double base, float key, float value)
+    {
+        const double s = base * (double)key;
+        sk = (float)s;
+        sk_rest = (float)(s - (double)sk);
+        sv = value;
+    }
+};
+
+template <int D>
+struct Attend32 {
+    static constexpr int NF = D / 32;      // 16-byte K fragments per lane (a lane owns a quarter of a token row)
+    static constexpr int NC = D / 16;      // head elements of a V row per lane = 16-row tiles of out^T
+    typedef uint32_t vrow_t __attribute__((ext_vector_type(NC / 2)));
+
+    float m = -INFINITY, l = 0.0f;         // running maximum (base 2) and sum of this lane's row
+    attend_f32x4 o[NC];                    // o[c][v]: head element NC (4 kg + v) + c of this lane's row
+
+    __device__ __forceinline__ Attend32()
+    {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            o[c] = attend_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // k0, k1: K fragments of the two pieces; vr: V rows, [4 piece + i] = token 4 kg + i.  Tokens 4 kg + i with i < left are
+    // inside the context; `full`, uniform, says that all are.
+    __device__ __forceinline__ void step(const uint4 (&qf)[NF], const uint4 (&k0)[NF], const uint4 (&k1)[NF], vrow_t (&vr)[8],
+                                         const AttendScale &s0, const AttendScale &s1, bool full, int left0, int left1)
+    {
+        attend_f32x4 z0 = {0.0f, 0.0f, 0.0f, 0.0f}, z1 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            attend_mma(k0[f], qf[f], z0);
+            attend_mma(k1[f], qf[f], z1);
+        }
+        // ---- online softmax for this lane's row over its 8 tokens, then over the 4 token groups
+        float bmax = -INFINITY;
+        bool in[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            in[v] = full || (v & 3) < (v < 4 ? left0 : left1);
+            const float zz = (v < 4 ? z0[v & 3] : z1[v & 3]) * (v < 4 ? s0.sk : s1.sk);
+            bmax = fmaxf(bmax, in[v] ? zz : -INFINITY);
+        }
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        const float m_new = fmaxf(m, bmax);
+        // 0 on the first step (m = -inf); a step may hold no visible token at all
+        const float corr = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+        float psum = 0.0f, w[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const AttendScale &s = v < 4 ? s0 : s1;
+            const float z = v < 4 ? z0[v & 3] : z1[v & 3];
+            const float pr = in[v] ? __builtin_amdgcn_exp2f(fmaf(z, s.sk, fmaf(z, s.sk_rest, -m_new))) : 0.0f;
+            psum += pr;
+            w[v] = pr * s.sv;
+        }
+        psum += __shfl_xor(psum, 16, 64);
+        psum += __shfl_xor(psum, 32, 64);
+        l = l * corr + psum;
+        m = m_new;
+        if (!full) {                                   // rows past the context may hold anything, even NaN
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if ((j & 3) >= (j < 4 ? left0 : left1))
+                    vr[j] = (vrow_t)(0u);
+        }
+        // ---- the weights as three bfloat16 parts (upper halves of what is left), two values to a word
+        uint32_t ph[3][4];
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                const uint32_t a = __float_as_uint(w[j]), c = __float_as_uint(w[j + 1]);
+                ph[part][j / 2] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+                w[j] -= __uint_as_float(a & 0xFFFF0000u);
+                w[j + 1] -= __uint_as_float(c & 0xFFFF0000u);
+            }
+        // ---- out^T += V^T P^T
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+            uint4 va;
+            va.x = __builtin_amdgcn_perm(vr[1][c / 2], vr[0][c / 2], sel);
+            va.y = __builtin_amdgcn_perm(vr[3][c / 2], vr[2][c / 2], sel);
+            va.z = __builtin_amdgcn_perm(vr[5][c / 2], vr[4][c / 2], sel);
+            va.w = __builtin_amdgcn_perm(vr[7][c / 2], vr[6][c / 2], sel);
+            attend_f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};  // the smallest part first; one rounding against the sums so far
+#pragma unroll
+            for (int part = 2; part >= 0; --part)
+                attend_mma(va, make_uint4(ph[part][0], ph[part][1], ph[part][2], ph[part][3]), s);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                o[c][v] = fmaf(o[c][v], corr, s[v]);
+        }
+    }
+
+    // This lane's part of the row's sums into row[0 .. D - 1].
+    __device__ __forceinline__ void store(float *row, int kg) const
+    {
+        float *dst = row + 4 * kg * NC;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int c = 0; c < NC; c += 4)
+                *reinterpret_cast<float4 *>(dst + v * NC + c) = make_float4(o[c][v], o[c + 1][v], o[c + 2][v], o[c + 3][v]);
+    }
+};
+
+}  // namespace kvfuse
+
+#endif

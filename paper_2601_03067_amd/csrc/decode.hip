@@ -15,7 +15,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "common.h"
+#include "attend.h"
 
 namespace kvfuse {
 
@@ -261,16 +261,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
     }
 }
 
-// bfloat16 pools: 32 tokens (two 16-token pieces) per step of a wavefront, both products on the matrix cores and no LDS
-// inside the walk.
-//   logits  two 16 tokens x 16 heads groups: lane (head = lane & 15, kg = lane >> 4) ends up with the tokens 4 kg .. + 3 of
-//           both pieces, which are the 8 summation indices of the same lane in the second product.
-//   P.V     out^T (16 head elements x 16 heads) += V^T P^T, once per column c of the lane's slice: lane (n = lane & 15, kg)
-//           loads the rows of its own 8 tokens at the head elements NC n .. NC n + NC - 1 (16 lanes read a row end to end)
-//           and V^T's fragment c is element c of its 8 rows, one v_perm per two values.  The order of the summation
-//           indices is free as long as both operands agree, so the weights never leave their lane.
-// The weights are split exactly: three truncated bfloat16 parts hold all 24 bits of a binary32, so every product is exact
-// and the sums are binary32, smallest parts first.  The exponent's argument is rounded once (scale carried in two words).
+// bfloat16 pools: 32 tokens (two 16-token pieces) per step of a wavefront (attend.h).
 // Error against binary64, relative in the 2-norm, this kernel / the vector-ALU kernel it replaced: 1.57e-7 / 1.77e-7 (one
 // request of 1000 tokens, d = 128), 1.99e-7 / 2.41e-7 (48 ragged requests), 1.66e-7 / 2.29e-7 (256 requests of 4096 tokens).
 //
@@ -280,9 +271,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
 template <int D, bool AH>
 __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
 {
-    constexpr int NF = D / 32;             // 16-byte K fragments per lane (a lane owns a quarter of a token row)
-    constexpr int NC = D / 16;             // head elements of a V row per lane = 16-row tiles of out^T
-    typedef uint32_t vrow_t __attribute__((ext_vector_type(NC / 2)));
+    constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
+    typedef typename Attend32<D>::vrow_t vrow_t;
 
     extern __shared__ __attribute__((aligned(16))) float w_o[];      // [wave][rep_pad][D]
     __shared__ float w_m[4][16], w_l[4][16];
@@ -318,11 +308,6 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
             qf[f] = head < A.rep ? reinterpret_cast<const uint4 *>(qrow)[f] : make_uint4(0, 0, 0, 0);
     }
 
-    // One 16-token piece: where its rows start (elements of the group's pool) and the two scales of its logical block.
-    struct Piece {
-        int64_t off;
-        float sk, sk_rest, sv;     // logits in base 2, exp(x) = exp2(x log2(e)): sk + sk_rest = scale * softmax scale * log2(e)
-    };
     const double base = (double)A.sm_scale * 1.4426950408889634;
     const int pshift = (ppb & (ppb - 1)) == 0 ? __builtin_ctz(ppb) : -1;
     struct Entry {                     // the table's words for a piece, loaded a step ahead
@@ -333,17 +318,9 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         const int xb = pshift >= 0 ? p >> pshift : p / ppb;
         return Entry{btg[x0 + xb], (p - xb * ppb) * 16, skg[x0 + xb], svg[x0 + xb]};
     };
-    auto piece = [&](const Entry &en) __attribute__((always_inline)) {
-        Piece pc;
-        pc.off = (int64_t)en.phys * r + (int64_t)en.sub * row;
-        const double sk = base * (double)en.sk;
-        pc.sk = (float)sk;
-        pc.sk_rest = (float)(sk - (double)pc.sk);
-        pc.sv = en.sv;
-        return pc;
-    };
-    auto logits = [&](const Piece &pc) __attribute__((always_inline)) {
-        const uint4 *krow = reinterpret_cast<const uint4 *>(kg_ + pc.off + k_off);
+    auto rows_of = [&](const Entry &en) __attribute__((always_inline)) { return (int64_t)en.phys * r + (int64_t)en.sub * row; };
+    auto logits = [&](int64_t off) __attribute__((always_inline)) {
+        const uint4 *krow = reinterpret_cast<const uint4 *>(kg_ + off + k_off);
         floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
         uint4 kf[NF];
 #pragma unroll
@@ -355,12 +332,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         return z;
     };
 
-    float m_run = -INFINITY, l_run = 0.0f;
-    floatx4 o[NC];                         // o[c][v]: head element NC (4 kg + v) + c of this lane's head
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        o[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-
+    Attend32<D> st;
     const int p_first = p_lo + 2 * wave;
     Entry en0 = {}, en1 = {};
     if (p_first < p_hi) {
@@ -369,90 +341,25 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
     }
     for (int p = p_first; p < p_hi; p += 8) {
         const bool two = p + 1 < p_hi;                              // an odd last piece is paired with itself, masked
-        const Piece pc0 = piece(en0), pc1 = piece(en1);
+        const int64_t off0 = rows_of(en0), off1 = rows_of(en1);
+        const AttendScale s0(base, en0.sk, en0.sv), s1(base, en1.sk, en1.sv);
         uint4 k0[NF], k1[NF];
         vrow_t vr[8];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            k0[f] = reinterpret_cast<const uint4 *>(kg_ + pc0.off + k_off)[f];
-            k1[f] = reinterpret_cast<const uint4 *>(kg_ + pc1.off + k_off)[f];
+            k0[f] = reinterpret_cast<const uint4 *>(kg_ + off0 + k_off)[f];
+            k1[f] = reinterpret_cast<const uint4 *>(kg_ + off1 + k_off)[f];
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            vr[j] = *reinterpret_cast<const vrow_t *>(vg_ + (j < 4 ? pc0.off : pc1.off) + v_off + (int64_t)(j & 3) * row);
+            vr[j] = *reinterpret_cast<const vrow_t *>(vg_ + (j < 4 ? off0 : off1) + v_off + (int64_t)(j & 3) * row);
         if (p + 8 < p_hi) {
             en0 = entry_at(p + 8);
             en1 = entry_at(min(p + 9, p_hi - 1));
         }
         __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
-        floatx4 z0 = {0.0f, 0.0f, 0.0f, 0.0f}, z1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            QkMma<bf16_t>::run(k0[f], qf[f], z0);
-            QkMma<bf16_t>::run(k1[f], qf[f], z1);
-        }
-        // ---- online softmax for this lane's head over its 8 tokens, then over the 4 token groups
-        const bool full = two && 16 * (p + 2) <= ctx;
-        const int left0 = ctx - 16 * p - 4 * kg, left1 = two ? left0 - 16 : 0;   // tokens v < left of a piece are inside the context
-        float bmax = -INFINITY;
-        bool in[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            in[v] = full || (v & 3) < (v < 4 ? left0 : left1);
-            const float zz = (v < 4 ? z0[v & 3] : z1[v & 3]) * (v < 4 ? pc0.sk : pc1.sk);
-            bmax = fmaxf(bmax, in[v] ? zz : -INFINITY);
-        }
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        const float m_new = fmaxf(m_run, bmax);
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_new);      // 0 on the first step (m_run = -inf)
-        float psum = 0.0f, w[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const Piece &pc = v < 4 ? pc0 : pc1;
-            const float z = v < 4 ? z0[v & 3] : z1[v & 3];
-            const float pr = in[v] ? __builtin_amdgcn_exp2f(fmaf(z, pc.sk, fmaf(z, pc.sk_rest, -m_new))) : 0.0f;
-            psum += pr;
-            w[v] = pr * pc.sv;
-        }
-        psum += __shfl_xor(psum, 16, 64);
-        psum += __shfl_xor(psum, 32, 64);
-        l_run = l_run * corr + psum;
-        m_run = m_new;
-        if (!full) {                                   // rows past the context may hold anything, even NaN
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if ((j & 3) >= (j < 4 ? left0 : left1))
-                    vr[j] = (vrow_t)(0u);
-        }
-        // ---- the weights as three bfloat16 parts (upper halves of what is left), two values to a word
-        uint32_t ph[3][4];
-#pragma unroll
-        for (int part = 0; part < 3; ++part)
-#pragma unroll
-            for (int j = 0; j < 8; j += 2) {
-                const uint32_t a = __float_as_uint(w[j]), c = __float_as_uint(w[j + 1]);
-                ph[part][j / 2] = __builtin_amdgcn_perm(c, a, 0x07060302u);
-                w[j] -= __uint_as_float(a & 0xFFFF0000u);
-                w[j + 1] -= __uint_as_float(c & 0xFFFF0000u);
-            }
-        // ---- out^T += V^T P^T
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-            uint4 va;
-            va.x = __builtin_amdgcn_perm(vr[1][c / 2], vr[0][c / 2], sel);
-            va.y = __builtin_amdgcn_perm(vr[3][c / 2], vr[2][c / 2], sel);
-            va.z = __builtin_amdgcn_perm(vr[5][c / 2], vr[4][c / 2], sel);
-            va.w = __builtin_amdgcn_perm(vr[7][c / 2], vr[6][c / 2], sel);
-            floatx4 s = {0.0f, 0.0f, 0.0f, 0.0f};       // the smallest part first; one rounding against the sums so far
-#pragma unroll
-            for (int part = 2; part >= 0; --part)
-                QkMma<bf16_t>::run(va, make_uint4(ph[part][0], ph[part][1], ph[part][2], ph[part][3]), s);
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                o[c][v] = fmaf(o[c][v], corr, s[v]);
-        }
+        const int left0 = ctx - 16 * p - 4 * kg;
+        st.step(qf, k0, k1, vr, s0, s1, two && 16 * (p + 2) <= ctx, left0, two ? left0 - 16 : 0);
     }
 
     // ---- An infinite value of V meets a part of a weight that is zero: NaN where a binary32 product is infinite.  A
@@ -462,41 +369,37 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            finite = finite && fabsf(o[c][v]) < INFINITY;
+            finite = finite && fabsf(st.o[c][v]) < INFINITY;
     if (__builtin_amdgcn_ballot_w64(!finite && head < A.rep)) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            o[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            st.o[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int p = p_lo + 2 * wave; p < p_hi; p = (p - p_lo) & 1 ? p + 7 : p + 1) {
-            const Piece pc = piece(entry_at(p));
-            const floatx4 z = logits(pc);
+            const Entry en = entry_at(p);
+            const int64_t off = rows_of(en);
+            const AttendScale sc(base, en.sk, en.sv);
+            const floatx4 z = logits(off);
             const int here = min(16, ctx - 16 * p);
             for (int tok = 0; tok < here; ++tok) {
                 const float zt = (tok & 2) ? ((tok & 1) ? z[3] : z[2]) : ((tok & 1) ? z[1] : z[0]);
                 const float zw = __shfl(zt, head + 16 * (tok >> 2), 64);
-                const float wt = __builtin_amdgcn_exp2f(fmaf(zw, pc.sk, fmaf(zw, pc.sk_rest, -m_run))) * pc.sv;
-                const bf16_t *vt = vg_ + pc.off + (int64_t)tok * row + 4 * kg * NC;
+                const float wt = __builtin_amdgcn_exp2f(fmaf(zw, sc.sk, fmaf(zw, sc.sk_rest, -st.m))) * sc.sv;
+                const bf16_t *vt = vg_ + off + (int64_t)tok * row + 4 * kg * NC;
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        o[c][v] = fmaf(wt, __uint_as_float((uint32_t)vt[v * NC + c] << 16), o[c][v]);
+                        st.o[c][v] = fmaf(wt, __uint_as_float((uint32_t)vt[v * NC + c] << 16), st.o[c][v]);
             }
         }
     }
 
     // ---- publish the wavefront's state, merge the four
-    if (head < A.rep) {
-        float *dst = w_o + ((int64_t)wave * A.rep_pad + head) * D + 4 * kg * NC;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int c = 0; c < NC; c += 4)
-                *reinterpret_cast<float4 *>(dst + v * NC + c) = make_float4(o[c][v], o[c + 1][v], o[c + 2][v], o[c + 3][v]);
-    }
+    if (head < A.rep)
+        st.store(w_o + ((int64_t)wave * A.rep_pad + head) * D, kg);
     if (kg == 0) {
-        w_m[wave][head] = m_run;
-        w_l[wave][head] = l_run;
+        w_m[wave][head] = st.m;
+        w_l[wave][head] = st.l;
     }
     __syncthreads();
 

@@ -12,12 +12,12 @@
 // tile.  Everything else (unshared blocks, small clusters, partial last blocks) becomes per-request items.  Every
 // (item, request) pair owns one slot of partial softmax state; a last kernel merges a request's slots.
 //
-// Device side.  One kernel, templated on the number of rows it carries through P.V (ROWS = rep for per-request
+// Device side.  binary32 pools: one kernel, templated on the number of rows it carries through P.V (ROWS = rep for per-request
 // items, NREQ x rep for cluster items): same structure as the per-request decode kernel -- logits on the MFMA units
 // from K fragments loaded straight from global memory, online softmax in fp32, P.V on the vector ALU -- except that
 // the block list comes from the plan and the scale factors of a block are per row (they belong to the logical
-// entry of the row's request).
-#include "common.h"
+// entry of the row's request).  bfloat16 pools: decode_items_bf16_kernel, all items in one launch.
+#include "attend.h"
 
 #include <algorithm>
 #include <map>
@@ -27,7 +27,6 @@
 namespace kvfuse {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kMaxTileReq = 4;        // requests per cluster tile (entries carry that many logical indices)
 constexpr int kClusterChunk = 32;     // blocks per cluster work item, about
@@ -58,12 +57,6 @@ struct SharedArgs {
 };
 
 template <typename T> struct SQkMma;
-template <> struct SQkMma<bf16_t> {
-    __device__ static __forceinline__ void run(const uint4 &a, const uint4 &b, floatx4 &c)
-    {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    }
-};
 template <> struct SQkMma<float> {
     __device__ static __forceinline__ void run(const uint4 &a, const uint4 &b, floatx4 &c)
     {
@@ -75,15 +68,6 @@ template <> struct SQkMma<float> {
 };
 
 template <typename T> struct SToF32;
-template <> struct SToF32<bf16_t> {
-    __device__ static __forceinline__ void run(const uint4 &raw, float *o)
-    {
-        o[0] = __uint_as_float(raw.x << 16); o[1] = __uint_as_float(raw.x & 0xFFFF0000u);
-        o[2] = __uint_as_float(raw.y << 16); o[3] = __uint_as_float(raw.y & 0xFFFF0000u);
-        o[4] = __uint_as_float(raw.z << 16); o[5] = __uint_as_float(raw.z & 0xFFFF0000u);
-        o[6] = __uint_as_float(raw.w << 16); o[7] = __uint_as_float(raw.w & 0xFFFF0000u);
-    }
-};
 template <> struct SToF32<float> {
     __device__ static __forceinline__ void run(const uint4 &raw, float *o)
     {
@@ -304,168 +288,99 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
     }
 }
 
-// bfloat16 pools: the same work item with P.V on the MFMA units as well.  The logits tile S[token][row] comes out of
-// the first MFMA with each lane holding (row = lane % 16, tokens 4 * (lane / 16) .. + 3): exactly the A-operand
-// layout of v_mfma_f32_16x16x16_bf16 for P[row][token].  V's layout ([token][d], d contiguous) is the wrong way
-// round for the B operand (which wants 4 consecutive tokens of one column per lane), so every 16 x 16 piece of V
-// first goes through one MFMA against the identity: its fp32 result (exact, the inputs are bfloat16) arrives with
-// (tokens 4 * (lane / 16) .. + 3, column lane % 16) per lane, i.e. transposed into the B layout.  Probabilities are
-// split into a bfloat16 head and a bfloat16 remainder (two MFMAs), which keeps them to 16 bits of mantissa.
-// The 16 columns of a piece are those that the lanes' 16-byte loads deliver together, not 16 consecutive ones:
-// piece (f, hs), slot n holds column 32 * (n / 4) + 8 * f + 4 * hs + n % 4 (for D = 128; D / 4 instead of 32 in
-// general); the mapping is undone when the accumulators are written out.
-typedef short short4v __attribute__((ext_vector_type(4)));
-
+// bfloat16 pools: the same work item, 32 tokens per step of a wavefront (attend.h).  Cluster and per-request items share one
+// launch: each XCD takes a contiguous range of both kinds, so that the tiles of a cluster, which read the same blocks, meet in
+// its L2, and deals them out in proportion, so that its compute units see cluster blocks (from L2) and blocks of single requests
+// (from HBM) at the same time.
 template <int D>
-__global__ __launch_bounds__(256, 4) void decode_items_mfma_kernel(SharedArgs A, int item_base)
+__global__ __launch_bounds__(256, 3) void decode_items_bf16_kernel(SharedArgs A, int n_cluster, int n_residual, uint64_t cluster_share)
 {
-    typedef bf16_t T;
-    constexpr int NF = D / 32;             // 16-byte fragments per lane (a lane owns a quarter of a token row)
-    constexpr int NT = 2 * NF;             // 16-column accumulator tiles
+    constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
+    typedef typename Attend32<D>::vrow_t vrow_t;
 
-    __shared__ __attribute__((aligned(16))) float c_lds[4][16];   // per wave: rescale factor per row
     __shared__ float w_m[4][16], w_l[4][16];
-    __shared__ float w_o[4][16][D];
+    __shared__ __attribute__((aligned(16))) float w_o[4][16][D];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const DItem item = A.items[item_base + blockIdx.x];
+    // cluster_share: cluster items per seat of an XCD, times 2^32 and rounded up
+    const int xcd = blockIdx.x & 7, seat = blockIdx.x >> 3;
+    const int before = (int)((uint64_t)seat * cluster_share >> 32), after = (int)((uint64_t)(seat + 1) * cluster_share >> 32);
+    const int which = after > before ? xcd * ((n_cluster + 7) >> 3) + before : xcd * ((n_residual + 7) >> 3) + seat - before;
+    if (which >= (after > before ? n_cluster : n_residual))
+        return;
+    const DItem item = A.items[after > before ? which : n_cluster + which];
     const int li = item.li, kvh = item.kvh, nreq = item.nreq;
     const int g = (A.layer_begin + li) * A.kv_heads + kvh;
     const int64_t r = (int64_t)A.t * D;
-    const T *kg = (const T *)A.kpool + (int64_t)g * A.P * r;
-    const T *vg = (const T *)A.vpool + (int64_t)g * A.P * r;
+    const bf16_t *kgrp = (const bf16_t *)A.kpool + (int64_t)g * A.P * r;
+    const bf16_t *vgrp = (const bf16_t *)A.vpool + (int64_t)g * A.P * r;
     const float *skg = A.scale_k + (int64_t)g * A.n;
     const float *svg = A.scale_v + (int64_t)g * A.n;
 
-    const int head = lane & 15, tg = lane >> 4;      // logits / P: row, token group;  K and V loads: token, row quarter
+    const int head = lane & 15, kg = lane >> 4;      // row and token group;  also: token of a K row, column slice of a V row
     const int rs_raw = head / A.rep_pad, hh = head - rs_raw * A.rep_pad;
     const bool row_used = rs_raw < nreq && hh < A.rep;
     const int rs = row_used ? rs_raw : 0;
     const int my_req = rs == 0 ? item.req[0] : (rs == 1 ? item.req[1] : (rs == 2 ? item.req[2] : item.req[3]));
+    const int k_off = head * D + kg * (D / 4), v_off = 4 * kg * D + head * NC;
 
     uint4 qf[NF];
     {
-        const T *qrow = (const T *)A.q + (((int64_t)li * A.B + my_req) * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + tg * (D / 4);
+        const bf16_t *qrow = (const bf16_t *)A.q + (((int64_t)li * A.B + my_req) * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + kg * (D / 4);
 #pragma unroll
         for (int f = 0; f < NF; ++f)
             qf[f] = row_used ? reinterpret_cast<const uint4 *>(qrow)[f] : make_uint4(0, 0, 0, 0);
     }
-    // identity as a B operand: this lane holds I[k = 4 * tg + i][n = head]
-    short4v ident;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        ident[i] = (4 * tg + i == head) ? (short)0x3F80 : (short)0;
 
-    float m_run = -INFINITY, l_run = 0.0f;
-    floatx4 o[NT];
+    // 16-token piece p of the item: piece p % ppb of entry p / ppb; the table's words are loaded a step ahead
+    const int ppb = A.t >> 4, n_pieces = item.entry_cnt * ppb;
+    const int pshift = (ppb & (ppb - 1)) == 0 ? __builtin_ctz(ppb) : -1;
+    const double base = (double)A.sm_scale * 1.4426950408889634;
+    struct Entry {
+        int phys, ntok, sub, x0, x1, x2, x3;
+    };
+    auto entry_at = [&](int p) __attribute__((always_inline)) {
+        const int e = pshift >= 0 ? p >> pshift : p / ppb;
+        const DEntry &en = A.entries[item.entry_off + e];
+        return Entry{en.phys, en.ntok, (p - e * ppb) * 16, en.x[0], en.x[1], en.x[2], en.x[3]};
+    };
+    Attend32<D> st;
+    Entry en0 = {}, en1 = {};
+    if (2 * wave < n_pieces) {
+        en0 = entry_at(2 * wave);
+        en1 = entry_at(min(2 * wave + 1, n_pieces - 1));
+    }
+    for (int p = 2 * wave; p < n_pieces; p += 8) {
+        const bool two = p + 1 < n_pieces;                          // an odd last piece is paired with itself, masked
+        const int xa = rs == 0 ? en0.x0 : (rs == 1 ? en0.x1 : (rs == 2 ? en0.x2 : en0.x3));
+        const int xb = rs == 0 ? en1.x0 : (rs == 1 ? en1.x1 : (rs == 2 ? en1.x2 : en1.x3));
+        const float ska = skg[xa], sva = svg[xa], skb = skg[xb], svb = svg[xb];
+        const int64_t off0 = (int64_t)en0.phys * r + (int64_t)en0.sub * D, off1 = (int64_t)en1.phys * r + (int64_t)en1.sub * D;
+        const int left0 = en0.ntok - en0.sub, left1 = two ? en1.ntok - en1.sub : 0;
+        uint4 k0[NF], k1[NF];
+        vrow_t vr[8];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-        o[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    for (int eb = wave; eb < item.entry_cnt; eb += 4) {
-        const DEntry ent = A.entries[item.entry_off + eb];
-        const int phys = ent.phys, ntok = ent.ntok;
-        const int x = rs == 0 ? ent.x[0] : (rs == 1 ? ent.x[1] : (rs == 2 ? ent.x[2] : ent.x[3]));
-        const float zs = A.sm_scale * skg[x];
-        const float sv = svg[x];
-        const T *kblk = kg + (int64_t)phys * r;
-        const T *vblk = vg + (int64_t)phys * r;
-        for (int sub = 0; sub < A.t; sub += 16) {
-            if (sub >= ntok)
-                break;
-            const uint4 *krow = reinterpret_cast<const uint4 *>(kblk + (int64_t)(sub + head) * D + tg * (D / 4));
-            const uint4 *vrow = reinterpret_cast<const uint4 *>(vblk + (int64_t)(sub + head) * D + tg * (D / 4));
-            uint4 kf[NF], vf[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-                kf[f] = krow[f];
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-                vf[f] = vrow[f];
-            // ---- logits: 16 tokens x 16 rows
-            floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-                z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[f]), __builtin_bit_cast(bf16x8, qf[f]), z, 0, 0, 0);
-            // ---- online softmax for this lane's row over its 4 tokens, then over the 4 token groups
-            const int tok0 = sub + tg * 4;
-            float zz[4];
-            float bmax = -INFINITY;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                zz[v] = (tok0 + v < ntok) ? z[v] * zs : -INFINITY;
-                bmax = fmaxf(bmax, zz[v]);
-            }
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-            const float m_new = fmaxf(m_run, bmax);
-            const float corr = __expf(m_run - m_new);      // 0 on the first block (m_run = -inf)
-            float psum = 0.0f;
-            short4v p_hi, p_lo;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float pr = __expf(zz[v] - m_new);
-                psum += pr;
-                const float pw = pr * sv;
-                const uint32_t hb = __float_as_uint(pw) & 0xFFFF0000u;           // bfloat16 head (truncated)
-                const float rest = pw - __uint_as_float(hb);                      // exact
-                p_hi[v] = (short)(hb >> 16);
-                p_lo[v] = (short)((__float_as_uint(rest) + 0x8000u) >> 16);       // bfloat16 remainder (rounded)
-            }
-            psum += __shfl_xor(psum, 16, 64);
-            psum += __shfl_xor(psum, 32, 64);
-            l_run = l_run * corr + psum;
-            m_run = m_new;
-            if (tg == 0)
-                c_lds[wave][head] = corr;
-            __builtin_amdgcn_wave_barrier();
-            // ---- rescale the accumulators: this lane holds rows 4 * tg .. + 3 of every tile
-            const float4 c4 = *reinterpret_cast<const float4 *>(&c_lds[wave][4 * tg]);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                o[nt][0] *= c4.x; o[nt][1] *= c4.y; o[nt][2] *= c4.z; o[nt][3] *= c4.w;
-            }
-            // ---- P.V.  V rows past the context may hold anything, even NaN: this lane's row is token `head`
-            if (sub + head >= ntok) {
-#pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    vf[f] = make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-#pragma unroll
-                for (int hs = 0; hs < 2; ++hs) {
-                    const uint32_t w0 = hs ? vf[f].z : vf[f].x, w1 = hs ? vf[f].w : vf[f].y;
-                    short4v va;
-                    va[0] = (short)(w0 & 0xFFFFu); va[1] = (short)(w0 >> 16);
-                    va[2] = (short)(w1 & 0xFFFFu); va[3] = (short)(w1 >> 16);
-                    const floatx4 vt = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, ident, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
-                    short4v vb;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        vb[i] = (short)(__float_as_uint(vt[i]) >> 16);
-                    o[2 * f + hs] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p_hi, vb, o[2 * f + hs], 0, 0, 0);
-                    o[2 * f + hs] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p_lo, vb, o[2 * f + hs], 0, 0, 0);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
+        for (int f = 0; f < NF; ++f) {
+            k0[f] = reinterpret_cast<const uint4 *>(kgrp + off0 + k_off)[f];
+            k1[f] = reinterpret_cast<const uint4 *>(kgrp + off1 + k_off)[f];
         }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            vr[j] = *reinterpret_cast<const vrow_t *>(vgrp + (j < 4 ? off0 : off1) + v_off + (j & 3) * D);
+        if (p + 8 < n_pieces) {
+            en0 = entry_at(p + 8);
+            en1 = entry_at(min(p + 9, n_pieces - 1));
+        }
+        __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
+        const AttendScale s0(base, ska, sva), s1(base, skb, svb);
+        st.step(qf, k0, k1, vr, s0, s1, left0 >= 16 && left1 >= 16, left0 - 4 * kg, left1 - 4 * kg);
     }
 
-    // ---- publish the wave's state: this lane holds o[row 4 * tg + i][column slot head] of every tile
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int hs = 0; hs < 2; ++hs) {
-            const int col = (D / 4) * (head >> 2) + 8 * f + 4 * hs + (head & 3);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w_o[wave][4 * tg + i][col] = o[2 * f + hs][i];
-        }
-    if (tg == 0) {
-        w_m[wave][head] = m_run;
-        w_l[wave][head] = l_run;
+    st.store(w_o[wave][head], kg);
+    if (kg == 0) {
+        w_m[wave][head] = st.m;
+        w_l[wave][head] = st.l;
     }
     __syncthreads();
 
@@ -474,11 +389,11 @@ __global__ __launch_bounds__(256, 4) void decode_items_mfma_kernel(SharedArgs A,
         const int hs = h / A.rep_pad, hq = h - hs * A.rep_pad;
         if (hs >= nreq || hq >= A.rep)
             continue;
-        float M = fmaxf(fmaxf(w_m[0][h], w_m[1][h]), fmaxf(w_m[2][h], w_m[3][h]));
+        const float M = fmaxf(fmaxf(w_m[0][h], w_m[1][h]), fmaxf(w_m[2][h], w_m[3][h]));
         float L = 0.0f, O = 0.0f;
 #pragma unroll
         for (int wv = 0; wv < 4; ++wv) {
-            const float f = w_m[wv][h] == -INFINITY ? 0.0f : __expf(w_m[wv][h] - M);
+            const float f = w_m[wv][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(w_m[wv][h] - M);
             L += w_l[wv][h] * f;
             O += w_o[wv][h][e] * f;
         }
@@ -492,26 +407,58 @@ __global__ __launch_bounds__(256, 4) void decode_items_mfma_kernel(SharedArgs A,
     }
 }
 
-// Merge of a request's partial states: one workgroup per (layer, request, KV head).
-template <int D>
+// Merge of a request's partial states: one workgroup per (layer, request, query head), as in decode_combine_kernel: the states
+// of up to 64 slots are loaded by the lanes at once, the threads of a head element share the slots out among them.  BASE2: the
+// maxima are base-2 logarithms.
+template <int D, bool BASE2>
 __global__ __launch_bounds__(256) void decode_shared_combine_kernel(SharedArgs A)
 {
+    constexpr int GROUPS = 256 / D;
+    __shared__ float s_o[GROUPS][D];
     const int64_t tuple = blockIdx.x;
+    const int h = blockIdx.y;
     const int kvh = (int)(tuple % A.kv_heads);
     const int64_t lb = tuple / A.kv_heads;       // li * B + b
     const int s0 = A.slot_begin[tuple], s1 = A.slot_begin[tuple + 1];
-    for (int idx = threadIdx.x; idx < A.rep * D; idx += 256) {
-        const int h = idx / D, e = idx - h * D;
-        float M = -INFINITY;
-        for (int s = s0; s < s1; ++s)
-            M = fmaxf(M, A.part[((int64_t)s * A.rep_pad + h) * (D + 2) + D]);
-        float L = 0.0f, O = 0.0f;
-        for (int s = s0; s < s1; ++s) {
-            const float *pp = A.part + ((int64_t)s * A.rep_pad + h) * (D + 2);
-            const float f = pp[D] == -INFINITY ? 0.0f : __expf(pp[D] - M);
-            L += pp[D + 1] * f;
-            O += pp[e] * f;
+    const int lane = threadIdx.x & 63, e = threadIdx.x % D;
+    const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / D);      // uniform: D is a multiple of 64
+    const float *part = A.part + ((int64_t)s0 * A.rep_pad + h) * (D + 2);
+    const int64_t stride = (int64_t)A.rep_pad * (D + 2);
+    const int n = s1 - s0;
+    float M = -INFINITY;
+    for (int s = lane; s < n; s += 64)
+        M = fmaxf(M, part[s * stride + D]);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+        M = fmaxf(M, __shfl_xor(M, off, 64));
+    float L = 0.0f, O = 0.0f;
+    for (int c0 = 0; c0 < n; c0 += 64) {
+        const int cnt = min(64, n - c0);
+        const float m = lane < cnt ? part[(c0 + lane) * stride + D] : -INFINITY;
+        const float f = m == -INFINITY ? 0.0f : BASE2 ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M);
+        L += lane < cnt ? part[(c0 + lane) * stride + D + 1] * f : 0.0f;
+        for (int s = grp; s < cnt; s += 4 * GROUPS) {
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[k] = part[(c0 + min(s + k * GROUPS, cnt - 1)) * stride + e];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int sk = s + k * GROUPS;
+                if (sk < cnt)
+                    O += v[k] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), sk));
+            }
         }
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+        L += __shfl_xor(L, off, 64);
+    s_o[grp][e] = O;
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int k = 1; k < GROUPS; ++k)
+            O += s_o[k][e];
         A.out[(lb * A.Hq + (int64_t)kvh * A.rep + h) * D + e] = L > 0.0f ? O / L : 0.0f;
     }
 }
@@ -867,9 +814,10 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
     A.sm_scale = sm_scale;
     const int nc = (int)plan->items_cluster.size(), nr = (int)plan->items_residual.size();
     const int rows_cluster = plan->nreq_max * plan->rep_pad, rows_residual = plan->rep_pad;
-    // The cluster pass is bound by the vector ALU, the per-request pass by HBM: they run side by side, the cluster
-    // pass on the context's second stream, and meet again before the merge.
-    const bool fork = nc > 0 && nr > 0;
+    const dim3 cgrid((unsigned)tuples, (unsigned)plan->rep);
+    // binary32 pools: the cluster pass is bound by the vector ALU, the per-request pass by HBM: they run side by side, the
+    // cluster pass on the context's second stream, and meet again before the merge.
+    const bool fork = pool->dtype == KVFUSE_F32 && nc > 0 && nr > 0;
     if (fork) {
         if (!c->aux) {
             hipStream_t st = nullptr;
@@ -899,24 +847,22 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             (void)hipEventRecord(c->join, c->aux);                                     \
             (void)hipStreamWaitEvent(c->stream, c->join, 0);                           \
         }                                                                              \
-        decode_shared_combine_kernel<D><<<(unsigned)tuples, 256, 0, c->stream>>>(A);   \
+        decode_shared_combine_kernel<D, false><<<cgrid, 256, 0, c->stream>>>(A);       \
     } while (0)
     if (pool->dtype == KVFUSE_BF16) {
-#define KVF_SHARED_LAUNCH_MFMA(D)                                                                   \
-    do {                                                                                            \
-        if (nc > 0)                                                                                 \
-            decode_items_mfma_kernel<D><<<nc, 256, 0, cs>>>(A, 0);                                  \
-        if (nr > 0)                                                                                 \
-            decode_items_mfma_kernel<D><<<nr, 256, 0, c->stream>>>(A, nc);                          \
-        if (fork) {                                                                                 \
-            (void)hipEventRecord(c->join, c->aux);                                                  \
-            (void)hipStreamWaitEvent(c->stream, c->join, 0);                                        \
-        }                                                                                           \
-        decode_shared_combine_kernel<D><<<(unsigned)tuples, 256, 0, c->stream>>>(A);                \
-    } while (0)
-        if (pool->d == 128) KVF_SHARED_LAUNCH_MFMA(128);
-        else KVF_SHARED_LAUNCH_MFMA(64);
-#undef KVF_SHARED_LAUNCH_MFMA
+        // (any split of an XCD's seats between the two kinds is correct as long as the last seat completes both)
+        const uint64_t nc8 = ((uint64_t)nc + 7) / 8, seats = nc8 + ((uint64_t)nr + 7) / 8;
+        const uint64_t share = seats > 0 ? ((nc8 << 32) + seats - 1) / seats : 0;
+        if (seats > 0) {
+            if (pool->d == 128)
+                decode_items_bf16_kernel<128><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(A, nc, nr, share);
+            else
+                decode_items_bf16_kernel<64><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(A, nc, nr, share);
+        }
+        if (pool->d == 128)
+            decode_shared_combine_kernel<128, true><<<cgrid, 256, 0, c->stream>>>(A);
+        else
+            decode_shared_combine_kernel<64, true><<<cgrid, 256, 0, c->stream>>>(A);
     } else {
         if (pool->d == 128) KVF_SHARED_LAUNCH(float, 128);
         else KVF_SHARED_LAUNCH(float, 64);
