@@ -53,6 +53,7 @@ struct HeightDesc {
     const int64_t *s_base;            // [n_nodes + 1] prefix sums of l_cap * r_cap
     int32_t item_cap;                 // most similarity work items one group can have at this height (see similarity.hip)
     int32_t small_tiles;              // most 32 x 32 tiles one node can have
+    int32_t max_cap;                  // largest left or right set of a node
     bool use_big_tiles;
     int64_t total_s;
 };
@@ -169,13 +170,13 @@ void launch_tree_norms(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
 void launch_centre_direction(hipStream_t s, const PoolDesc &pool, const WorkDesc &w);
 void launch_leaf_sets(hipStream_t s, const WorkDesc &w, const TableDesc &tab, int P, const int32_t *slot_init, const double *norm_k);
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
-                       float *dense_s);
+                       float *dense_s, bool cleared = false);
 // early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
 void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
 void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height);
 void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const HeightDesc &h,
-                   int height, double thr, double band, int rule);
+                   int height, double thr, double band, int rule, bool clear_lists = false);
 void launch_merge(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height);
 // prefix screen: tail shares of all key blocks (for callers that run the steps one by one)
 void launch_prefix_tails(hipStream_t s, const PoolDesc &pool, const WorkDesc &w);
@@ -249,8 +250,9 @@ __device__ __forceinline__ double block_sum_256(double x, double *lds4)
     return ((lds4[0] + lds4[1]) + lds4[2]) + lds4[3];
 }
 
-// Exclusive scan of one int64 per thread over a 256-thread workgroup; returns the exclusive prefix and the total.
-__device__ __forceinline__ int64_t block_exscan_256(int64_t x, int64_t *lds4, int64_t &total)
+// Exclusive scan of one int64 per thread over a workgroup of NT threads; returns the exclusive prefix and the total.
+template <int NT>
+__device__ __forceinline__ int64_t block_exscan(int64_t x, int64_t (&waves)[NT / 64], int64_t &total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int64_t inc = x;
@@ -262,12 +264,16 @@ __device__ __forceinline__ int64_t block_exscan_256(int64_t x, int64_t *lds4, in
     }
     __syncthreads();
     if (lane == 63)
-        lds4[wave] = inc;
+        waves[wave] = inc;
     __syncthreads();
     int64_t pre = 0;
-    for (int k = 0; k < wave; ++k)
-        pre += lds4[k];
-    total = lds4[0] + lds4[1] + lds4[2] + lds4[3];
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) {
+        const int64_t s = waves[k];
+        pre += k < wave ? s : 0;
+        total += s;
+    }
     return pre + inc - x;
 }
 

@@ -32,7 +32,7 @@ struct Node {
 struct HostHeight {
     std::vector<int32_t> l_off, r_off, l_slot, r_slot, out_slot, l_cap, r_cap, l_base, r_base;
     int item_cap = 0;                                          // most similarity work items of one group
-    int small_tiles = 1;
+    int small_tiles = 1, max_cap = 0;
     bool big = false;
     std::vector<int64_t> s_base;
     HeightDesc dev;
@@ -230,6 +230,7 @@ static void build_heights(const std::vector<Node> &nodes, std::vector<HostHeight
             const int n_cp = (h.r_cap[k] + bn - 1) / bn;
             const int n_rtile = (h.l_cap[k] + bm - 1) / bm;
             cap += (int64_t)n_cp * (n_rtile < 4 ? n_rtile : std::max(4, (n_rtile + 3) / 4));
+            h.max_cap = std::max({h.max_cap, h.l_cap[k], h.r_cap[k]});
             const int64_t small = (int64_t)((h.l_cap[k] + 31) / 32) * ((h.r_cap[k] + 31) / 32);
             h.small_tiles = (int)std::min<int64_t>(std::max<int64_t>(h.small_tiles, small), INT32_MAX);
         }
@@ -305,6 +306,7 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
         d.total_r_cap = h.r_base[nn];
         d.total_s = h.s_base[nn];
         d.small_tiles = h.small_tiles;
+        d.max_cap = h.max_cap;
         d.use_big_tiles = h.big;
         d.item_cap = h.item_cap;
         d.l_off = cv.take<int32_t>(nn);
@@ -672,11 +674,11 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     for (int hgt = 0; hgt < nh; ++hgt) {
         const HeightDesc &d = p.heights[hgt].dev;
         w.n_pairs = w.n_pairs_all + hgt;
-        launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr);
+        launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);
         if (early)
             launch_finish_pairs(c->stream, p.pool, w, floor_f);
         KVF_TRY(mark());
-        launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule);
+        launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule, hgt + 1 < nh);
         KVF_TRY(mark());
         launch_merge(c->stream, p.pool, w, d, hgt);
         KVF_TRY(mark());

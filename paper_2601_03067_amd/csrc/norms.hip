@@ -236,6 +236,10 @@ __global__ __launch_bounds__(256) void tree_clear_kernel(TableDesc tab, WorkDesc
         w.counters[i] = 0;
     if (i < (int64_t)w.G * w.n_slots)
         w.set_cnt[i] = slot_init[i % w.n_slots];
+    if (i < (int64_t)w.G * w.r_stride) {          // the candidate lists of the first height (assign_finalize_kernel: of the next)
+        w.best_packed[i] = 0ull;
+        w.cand_cnt[i] = 0;
+    }
     if (i < n_heights) {
         w.n_active[i] = 0;
         w.n_refine[i] = 0;
@@ -288,7 +292,7 @@ void launch_tree_entries(hipStream_t s, const PoolDesc &pool, const WorkDesc &w,
                          int n_heights)
 {
     const int64_t nb = (int64_t)pool.G * pool.P, ne = (int64_t)w.G * w.n;
-    const int64_t total = std::max({nb, (int64_t)w.G * w.n_slots, (int64_t)w.G * 8, (int64_t)n_heights});
+    const int64_t total = std::max({nb, (int64_t)w.G * w.r_stride, (int64_t)w.G * w.n_slots, (int64_t)w.G * 8, (int64_t)n_heights});
     tree_clear_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(tab, w, nb, slot_init, n_heights);
     if (ne > 0)
         tree_entries_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, w, pool.P);

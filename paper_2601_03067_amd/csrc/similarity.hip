@@ -937,7 +937,7 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
                               n_cp, rt, n_rc);
         }
         int64_t total;
-        const int64_t pre = block_exscan_256((int64_t)c, lds4, total);
+        const int64_t pre = block_exscan<256>((int64_t)c, lds4, total);
         if (k < h.n_nodes)
             base[k] = (int)min(run + pre, (int64_t)h.item_cap);
         run += total;
@@ -1125,10 +1125,10 @@ static void launch_small(hipStream_t s, const PoolDesc &pool, const WorkDesc &w,
 }
 
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
-                       float *dense_s)
+                       float *dense_s, bool cleared)
 {
     const int64_t cols = (int64_t)w.G * w.r_stride;
-    if (cols > 0)
+    if (cols > 0 && !cleared)
         similarity_clear_kernel<<<(unsigned)((cols + 255) / 256), 256, 0, s>>>(w.best_packed, w.cand_cnt, cols);
     const bool big = h.use_big_tiles;
     const bool full = !dense_s && !w.q8.k && !w.early_nk && w.screen_prefix == 0;
