@@ -2,8 +2,8 @@
 // hands the scheduler the updated tables so that it can free unused blocks and raise reference counts).
 //
 // Integer gather/scatter, HBM-bound and small: one pass over the table follows the remap chain of each entry to
-// its surviving block and recounts references; a second pass refreshes the per-logical scales; a per-group pass
-// lists the freed ids in ascending order.
+// its surviving block and recounts references; a second one refreshes the per-logical scales and lists every group's
+// freed ids in ascending order.
 #include "common.h"
 
 namespace kvfuse {
@@ -36,12 +36,10 @@ __global__ void rewrite_chase_kernel(TableDesc tab, int G, int P)
     atomicAdd(&tab.refcount[gp + p], 1);
 }
 
-__global__ void rewrite_scale_kernel(TableDesc tab, int G, int P, const double *__restrict__ norm_k,
-                                     const double *__restrict__ norm_v)
+// The scales of table entry i.
+__device__ __forceinline__ void rewrite_scale(const TableDesc &tab, int64_t i, int P, const double *__restrict__ norm_k,
+                                              const double *__restrict__ norm_v)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)G * tab.n)
-        return;
     const int64_t gp = (i / tab.n) * P;
     const int p = tab.bt[i];
     if (p < 0 || p >= P)
@@ -56,29 +54,46 @@ __global__ void rewrite_scale_kernel(TableDesc tab, int G, int P, const double *
     tab.scale_v[i] = nv == 0.0 ? 0.0f : (float)(tab.orig_norm_v[i] / nv);
 }
 
-// One workgroup per group: freed ids (blocks that were fused away) in ascending order, and the live count.
-__global__ __launch_bounds__(256) void rewrite_free_kernel(TableDesc tab, int P, int32_t *__restrict__ free_list,
-                                                          int32_t *__restrict__ n_free, int32_t *__restrict__ n_phys)
+// Two passes that do not depend on each other, in one launch.  The first n_lists workgroups take a group each: freed ids
+// (blocks that were fused away) in ascending order, and the live count; their walk over the pool is a chain of barriers, so they
+// start first, are as wide as can be and load a step ahead (141 355 blocks a group: 394 us with 256 threads, 109 us).  The
+// others refresh the scales.
+constexpr int kFinishThreads = 1024;
+
+__global__ __launch_bounds__(kFinishThreads) void rewrite_finish_kernel(TableDesc tab, int G, int P, const double *__restrict__ norm_k,
+                                                                        const double *__restrict__ norm_v, int n_lists,
+                                                                        int32_t *__restrict__ free_list, int32_t *__restrict__ n_free,
+                                                                        int32_t *__restrict__ n_phys)
 {
-    __shared__ int wave_tot[4];
-    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = kFinishThreads / 64;
+    __shared__ int wave_tot[2][NW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if ((int)blockIdx.x >= n_lists) {
+        const int64_t i = (int64_t)(blockIdx.x - n_lists) * kFinishThreads + tid;
+        if (i < (int64_t)G * tab.n)
+            rewrite_scale(tab, i, P, norm_k, norm_v);
+        return;
+    }
+    const int g = blockIdx.x;
     const int64_t gp = (int64_t)g * P;
     int freed = 0, live = 0;
-    for (int p0 = 0; p0 < P; p0 += 256) {
-        const int p = p0 + tid;
-        const bool is_free = p < P && tab.remap[gp + p] >= 0;
-        const bool is_live = p < P && tab.refcount[gp + p] > 0;
-        const unsigned long long mf = __ballot(is_free);
-        const unsigned long long ml = __ballot(is_live);
-        __syncthreads();
+    int next_remap = tid < P ? tab.remap[gp + tid] : -1, next_refs = tid < P ? tab.refcount[gp + tid] : 0;
+    for (int p0 = 0, buf = 0; p0 < P; p0 += kFinishThreads, buf ^= 1) {
+        const int p = p0 + tid, ahead = p + kFinishThreads;
+        const unsigned long long mf = __ballot(next_remap >= 0);
+        const unsigned long long ml = __ballot(next_refs > 0);
+        const bool is_free = next_remap >= 0;
+        next_remap = ahead < P ? tab.remap[gp + ahead] : -1;
+        next_refs = ahead < P ? tab.refcount[gp + ahead] : 0;
         if (lane == 0)
-            wave_tot[wave] = __popcll(mf);
-        __syncthreads();
+            wave_tot[buf][wave] = __popcll(mf);
+        __syncthreads();                 // (one barrier a step: the other buffer is written before the next one)
         int pre = 0, tot = 0;
-        for (int k = 0; k < 4; ++k) {
-            if (k < wave)
-                pre += wave_tot[k];
-            tot += wave_tot[k];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const int c = wave_tot[buf][k];
+            pre += k < wave ? c : 0;
+            tot += c;
         }
         if (is_free && free_list)
             free_list[gp + freed + pre + __popcll(mf & ((1ull << lane) - 1ull))] = p;
@@ -88,13 +103,17 @@ __global__ __launch_bounds__(256) void rewrite_free_kernel(TableDesc tab, int P,
     // live counts are per wave: add them up
     __syncthreads();
     if (lane == 0)
-        wave_tot[wave] = live;
+        wave_tot[0][wave] = live;
     __syncthreads();
     if (tid == 0) {
         if (n_free)
             n_free[g] = freed;
-        if (n_phys)
-            n_phys[g] = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
+        if (n_phys) {
+            int sum = 0;
+            for (int k = 0; k < NW; ++k)
+                sum += wave_tot[0][k];
+            n_phys[g] = sum;
+        }
     }
 }
 
@@ -105,12 +124,13 @@ void launch_rewrite(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, i
     const int64_t ne = (int64_t)pool.G * tab.n;
     if (nb > 0)
         rewrite_clear_kernel<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(tab.refcount, nb);
-    if (ne > 0) {
+    if (ne > 0)
         rewrite_chase_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, pool.G, pool.P);
-        rewrite_scale_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v);
-    }
-    if (pool.G > 0 && (free_list || n_free || n_phys))
-        rewrite_free_kernel<<<(unsigned)pool.G, 256, 0, s>>>(tab, pool.P, free_list, n_free, n_phys);
+    const int n_lists = free_list || n_free || n_phys ? pool.G : 0;
+    const int64_t grid = n_lists + (ne + kFinishThreads - 1) / kFinishThreads;
+    if (grid > 0)
+        rewrite_finish_kernel<<<(unsigned)grid, kFinishThreads, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v, n_lists, free_list,
+                                                                        n_free, n_phys);
 }
 
 }  // namespace kvfuse
