@@ -463,6 +463,63 @@ __global__ __launch_bounds__(256) void decode_shared_combine_kernel(SharedArgs A
     }
 }
 
+// The same merge, one wavefront per (layer, request, query head): for calls with enough of them to fill the chip several
+// times, where a workgroup each runs in rounds of 2048 (64 requests, 64 groups of 4 heads: 33 -> COMBINE_US us).  The sums of
+// the first slots are asked for together with the states.
+template <int D>
+__global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(SharedArgs A, int64_t heads_total)
+{
+    constexpr int PL = D / 64, BATCH = 8;          // head elements per lane, slots loaded at a time
+    typedef float elems_t __attribute__((ext_vector_type(PL)));
+    const int lane = threadIdx.x & 63;
+    const int64_t id = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (id >= heads_total)
+        return;
+    const int64_t tuple = id / A.rep;
+    const int h = (int)(id - tuple * A.rep);
+    const int kvh = (int)(tuple % A.kv_heads);
+    const int64_t lb = tuple / A.kv_heads;         // li * B + b
+    const int s0 = A.slot_begin[tuple], n = A.slot_begin[tuple + 1] - s0;
+    const float *part = A.part + ((int64_t)s0 * A.rep_pad + h) * (D + 2);
+    const int64_t stride = (int64_t)A.rep_pad * (D + 2);
+    elems_t v[BATCH];
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
+            v[k] = *reinterpret_cast<const elems_t *>(part + min(s + k, n - 1) * stride + lane * PL);
+    };
+    elems_t O = (elems_t)(0.0f);
+    float L = 0.0f;
+    if (n > 0) {
+        fetch(0);
+        float M = -INFINITY;
+        for (int s = lane; s < n; s += 64)
+            M = fmaxf(M, part[s * stride + D]);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1)
+            M = fmaxf(M, __shfl_xor(M, off, 64));
+        for (int c0 = 0; c0 < n; c0 += 64) {
+            const int cnt = min(64, n - c0);
+            const float m = lane < cnt ? part[(c0 + lane) * stride + D] : -INFINITY;
+            const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
+            L += lane < cnt ? part[(c0 + lane) * stride + D + 1] * f : 0.0f;
+            for (int s = 0; s < cnt; s += BATCH) {
+                if (c0 + s > 0)
+                    fetch(c0 + s);
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k)
+                    if (s + k < cnt)
+                        O += v[k] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), s + k));
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1)
+            L += __shfl_xor(L, off, 64);
+    }
+    const elems_t out = L > 0.0f ? O / L : (elems_t)(0.0f);
+    *reinterpret_cast<elems_t *>(A.out + (lb * A.Hq + (int64_t)kvh * A.rep + h) * D + lane * PL) = out;
+}
+
 static int pad_pow2(int rep)
 {
     int p = 1;
@@ -859,7 +916,14 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             else
                 decode_items_bf16_kernel<64><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(A, nc, nr, share);
         }
-        if (pool->d == 128)
+        const int64_t heads_total = tuples * plan->rep;
+        if (heads_total >= 4096) {
+            const unsigned grid = (unsigned)((heads_total + 3) / 4);
+            if (pool->d == 128)
+                decode_shared_combine_waves_kernel<128><<<grid, 256, 0, c->stream>>>(A, heads_total);
+            else
+                decode_shared_combine_waves_kernel<64><<<grid, 256, 0, c->stream>>>(A, heads_total);
+        } else if (pool->d == 128)
             decode_shared_combine_kernel<128, true><<<cgrid, 256, 0, c->stream>>>(A);
         else
             decode_shared_combine_kernel<64, true><<<cgrid, 256, 0, c->stream>>>(A);

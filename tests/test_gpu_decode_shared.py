@@ -16,7 +16,7 @@ def test_against_binary64(t, d, heads, rep, least, blocks):
     print("shared decode", t, d, heads, rep, least, blocks, flush=True)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(t + d + blocks)
-    B, layers = 9, 2
+    B, layers = 9, 2 if blocks > 1 else 300
     groups = layers * heads
     # request b takes stored block j in the set j if bit b of j is set (request 0: of all), so that the sets of requests that
     # share a block differ from block to block; every other block is its own
