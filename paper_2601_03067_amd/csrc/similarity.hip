@@ -596,31 +596,32 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     bool whole = !EARLY || nk == nk_full;       // this pass ends with whole products
     for (;;) {
         const bool act_m1 = row_end - (row0 + rt * BM) > MT_STRIDE;
+        // The fragments of the next row tile's first slice are on their way when the last slice is done.  They are waited for
+        // inside the loop: what follows it is free to copy those registers, or to use them for something else, before a wait
+        // that stands behind it (both happened: a candidate of a ragged tile was lost now and then).
+#define KVF_SLICES(SLICE, WAIT)                                                                                    \
+    _Pragma("unroll 1") for (int kt = 0;;)                                                                         \
+    {                                                                                                              \
+        SLICE;                                                                                                     \
+        ++it;                                                                                                      \
+        if (++kt >= n_slices) {                                                                                    \
+            WAIT;                                                                                                  \
+            __builtin_amdgcn_sched_barrier(0);                                                                     \
+            break;                                                                                                 \
+        }                                                                                                          \
+    }
         if constexpr (Q8) {
-            if (act_m1 && act_n[TN - 1]) {
-#pragma unroll 1
-                for (int kt = 0; kt < n_slices; ++kt, ++it)
-                    KVF_Q8_SLICE(KVF_Q8_MMA, KVF_Q8_MMA_HI);
-            } else {
-#pragma unroll 1
-                for (int kt = 0; kt < n_slices; ++kt, ++it)
-                    KVF_Q8_SLICE(KVF_Q8_MMA_IF, KVF_Q8_MMA_HI_IF);
-            }
-            KVF_Q8_WAIT_SET0();
+            if (act_m1 && act_n[TN - 1])
+                KVF_SLICES(KVF_Q8_SLICE(KVF_Q8_MMA, KVF_Q8_MMA_HI), KVF_Q8_WAIT_SET0())
+            else
+                KVF_SLICES(KVF_Q8_SLICE(KVF_Q8_MMA_IF, KVF_Q8_MMA_HI_IF), KVF_Q8_WAIT_SET0())
         } else {
-            if (act_m1 && act_n[TN - 1]) {
-#pragma unroll 1
-                for (int kt = 0; kt < n_slices; ++kt, ++it)
-                    KVF_SLICE(KVF_MMA, KVF_MMA_HI);
-            } else {
-#pragma unroll 1
-                for (int kt = 0; kt < n_slices; ++kt, ++it)
-                    KVF_SLICE(KVF_MMA_IF, KVF_MMA_HI_IF);
-            }
-            // the prefetched fragments of the next row tile's first slice must be in their registers before anything
-            // else may touch them
-            KVF_WAIT_SET(0);
+            if (act_m1 && act_n[TN - 1])
+                KVF_SLICES(KVF_SLICE(KVF_MMA, KVF_MMA_HI), KVF_WAIT_SET(0))
+            else
+                KVF_SLICES(KVF_SLICE(KVF_MMA_IF, KVF_MMA_HI_IF), KVF_WAIT_SET(0))
         }
+#undef KVF_SLICES
 
         // ---- epilogue of row tile rt
         {
