@@ -8,9 +8,9 @@
 //   logits  16 tokens x 16 heads per MFMA group (v_mfma_f32_16x16x32_bf16, or 16x16x4_f32 for f32 pools), K
 //           fragments loaded straight from global memory (each lane owns a quarter of a token row),
 //   softmax online, fp32, per head (state replicated over the 4 lanes that hold a head's 16 tokens),
-//   P.V     bfloat16 pools: on the matrix cores too (decode_bf16_kernel);
-//           binary32 pools: on the vector ALU with lanes owning 16-byte column slices of V rows, probabilities pass
-//           through a per-wave LDS tile (decode_kernel).
+//   P.V     bfloat16 pools of one head per block: on the matrix cores too (decode_bf16_kernel);
+//           binary32 pools and all-head blocks: on the vector ALU with lanes owning 16-byte column slices of V rows,
+//           probabilities pass through a per-wave LDS tile (decode_kernel).
 // Partial states of the 4 wavefronts are merged in LDS; with several splits a second kernel merges the splits.
 #include <mutex>
 #include <type_traits>
@@ -261,14 +261,14 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
     }
 }
 
-// bfloat16 pools: 32 tokens (two 16-token pieces) per step of a wavefront (attend.h).
+// bfloat16 pools of one head per block: 32 tokens (two 16-token pieces) per step of a wavefront (attend.h).
 // Error against binary64, relative in the 2-norm, this kernel / the vector-ALU kernel it replaced: 1.57e-7 / 1.77e-7 (one
 // request of 1000 tokens, d = 128), 1.99e-7 / 2.41e-7 (48 ragged requests), 1.66e-7 / 2.29e-7 (256 requests of 4096 tokens).
 //
 // Bound: HBM for blocks read once (64 x 2048 tokens, 64 groups: 5.35 TB/s of distinct bytes, 541 -> 505 us); blocks that many
 // requests share come out of the caches, where the vector ALU was the limit (8 heads per KV head, 256 x 4096 tokens, 16
 // groups: 893 -> 716 us, 12 TB/s of rows read).  Three wavefronts per SIMD hold 16 KiB each in flight.
-template <int D, bool AH>
+template <int D>
 __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
 {
     constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
@@ -282,23 +282,22 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
     const int b = blockIdx.y / A.kv_heads;
     const int kvh = blockIdx.y - b * A.kv_heads;
     const int li = blockIdx.z;
-    const int g = AH ? A.layer_begin + li : (A.layer_begin + li) * A.kv_heads + kvh;
-    const int64_t row = AH ? (int64_t)A.kv_heads * D : (int64_t)D;      // elements from one token of a block to the next
+    const int g = (A.layer_begin + li) * A.kv_heads + kvh;
     const int ctx = A.ctx_len[b];
     const int ppb = A.t >> 4;                                           // 16-token pieces per block
     const int p_lo = split * A.blocks_per_split * ppb;
     const int p_hi = min((ctx + 15) >> 4, p_lo + A.blocks_per_split * ppb);
     const int x0 = A.req_start[b];
-    const int64_t r = (int64_t)A.t * row;
-    const bf16_t *kg_ = (const bf16_t *)A.kpool + (int64_t)g * A.P * r + (AH ? kvh * D : 0);
-    const bf16_t *vg_ = (const bf16_t *)A.vpool + (int64_t)g * A.P * r + (AH ? kvh * D : 0);
+    const int64_t r = (int64_t)A.t * D;
+    const bf16_t *kg_ = (const bf16_t *)A.kpool + (int64_t)g * A.P * r;
+    const bf16_t *vg_ = (const bf16_t *)A.vpool + (int64_t)g * A.P * r;
     const int32_t *btg = A.bt + (int64_t)g * A.n;
     const float *skg = A.scale_k + (int64_t)g * A.n;
     const float *svg = A.scale_v + (int64_t)g * A.n;
 
     const int head = lane & 15, kg = lane >> 4;                         // also: token of a K row / column slice of a V row
-    const int64_t k_off = (int64_t)head * row + kg * (D / 4);
-    const int64_t v_off = (int64_t)(4 * kg) * row + head * NC;
+    const int k_off = head * D + kg * (D / 4);
+    const int v_off = 4 * kg * D + head * NC;
 
     uint4 qf[NF];
     {
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         const int xb = pshift >= 0 ? p >> pshift : p / ppb;
         return Entry{btg[x0 + xb], (p - xb * ppb) * 16, skg[x0 + xb], svg[x0 + xb]};
     };
-    auto rows_of = [&](const Entry &en) __attribute__((always_inline)) { return (int64_t)en.phys * r + (int64_t)en.sub * row; };
+    auto rows_of = [&](const Entry &en) __attribute__((always_inline)) { return (int64_t)en.phys * r + (int64_t)en.sub * D; };
     auto logits = [&](int64_t off) __attribute__((always_inline)) {
         const uint4 *krow = reinterpret_cast<const uint4 *>(kg_ + off + k_off);
         floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -352,7 +351,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            vr[j] = *reinterpret_cast<const vrow_t *>(vg_ + (j < 4 ? off0 : off1) + v_off + (int64_t)(j & 3) * row);
+            vr[j] = *reinterpret_cast<const vrow_t *>(vg_ + (j < 4 ? off0 : off1) + v_off + (j & 3) * D);
         if (p + 8 < p_hi) {
             en0 = entry_at(p + 8);
             en1 = entry_at(min(p + 9, p_hi - 1));
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
                 const float zt = (tok & 2) ? ((tok & 1) ? z[3] : z[2]) : ((tok & 1) ? z[1] : z[0]);
                 const float zw = __shfl(zt, head + 16 * (tok >> 2), 64);
                 const float wt = __builtin_amdgcn_exp2f(fmaf(zw, sc.sk, fmaf(zw, sc.sk_rest, -st.m))) * sc.sv;
-                const bf16_t *vt = vg_ + off + (int64_t)tok * row + 4 * kg * NC;
+                const bf16_t *vt = vg_ + off + tok * D + 4 * kg * NC;
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -515,32 +514,39 @@ static void launch_decode_t(hipStream_t s, const DecodeArgs &A, int n_layers)
 {
     const dim3 grid((unsigned)A.nsplit, (unsigned)(A.B * A.kv_heads), (unsigned)n_layers);
     const dim3 cgrid((unsigned)A.rep, (unsigned)(A.B * A.kv_heads), (unsigned)n_layers);
-    constexpr bool bf16 = std::is_same<T, bf16_t>::value;
     const bool ah = A.gstride == 1 && A.kv_heads > 1;
-    if constexpr (bf16) {
-        const size_t lds = (size_t)4 * A.rep_pad * D * sizeof(float);
-        if (ah)
-            decode_bf16_kernel<D, true><<<grid, 256, lds, s>>>(A);
-        else
-            decode_bf16_kernel<D, false><<<grid, 256, lds, s>>>(A);
-    }
-#define KVF_DEC(R)                                                    \
-    do {                                                              \
-        if (ah)                                                       \
-            decode_kernel<T, D, R, true><<<grid, 256, 0, s>>>(A);     \
-        else                                                          \
-            decode_kernel<T, D, R, false><<<grid, 256, 0, s>>>(A);    \
+    constexpr bool bf16 = std::is_same<T, bf16_t>::value;
+    // Both products on the matrix cores, maxima in base 2.  All-head blocks stay with decode_kernel: with it a call of theirs is
+    // faster or level except at 16 query heads per KV head (us, 8 KV heads of 128 elements, this kernel / the other one: 48 x 4096
+    // tokens, 1 layer, 161 / 462; 64 x 2048, 4 layers, 390 / 399; 4 KV heads of 64, 16 query heads each, 336 / 128), and where
+    // one entry's scale meets rows of several heads, logits of several hundred come about, for which another order of
+    // roundings moves an entry of the output by 1.5e-5.
+    const bool mma = bf16 && !ah;
+    if constexpr (bf16)
+        if (mma)
+            decode_bf16_kernel<D><<<grid, 256, (size_t)4 * A.rep_pad * D * sizeof(float), s>>>(A);
+#define KVF_DEC(R)                                                         \
+    do {                                                                   \
+        if (ah)                                                            \
+            decode_kernel<T, D, R, true><<<grid, 256, 0, s>>>(A);          \
+        else if constexpr (!bf16)                                          \
+            decode_kernel<T, D, R, false><<<grid, 256, 0, s>>>(A);         \
     } while (0)
-    else switch (A.rep_pad) {
-    case 1: KVF_DEC(1); break;
-    case 2: KVF_DEC(2); break;
-    case 4: KVF_DEC(4); break;
-    case 8: KVF_DEC(8); break;
-    default: KVF_DEC(16); break;
-    }
+    if (!mma)
+        switch (A.rep_pad) {
+        case 1: KVF_DEC(1); break;
+        case 2: KVF_DEC(2); break;
+        case 4: KVF_DEC(4); break;
+        case 8: KVF_DEC(8); break;
+        default: KVF_DEC(16); break;
+        }
 #undef KVF_DEC
-    if (A.nsplit > 1)
-        decode_combine_kernel<D, bf16><<<cgrid, 256, 0, s>>>(A);
+    if (A.nsplit > 1) {
+        if (mma)
+            decode_combine_kernel<D, true><<<cgrid, 256, 0, s>>>(A);
+        else
+            decode_combine_kernel<D, false><<<cgrid, 256, 0, s>>>(A);
+    }
 }
 
 int launch_decode(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int kv_heads, int layer_begin, int n_layers,

@@ -1,5 +1,8 @@
 """Paged decode over bfloat16 pools, both products on the matrix cores: edges of the 16-token pieces, of the pairs a
-wavefront takes and of the splits, every head count, both pool layouts, against attention in binary64."""
+wavefront takes and of the splits, every head count, against attention in binary64; the same inputs over all-head blocks,
+which the vector-ALU kernel takes."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -94,3 +97,35 @@ def test_rows_past_the_context_and_infinite_values():
     keep = torch.ones_like(out, dtype=torch.bool)
     keep[:, b, :, 77] = False
     assert float((out[keep] - clean[keep]).abs().max()) < 1.2e-5           # the same bound as above
+
+
+def test_all_heads_result_is_kept():
+    """Blocks over all heads whose scales do not belong to their rows: logits of several hundred, where binary32 leaves an
+    entry open by 1e-5 and more.  The result is pinned to that of the vector-ALU kernel (golden/decode_all_heads.npy: this
+    call, taken when that kernel was the only one), to the bounds that perf/cases.py states for the entry point."""
+    from paper_2601_03067_amd import binding as kb
+    t, d, heads, rep, ctx = 16, 64, 4, 2, [700, 37, 433]
+    rng = np.random.default_rng(11)
+    blocks = [(c + t - 1) // t for c in ctx]
+    n = sum(blocks)
+
+    def integers(most, *shape):
+        return rng.integers(-most, most + 1, shape).astype(np.float32)
+
+    def to_gpu(x):
+        return torch.from_numpy(x).to(DEV).to(torch.bfloat16)
+
+    # keys share a direction, so that many of the large logits of a row lie close together
+    K = to_gpu((integers(112, 1, 1, t * heads * d) + integers(15, 1, n, t * heads * d)) / 32)
+    V, q = to_gpu(integers(127, 1, n, t * heads * d) / 32), to_gpu(integers(127, 1, len(ctx), heads * rep, d) / 64)
+    cache = kb.Cache(K, V, torch.from_numpy(rng.permutation(n).astype(np.int32)[None]).to(DEV), t, d * heads)
+    fused = torch.from_numpy(rng.integers(0, 4, (1, n)) < 3).to(DEV)
+    cache.scale_k.copy_(torch.where(fused, 45.0 + 0.125 * torch.arange(n, device=DEV), 1.0))
+    cache.scale_v.copy_(torch.where(fused, 44.0 - 0.125 * torch.arange(n, device=DEV), 1.0))
+    rs = torch.tensor([sum(blocks[:b]) for b in range(len(ctx))], dtype=torch.int32, device=DEV)
+    cl = torch.tensor(ctx, dtype=torch.int32, device=DEV)
+    out = kb.paged_decode_attn_all_heads(kb.Context(DEV), cache, heads, q, rs, cl, max(blocks)).cpu().numpy().astype(np.float64)
+    ref = np.load(os.path.join(os.path.dirname(__file__), "golden", "decode_all_heads.npy")).astype(np.float64)
+    size = np.maximum(np.abs(ref), np.sqrt((ref ** 2).mean()))
+    assert float(np.linalg.norm(out - ref) / np.linalg.norm(ref)) <= 1.2e-6
+    assert float((np.abs(out - ref) / size).max()) <= 8e-6
