@@ -35,6 +35,12 @@ struct AttendScale {
         sk_rest = (float)(s - (double)sk);
         sv = value;
     }
+    // exp2(z (sk + sk_rest) - m) for z sk above -inf.  A logit of -inf has weight 0, which its callers see to: sk_rest is of
+    // either sign or zero, and -inf times it is +inf or NaN.
+    __device__ __forceinline__ float weight(float z, float m) const
+    {
+        return __builtin_amdgcn_exp2f(fmaf(z, sk, fmaf(z, sk_rest, -m)));
+    }
 };
 
 template <int D>
@@ -65,13 +71,13 @@ struct Attend32 {
             attend_mma(k1[f], qf[f], z1);
         }
         // ---- online softmax for this lane's row over its 8 tokens, then over the 4 token groups
-        float bmax = -INFINITY;
-        bool in[8];
+        float bmax = -INFINITY, zz[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
-            in[v] = full || (v & 3) < (v < 4 ? left0 : left1);
-            const float zz = (v < 4 ? z0[v & 3] : z1[v & 3]) * (v < 4 ? s0.sk : s1.sk);
-            bmax = fmaxf(bmax, in[v] ? zz : -INFINITY);
+            zz[v] = (v < 4 ? z0[v & 3] : z1[v & 3]) * (v < 4 ? s0.sk : s1.sk);
+            if (!full)
+                zz[v] = (v & 3) < (v < 4 ? left0 : left1) ? zz[v] : -INFINITY;
+            bmax = fmaxf(bmax, zz[v]);
         }
         bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
         bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
@@ -83,7 +89,7 @@ struct Attend32 {
         for (int v = 0; v < 8; ++v) {
             const AttendScale &s = v < 4 ? s0 : s1;
             const float z = v < 4 ? z0[v & 3] : z1[v & 3];
-            const float pr = in[v] ? __builtin_amdgcn_exp2f(fmaf(z, s.sk, fmaf(z, s.sk_rest, -m_new))) : 0.0f;
+            const float pr = zz[v] == -INFINITY ? 0.0f : s.weight(z, m_new);
             psum += pr;
             w[v] = pr * s.sv;
         }

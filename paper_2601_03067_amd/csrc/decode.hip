@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
             for (int tok = 0; tok < here; ++tok) {
                 const float zt = (tok & 2) ? ((tok & 1) ? z[3] : z[2]) : ((tok & 1) ? z[1] : z[0]);
                 const float zw = __shfl(zt, head + 16 * (tok >> 2), 64);
-                const float wt = __builtin_amdgcn_exp2f(fmaf(zw, sc.sk, fmaf(zw, sc.sk_rest, -st.m))) * sc.sv;
+                const float wt = (zw * sc.sk == -INFINITY ? 0.0f : sc.weight(zw, st.m)) * sc.sv;
                 const bf16_t *vt = vg_ + off + tok * D + 4 * kg * NC;
 #pragma unroll
                 for (int c = 0; c < NC; ++c)

@@ -129,3 +129,38 @@ def test_all_heads_result_is_kept():
     size = np.maximum(np.abs(ref), np.sqrt((ref ** 2).mean()))
     assert float(np.linalg.norm(out - ref) / np.linalg.norm(ref)) <= 1.2e-6
     assert float((np.abs(out - ref) / size).max()) <= 8e-6
+
+
+@pytest.mark.parametrize("step", ["paged", "static", "all_heads", "shared"])
+def test_logits_of_minus_infinity(step):
+    """A token with an infinite key element may give a logit of -inf: it has no weight, and the row is that of the others."""
+    from paper_2601_03067_amd import binding as kb
+    t, d, heads, rep = 16, 128, 2, 4
+    all_heads = step == "all_heads"
+    _, cache, start, max_blocks, gen = _setup(t, d, heads, 9, all_heads=all_heads)
+    n = cache.bt.shape[1]
+    cache.bt.copy_(torch.arange(n, dtype=torch.int32, device=DEV))
+    b, other = CONTEXTS.index(1000), CONTEXTS.index(300)
+    cache.bt[:, int(start[other]):int(start[other]) + 12] = cache.bt[:, int(start[b]):int(start[b]) + 12]     # shared by two
+    cache.scale_k[:, ::3] = 1.0                                                # the scale of a block that was not fused
+    cache.scale_v[:, ::3] = 1.0
+    q = torch.randn(2, len(CONTEXTS), heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
+    q[..., 7] = q[..., 7].abs() + 0.5
+    q[..., 90] = -q[..., 90].abs() - 0.5
+    K = cache.K.view(cache.K.shape[0], -1, t, heads if all_heads else 1, d)
+    K[:, ::2, 5, :, 7] = float("-inf")                                         # one token of every other block
+    K[:, 1::5, 11, :, 90] = float("inf")                                       # q < 0 there
+    ctx = kb.Context(DEV)
+    rs, cl = torch.from_numpy(start).to(DEV), torch.tensor(CONTEXTS, dtype=torch.int32, device=DEV)
+    if step == "shared":
+        plan = kb.SharedDecodePlan(ctx, cache, heads, start, np.array(CONTEXTS, np.int32), heads * rep, min_cluster_blocks=1)
+        assert plan.info.clusters > 0
+        out = kb.paged_decode_attn_shared(ctx, cache, plan, q)
+    elif step == "static":
+        out = torch.empty(q.shape, dtype=torch.float32, device=DEV)
+        kb.paged_decode_attn_static(ctx, cache, heads, q, rs, cl, max_blocks, out)
+    else:
+        out = (kb.paged_decode_attn_all_heads if all_heads else kb.paged_decode_attn)(ctx, cache, heads, q, rs, cl, max_blocks)
+    ref = _reference(cache, t, d, heads, q, start, all_heads)
+    assert bool(torch.isfinite(ref).all())
+    assert float((out.cpu().double() - ref).abs().max()) < 1.2e-5              # the bound of test_against_binary64
