@@ -7,7 +7,8 @@
 //           and V^T's fragment c is element c of its 8 rows, one v_perm per two values.  The order of the summation
 //           indices is free as long as both operands agree, so the weights never leave their lane.
 // The weights are split exactly: three truncated bfloat16 parts hold all 24 bits of a binary32, so every product is exact
-// and the sums are binary32, smallest parts first.  The exponent's argument is rounded once (scale carried in two words).
+// and the sums are binary32, smallest parts first.  The scale of the logits is carried in two words, so that the exponent's
+// argument, where the weight is not small, is as good as the logit (AttendScale::weight).
 #ifndef KVFUSE_ATTEND_H
 #define KVFUSE_ATTEND_H
 
@@ -36,10 +37,11 @@ struct AttendScale {
         sv = value;
     }
     // exp2(z (sk + sk_rest) - m) for z sk above -inf.  A logit of -inf has weight 0, which its callers see to: sk_rest is of
-    // either sign or zero, and -inf times it is +inf or NaN.
+    // either sign or zero, and -inf times it is +inf or NaN.  z sk - m is taken first: it is small where the weight is not, so
+    // that the second word survives the rounding of the sum; z sk_rest - m would be rounded to a unit of m.
     __device__ __forceinline__ float weight(float z, float m) const
     {
-        return __builtin_amdgcn_exp2f(fmaf(z, sk, fmaf(z, sk_rest, -m)));
+        return __builtin_amdgcn_exp2f(fmaf(z, sk_rest, fmaf(z, sk, -m)));
     }
 };
 

@@ -164,3 +164,23 @@ def test_logits_of_minus_infinity(step):
     ref = _reference(cache, t, d, heads, q, start, all_heads)
     assert bool(torch.isfinite(ref).all())
     assert float((out.cpu().double() - ref).abs().max()) < 1.2e-5              # the bound of test_against_binary64
+
+
+@pytest.mark.parametrize("d,scale", [(128, 45.25), (64, 31.7), (128, 300.1)])
+def test_weights_of_large_logits(d, scale):
+    """Logits of several hundred: the scale's rounding, 2^-24 of it, would move a weight by 1e-5.  The queries pick single key
+    elements, so that the products themselves are exact and the weights alone are tested."""
+    t, heads, rep = 16, 2, 4
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 3 * d)
+    q = torch.zeros(2, len(CONTEXTS), heads * rep, d, device=DEV)
+    q.scatter_(-1, torch.randint(0, d, q.shape[:-1] + (1,), generator=gen, device=DEV), 1.0)
+    # logits up to 255 / 16 * scale / sqrt(d), in steps that leave several tokens with a share of the weight
+    cache.K.copy_(240 / 16 + torch.randint(0, 16, cache.K.shape, generator=gen, device=DEV) / 16)
+    cache.scale_k.copy_(scale * (1.0 + torch.rand(cache.scale_k.shape, generator=gen, device=DEV) / 512))
+    q = q.to(torch.bfloat16)
+    # against the library's own softmax scale, a binary32
+    ref = _reference(cache, t, d, heads, q.double() * (float(np.float32(1.0 / d ** 0.5)) * d ** 0.5), start, False)
+    out = _call(kb, cache, heads, q, start, max_blocks, False)
+    # Two roundings of the exponent's argument x move a weight 2^-x by x 2^-x ln 2 * 2^-23 <= 0.37 * 2^-23 of the largest
+    # one, exp2, the sums of weights and of products and the division by a unit (2^-24) each: below 5 units of the values.
+    assert float((out - ref).abs().max()) < 5 * 2.0 ** -24 * float(cache.V.float().abs().max())
