@@ -34,6 +34,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <cmath>
 #include <new>
 #include <vector>
 
@@ -62,7 +63,8 @@ struct PrefillArgs {
     int32_t P, n, t, kv_heads, layer_begin, Hq, rep, rep_pad, npw;
     int32_t req_start, q_begin, q_end, chunk_begin;
     uint64_t ppb_inv;                // 2^40 / pieces per block, rounded up
-    float sm_scale;
+    float sm_scale;                  // its size; a negative one is turned into the sign of the queries
+    uint32_t q_sign;                 // 0, or the sign bits of two bfloat16
 };
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -154,6 +156,17 @@ struct PWalk {
         return sc;
     }
 };
+
+// The running maximum is taken before the softmax scale is applied, which must not turn it round: logits of a negative scale
+// are those of its size and the queries' opposites.  (Called once the first loads of the context are on their way, so that
+// they do not wait for the queries: 46.7 -> 45.7 us for 200 queries of 4296 tokens.)
+template <int KS>
+__device__ static __forceinline__ void sign_queries(uint4 (&qf)[KS], uint32_t sign)
+{
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        qf[ks] = make_uint4(qf[ks].x ^ sign, qf[ks].y ^ sign, qf[ks].z ^ sign, qf[ks].w ^ sign);
+}
 
 // max or sum over the two lanes that share a query row (lane, lane ^ 32)
 __device__ static __forceinline__ float halves_max(float x)
@@ -413,6 +426,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
     fetch(b0, b1, kr1, vr1);
     hide(a0, a1, vr0);
     stash(0, kr0, vr0);
+    sign_queries(qf, A.q_sign);
     __syncthreads();
     for (int ti = 0; ti < n_tiles; ti += 2) {
         // tile ti is in buffer 0, tile ti + 1 in register set 1
@@ -518,6 +532,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
 
     PRows r0 = walk.rows(A, 2 * wave), r1 = walk.rows(A, 2 * wave + 1);       // a tile ahead of their use
     PScales n0 = walk.scales(A, 2 * wave), n1 = walk.scales(A, 2 * wave + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    sign_queries(qf, A.q_sign);
     for (int ti = wave; ti < n_tiles; ti += kSplitWaves) {
         const int64_t u0 = walk.first_row(A, r0), u1 = walk.first_row(A, r1);
         const PScales s0 = n0, s1 = n1;
@@ -832,7 +848,8 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
     A.Hq = plan->Hq; A.rep = plan->rep; A.rep_pad = plan->rep_pad; A.npw = plan->npw;
     A.req_start = plan->req_start; A.q_begin = plan->q_begin; A.q_end = plan->q_end; A.chunk_begin = plan->chunk_begin;
     A.ppb_inv = ((1ull << 40) + (uint64_t)(pool->t / 16) - 1) / (uint64_t)(pool->t / 16);
-    A.sm_scale = sm_scale;
+    A.sm_scale = std::fabs(sm_scale);
+    A.q_sign = std::signbit(sm_scale) ? 0x80008000u : 0u;
     const int per_wg = 4 * plan->npw;
     const unsigned heads = (unsigned)plan->kv_heads, layers = (unsigned)plan->n_layers;
     const dim3 grid((unsigned)((nq + per_wg - 1) / per_wg), heads, layers);

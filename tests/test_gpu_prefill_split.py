@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _reference(cache, t, d, heads, layers, q, q_begin):
+def _reference(cache, t, d, heads, layers, q, q_begin, sm_scale=None):
     _, nq, Hq, _ = q.shape
     rep, ctx = Hq // heads, q_begin + nq
     out = torch.empty(q.shape, dtype=torch.float64, device=DEV)
@@ -20,7 +20,7 @@ def _reference(cache, t, d, heads, layers, q, q_begin):
         k = (cache.K[g][x].double().view(nb, t, d) * cache.scale_k[g, :nb, None, None].double()).reshape(-1, d)[:ctx]
         v = (cache.V[g][x].double().view(nb, t, d) * cache.scale_v[g, :nb, None, None].double()).reshape(-1, d)[:ctx]
         for j in range(h * rep, (h + 1) * rep):
-            z = (q[li, :, j].double() @ k.T) / d ** 0.5
+            z = (q[li, :, j].double() @ k.T) * (d ** -0.5 if sm_scale is None else sm_scale)
             out[li, :, j] = torch.softmax(z.masked_fill(hidden, float("-inf")), -1) @ v
     return out
 
@@ -36,9 +36,7 @@ CASES = [(1, 1, 1, 16, 64, 0, 0, 1),             # one token, nothing before it
          (4, 8, 16, 32, 64, 96, 31, 57)]         # 256, staged
 
 
-@pytest.mark.parametrize("reuse", [True, False])
-@pytest.mark.parametrize("case", CASES, ids=[str(i) for i in range(len(CASES))])
-def test_against_binary64(case, reuse):
+def _compare(case, reuse, sm_scale=None, signed_scales=False):
     from paper_2601_03067_amd import binding as kb
     layers, heads, rep, t, d, begin, skip, nq = case
     print("prefill", case, "reuse", reuse, flush=True)
@@ -60,13 +58,30 @@ def test_against_binary64(case, reuse):
     cache = kb.Cache(K, V, bt.contiguous(), t, d)
     cache.scale_k.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
     cache.scale_v.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
+    if signed_scales:
+        cache.scale_k[:, ::3] *= -1.0
     ctx = kb.Context(DEV)
     q = torch.randn(layers, nq, heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
     plan = kb.PrefillPlan(ctx, cache, heads, heads * rep, 0, begin, q_begin, q_begin + nq, reuse=reuse)
-    out = kb.prefill_attn(ctx, cache, plan, q)
-    ref = _reference(cache, t, d, heads, layers, q, q_begin)
+    out = kb.prefill_attn(ctx, cache, plan, q, sm_scale=sm_scale)
+    ref = _reference(cache, t, d, heads, layers, q, q_begin, sm_scale)
     # The weights are kept as a bfloat16 head and remainder, 2^-17 of their size at most (half a unit of the ninth bit of the
     # ninth), and values are below 1.5 * 6: 7e-5 for a row that is a single weight, on top of 1.2e-5 of binary32 roundings of
     # logits below 15.
     err = float((out.double() - ref).abs().max())
     assert err < 8.2e-5, err
+
+
+@pytest.mark.parametrize("reuse", [True, False])
+@pytest.mark.parametrize("case", CASES, ids=[str(i) for i in range(len(CASES))])
+def test_against_binary64(case, reuse):
+    _compare(case, reuse)
+
+
+@pytest.mark.parametrize("sm_scale", [-0.1, 0.0])
+@pytest.mark.parametrize("signed_scales", [False, True])
+@pytest.mark.parametrize("case", CASES, ids=[str(i) for i in range(len(CASES))])
+def test_softmax_scale_of_either_sign(case, signed_scales, sm_scale):
+    """Logits times a scale that is not positive: the largest ones are then the smallest products (of either sign, with scales
+    of either sign); rows that see nothing of a tile are among them.  Logits stay below those of the test above."""
+    _compare(case, True, sm_scale=sm_scale, signed_scales=signed_scales)
