@@ -159,6 +159,9 @@ template <typename K> static int resident_workgroups(K kernel, int threads = 256
     return cached;
 }
 
+// A launch has fewer than 2^32 threads along one axis.
+static inline bool launch_fits(int64_t workgroups, int threads) { return workgroups <= (int64_t)0xFFFFFFFF / threads; }
+
 // launchers, one per source file
 void launch_block_norms(hipStream_t s, const PoolDesc &pool, const TableDesc &tab);
 // the same norms and table for a tree call, with everything its heights expect cleared, the leaf sets and the checks of

@@ -1119,10 +1119,12 @@ __global__ __launch_bounds__(64 * kSmallWaves, 2) void similarity_small_kernel(P
     }
 }
 
-// One tile per node, or few enough tiles to run side by side (two workgroups per compute unit).
+// One tile per node, or few enough tiles to run side by side (two workgroups per compute unit); and no more workgroups than a
+// launch has threads for.
 static bool small_height(const WorkDesc &w, const HeightDesc &h)
 {
-    return h.small_tiles == 1 || (int64_t)w.G * h.n_nodes * h.small_tiles <= kSmallTiles;
+    const int64_t tiles = (int64_t)w.G * h.n_nodes * h.small_tiles;
+    return (h.small_tiles == 1 && launch_fits(tiles, 64 * kSmallWaves)) || tiles <= kSmallTiles;
 }
 
 template <typename T>

@@ -1,0 +1,65 @@
+"""More nodes, groups or requests than the widest workgroups of a kernel have launches for (a launch has fewer than 2^32 threads
+along one axis): the narrower variants take over, and the results are those that the inputs were made for."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+R = 64                                # the shortest blocks: 128 bytes
+
+
+def _fuse(G, leaves):
+    """G groups of sum(leaves) blocks.  Every second block is an exact copy of the one before it, all others point their own
+    way; -> the fused cache and the statistics."""
+    from paper_2601_03067_amd import binding as kb
+    n = sum(leaves)
+    print("groups", G, "leaves", len(leaves), "blocks", n, flush=True)
+    # one-hot blocks with signs: block pair m of a group is +-e_(m mod R) on top of a length of its own, so that pairs of
+    # different m are orthogonal, opposite, or (beyond 2 R pairs) the same direction
+    m = torch.arange(n, device=DEV) // 2
+    K1 = torch.zeros(n, R, device=DEV, dtype=torch.bfloat16)
+    K1[torch.arange(n, device=DEV), m % R] = torch.where((m // R) % 2 == 0, 1.0, -1.0).to(torch.bfloat16)
+    K = K1.repeat(G, 1, 1).view(G, n, R)
+    bt = torch.arange(n, device=DEV, dtype=torch.int32).repeat(G, 1)
+    ctx = kb.Context(DEV)
+    cache = kb.Cache(K, K.clone(), bt, 1, R)
+    start = np.concatenate([[0], np.cumsum(leaves)[:-1]]).astype(np.int32)
+    plan = kb.Plan(ctx, cache, kb.tree_spec(start, np.array(leaves, np.int32), np.arange(len(leaves) + 1, dtype=np.int32)), cand_cap=2)
+    stats = kb.fuse_tree(ctx, plan, 0.9)
+    torch.cuda.synchronize()
+    return cache, stats
+
+
+def _kept(leaves):
+    """Blocks that survive in a group: a right block fuses where the left set holds its direction."""
+    n = sum(leaves)
+    way = (np.arange(n) // 2) % (2 * R)
+
+    def over(sets):
+        if len(sets) == 1:
+            return sets[0]
+        a, b = over(sets[:len(sets) // 2]), over(sets[len(sets) // 2:])
+        return np.concatenate([a, b[~np.isin(b, a)]])
+
+    return len(over(np.split(way, np.cumsum(leaves)[:-1])))
+
+
+def _check(cache, stats, leaves):
+    G, n = cache.bt.shape
+    kept = _kept(leaves)
+    assert stats.physical_blocks == G * kept and stats.fused == G * (n - kept)
+    for x in (cache.bt, cache.refcount, cache.scale_k, cache.remap):
+        assert bool((x == x[0]).all())
+    assert bool((cache.n_phys == kept).all()) and bool((cache.n_free == n - kept).all())
+    assert bool((cache.free_list[:, :n - kept] == cache.free_list[0, :n - kept]).all())
+    # every block still points its own way, with its own length
+    m = torch.arange(n, device=DEV) // 2
+    own = cache.K.view(G, n, R)[0][cache.bt[0].long(), m % R].float() * cache.scale_k[0]
+    assert torch.equal(own, torch.where((m // R) % 2 == 0, 1.0, -1.0))
+
+
+def test_more_one_tile_nodes_than_wide_workgroups():
+    """8 392 704 nodes of one 32 x 32 tile: 512 threads each would be more than a launch has."""
+    leaves = [1] * 4098
+    _check(*_fuse(4096, leaves), leaves)
