@@ -881,8 +881,10 @@ void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, co
         const unsigned grid = (unsigned)(w.G * h.n_nodes);
         if (h.max_cap <= kLocalSet)
             assign_finalize_kernel<256, true><<<grid, 256, 0, s>>>(pool.P, tab, w, h, height, clear_lists);
-        else
+        else if (launch_fits(grid, 1024))
             assign_finalize_kernel<1024, false><<<grid, 1024, 0, s>>>(pool.P, tab, w, h, height, clear_lists);
+        else               // (a few large sets among millions of small ones)
+            assign_finalize_kernel<256, false><<<grid, 256, 0, s>>>(pool.P, tab, w, h, height, clear_lists);
     }
 }
 

@@ -25,7 +25,7 @@ def _fuse(G, leaves):
     ctx = kb.Context(DEV)
     cache = kb.Cache(K, K.clone(), bt, 1, R)
     start = np.concatenate([[0], np.cumsum(leaves)[:-1]]).astype(np.int32)
-    plan = kb.Plan(ctx, cache, kb.tree_spec(start, np.array(leaves, np.int32), np.arange(len(leaves) + 1, dtype=np.int32)), cand_cap=2)
+    plan = kb.Plan(ctx, cache, kb.tree_spec(start, np.array(leaves, np.int32), np.arange(len(leaves) + 1, dtype=np.int32)), cand_cap=16)
     stats = kb.fuse_tree(ctx, plan, 0.9)
     torch.cuda.synchronize()
     return cache, stats
@@ -63,3 +63,9 @@ def test_more_one_tile_nodes_than_wide_workgroups():
     """8 392 704 nodes of one 32 x 32 tile: 512 threads each would be more than a launch has."""
     leaves = [1] * 4098
     _check(*_fuse(4096, leaves), leaves)
+
+
+def test_more_large_nodes_than_the_widest_bookkeeping():
+    """4 196 352 nodes, one in 2049 of them with a set too large for LDS: 1024 threads each would be more than a launch has."""
+    leaves = [1100] + [1] * 4097
+    _check(*_fuse(2048, leaves), leaves)
