@@ -54,7 +54,7 @@ __device__ __forceinline__ void rewrite_scale(const TableDesc &tab, int64_t i, i
     tab.scale_v[i] = nv == 0.0 ? 0.0f : (float)(tab.orig_norm_v[i] / nv);
 }
 
-// Two passes that do not depend on each other, in one launch.  The first n_lists workgroups take a group each: freed ids
+// Two passes that do not depend on each other, in one launch.  The first n_lists workgroups take a group at a time: freed ids
 // (blocks that were fused away) in ascending order, and the live count; their walk over the pool is a chain of barriers, so they
 // start first, are as wide as can be and load a step ahead (141 355 blocks a group: 394 us with 256 threads, 109 us).  The
 // others refresh the scales.
@@ -69,51 +69,53 @@ __global__ __launch_bounds__(kFinishThreads) void rewrite_finish_kernel(TableDes
     __shared__ int wave_tot[2][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if ((int)blockIdx.x >= n_lists) {
-        const int64_t i = (int64_t)(blockIdx.x - n_lists) * kFinishThreads + tid;
-        if (i < (int64_t)G * tab.n)
+        const int64_t step = (int64_t)(gridDim.x - n_lists) * kFinishThreads;
+        for (int64_t i = (int64_t)(blockIdx.x - n_lists) * kFinishThreads + tid; i < (int64_t)G * tab.n; i += step)
             rewrite_scale(tab, i, P, norm_k, norm_v);
         return;
     }
-    const int g = blockIdx.x;
-    const int64_t gp = (int64_t)g * P;
-    int freed = 0, live = 0;
-    int next_remap = tid < P ? tab.remap[gp + tid] : -1, next_refs = tid < P ? tab.refcount[gp + tid] : 0;
-    for (int p0 = 0, buf = 0; p0 < P; p0 += kFinishThreads, buf ^= 1) {
-        const int p = p0 + tid, ahead = p + kFinishThreads;
-        const unsigned long long mf = __ballot(next_remap >= 0);
-        const unsigned long long ml = __ballot(next_refs > 0);
-        const bool is_free = next_remap >= 0;
-        next_remap = ahead < P ? tab.remap[gp + ahead] : -1;
-        next_refs = ahead < P ? tab.refcount[gp + ahead] : 0;
-        if (lane == 0)
-            wave_tot[buf][wave] = __popcll(mf);
-        __syncthreads();                 // (one barrier a step: the other buffer is written before the next one)
-        int pre = 0, tot = 0;
+    for (int g = blockIdx.x; g < G; g += n_lists) {
+        const int64_t gp = (int64_t)g * P;
+        int freed = 0, live = 0;
+        int next_remap = tid < P ? tab.remap[gp + tid] : -1, next_refs = tid < P ? tab.refcount[gp + tid] : 0;
+        for (int p0 = 0, buf = 0; p0 < P; p0 += kFinishThreads, buf ^= 1) {
+            const int p = p0 + tid, ahead = p + kFinishThreads;
+            const unsigned long long mf = __ballot(next_remap >= 0);
+            const unsigned long long ml = __ballot(next_refs > 0);
+            const bool is_free = next_remap >= 0;
+            next_remap = ahead < P ? tab.remap[gp + ahead] : -1;
+            next_refs = ahead < P ? tab.refcount[gp + ahead] : 0;
+            if (lane == 0)
+                wave_tot[buf][wave] = __popcll(mf);
+            __syncthreads();                 // (one barrier a step: the other buffer is written before the next one)
+            int pre = 0, tot = 0;
 #pragma unroll
-        for (int k = 0; k < NW; ++k) {
-            const int c = wave_tot[buf][k];
-            pre += k < wave ? c : 0;
-            tot += c;
+            for (int k = 0; k < NW; ++k) {
+                const int c = wave_tot[buf][k];
+                pre += k < wave ? c : 0;
+                tot += c;
+            }
+            if (is_free && free_list)
+                free_list[gp + freed + pre + __popcll(mf & ((1ull << lane) - 1ull))] = p;
+            freed += tot;
+            live += __popcll(ml);
         }
-        if (is_free && free_list)
-            free_list[gp + freed + pre + __popcll(mf & ((1ull << lane) - 1ull))] = p;
-        freed += tot;
-        live += __popcll(ml);
-    }
-    // live counts are per wave: add them up
-    __syncthreads();
-    if (lane == 0)
-        wave_tot[0][wave] = live;
-    __syncthreads();
-    if (tid == 0) {
-        if (n_free)
-            n_free[g] = freed;
-        if (n_phys) {
-            int sum = 0;
-            for (int k = 0; k < NW; ++k)
-                sum += wave_tot[0][k];
-            n_phys[g] = sum;
+        // live counts are per wave: add them up
+        __syncthreads();
+        if (lane == 0)
+            wave_tot[0][wave] = live;
+        __syncthreads();
+        if (tid == 0) {
+            if (n_free)
+                n_free[g] = freed;
+            if (n_phys) {
+                int sum = 0;
+                for (int k = 0; k < NW; ++k)
+                    sum += wave_tot[0][k];
+                n_phys[g] = sum;
+            }
         }
+        __syncthreads();         // the counts are read before the next group's are written
     }
 }
 
@@ -126,8 +128,9 @@ void launch_rewrite(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, i
         rewrite_clear_kernel<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(tab.refcount, nb);
     if (ne > 0)
         rewrite_chase_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, pool.G, pool.P);
-    const int n_lists = free_list || n_free || n_phys ? pool.G : 0;
-    const int64_t grid = n_lists + (ne + kFinishThreads - 1) / kFinishThreads;
+    // (at most 2^20 workgroups of the one and 2^21 of the other kind: 2^20 times 1024 threads short of what a launch holds)
+    const int n_lists = free_list || n_free || n_phys ? std::min(pool.G, 1 << 20) : 0;
+    const int64_t grid = n_lists + std::min<int64_t>((ne + kFinishThreads - 1) / kFinishThreads, 1 << 21);
     if (grid > 0)
         rewrite_finish_kernel<<<(unsigned)grid, kFinishThreads, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v, n_lists, free_list,
                                                                         n_free, n_phys);

@@ -69,3 +69,9 @@ def test_more_large_nodes_than_the_widest_bookkeeping():
     """4 196 352 nodes, one in 2049 of them with a set too large for LDS: 1024 threads each would be more than a launch has."""
     leaves = [1100] + [1] * 4097
     _check(*_fuse(2048, leaves), leaves)
+
+
+def test_more_groups_than_the_widest_lists():
+    """4 194 400 groups of two blocks: the free lists of the table rewrite have 1024 threads a group."""
+    leaves = [1, 1]
+    _check(*_fuse(4194400, leaves), leaves)
