@@ -907,17 +907,27 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
         decode_shared_combine_kernel<D, false><<<cgrid, 256, 0, c->stream>>>(A);       \
     } while (0)
     if (pool->dtype == KVFUSE_BF16) {
-        // (any split of an XCD's seats between the two kinds is correct as long as the last seat completes both)
-        const uint64_t nc8 = ((uint64_t)nc + 7) / 8, seats = nc8 + ((uint64_t)nr + 7) / 8;
-        const uint64_t share = seats > 0 ? ((nc8 << 32) + seats - 1) / seats : 0;
-        if (seats > 0) {
+        auto items = [&](const SharedArgs &part, int n_cluster, int n_residual) {
+            // (any split of an XCD's seats between the two kinds is correct as long as the last seat completes both)
+            const uint64_t nc8 = ((uint64_t)n_cluster + 7) / 8, seats = nc8 + ((uint64_t)n_residual + 7) / 8;
+            const uint64_t share = seats > 0 ? ((nc8 << 32) + seats - 1) / seats : 0;
+            if (seats == 0)
+                return;
             if (pool->d == 128)
-                decode_items_bf16_kernel<128><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(A, nc, nr, share);
+                decode_items_bf16_kernel<128><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(part, n_cluster, n_residual, share);
             else
-                decode_items_bf16_kernel<64><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(A, nc, nr, share);
+                decode_items_bf16_kernel<64><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(part, n_cluster, n_residual, share);
+        };
+        if (launch_fits((int64_t)nc + nr + 14, 256)) {
+            items(A, nc, nr);
+        } else {                       // more items than a launch holds: one launch for each kind
+            items(A, nc, 0);
+            SharedArgs rest = A;
+            rest.items += nc;
+            items(rest, 0, nr);
         }
         const int64_t heads_total = tuples * plan->rep;
-        if (heads_total >= 4096) {
+        if (heads_total >= 4096 && launch_fits((heads_total + 3) / 4, 256)) {
             const unsigned grid = (unsigned)((heads_total + 3) / 4);
             if (pool->d == 128)
                 decode_shared_combine_waves_kernel<128><<<grid, 256, 0, c->stream>>>(A, heads_total);

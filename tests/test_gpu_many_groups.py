@@ -75,3 +75,29 @@ def test_more_groups_than_the_widest_lists():
     """4 194 400 groups of two blocks: the free lists of the table rewrite have 1024 threads a group."""
     leaves = [1, 1]
     _check(*_fuse(4194400, leaves), leaves)
+
+
+def test_shared_decode_of_more_heads_than_merging_wavefronts():
+    """67 110 400 query heads: the merge with a wavefront each would take more threads than a launch has."""
+    from paper_2601_03067_amd import binding as kb
+    B, rep, t, d = 4194400, 16, 16, 64
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(4)
+    K = torch.randn(1, 1, t * d, generator=gen, device=DEV).to(torch.bfloat16)
+    V = torch.randn(1, 1, t * d, generator=gen, device=DEV).to(torch.bfloat16)
+    cache = kb.Cache(K, V, torch.zeros(1, 1, device=DEV, dtype=torch.int32), t, d)
+    cache.identity_scales()
+    ctx_len = np.zeros(B, np.int32)
+    some = np.concatenate([np.arange(0, B, 997), [B - 1]])                # the others have no context: zeros
+    ctx_len[some] = t
+    ctx = kb.Context(DEV)
+    plan = kb.SharedDecodePlan(ctx, cache, 1, np.zeros(B, np.int32), ctx_len, rep)
+    q = torch.randn(1, B, rep, d, generator=gen, device=DEV, dtype=torch.bfloat16)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device=DEV)
+    kb.paged_decode_attn_shared(ctx, cache, plan, q, out=out)
+    pick = torch.from_numpy(some).to(DEV)
+    ref = torch.softmax(q[0, pick].double() @ K.view(t, d).double().T / d ** 0.5, -1) @ V.view(t, d).double()
+    # logits below 15, values below 6: as in test_gpu_decode_bf16.py
+    assert float((out[0, pick].double() - ref).abs().max()) < 1.2e-5
+    out[0, pick] = 0.0
+    assert not bool(out.any())
