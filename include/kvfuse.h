@@ -223,6 +223,13 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
  * stream.  n_groups must be the plan's G. */
 int kvfuse_plan_group_counters(kvfuse_ctx *ctx, const kvfuse_plan *plan, int32_t *out, int32_t n_groups);
 
+/* What stopping early did in the last kvfuse_fuse_tree call on this plan, for tests and tools.  slices: host [G] int32, the
+ * 64-byte slices of a block row after which the similarity step tested the tiles of a group (a row's whole length / 64: the
+ * group's products ran at full length).  open_pairs: host [n_heights] int32, pairs that the tests left to be finished one
+ * by one; the list for them holds *room.  Waits for the context's stream.  n_groups and n_heights must be the plan's. */
+int kvfuse_plan_early_counts(kvfuse_ctx *ctx, const kvfuse_plan *plan, int32_t *slices, int32_t n_groups, int32_t *open_pairs,
+                             int32_t n_heights, int32_t *room);
+
 /* ---- a7: paged decode attention through the (fused) table -------------------------------------------- */
 
 /* Workspace bytes for a decode call over n_layers layers, B requests, Hq query heads, kv_heads KV heads. */

@@ -127,6 +127,7 @@ lib.kvfuse_threshold_feedback.restype = _f64
 lib.kvfuse_plan_set_group_mask.argtypes = [_vp, _vp, _vp]
 lib.kvfuse_plan_set_assign_rule.argtypes = [_vp, _vp, _i32]
 lib.kvfuse_plan_group_counters.argtypes = [_vp, _vp, _vp, _i32]
+lib.kvfuse_plan_early_counts.argtypes = [_vp, _vp, _vp, _i32, _vp, _i32, C.POINTER(_i32)]
 lib.kvfuse_plan_set_screen_prefix.argtypes = [_vp, _vp, _i32, _vp]
 lib.kvfuse_plan_set_screen_fp8.argtypes = [_vp, _vp, _vp, C.c_size_t, _vp, C.c_size_t, C.c_int32]
 lib.kvfuse_tree_spec_shortest_first.argtypes = [C.POINTER(TreeSpec), _vp, _vp, _vp, _vp]
@@ -486,6 +487,13 @@ def group_counters(ctx, plan):
     out = np.zeros((plan.cache.G, 4), np.int32)
     ctx.check(lib.kvfuse_plan_group_counters(ctx.h, plan.h, out.ctypes.data, plan.cache.G))
     return out
+
+
+def early_counts(ctx, plan):
+    """kvfuse_plan_early_counts -> (numpy [G] slices before the test, numpy [heights] open pairs, room for open pairs)."""
+    slices, pairs, room = np.zeros(plan.cache.G, np.int32), np.zeros(plan.n_heights, np.int32), _i32(0)
+    ctx.check(lib.kvfuse_plan_early_counts(ctx.h, plan.h, slices.ctypes.data, slices.size, pairs.ctypes.data, pairs.size, C.byref(room)))
+    return slices, pairs, room.value
 
 
 def set_assign_rule(ctx, plan, rule):

@@ -55,6 +55,7 @@ struct Plan {
     int max_r = 0, max_l = 0;
     std::vector<uint8_t> group_enable_host;   // copy of the group mask for the statistics; empty = all groups
     int assign_rule = KVFUSE_RULE_ARGMAX;
+    int32_t early_room = 0;         // last tree call: open pairs that early rejection had room for, 0 = it was not used
     float *q8_dir_mem = nullptr;    // fp8 screen with centring asked for: the caller's [G][r] floats for the directions
 
     // Early rejection in a tree call (early.hip), by a rule on sizes: see kEarlyMinFlops.
@@ -655,12 +656,14 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     const float floor_f = std::nextafterf((float)(thr - 2.0 * band), -INFINITY);
     WorkDesc w = p.work;
     const bool early = p.early_pays(floor_f);
+    p.early_room = 0;
     if (early) {
         // Until the rewrite counts references anew, tab.refcount holds the tail shares; the merge work list, which the
         // assignment step fills, holds the open pairs of the similarity step before it.
         w.rem_k = reinterpret_cast<float *>(p.tab.refcount);
         w.early_nk = w.early_nk_mem;
         w.pair_cap = (int32_t)((size_t)w.G * w.l_stride * 2 * sizeof(int4) / (sizeof(int4) + sizeof(float)));
+        p.early_room = w.pair_cap;
         w.pairs = w.active;
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
@@ -766,6 +769,29 @@ int kvfuse_plan_group_counters(kvfuse_ctx *ctx, const kvfuse_plan *plan, int32_t
     for (int g = 0; g < w.G; ++g)
         for (int k = 0; k < 4; ++k)
             out[(size_t)g * 4 + k] = raw[(size_t)g * 8 + k];
+    return KVFUSE_OK;
+}
+
+int kvfuse_plan_early_counts(kvfuse_ctx *ctx, const kvfuse_plan *plan, int32_t *slices, int32_t n_groups, int32_t *open_pairs,
+                             int32_t n_heights, int32_t *room)
+{
+    if (!ctx)
+        return KVFUSE_EINVAL;
+    Ctx *c = &ctx->c;
+    if (!plan || !slices || !open_pairs || !room)
+        return fail(c, KVFUSE_EINVAL, "early counts: null plan or output");
+    const Plan &p = plan->p;
+    if (n_groups != p.work.G || n_heights != (int)p.heights.size())
+        return fail(c, KVFUSE_EINVAL, "early counts: n_groups and n_heights must be the plan's numbers of groups and heights");
+    *room = p.early_room;
+    if (p.early_room == 0) {
+        std::fill(slices, slices + n_groups, p.pool.r * (p.pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64);
+        std::fill(open_pairs, open_pairs + n_heights, 0);
+        return KVFUSE_OK;
+    }
+    KVF_HIP(c, hipStreamSynchronize(c->stream));
+    KVF_HIP(c, hipMemcpy(slices, p.work.early_nk_mem, (size_t)n_groups * 4, hipMemcpyDeviceToHost));
+    KVF_HIP(c, hipMemcpy(open_pairs, p.work.n_pairs_all, (size_t)n_heights * 4, hipMemcpyDeviceToHost));
     return KVFUSE_OK;
 }
 

@@ -17,13 +17,13 @@ def _case(which):
     """-> (recipe, offset that every key block of a group shares, candidate slots)"""
     bff = dict(t=16, d=64)                                   # 2 KiB rows: 32 slices
     if which == "white":                                     # a few pairs per tile stay open, sets ragged against the tiles
-        return wl.llama8b_bff(n_req=9, tokens=16 * 150, layers=12, kv_heads=2, prefix_tokens=16 * 9, near_pool=60, **bff), 0.0, 16
+        return wl.llama8b_bff(n_req=9, tokens=16 * 150, layers=20, kv_heads=2, prefix_tokens=16 * 9, near_pool=60, **bff), 0.0, 16
     if which == "shared_direction":                          # unrelated cosines around 0.5: a longer part before the test
-        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=12, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 1.0, 16
+        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=20, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 1.0, 16
     if which == "no_test":                                   # unrelated cosines around 0.85 against thr 0.9: full length
-        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=12, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 2.35, 64
+        return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=20, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 2.35, 64
     if which == "dense":                                     # most tiles hold more related pairs than are finished one by one
-        return wl.zipf_bff(n_req=8, tokens=32 * 150, layers=8, kv_heads=2, pool=150, t=32, d=64, thr=0.9), 0.0, 64
+        return wl.zipf_bff(n_req=8, tokens=32 * 150, layers=12, kv_heads=2, pool=150, t=32, d=64, thr=0.9), 0.0, 64
     if which == "pair_list_full":                            # 2.4 open pairs per left block; the list holds 1.6
         return wl.llama8b_bff(n_req=2, tokens=16 * 1300, layers=8, kv_heads=2, prefix_tokens=0, near_pool=560, near_frac=1.0, **bff), 0.0, 64
     if which == "f32":
@@ -55,6 +55,22 @@ def test_tree_with_early_rejection_matches_oracle(oracle, which, rule):
     gu.check_ambiguity(res, which)
     for r, g in zip(res, pick):
         gu.compare_group(r, cache, g, rec.dtype == torch.float32, which)
+    # the path that the case is for was taken
+    slices, open_pairs, room = kb.early_counts(ctx, plan)
+    row = rec.r * mat["K"].element_size() // 64
+    print("slices", sorted(set(slices.tolist())), "of", row, "open pairs", open_pairs.tolist(), "room", room, "fused", stats.fused, flush=True)
+    assert room > 0
+    if which == "no_test":                           # (the choice is a group's own: a few groups do test)
+        assert np.mean(slices == row) > 0.8 and np.all(slices[pick] == row)
+    else:
+        assert np.all((slices >= 2) & (slices <= row * 3 // 4)) and open_pairs.any()
+    if which == "shared_direction":
+        assert np.median(slices) > row / 4           # unrelated white blocks need less at this threshold
+    if which == "white":
+        assert np.median(slices) < row / 4
+    if which == "dense":
+        assert open_pairs.sum() < stats.fused        # a pair that fused and was not left open comes from a tile at full length
+    assert (open_pairs.max() > room) == (which == "pair_list_full")
     per_group = kb.group_counters(ctx, plan)
     assert per_group[pick, 0].tolist() == [int(r.stats[1]) for r in res]
     assert per_group[pick, 1].tolist() == [int(r.stats[2]) for r in res]
