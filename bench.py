@@ -101,7 +101,7 @@ def run_whole_config(args, torch, kb, wl):
         torch.cuda.synchronize()
         t_gen += time.perf_counter() - t0
         for thr in thresholds:
-            acc = per_thr.setdefault(thr, {"ms": [], "stage": {}, "fused": 0, "physical": 0, "logical": 0, "flops": 0.0,
+            acc = per_thr.setdefault(thr, {"ms": [], "stage": {}, "fused": 0, "physical": 0, "logical": 0, "flops": 0.0, "counted": 0.0,
                                            "refined": 0, "overflow": 0, "near": 0, "targets": 0})
             reps = args.steps + (args.warmup if si == 0 else 0)
             for rep in range(reps):
@@ -123,7 +123,8 @@ def run_whole_config(args, torch, kb, wl):
                     acc["stage"][k2] = acc["stage"].get(k2, 0.0) + v2 / args.steps
                 if rep == reps - 1:
                     acc["fused"] += st.fused; acc["physical"] += st.physical_blocks; acc["logical"] += st.logical_blocks
-                    acc["flops"] += st.sim_flops; acc["refined"] += st.refined; acc["overflow"] += st.cand_overflow
+                    acc["flops"] += st.sim_flops; acc["counted"] += st.sim_flops * counted_share(kb, ctx, plan, rec.r * elem)
+                    acc["refined"] += st.refined; acc["overflow"] += st.cand_overflow
                     acc["near"] += st.near_threshold; acc["targets"] += st.merge_targets
         print(f"bench.py: slab {si + 1}/{n_slabs} (layers {layers[0]}..{layers[-1]}) done, "
               + ", ".join(f"thr {t}: {per_thr[t]['ms'][-1]:.1f} ms" for t in thresholds), file=sys.stderr, flush=True)
@@ -134,7 +135,7 @@ def run_whole_config(args, torch, kb, wl):
     blocks = a["logical"]
     peak = 2500.0 if rec.dtype == torch.bfloat16 else 157.3
     sim_tflops = a["flops"] / (a["stage"]["similarity"] * 1e-3) / 1e12
-    share = counted_share(args, a["flops"], main_thr)
+    share = a["counted"] / a["flops"] if a["flops"] else 1.0
     phys_bytes = a["physical"] * rec.r * elem * 2
     line = {
         "metric": "KV blocks fused/sec (+ % MFMA peak); fused-table decode attn HBM GB/s",
@@ -171,15 +172,17 @@ def run_whole_config(args, torch, kb, wl):
     print(json.dumps(line))
 
 
-def counted_share(args, flops, thr):
-    """Share of the full-length product that the roofline counts.  A large tree call without a screen stops the product of a
-    tile as soon as a Cauchy-Schwarz bound settles it; what no exact method is without is the share 1 - thr of every row
-    (csrc/early.hip), less than what the kernel executes, so the rate stated is a lower bound of the executed one."""
-    return 1.0 - thr if not args.screen_prefix and not args.screen_fp8 and flops >= 5e10 else 1.0
+def counted_share(kb, ctx, plan, row_bytes):
+    """Share of the full-length product that the roofline counts, for the last tree call on this plan.  A large call without a
+    screen tests every tile after so many 64-byte slices of the rows, chosen per group (kvfuse_plan_early_counts): those
+    slices have been multiplied for all pairs.  What tiles that went on to their full length and pairs that were finished one
+    by one add is not counted, so the rate stated is a lower bound of the executed one."""
+    slices, _, room = kb.early_counts(ctx, plan)
+    return float(slices.mean()) / (row_bytes // 64) if room else 1.0
 
 
-ROOFLINE_NOTE = ("counts the share 1 - thr of every row, the part of the product that no exact method is without; the kernel stops a "
-                 "tile where a bound settles it.  full_length_equivalent counts whole rows and can exceed the peak")
+ROOFLINE_NOTE = ("counts the slices of every row that the kernel multiplied before it tested a tile for stopping early; tiles that "
+                 "went on to full length are counted no further.  full_length_equivalent counts whole rows and can exceed the peak")
 
 
 def cpu_baseline(wl, reduced=False):
@@ -514,6 +517,7 @@ def main():
         stats = st
         stage["norms"] += st.ms_norms; stage["similarity"] += st.ms_similarity; stage["assign"] += st.ms_assign
         stage["merge"] += st.ms_merge; stage["rewrite"] += st.ms_rewrite; stage["decode"] += dec
+    share = counted_share(kb, ctx, plan, rec.r * (2 if rec.dtype == torch.bfloat16 else 4))
     # shared-block decode attention (the first "next" row): same outputs, blocks common to several requests read
     # once per tile of requests.  Measured on the table the last step left, outside the timed steps.
     t_plan = time.perf_counter()
@@ -822,7 +826,6 @@ def main():
     elem = 2 if rec.dtype == torch.bfloat16 else 4
     blk_bytes = rec.r * elem
     full_tflops = stats.sim_flops / (stage["similarity"] * 1e-3) / 1e12 if stage["similarity"] > 0 else 0.0
-    share = counted_share(args, stats.sim_flops, rec.thr)
     sim_tflops = full_tflops * share
     peak = 2500.0 if rec.dtype == torch.bfloat16 else 157.3
     phys_bytes = stats.physical_blocks * blk_bytes * 2
