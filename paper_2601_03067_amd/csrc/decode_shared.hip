@@ -56,37 +56,25 @@ struct SharedArgs {
     float sm_scale;
 };
 
-template <typename T> struct SQkMma;
-template <> struct SQkMma<float> {
-    __device__ static __forceinline__ void run(const uint4 &a, const uint4 &b, floatx4 &c)
-    {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-    }
-};
+__device__ static __forceinline__ void mma_f32(const uint4 &a, const uint4 &b, floatx4 &c)
+{
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+}
 
-template <typename T> struct SToF32;
-template <> struct SToF32<float> {
-    __device__ static __forceinline__ void run(const uint4 &raw, float *o)
-    {
-        o[0] = __uint_as_float(raw.x); o[1] = __uint_as_float(raw.y);
-        o[2] = __uint_as_float(raw.z); o[3] = __uint_as_float(raw.w);
-    }
-};
-
-// One workgroup per plan item; its 4 wavefronts walk the item's blocks round-robin.  Row `head` (0..15) of the MFMA
+// binary32 pools: one workgroup per plan item; its 4 wavefronts walk the item's blocks round-robin.  Row `head` (0..15) of the MFMA
 // tile belongs to request slot head / rep_pad of the item and query head head % rep_pad of the KV head's group.
 // With 16 rows two wavefronts share a block: both compute its logits and softmax state, each carries half of the
 // rows through P.V (64 instead of 128 accumulators per lane, so that three workgroups fit a compute unit).
-template <typename T, int D, int ROWS>
+template <int D, int ROWS>
 __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int item_base)
 {
     constexpr int RSPLIT = ROWS == 16 ? 2 : 1;     // wavefronts per block
     constexpr int NSTREAM = 4 / RSPLIT;            // blocks in flight per workgroup
     constexpr int RPW = ROWS / RSPLIT;             // rows a wavefront carries through P.V
-    constexpr int PER = Elem<T>::PER16;
+    constexpr int PER = Elem<float>::PER16;
     constexpr int NF = D / (4 * PER);      // 16-byte K fragments per lane (a lane owns a quarter of a token row)
     constexpr int LPR = D / PER;           // lanes per V row
     constexpr int RPP = 64 / LPR;          // V rows per pass
@@ -104,8 +92,8 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
     const int li = item.li, kvh = item.kvh, nreq = item.nreq;
     const int g = (A.layer_begin + li) * A.kv_heads + kvh;
     const int64_t r = (int64_t)A.t * D;
-    const T *kg = (const T *)A.kpool + (int64_t)g * A.P * r;
-    const T *vg = (const T *)A.vpool + (int64_t)g * A.P * r;
+    const float *kg = (const float *)A.kpool + (int64_t)g * A.P * r;
+    const float *vg = (const float *)A.vpool + (int64_t)g * A.P * r;
     const float *skg = A.scale_k + (int64_t)g * A.n;
     const float *svg = A.scale_v + (int64_t)g * A.n;
 
@@ -123,7 +111,7 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
 
     uint4 qf[NF];
     {
-        const T *qrow = (const T *)A.q + (((int64_t)li * A.B + my_req) * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + kq * (D / 4);
+        const float *qrow = (const float *)A.q + (((int64_t)li * A.B + my_req) * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + kq * (D / 4);
 #pragma unroll
         for (int f = 0; f < NF; ++f)
             qf[f] = row_used ? reinterpret_cast<const uint4 *>(qrow)[f] : make_uint4(0, 0, 0, 0);
@@ -143,8 +131,8 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
         const int x = rs == 0 ? ent.x[0] : (rs == 1 ? ent.x[1] : (rs == 2 ? ent.x[2] : ent.x[3]));
         const float zs = A.sm_scale * skg[x];
         const float sv = svg[x];
-        const T *kblk = kg + (int64_t)phys * r;
-        const T *vblk = vg + (int64_t)phys * r;
+        const float *kblk = kg + (int64_t)phys * r;
+        const float *vblk = vg + (int64_t)phys * r;
         for (int sub = 0; sub < A.t; sub += 16) {
             if (sub >= ntok)
                 break;
@@ -161,7 +149,7 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
                 vf[ps] = reinterpret_cast<const uint4 *>(vblk + (int64_t)(sub + ps * RPP + tr) * D)[dl];
 #pragma unroll
             for (int f = 0; f < NF; ++f)
-                SQkMma<T>::run(kf[f], qf[f], z);
+                mma_f32(kf[f], qf[f], z);
             // ---- online softmax for this lane's row over its 4 tokens, then over the 4 token groups
             const int tok0 = sub + tg * 4;
             float zz[4];
@@ -206,7 +194,7 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
 #pragma unroll
             for (int ps = 0; ps < NPASS; ++ps) {
                 float vv[PER];
-                SToF32<T>::run(vf[ps], vv);
+                widen_f32<float>(vf[ps], vv);
                 const int tok = ps * RPP + tr;
                 if (sub + tok >= ntok) {             // rows past the context may hold anything, even NaN
 #pragma unroll
@@ -528,17 +516,17 @@ static int pad_pow2(int rep)
     return p;
 }
 
-template <typename T, int D>
+template <int D>
 static void launch_items(hipStream_t s, const SharedArgs &A, int rows, int item_base, int n_items)
 {
     if (n_items <= 0)
         return;
     switch (rows) {
-    case 1: decode_items_kernel<T, D, 1><<<n_items, 256, 0, s>>>(A, item_base); break;
-    case 2: decode_items_kernel<T, D, 2><<<n_items, 256, 0, s>>>(A, item_base); break;
-    case 4: decode_items_kernel<T, D, 4><<<n_items, 256, 0, s>>>(A, item_base); break;
-    case 8: decode_items_kernel<T, D, 8><<<n_items, 256, 0, s>>>(A, item_base); break;
-    default: decode_items_kernel<T, D, 16><<<n_items, 256, 0, s>>>(A, item_base); break;
+    case 1: decode_items_kernel<D, 1><<<n_items, 256, 0, s>>>(A, item_base); break;
+    case 2: decode_items_kernel<D, 2><<<n_items, 256, 0, s>>>(A, item_base); break;
+    case 4: decode_items_kernel<D, 4><<<n_items, 256, 0, s>>>(A, item_base); break;
+    case 8: decode_items_kernel<D, 8><<<n_items, 256, 0, s>>>(A, item_base); break;
+    default: decode_items_kernel<D, 16><<<n_items, 256, 0, s>>>(A, item_base); break;
     }
 }
 
@@ -896,15 +884,15 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
         KVF_HIP(c, hipStreamWaitEvent(c->aux, c->fork, 0));
     }
     hipStream_t cs = fork ? c->aux : c->stream;
-#define KVF_SHARED_LAUNCH(T, D)                                                        \
-    do {                                                                               \
-        launch_items<T, D>(cs, A, rows_cluster, 0, nc);                                \
-        launch_items<T, D>(c->stream, A, rows_residual, nc, nr);                       \
-        if (fork) {                                                                    \
-            (void)hipEventRecord(c->join, c->aux);                                     \
-            (void)hipStreamWaitEvent(c->stream, c->join, 0);                           \
-        }                                                                              \
-        decode_shared_combine_kernel<D, false><<<cgrid, 256, 0, c->stream>>>(A);       \
+#define KVF_SHARED_LAUNCH(D)                                                     \
+    do {                                                                         \
+        launch_items<D>(cs, A, rows_cluster, 0, nc);                             \
+        launch_items<D>(c->stream, A, rows_residual, nc, nr);                    \
+        if (fork) {                                                              \
+            (void)hipEventRecord(c->join, c->aux);                               \
+            (void)hipStreamWaitEvent(c->stream, c->join, 0);                     \
+        }                                                                        \
+        decode_shared_combine_kernel<D, false><<<cgrid, 256, 0, c->stream>>>(A); \
     } while (0)
     if (pool->dtype == KVFUSE_BF16) {
         auto items = [&](const SharedArgs &part, int n_cluster, int n_residual) {
@@ -926,6 +914,9 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             rest.items += nc;
             items(rest, 0, nr);
         }
+        // The whole call with either merge (us, a workgroup / a wavefront per head; 512 tokens, half shared): 512 heads 13.7 / 13.9,
+        // 2048 28.1 / 27.1, 4096 36.2 / 33.4, 8192 59.1 / 53.2, 32768 272 / 243; head size 64: 512 10.3 / 10.5 - 11.4, 4096 23.7 / 21.0,
+        // 32768 157 / 132; 2048 heads of 28 slots 275.1 / 274.0, 8192 of 7 slots 279 / 270.
         const int64_t heads_total = tuples * plan->rep;
         if (heads_total >= 4096 && launch_fits((heads_total + 3) / 4, 256)) {
             const unsigned grid = (unsigned)((heads_total + 3) / 4);
@@ -938,8 +929,8 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
         else
             decode_shared_combine_kernel<64, true><<<cgrid, 256, 0, c->stream>>>(A);
     } else {
-        if (pool->d == 128) KVF_SHARED_LAUNCH(float, 128);
-        else KVF_SHARED_LAUNCH(float, 64);
+        if (pool->d == 128) KVF_SHARED_LAUNCH(128);
+        else KVF_SHARED_LAUNCH(64);
     }
 #undef KVF_SHARED_LAUNCH
     KVF_HIP(c, hipGetLastError());

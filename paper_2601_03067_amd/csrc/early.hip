@@ -22,7 +22,8 @@ constexpr int kSamples = 64;      // sampled pairs per group: one per lane of a 
 constexpr int kSteps = 32;        // lengths considered: (k / 32) of the block's slices
 static_assert(kSteps * kSamples * sizeof(float) <= 256 * 2 * sizeof(int4), "the bounds of a group fit its share of the merge work list");
 
-// Fixed pseudo-random logical entries: the sample depends on the sizes alone.
+// Fixed pseudo-random logical entries: the sample depends on the sizes alone.  The mixing steps and constants are those of
+// "lowbias32", the published result of Chris Wellons' search for 32-bit integer hashes of low bias (hash-prospector).
 __device__ __forceinline__ uint32_t mix32(uint32_t x)
 {
     x ^= x >> 16;

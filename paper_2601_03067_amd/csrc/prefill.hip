@@ -29,7 +29,7 @@
 //   transpose read ds_read_b64_tr_b16 (16 lanes x 4 values: lane i receives element i & 3 of the rows that lanes
 //   i >> 2, 4 + (i >> 2), 8 + (i >> 2), 12 + (i >> 2) point at -- so when source lane s points at 4 consecutive head
 //   elements 4 (s & 3) .. of token (s >> 2), lane i ends up with head element i of 4 consecutive tokens).
-//   Weights are split into a bfloat16 head and remainder (two MFMAs) as in the decode kernels.
+//   Weights are split into a bfloat16 head and remainder (two MFMAs).
 // bfloat16 pools only.
 #include "common.h"
 

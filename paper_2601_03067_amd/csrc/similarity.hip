@@ -852,9 +852,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 for (int k = wave; k < nc && first + lds_npairs > early.pair_cap; k += NT / 64) {
                     if (lds_cand_row[k] < 0 && first + (lds_cand_col[k] >> 8) >= early.pair_cap) {
                         const int row = lds_cand_row[k] & ~OPEN, cl = lds_cand_col[k] & 255, col = col0 + cl;
-                        using E = typename std::conditional<Q8, bf16_t, T>::type;
-                        float dot = product_from<E>((const E *)(kg + (int64_t)l_ids[row] * row_bytes),
-                                                    (const E *)(kg + (int64_t)r_ids[col] * row_bytes), 4 * nk, 4 * nk_full, lane, 64);
+                        float dot = product_from<T>((const T *)(kg + (int64_t)l_ids[row] * row_bytes),
+                                                    (const T *)(kg + (int64_t)r_ids[col] * row_bytes), 4 * nk, 4 * nk_full, lane, 64);
 #pragma unroll
                         for (int off = 32; off >= 1; off >>= 1)
                             dot += __shfl_xor(dot, off, 64);
