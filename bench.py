@@ -830,9 +830,10 @@ def main():
     peak = 2500.0 if rec.dtype == torch.bfloat16 else 157.3
     phys_bytes = stats.physical_blocks * blk_bytes * 2
     logi_bytes = stats.logical_blocks * blk_bytes * 2
-    traffic = None      # HBM bytes per similarity launch, from the committed rocprofv3 counter summary of this workload
+    # bytes beyond L2 per similarity launch of the default tree call, from the committed rocprofv3 counter summary of this workload
+    traffic = None
     prof = os.path.join(ROOT, "profiles", f"{rec.name}_kernels.md")
-    if args.workload == rec.name and os.path.exists(prof):
+    if args.workload == rec.name and not args.screen_fp8 and not args.screen_prefix and os.path.exists(prof):
         for ln in open(prof):
             if ln.startswith("traffic_bytes_per_similarity_launch"):
                 traffic = float(ln.split("=")[1].split()[0])

@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
     const int v_off = (4 * h2 + (l16 >> 2)) * VSTR + (16 * ((lane >> 4) & 1) + 4 * (l16 & 3)) * 2;
 
     // Bound: the softmax's vector instructions and the matrix instructions of a SIMD's two wavefronts hardly overlap (per tile
-    // 270 of the former, 24 of the latter: 51 and 30 % of the cycles).  2048 queries of a 32768-token prompt, 4 layers of 8 KV
+    // 270 of the former, 24 of the latter: 54 and 32 % of the cycles).  2048 queries of a 32768-token prompt, 4 layers of 8 KV
     // heads, a third of the blocks fused: 7.15 -> 5.70 ms since table words and fragments come ahead of their use and the
     // maximum is taken before the scales are applied.
     // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
