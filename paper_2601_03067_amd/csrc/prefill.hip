@@ -486,11 +486,6 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
 //   V^T fragment dt of a lane (m = lane & 31): element dt of the DT consecutive head elements DT m .. that it loads of its 8
 //   tokens, one v_perm per two values; the tokens are those whose weights the lane already holds.
 constexpr int kSplitWaves = 8;
-// Grids of the staged kernel up to this many workgroups take the split kernel.  Both measured, staged / split, one layer of 8
-// KV heads and 4 query heads each over 4096 tokens: 8 workgroups (16 queries) 151 / 43 us, 64: 181 / 50, 128: 187 / 99, 192:
-// 188 / 149; over 512 tokens 128: 31 / 31.  At 256 they are level (195 / 198), over 512 tokens the split kernel loses (36 / 54).
-constexpr int64_t kSplitBelow = 192;
-
 template <int D>
 __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(PrefillArgs A)
 {
@@ -642,6 +637,28 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
             *reinterpret_cast<orow_t *>(dst + DT * (8 * (i >> 2) + 4 * h2 + (i & 3))) = w;
         }
     }
+}
+
+// Whether the split kernel is the faster one, for a walk of `tiles` tiles: grids of the staged kernel of up to 192 workgroups, and
+// among them those for which the rounds of split workgroups that the chip runs, one (head size 128) or two (64) per compute
+// unit, cost less than one round of staged ones.  In units of a staged tile (1.7 / 1.4 us): 3.5 + tiles for the staged kernel, 4.2 +
+// 0.2 tiles for a round of the other.  Both measured (us, staged / split; 4 query heads per KV head, three in ten blocks before the
+// chunk fused away), by workgroups of the staged grid, head size 128:
+//   tokens   up to 64      128          192          256       head size 64, 192
+//      64    9.4 / 8.9   10.0 / 16.4                               7.9 / 8.2
+//     128   12.5 / 9.3   13.0 / 17.0  13.8 / 24.4                 10.9 / 12.0
+//     256   17.0 / 10.8  17.9 / 20.1  19.7 / 29.0                 15.0 / 14.2
+//     512   28.1 / 14.5  30.1 / 26.7  31.2 / 38.1  34.2 / 51.5    23.9 / 18.1
+//    1024   45.2 / 17.7  51.4 / 32.3  52.1 / 47.9  53.3 / 62.9    43.7 / 24.4
+//    4096    178 / 46     178 / 87     168 / 120    182 / 165      155 / 62
+// (Without the second condition 96 queries over 112 tokens, 16 layers of one KV head, took 23.4 us where the staged kernel
+// takes 13.5.)
+constexpr int64_t kSplitBelow = 192;
+
+static bool split_pays(int64_t staged_wgs, int64_t split_wgs, int64_t tiles, int d)
+{
+    const int64_t half_rounds = std::max<int64_t>(2, (split_wgs + 255) / 256 * (d == 64 ? 1 : 2));
+    return staged_wgs <= kSplitBelow && half_rounds * (42 + 2 * tiles) < 2 * (35 + 10 * tiles);
 }
 
 static int pad_pow2_p(int rep)
@@ -853,8 +870,10 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
     const int per_wg = 4 * plan->npw;
     const unsigned heads = (unsigned)plan->kv_heads, layers = (unsigned)plan->n_layers;
     const dim3 grid((unsigned)((nq + per_wg - 1) / per_wg), heads, layers);
-    if ((int64_t)grid.x * heads * layers <= kSplitBelow) {
-        const dim3 sgrid((unsigned)((nq + plan->npw - 1) / plan->npw), heads, layers);
+    const dim3 sgrid((unsigned)((nq + plan->npw - 1) / plan->npw), heads, layers);
+    const int64_t per_layer = heads, stored = (int64_t)plan->entries.size() / (per_layer * layers);
+    const int64_t tiles = (stored * (pool->t / 16) + (plan->q_end - 1 - plan->chunk_begin) / 16 + 2) / 2;
+    if (split_pays(grid.x * per_layer * layers, sgrid.x * per_layer * layers, tiles, pool->d)) {
         if (pool->d == 128)
             prefill_split_kernel<128><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
         else

@@ -31,9 +31,12 @@ CASES = [(1, 1, 1, 16, 64, 0, 0, 1),             # one token, nothing before it
          (1, 2, 4, 16, 128, 32, 3, 5),           # 2 blocks before the chunk: fewer tiles than wavefronts
          (2, 1, 16, 48, 64, 48 * 9, 17, 2),      # three pieces per block, two positions per workgroup
          (1, 3, 3, 32, 128, 1024, 0, 100),       # heads padded from 3 to 4
-         (3, 8, 4, 16, 128, 512, 0, 256),        # 192: the last grid of the split kernel
+         (3, 8, 4, 16, 128, 512, 0, 256),        # 192, three rounds of split workgroups: the context is too short for them
          (3, 8, 4, 16, 128, 512, 0, 257),        # 216: the staged kernel, one row in its last workgroup
-         (4, 8, 16, 32, 64, 96, 31, 57)]         # 256, staged
+         (4, 8, 16, 32, 64, 96, 31, 57),         # 256, staged
+         (3, 8, 4, 16, 128, 2048, 0, 256),       # 192: the last grid of the split kernel, a context long enough with or without reuse
+         (4, 8, 4, 16, 128, 160, 5, 128),        # 128, two rounds: staged with reuse, split without
+         (4, 8, 4, 16, 64, 160, 5, 128)]         # the same heads of 64 elements: one round, split
 
 
 def _compare(case, reuse, sm_scale=None, signed_scales=False):
