@@ -268,14 +268,17 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
 // Bound: HBM for blocks read once (64 x 2048 tokens, 64 groups: 5.35 TB/s of distinct bytes, 541 -> 505 us); blocks that many
 // requests share come out of the caches, where the vector ALU was the limit (8 heads per KV head, 256 x 4096 tokens, 16
 // groups: 893 -> 716 us, 12 TB/s of rows read).  Three wavefronts per SIMD hold 16 KiB each in flight.
-template <int D>
-__global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
+// NW: wavefronts of a workgroup, as many as the longest split has steps of 32 tokens, up to four: idle ones would keep others off
+// the chip (512 requests, 64 groups, four / NW wavefronts: 16 tokens, one head 158 / 56 us, four 175 / 69; 64 tokens 214 / 197
+// and 234 / 211).  The pieces fall to the same wavefronts whatever NW.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
 {
     constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
     typedef typename Attend32<D>::vrow_t vrow_t;
 
     extern __shared__ __attribute__((aligned(16))) float w_o[];      // [wave][rep_pad][D]
-    __shared__ float w_m[4][16], w_l[4][16];
+    __shared__ float w_m[NW][16], w_l[NW][16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int split = blockIdx.x;
@@ -338,7 +341,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         en0 = entry_at(p_first);
         en1 = entry_at(min(p_first + 1, p_hi - 1));
     }
-    for (int p = p_first; p < p_hi; p += 8) {
+    for (int p = p_first; p < p_hi; p += 2 * NW) {
         const bool two = p + 1 < p_hi;                              // an odd last piece is paired with itself, masked
         const int64_t off0 = rows_of(en0), off1 = rows_of(en1);
         const AttendScale s0(base, en0.sk, en0.sv), s1(base, en1.sk, en1.sv);
@@ -352,9 +355,9 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             vr[j] = *reinterpret_cast<const vrow_t *>(vg_ + (j < 4 ? off0 : off1) + v_off + (j & 3) * D);
-        if (p + 8 < p_hi) {
-            en0 = entry_at(p + 8);
-            en1 = entry_at(min(p + 9, p_hi - 1));
+        if (p + 2 * NW < p_hi) {
+            en0 = entry_at(p + 2 * NW);
+            en1 = entry_at(min(p + 2 * NW + 1, p_hi - 1));
         }
         __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
         const int left0 = ctx - 16 * p - 4 * kg;
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             st.o[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int p = p_lo + 2 * wave; p < p_hi; p = (p - p_lo) & 1 ? p + 7 : p + 1) {
+        for (int p = p_lo + 2 * wave; p < p_hi; p = (p - p_lo) & 1 ? p + 2 * NW - 1 : p + 1) {
             const Entry en = entry_at(p);
             const int64_t off = rows_of(en);
             const AttendScale sc(base, en.sk, en.sv);
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
         }
     }
 
-    // ---- publish the wavefront's state, merge the four
+    // ---- publish the wavefront's state, merge them
     if (head < A.rep)
         st.store(w_o + ((int64_t)wave * A.rep_pad + head) * D, kg);
     if (kg == 0) {
@@ -403,12 +406,15 @@ __global__ __launch_bounds__(256, 3) void decode_bf16_kernel(DecodeArgs A)
     __syncthreads();
 
     const int64_t tuple = ((int64_t)li * A.B + b) * A.kv_heads + kvh;
-    for (int idx = tid; idx < A.rep * D; idx += 256) {
+    for (int idx = tid; idx < A.rep * D; idx += 64 * NW) {
         const int h = idx / D, e = idx - h * D;
-        const float M = fmaxf(fmaxf(w_m[0][h], w_m[1][h]), fmaxf(w_m[2][h], w_m[3][h]));
+        float M = w_m[0][h];
+#pragma unroll
+        for (int wv = 1; wv < NW; ++wv)
+            M = fmaxf(M, w_m[wv][h]);
         float L = 0.0f, O = 0.0f;
 #pragma unroll
-        for (int wv = 0; wv < 4; ++wv) {
+        for (int wv = 0; wv < NW; ++wv) {
             const float f = w_m[wv][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(w_m[wv][h] - M);
             L += w_l[wv][h] * f;
             O += w_o[(wv * A.rep_pad + h) * D + e] * f;
@@ -523,8 +529,16 @@ static void launch_decode_t(hipStream_t s, const DecodeArgs &A, int n_layers)
     // roundings moves an entry of the output by 1.5e-5.
     const bool mma = bf16 && !ah;
     if constexpr (bf16)
-        if (mma)
-            decode_bf16_kernel<D><<<grid, 256, (size_t)4 * A.rep_pad * D * sizeof(float), s>>>(A);
+        if (mma) {
+            const size_t wave_lds = (size_t)A.rep_pad * D * sizeof(float);
+            const int64_t pieces = (int64_t)A.blocks_per_split * (A.t / 16);          // of the longest split
+            if (pieces <= 2)
+                decode_bf16_kernel<D, 1><<<grid, 64, wave_lds, s>>>(A);
+            else if (pieces <= 4)
+                decode_bf16_kernel<D, 2><<<grid, 128, 2 * wave_lds, s>>>(A);
+            else
+                decode_bf16_kernel<D, 4><<<grid, 256, 4 * wave_lds, s>>>(A);
+        }
 #define KVF_DEC(R)                                                         \
     do {                                                                   \
         if (ah)                                                            \

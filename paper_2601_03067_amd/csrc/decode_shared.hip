@@ -280,14 +280,17 @@ __global__ __launch_bounds__(256) void decode_items_kernel(SharedArgs A, int ite
 // launch: each XCD takes a contiguous range of both kinds, so that the tiles of a cluster, which read the same blocks, meet in
 // its L2, and deals them out in proportion, so that its compute units see cluster blocks (from L2) and blocks of single requests
 // (from HBM) at the same time.
-template <int D>
-__global__ __launch_bounds__(256, 3) void decode_items_bf16_kernel(SharedArgs A, int n_cluster, int n_residual, uint64_t cluster_share)
+// NW: wavefronts of a workgroup, as many as the plan's longest item has steps of 32 tokens, up to four (decode_bf16_kernel): 200
+// requests of 64 tokens, 64 groups of 4 heads, four / NW wavefronts: 110 / 84 us, and 76 since only the rows and slots that
+// there are go through memory.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArgs A, int n_cluster, int n_residual, uint64_t cluster_share)
 {
     constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
     typedef typename Attend32<D>::vrow_t vrow_t;
 
-    __shared__ float w_m[4][16], w_l[4][16];
-    __shared__ __attribute__((aligned(16))) float w_o[4][16][D];
+    __shared__ float w_m[NW][16], w_l[NW][16];
+    __shared__ __attribute__((aligned(16))) float w_o[NW][16][D];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -339,7 +342,7 @@ __global__ __launch_bounds__(256, 3) void decode_items_bf16_kernel(SharedArgs A,
         en0 = entry_at(2 * wave);
         en1 = entry_at(min(2 * wave + 1, n_pieces - 1));
     }
-    for (int p = 2 * wave; p < n_pieces; p += 8) {
+    for (int p = 2 * wave; p < n_pieces; p += 2 * NW) {
         const bool two = p + 1 < n_pieces;                          // an odd last piece is paired with itself, masked
         const int xa = rs == 0 ? en0.x0 : (rs == 1 ? en0.x1 : (rs == 2 ? en0.x2 : en0.x3));
         const int xb = rs == 0 ? en1.x0 : (rs == 1 ? en1.x1 : (rs == 2 ? en1.x2 : en1.x3));
@@ -356,31 +359,35 @@ __global__ __launch_bounds__(256, 3) void decode_items_bf16_kernel(SharedArgs A,
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             vr[j] = *reinterpret_cast<const vrow_t *>(vgrp + (j < 4 ? off0 : off1) + v_off + (j & 3) * D);
-        if (p + 8 < n_pieces) {
-            en0 = entry_at(p + 8);
-            en1 = entry_at(min(p + 9, n_pieces - 1));
+        if (p + 2 * NW < n_pieces) {
+            en0 = entry_at(p + 2 * NW);
+            en1 = entry_at(min(p + 2 * NW + 1, n_pieces - 1));
         }
         __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
         const AttendScale s0(base, ska, sva), s1(base, skb, svb);
         st.step(qf, k0, k1, vr, s0, s1, left0 >= 16 && left1 >= 16, left0 - 4 * kg, left1 - 4 * kg);
     }
 
-    st.store(w_o[wave][head], kg);
+    if (row_used)
+        st.store(w_o[wave][head], kg);
     if (kg == 0) {
         w_m[wave][head] = st.m;
         w_l[wave][head] = st.l;
     }
     __syncthreads();
 
-    for (int idx = tid; idx < 16 * D; idx += 256) {
+    for (int idx = tid; idx < nreq * A.rep_pad * D; idx += 64 * NW) {
         const int h = idx / D, e = idx - h * D;
         const int hs = h / A.rep_pad, hq = h - hs * A.rep_pad;
-        if (hs >= nreq || hq >= A.rep)
+        if (hq >= A.rep)
             continue;
-        const float M = fmaxf(fmaxf(w_m[0][h], w_m[1][h]), fmaxf(w_m[2][h], w_m[3][h]));
+        float M = w_m[0][h];
+#pragma unroll
+        for (int wv = 1; wv < NW; ++wv)
+            M = fmaxf(M, w_m[wv][h]);
         float L = 0.0f, O = 0.0f;
 #pragma unroll
-        for (int wv = 0; wv < 4; ++wv) {
+        for (int wv = 0; wv < NW; ++wv) {
             const float f = w_m[wv][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(w_m[wv][h] - M);
             L += w_l[wv][h] * f;
             O += w_o[wv][h][e] * f;
@@ -474,7 +481,8 @@ __global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(Shared
     auto fetch = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < BATCH; ++k)
-            v[k] = *reinterpret_cast<const elems_t *>(part + min(s + k, n - 1) * stride + lane * PL);
+            if (s + k < n)
+                v[k] = *reinterpret_cast<const elems_t *>(part + (s + k) * stride + lane * PL);
     };
     elems_t O = (elems_t)(0.0f);
     float L = 0.0f;
@@ -546,6 +554,7 @@ struct kvfuse_decode_plan {
     kvfuse_decode_plan_info info = {};
     // device placement
     size_t off_items = 0, off_entries = 0, off_slots = 0, off_part = 0, bytes = 0;
+    int64_t max_pieces = 0;      // 16-token pieces of the longest item
     char *dev = nullptr;
 };
 
@@ -775,6 +784,9 @@ int kvfuse_shared_decode_plan_build(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
     };
     make_absolute(pl->items_cluster);
     make_absolute(pl->items_residual);
+    for (const std::vector<DItem> *v : {&pl->items_cluster, &pl->items_residual})
+        for (const DItem &it : *v)
+            pl->max_pieces = std::max(pl->max_pieces, (int64_t)it.entry_cnt * (t / 16));
     I.items_cluster = (int64_t)pl->items_cluster.size();
     I.items_residual = (int64_t)pl->items_residual.size();
     // device layout
@@ -901,10 +913,18 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             const uint64_t share = seats > 0 ? ((nc8 << 32) + seats - 1) / seats : 0;
             if (seats == 0)
                 return;
-            if (pool->d == 128)
-                decode_items_bf16_kernel<128><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(part, n_cluster, n_residual, share);
-            else
-                decode_items_bf16_kernel<64><<<(unsigned)(8 * seats), 256, 0, c->stream>>>(part, n_cluster, n_residual, share);
+#define KVF_ITEMS(D, NW)                                                                                            \
+    decode_items_bf16_kernel<D, NW><<<(unsigned)(8 * seats), 64 * NW, 0, c->stream>>>(part, n_cluster, n_residual, share)
+#define KVF_ITEMS_NW(D)                                                                                             \
+    do {                                                                                                            \
+        if (plan->max_pieces <= 2) KVF_ITEMS(D, 1);                                                                 \
+        else if (plan->max_pieces <= 4) KVF_ITEMS(D, 2);                                                            \
+        else KVF_ITEMS(D, 4);                                                                                       \
+    } while (0)
+            if (pool->d == 128) KVF_ITEMS_NW(128);
+            else KVF_ITEMS_NW(64);
+#undef KVF_ITEMS_NW
+#undef KVF_ITEMS
         };
         if (launch_fits((int64_t)nc + nr + 14, 256)) {
             items(A, nc, nr);

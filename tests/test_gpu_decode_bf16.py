@@ -14,11 +14,11 @@ DEV = "cuda:0"
 CONTEXTS = [0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 127, 128, 129, 255, 300, 1000]
 
 
-def _setup(t, d, heads, seed, layers=2, all_heads=False):
+def _setup(t, d, heads, seed, layers=2, all_heads=False, contexts=CONTEXTS):
     from paper_2601_03067_amd import binding as kb
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
-    blocks = [(c + t - 1) // t for c in CONTEXTS]
+    blocks = [(c + t - 1) // t for c in contexts]
     n, groups, width = sum(blocks), layers * (1 if all_heads else heads), d * (heads if all_heads else 1)
     P = n + 3
     K = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(torch.bfloat16)
@@ -31,17 +31,17 @@ def _setup(t, d, heads, seed, layers=2, all_heads=False):
     return kb, cache, start, max(blocks), gen
 
 
-def _call(kb, cache, heads, q, start, max_blocks, all_heads):
+def _call(kb, cache, heads, q, start, max_blocks, all_heads, contexts=CONTEXTS):
     ctx = kb.Context(DEV)
     rs = torch.from_numpy(start).to(DEV)
-    cl = torch.tensor(CONTEXTS, dtype=torch.int32, device=DEV)
+    cl = torch.tensor(contexts, dtype=torch.int32, device=DEV)
     step = kb.paged_decode_attn_all_heads if all_heads else kb.paged_decode_attn
     out = step(ctx, cache, heads, q, rs, cl, max_blocks)
     torch.cuda.synchronize()
     return out.cpu().double()
 
 
-def _reference(cache, t, d, heads, q, start, all_heads):
+def _reference(cache, t, d, heads, q, start, all_heads, contexts=CONTEXTS):
     layers, B, Hq, _ = q.shape
     rep = Hq // heads
     out = torch.zeros(q.shape, dtype=torch.float64)
@@ -50,7 +50,7 @@ def _reference(cache, t, d, heads, q, start, all_heads):
     for li in range(layers):
         for h in range(heads):
             g, w, s = (li, heads, h) if all_heads else (li * heads + h, 1, 0)
-            for b, c in enumerate(CONTEXTS):
+            for b, c in enumerate(contexts):
                 if c == 0:
                     continue
                 x = slice(int(start[b]), int(start[b]) + (c + t - 1) // t)
@@ -184,3 +184,24 @@ def test_weights_of_large_logits(d, scale):
     # Two roundings of the exponent's argument x move a weight 2^-x by x 2^-x ln 2 * 2^-23 <= 0.37 * 2^-23 of the largest
     # one, exp2, the sums of weights and of products and the division by a unit (2^-24) each: below 5 units of the values.
     assert float((out - ref).abs().max()) < 5 * 2.0 ** -24 * float(cache.V.float().abs().max())
+
+
+# longest contexts of one and of two steps (workgroups of one and two wavefronts), and one token more
+@pytest.mark.parametrize("t,d,rep,longest", [(16, 128, 1, 16), (16, 128, 4, 32), (32, 64, 16, 32), (16, 64, 2, 33), (48, 128, 3, 48),
+                                             (16, 128, 8, 64), (64, 64, 4, 64), (16, 128, 4, 65)])
+def test_short_contexts(t, d, rep, longest):
+    heads, contexts = 2, [0, 1, 15, longest // 2, longest - 1, longest]
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, t + longest, contexts=contexts)
+    cache.bt.copy_(torch.arange(cache.bt.shape[1], dtype=torch.int32, device=DEV))
+    V = cache.V.view(cache.V.shape[0], -1, t, d)
+    q = torch.randn(2, len(contexts), heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
+    ref = _reference(cache, t, d, heads, q, start, False, contexts)
+    out = _call(kb, cache, heads, q, start, max_blocks, False, contexts)
+    assert float((out - ref).abs().max()) < 1.2e-5               # the bound of test_against_binary64
+    # an infinite value: that column of that request, and no other
+    b = len(contexts) - 1
+    V[:, int(start[b]) + (longest - 1) // t, (longest - 1) % t, 3] = float("inf")
+    spoilt = _call(kb, cache, heads, q, start, max_blocks, False, contexts)
+    assert bool((spoilt[:, b, :, 3] == float("inf")).all())
+    spoilt[:, b, :, 3] = out[:, b, :, 3]
+    assert float((spoilt - out).abs().max()) < 1.2e-5
