@@ -1,4 +1,4 @@
-// One step of decode attention over bfloat16 blocks, shared by the paged and the shared-block kernels: 32 tokens (two
+// What the paged and the shared-block decode kernels share.  One step of decode attention over bfloat16 blocks: 32 tokens (two
 // 16-token pieces) against 16 query rows, both products on the matrix cores and no LDS.
 //   logits  two 16 tokens x 16 rows groups: lane (row = lane & 15, kg = lane >> 4) ends up with the tokens 4 kg .. + 3 of
 //           both pieces, which are the 8 summation indices of the same lane in the second product.
@@ -146,6 +146,29 @@ struct Attend32 {
                 *reinterpret_cast<float4 *>(dst + v * NC + c) = make_float4(o[c][v], o[c + 1][v], o[c + 2][v], o[c + 3][v]);
     }
 };
+
+// Merge of a few partial states of all query heads of a (layer, request, KV head), by one workgroup of 256 threads: state s of
+// head h is at part + s * stride + h * (D + 2): the sums, then maximum and sum of weights; out: the heads end to end.  BASE2: the
+// maxima are base-2 logarithms.
+template <int D, bool BASE2>
+__device__ __forceinline__ void merge_few_states(const float *__restrict__ part, int n, int64_t stride, int rep, float *__restrict__ out)
+{
+    for (int idx = threadIdx.x; idx < rep * D; idx += 256) {
+        const int h = idx / D, e = idx - h * D;
+        const float *ph = part + h * (D + 2);
+        float M = -INFINITY;
+        for (int s = 0; s < n; ++s)
+            M = fmaxf(M, ph[s * stride + D]);
+        float L = 0.0f, O = 0.0f;
+        for (int s = 0; s < n; ++s) {
+            const float m = ph[s * stride + D];
+            const float f = m == -INFINITY ? 0.0f : BASE2 ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M);
+            L += ph[s * stride + D + 1] * f;
+            O += ph[s * stride + e] * f;
+        }
+        out[idx] = L > 0.0f ? O / L : 0.0f;
+    }
+}
 
 }  // namespace kvfuse
 

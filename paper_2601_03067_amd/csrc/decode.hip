@@ -484,6 +484,18 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs A)
     }
 }
 
+// Two splits of many requests: one workgroup for all heads of a (layer, request, KV head), see launch_decode_t.
+template <int D, bool BASE2>
+__global__ __launch_bounds__(256) void decode_combine_few_kernel(DecodeArgs A)
+{
+    const int b = blockIdx.x / A.kv_heads;
+    const int kvh = blockIdx.x - b * A.kv_heads;
+    const int li = blockIdx.y;
+    const int64_t tuple = ((int64_t)li * A.B + b) * A.kv_heads + kvh;
+    merge_few_states<D, BASE2>(A.part + tuple * A.nsplit * A.rep_pad * (D + 2), A.nsplit, (int64_t)A.rep_pad * (D + 2), A.rep,
+                               A.out + (((int64_t)li * A.B + b) * A.Hq + (int64_t)kvh * A.rep) * D);
+}
+
 static int pick_rep(int rep)
 {
     int p = 1;
@@ -555,7 +567,17 @@ static void launch_decode_t(hipStream_t s, const DecodeArgs &A, int n_layers)
         default: KVF_DEC(16); break;
         }
 #undef KVF_DEC
-    if (A.nsplit > 1) {
+    // Two splits leave a merge without a chain to shorten, and from 512 (layer, request, KV head) triples on a workgroup for each
+    // fills the chip where one per query head means more of them than run at once (whole call, us, the latter / the former, 16
+    // heads per KV head: 512 triples 29.9 / 30.4 (head size 64: 20.6 / 17.5), 1024 50.9 / 44.0, 1600 82.4 / 66.3, binary32 192 / 180; 256
+    // triples 17.9 / 21.7; 4 splits, 512 triples 42.3 / 50.4).
+    if (A.nsplit == 2 && (int64_t)grid.y * n_layers >= 512) {
+        const dim3 fgrid(grid.y, (unsigned)n_layers);
+        if (mma)
+            decode_combine_few_kernel<D, true><<<fgrid, 256, 0, s>>>(A);
+        else
+            decode_combine_few_kernel<D, false><<<fgrid, 256, 0, s>>>(A);
+    } else if (A.nsplit > 1) {
         if (mma)
             decode_combine_kernel<D, true><<<cgrid, 256, 0, s>>>(A);
         else

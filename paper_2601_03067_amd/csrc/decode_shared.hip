@@ -461,7 +461,7 @@ __global__ __launch_bounds__(256) void decode_shared_combine_kernel(SharedArgs A
 // The same merge, one wavefront per (layer, request, query head): for calls with enough of them to fill the chip several
 // times, where a workgroup each runs in rounds of 2048 (64 requests, 64 groups of 4 heads: 33 us of the call, which went from 274 to 255 us).  The sums of
 // the first slots are asked for together with the states.
-template <int D>
+template <int D, bool BASE2>
 __global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(SharedArgs A, int64_t heads_total)
 {
     constexpr int PL = D / 64, BATCH = 8;          // head elements per lane, slots loaded at a time
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(Shared
         for (int c0 = 0; c0 < n; c0 += 64) {
             const int cnt = min(64, n - c0);
             const float m = lane < cnt ? part[(c0 + lane) * stride + D] : -INFINITY;
-            const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
+            const float f = m == -INFINITY ? 0.0f : BASE2 ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M);
             L += lane < cnt ? part[(c0 + lane) * stride + D + 1] * f : 0.0f;
             for (int s = 0; s < cnt; s += BATCH) {
                 if (c0 + s > 0)
@@ -516,12 +516,44 @@ __global__ __launch_bounds__(256) void decode_shared_combine_waves_kernel(Shared
     *reinterpret_cast<elems_t *>(A.out + (lb * A.Hq + (int64_t)kvh * A.rep + h) * D + lane * PL) = out;
 }
 
+// Little more than one slot each: one workgroup for all heads of a (layer, request, KV head), see launch_merge_slots.
+template <int D, bool BASE2>
+__global__ __launch_bounds__(256) void decode_shared_combine_few_kernel(SharedArgs A)
+{
+    const int64_t tuple = blockIdx.x;
+    const int64_t lb = tuple / A.kv_heads;         // li * B + b
+    const int kvh = (int)(tuple - lb * A.kv_heads);
+    const int s0 = A.slot_begin[tuple], n = A.slot_begin[tuple + 1] - s0;
+    merge_few_states<D, BASE2>(A.part + (int64_t)s0 * A.rep_pad * (D + 2), n, (int64_t)A.rep_pad * (D + 2), A.rep,
+                               A.out + (lb * A.Hq + (int64_t)kvh * A.rep) * D);
+}
+
 static int pad_pow2(int rep)
 {
     int p = 1;
     while (p < rep)
         p <<= 1;
     return p;
+}
+
+// The merge of all slots.  Whole calls (us, a workgroup per head / a wavefront per head / a workgroup for all heads of a
+// (layer, request, KV head); head size 128 unless said, 4 heads per KV head):
+//   slots each   1, 12800 triples  . / 74 / 73, head size 64 . / 47 / 40, of 16 heads . / 108 / 68, binary32 221 / 182 / 180
+//                2, 2048 triples   59 / 53 / 53, 12800 triples . / 220 / 232
+//                5, 512 triples    28.1 / 27.1 / 30, of 16 heads . / 40 / 56
+//               28, 512 triples    275.1 / 274.0 / .
+// and by heads, a workgroup / a wavefront for each: 512 13.7 / 13.9 (head size 64 10.3 / 10.5 - 11.4), 4096 36.2 / 33.4, 8192 59.1 /
+// 53.2, 32768 272 / 243.
+template <int D, bool BASE2>
+static void launch_merge_slots(hipStream_t s, const SharedArgs &A, int64_t tuples, int64_t total_slots)
+{
+    const int64_t heads_total = tuples * A.rep;
+    if (4 * total_slots <= 5 * tuples)
+        decode_shared_combine_few_kernel<D, BASE2><<<(unsigned)tuples, 256, 0, s>>>(A);
+    else if (heads_total >= 4096 && launch_fits((heads_total + 3) / 4, 256))
+        decode_shared_combine_waves_kernel<D, BASE2><<<(unsigned)((heads_total + 3) / 4), 256, 0, s>>>(A, heads_total);
+    else
+        decode_shared_combine_kernel<D, BASE2><<<dim3((unsigned)tuples, (unsigned)A.rep), 256, 0, s>>>(A);
 }
 
 template <int D>
@@ -871,7 +903,6 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
     A.sm_scale = sm_scale;
     const int nc = (int)plan->items_cluster.size(), nr = (int)plan->items_residual.size();
     const int rows_cluster = plan->nreq_max * plan->rep_pad, rows_residual = plan->rep_pad;
-    const dim3 cgrid((unsigned)tuples, (unsigned)plan->rep);
     // binary32 pools: the cluster pass is bound by the vector ALU, the per-request pass by HBM: they run side by side, the
     // cluster pass on the context's second stream, and meet again before the merge.
     const bool fork = pool->dtype == KVFUSE_F32 && nc > 0 && nr > 0;
@@ -904,7 +935,7 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             (void)hipEventRecord(c->join, c->aux);                               \
             (void)hipStreamWaitEvent(c->stream, c->join, 0);                     \
         }                                                                        \
-        decode_shared_combine_kernel<D, false><<<cgrid, 256, 0, c->stream>>>(A); \
+        launch_merge_slots<D, false>(c->stream, A, tuples, plan->total_slots);   \
     } while (0)
     if (pool->dtype == KVFUSE_BF16) {
         auto items = [&](const SharedArgs &part, int n_cluster, int n_residual) {
@@ -934,20 +965,10 @@ int kvfuse_paged_decode_attn_shared(kvfuse_ctx *ctx, const kvfuse_pool *pool, co
             rest.items += nc;
             items(rest, 0, nr);
         }
-        // The whole call with either merge (us, a workgroup / a wavefront per head; 512 tokens, half shared): 512 heads 13.7 / 13.9,
-        // 2048 28.1 / 27.1, 4096 36.2 / 33.4, 8192 59.1 / 53.2, 32768 272 / 243; head size 64: 512 10.3 / 10.5 - 11.4, 4096 23.7 / 21.0,
-        // 32768 157 / 132; 2048 heads of 28 slots 275.1 / 274.0, 8192 of 7 slots 279 / 270.
-        const int64_t heads_total = tuples * plan->rep;
-        if (heads_total >= 4096 && launch_fits((heads_total + 3) / 4, 256)) {
-            const unsigned grid = (unsigned)((heads_total + 3) / 4);
-            if (pool->d == 128)
-                decode_shared_combine_waves_kernel<128><<<grid, 256, 0, c->stream>>>(A, heads_total);
-            else
-                decode_shared_combine_waves_kernel<64><<<grid, 256, 0, c->stream>>>(A, heads_total);
-        } else if (pool->d == 128)
-            decode_shared_combine_kernel<128, true><<<cgrid, 256, 0, c->stream>>>(A);
+        if (pool->d == 128)
+            launch_merge_slots<128, true>(c->stream, A, tuples, plan->total_slots);
         else
-            decode_shared_combine_kernel<64, true><<<cgrid, 256, 0, c->stream>>>(A);
+            launch_merge_slots<64, true>(c->stream, A, tuples, plan->total_slots);
     } else {
         if (pool->d == 128) KVF_SHARED_LAUNCH(128);
         else KVF_SHARED_LAUNCH(64);

@@ -205,3 +205,27 @@ def test_short_contexts(t, d, rep, longest):
     assert bool((spoilt[:, b, :, 3] == float("inf")).all())
     spoilt[:, b, :, 3] = out[:, b, :, 3]
     assert float((spoilt - out).abs().max()) < 1.2e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,heads,rep,B", [(128, 8, 1, 32), (64, 8, 3, 33), (128, 8, 16, 32), (64, 16, 4, 31)])
+def test_two_splits_of_many_requests(d, heads, rep, B, dtype):
+    """Two splits each, 512 (layer, request, KV head) triples and a few more or fewer: both merges of the splits' states."""
+    from paper_2601_03067_amd import binding as kb
+    t, layers = 16, 2
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B + rep)
+    contexts = [(37 * b) % 209 for b in range(B - 1)] + [208]             # 13 blocks: two splits of 7
+    blocks = [(c + t - 1) // t for c in contexts]
+    n = sum(blocks)
+    K = torch.randn(layers * heads, n, t * d, generator=gen, device=DEV).to(dtype)
+    V = torch.randn(layers * heads, n, t * d, generator=gen, device=DEV).to(dtype)
+    bt = torch.randperm(n, generator=gen, device=DEV).to(torch.int32).repeat(layers * heads, 1).contiguous()
+    cache = kb.Cache(K, V, bt, t, d)
+    cache.scale_k.copy_(0.5 + torch.rand(bt.shape, generator=gen, device=DEV))
+    cache.scale_v.copy_(0.5 + torch.rand(bt.shape, generator=gen, device=DEV))
+    q = torch.randn(layers, B, heads * rep, d, generator=gen, device=DEV).to(dtype)
+    start = np.concatenate([[0], np.cumsum(blocks)[:-1]]).astype(np.int32)
+    out = _call(kb, cache, heads, q, start, max(blocks), False, contexts)
+    ref = _reference(cache, t, d, heads, q, start, False, contexts)
+    assert float((out - ref).abs().max()) < 1.2e-5                        # the bound of test_against_binary64

@@ -1,4 +1,4 @@
-"""Shared-block decode over bfloat16 pools: blocks of one to four pieces, tails that leave whole pieces empty, more partial
+"""Shared-block decode: blocks of one to four pieces, tails that leave whole pieces empty, more partial
 states per request than a wavefront has lanes, padded head counts, against attention in binary64."""
 import numpy as np
 import pytest
@@ -9,15 +9,17 @@ DEV = "cuda:0"
 
 
 # (block size, head dim, KV heads, query heads per KV head, least blocks of a cluster, blocks of the longest request, layers);
-# from 4096 query heads on the partial states are merged by a wavefront per head, 8 states at a time in rounds of 64
+# from 4096 query heads on the partial states are merged by a wavefront per head, 8 states at a time in rounds of 64; plans of
+# little more than one state per request have a merge of their own (the cases with 1 or 2 blocks, and those without clusters)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("t,d,heads,rep,least,blocks,layers",
                          [(16, 128, 2, 4, 1, 75, 2), (16, 64, 1, 1, 1, 70, 2), (32, 128, 1, 8, 2, 20, 2), (48, 64, 2, 3, 1, 9, 2),
                           (64, 128, 1, 16, 1, 7, 2), (16, 128, 1, 2, 4, 1, 300), (16, 128, 2, 4, 1, 75, 57), (16, 64, 1, 16, 1, 75, 29),
                           (16, 128, 1, 16, 1, 20, 29), (32, 64, 2, 3, 1, 37, 76),
                           (16, 64, 2, 4, 1, 2, 2), (16, 128, 1, 2, 9, 4, 2), (64, 64, 1, 4, 1, 1, 2), (16, 128, 2, 5, 9, 5, 2)])
-def test_against_binary64(t, d, heads, rep, least, blocks, layers):
+def test_against_binary64(t, d, heads, rep, least, blocks, layers, dtype):
     from paper_2601_03067_amd import binding as kb
-    print("shared decode", t, d, heads, rep, least, blocks, flush=True)
+    print("shared decode", t, d, heads, rep, least, blocks, layers, dtype, flush=True)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(t + d + blocks)
     B, groups = 9, layers * heads
@@ -38,12 +40,12 @@ def test_against_binary64(t, d, heads, rep, least, blocks, layers):
     start = np.concatenate([[0], np.cumsum([len(m) for m in ids])[:-1]]).astype(np.int32)
     bt = torch.tensor(sum(ids, []), dtype=torch.int32, device=DEV).repeat(groups, 1).contiguous()
     n, P = bt.shape[1], nxt
-    K = torch.randn(groups, P, t * d, generator=gen, device=DEV).to(torch.bfloat16)
-    V = torch.randn(groups, P, t * d, generator=gen, device=DEV).to(torch.bfloat16)
+    K = torch.randn(groups, P, t * d, generator=gen, device=DEV).to(dtype)
+    V = torch.randn(groups, P, t * d, generator=gen, device=DEV).to(dtype)
     cache = kb.Cache(K, V, bt, t, d)
     cache.scale_k.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
     cache.scale_v.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
-    q = torch.randn(layers, B, heads * rep, d, generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randn(layers, B, heads * rep, d, generator=gen, device=DEV).to(dtype)
     ctx = kb.Context(DEV)
     plan = kb.SharedDecodePlan(ctx, cache, heads, start, ctx_len, heads * rep, min_cluster_blocks=least)
     out = kb.paged_decode_attn_shared(ctx, cache, plan, q)

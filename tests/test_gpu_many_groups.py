@@ -80,24 +80,28 @@ def test_more_groups_than_the_widest_lists():
 def test_shared_decode_of_more_heads_than_merging_wavefronts():
     """67 110 400 query heads: the merge with a wavefront each would take more threads than a launch has."""
     from paper_2601_03067_amd import binding as kb
-    B, rep, t, d = 4194400, 16, 16, 64
+    B, rep, t, d, shared, rest = 4194400, 16, 16, 64, 4, 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(4)
-    K = torch.randn(1, 1, t * d, generator=gen, device=DEV).to(torch.bfloat16)
-    V = torch.randn(1, 1, t * d, generator=gen, device=DEV).to(torch.bfloat16)
-    cache = kb.Cache(K, V, torch.zeros(1, 1, device=DEV, dtype=torch.int32), t, d)
+    K = torch.randn(1, shared + 2, t * d, generator=gen, device=DEV).to(torch.bfloat16)
+    V = torch.randn(1, shared + 2, t * d, generator=gen, device=DEV).to(torch.bfloat16)
+    cache = kb.Cache(K, V, torch.arange(shared + 2, device=DEV, dtype=torch.int32)[None].contiguous(), t, d)
     cache.identity_scales()
-    ctx_len = np.zeros(B, np.int32)
-    some = np.concatenate([np.arange(0, B, 997), [B - 1]])                # the others have no context: zeros
-    ctx_len[some] = t
+    # three in ten requests have the shared blocks and five tokens more (two partial states), the others five tokens
+    ctx_len = np.where(np.arange(B) % 10 < 3, shared * t + rest, rest).astype(np.int32)
+    start = np.where(ctx_len == rest, shared + 1, 0).astype(np.int32)
     ctx = kb.Context(DEV)
-    plan = kb.SharedDecodePlan(ctx, cache, 1, np.zeros(B, np.int32), ctx_len, rep)
+    plan = kb.SharedDecodePlan(ctx, cache, 1, start, ctx_len, rep, min_cluster_blocks=shared)
+    assert 4 * (plan.info.items_cluster + plan.info.items_residual) > 5 * B
+    print("plan built", flush=True)
     q = torch.randn(1, B, rep, d, generator=gen, device=DEV, dtype=torch.bfloat16)
     out = torch.full(q.shape, float("nan"), dtype=torch.float32, device=DEV)
     kb.paged_decode_attn_shared(ctx, cache, plan, q, out=out)
-    pick = torch.from_numpy(some).to(DEV)
-    ref = torch.softmax(q[0, pick].double() @ K.view(t, d).double().T / d ** 0.5, -1) @ V.view(t, d).double()
-    # logits below 15, values below 6: as in test_gpu_decode_bf16.py
-    assert float((out[0, pick].double() - ref).abs().max()) < 1.2e-5
-    out[0, pick] = 0.0
-    assert not bool(out.any())
+    for c in (shared * t + rest, rest):
+        pick = torch.from_numpy(np.nonzero(ctx_len == c)[0][::997]).to(DEV)
+        first = 0 if c > rest else (shared + 1) * t
+        k, v = K.view(-1, d)[first:first + c].double(), V.view(-1, d)[first:first + c].double()
+        ref = torch.softmax(q[0, pick].double() @ k.T / d ** 0.5, -1) @ v
+        # logits below 15, values below 6: as in test_gpu_decode_bf16.py
+        assert float((out[0, pick].double() - ref).abs().max()) < 1.2e-5
+    assert bool(torch.isfinite(out).all())
