@@ -56,21 +56,21 @@ __device__ __forceinline__ void rewrite_scale(const TableDesc &tab, int64_t i, i
 
 // Two passes that do not depend on each other, in one launch.  The first n_lists workgroups take a group at a time: freed ids
 // (blocks that were fused away) in ascending order, and the live count; their walk over the pool is a chain of barriers, so they
-// start first, are as wide as can be and load a step ahead (141 355 blocks a group: 394 us with 256 threads, 109 us).  The
-// others refresh the scales.
-constexpr int kFinishThreads = 1024;
-
-__global__ __launch_bounds__(kFinishThreads) void rewrite_finish_kernel(TableDesc tab, int G, int P, const double *__restrict__ norm_k,
-                                                                        const double *__restrict__ norm_v, int n_lists,
-                                                                        int32_t *__restrict__ free_list, int32_t *__restrict__ n_free,
-                                                                        int32_t *__restrict__ n_phys)
+// start first, are as wide as can be and load a step ahead (141 355 blocks a group: 394 us with 256 threads, 109 us).  Groups of
+// at most 256 blocks are one step either way, which 256 threads take (whole rewrite, us, 1024 / 256 threads: 100 000 groups of 8
+// blocks 235 / 62, 20 000 of 100 71 / 32).  The others refresh the scales.
+template <int NT>
+__global__ __launch_bounds__(NT) void rewrite_finish_kernel(TableDesc tab, int G, int P, const double *__restrict__ norm_k,
+                                                            const double *__restrict__ norm_v, int n_lists,
+                                                            int32_t *__restrict__ free_list, int32_t *__restrict__ n_free,
+                                                            int32_t *__restrict__ n_phys)
 {
-    constexpr int NW = kFinishThreads / 64;
+    constexpr int NW = NT / 64;
     __shared__ int wave_tot[2][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if ((int)blockIdx.x >= n_lists) {
-        const int64_t step = (int64_t)(gridDim.x - n_lists) * kFinishThreads;
-        for (int64_t i = (int64_t)(blockIdx.x - n_lists) * kFinishThreads + tid; i < (int64_t)G * tab.n; i += step)
+        const int64_t step = (int64_t)(gridDim.x - n_lists) * NT;
+        for (int64_t i = (int64_t)(blockIdx.x - n_lists) * NT + tid; i < (int64_t)G * tab.n; i += step)
             rewrite_scale(tab, i, P, norm_k, norm_v);
         return;
     }
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(kFinishThreads) void rewrite_finish_kernel(TableDes
         const int64_t gp = (int64_t)g * P;
         int freed = 0, live = 0;
         int next_remap = tid < P ? tab.remap[gp + tid] : -1, next_refs = tid < P ? tab.refcount[gp + tid] : 0;
-        for (int p0 = 0, buf = 0; p0 < P; p0 += kFinishThreads, buf ^= 1) {
-            const int p = p0 + tid, ahead = p + kFinishThreads;
+        for (int p0 = 0, buf = 0; p0 < P; p0 += NT, buf ^= 1) {
+            const int p = p0 + tid, ahead = p + NT;
             const unsigned long long mf = __ballot(next_remap >= 0);
             const unsigned long long ml = __ballot(next_refs > 0);
             const bool is_free = next_remap >= 0;
@@ -119,6 +119,17 @@ __global__ __launch_bounds__(kFinishThreads) void rewrite_finish_kernel(TableDes
     }
 }
 
+template <int NT>
+static void launch_finish(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int32_t *free_list, int32_t *n_free, int32_t *n_phys)
+{
+    // (at most 2^30 threads for the lists and 2^31 for the scales: a launch has fewer than 2^32)
+    const int64_t ne = (int64_t)pool.G * tab.n;
+    const int n_lists = free_list || n_free || n_phys ? std::min(pool.G, (1 << 30) / NT) : 0;
+    const int64_t grid = n_lists + std::min<int64_t>((ne + NT - 1) / NT, (1ll << 31) / NT);
+    if (grid > 0)
+        rewrite_finish_kernel<NT><<<(unsigned)grid, NT, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v, n_lists, free_list, n_free, n_phys);
+}
+
 void launch_rewrite(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int32_t *free_list, int32_t *n_free,
                     int32_t *n_phys)
 {
@@ -128,12 +139,10 @@ void launch_rewrite(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, i
         rewrite_clear_kernel<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(tab.refcount, nb);
     if (ne > 0)
         rewrite_chase_kernel<<<(unsigned)((ne + 255) / 256), 256, 0, s>>>(tab, pool.G, pool.P);
-    // (at most 2^20 workgroups of the one and 2^21 of the other kind: 2^20 times 1024 threads short of what a launch holds)
-    const int n_lists = free_list || n_free || n_phys ? std::min(pool.G, 1 << 20) : 0;
-    const int64_t grid = n_lists + std::min<int64_t>((ne + kFinishThreads - 1) / kFinishThreads, 1 << 21);
-    if (grid > 0)
-        rewrite_finish_kernel<<<(unsigned)grid, kFinishThreads, 0, s>>>(tab, pool.G, pool.P, pool.norm_k, pool.norm_v, n_lists, free_list,
-                                                                        n_free, n_phys);
+    if (pool.P <= 256)
+        launch_finish<256>(s, pool, tab, free_list, n_free, n_phys);
+    else
+        launch_finish<1024>(s, pool, tab, free_list, n_free, n_phys);
 }
 
 }  // namespace kvfuse

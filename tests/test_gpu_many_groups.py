@@ -72,7 +72,8 @@ def test_more_large_nodes_than_the_widest_bookkeeping():
 
 
 def test_more_groups_than_the_widest_lists():
-    """4 194 400 groups of two blocks: the free lists of the table rewrite have 1024 threads a group."""
+    """4 194 400 groups of two blocks: the free lists of the table rewrite have more threads than a launch holds with 1024 a group,
+    and more workgroups of 256 than it takes at once."""
     leaves = [1, 1]
     _check(*_fuse(4194400, leaves), leaves)
 
