@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
 }
 
 // bfloat16 pools of one head per block: 32 tokens (two 16-token pieces) per step of a wavefront (attend.h).
-// Error against binary64, relative in the 2-norm, this kernel / the vector-ALU kernel it replaced: 1.57e-7 / 1.77e-7 (one
-// request of 1000 tokens, d = 128), 1.99e-7 / 2.41e-7 (48 ragged requests), 1.66e-7 / 2.29e-7 (256 requests of 4096 tokens).
+// Error against binary64, relative in the 2-norm, this kernel / the vector-ALU kernel it replaced: 1.55e-7 / 1.77e-7 (one
+// request of 1000 tokens, d = 128), 1.91e-7 / 2.41e-7 (48 ragged requests), 1.64e-7 / 2.29e-7 (256 requests of 4096 tokens).
 //
 // Bound: HBM for blocks read once (64 x 2048 tokens, 64 groups: 5.35 TB/s of distinct bytes, 541 -> 505 us); blocks that many
 // requests share come out of the caches, where the vector ALU was the limit (8 heads per KV head, 256 x 4096 tokens, 16
