@@ -55,6 +55,7 @@ struct HeightDesc {
     int32_t small_tiles;              // most 32 x 32 tiles one node can have
     int32_t max_cap;                  // largest left or right set of a node
     bool use_big_tiles;
+    int32_t panel_run, panel_items;   // panel kernel (panel.hip): most 64-row stages of an item, 0 = not for this height; most items of a group
     int64_t total_s;
 };
 
@@ -71,6 +72,13 @@ struct Q8Desc {
     uint8_t *k;
     float *err, *scale, *alpha, *dir;
 };
+
+// Panel kernel (panel.hip): right blocks of a panel, left blocks of a stage, 64-byte slices of a right block that fit a wavefront's
+// registers; and the share of pairs (one in so many) left open at the height before up to which a group takes it.
+constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
+constexpr int kPanelCols = 512, kPanelRows = 64, kPanelSlices = 11, kPanelRun = 32, kPanelOpen = 1024;
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Group-strided work arrays of a plan (device).
 struct WorkDesc {
@@ -105,6 +113,12 @@ struct WorkDesc {
     float *pair_head;        // [pair_cap] ... and their product so far
     int32_t *n_pairs;        // counter of the current height
     int32_t pair_cap;
+    int32_t *open_cnt;       // [G] pairs that the current height's tests left open
+    // panel kernel (panel.hip); panel_on null = not at this height
+    int32_t *panel_on, *panel_on_mem;       // [G]
+    u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand
+    int4 *panel_items;       // (group, node, first column, first row)
+    int32_t *panel_total;    // [max_heights]
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
     int4 *dyn_items;     // [G][item_cap of the height] node, first column, first row, rows
     int32_t *dyn_base;   // [G][dyn_stride] first item of every node, and the total
@@ -176,6 +190,10 @@ void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
                        float *dense_s, bool cleared = false);
 // early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
+// bfloat16, and a group's keys within the 32-bit offsets of buffer loads
+static inline bool panel_fits(const PoolDesc &pool) { return pool.dtype == KVFUSE_BF16 && (int64_t)pool.P * pool.r * 2 <= 0xFFFFFFFFll; }
+void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, const HeightDesc &prev, int height,
+                             float thr_floor);
 void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
 void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height);
 void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const HeightDesc &h,

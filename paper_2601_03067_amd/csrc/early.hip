@@ -18,7 +18,7 @@
 
 namespace kvfuse {
 
-constexpr int kSamples = 64;      // sampled pairs per group: one per lane of a wavefront
+constexpr int kSamples = 64;      // sampled pairs per group: one per lane of a wavefront; twice as many where there is room for their bounds
 constexpr int kSteps = 32;        // lengths considered: (k / 32) of the block's slices
 static_assert(kSteps * kSamples * sizeof(float) <= 256 * 2 * sizeof(int4), "the bounds of a group fit its share of the merge work list");
 
@@ -39,12 +39,12 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x)
 // 256 groups and 174 us for 16 groups of 8 KiB blocks.)
 template <typename T>
 __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict__ kpool, const int32_t *__restrict__ bt, int G, int P, int n,
-                                                            int r, float *__restrict__ bounds)
+                                                            int r, int n_samples, float *__restrict__ bounds)
 {
     constexpr int PER = Elem<T>::PER16, BATCH = 4;
     __shared__ float seg[4][3][kSteps];               // <a, b>, <a, a>, <b, b> of every segment
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int id = blockIdx.x * 4 + wave, g = id / kSamples, s = id % kSamples;      // (the grid is exactly G * kSamples / 4)
+    const int id = blockIdx.x * 4 + wave, g = id / n_samples, s = id % n_samples;      // (the grid is exactly G * n_samples / 4)
     const int chunks = r / PER, nk = chunks / 4;
     const int per_seg = chunks / kSteps;
     const int lanes_per_seg = chunks % (64 * kSteps) == 0 || (chunks % kSteps == 0 && (per_seg & (per_seg - 1)) == 0) ? min(per_seg, 64) : 1;
@@ -110,51 +110,84 @@ __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict_
     if (!(bound < 1e30f))
         bound = 1e30f;                                // blocks beyond binary32's range: no early test
     if (lane < kSteps)
-        bounds[((int64_t)g * kSteps + len) * kSamples + s] = bound;
+        bounds[((int64_t)g * kSteps + len) * n_samples + s] = bound;
 }
 
-// One workgroup per group: for every length the bounds of all pairs are ranked; with their median m and the 84th
-// percentile q, m + 4 (q - m) estimates what one unrelated pair in 30 000 reaches, about two of a 256 x 256 tile.  The
+// One workgroup per group: for every length the bounds of all pairs are ranked; with their median m and the 16th and 84th
+// percentiles, m + 4 s estimates what one unrelated pair in 30 000 reaches, about two of a 256 x 256 tile.  The
 // shortest length for which that stays below the candidate floor is taken.  Ranks instead of moments because a few per cent
-// of the pairs may be related ones.
+// of the pairs may be related ones; s is half the distance of the two percentiles (which varies less from sample to sample than
+// either's distance from the median), but not much less than the upper one's, where the bounds are skewed.
+// PER: sampled pairs per lane.  One pair and the upper percentile alone: 10, 12 or 14 slices of 64 for groups of one kind, 55 of 256
+// of them 12 or more.
+template <int PER>
 __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
                                                             int32_t *__restrict__ early_nk)
 {
-    __shared__ int enough[kSteps];
+    constexpr int N = PER * kSamples;
+    __shared__ float reach[kSteps], rank16[kSteps], rank50[kSteps], rank84[kSteps];
+    __shared__ int best;
     const int g = blockIdx.x, lane = threadIdx.x & 63;
     for (int len = threadIdx.x >> 6; len < kSteps; len += 16) {
-        const float bound = bounds[((int64_t)g * kSteps + len) * kSamples + lane];
-        int rank = 0;
-#pragma unroll 8
-        for (int k = 0; k < kSamples; ++k) {
-            const float other = __shfl(bound, k, 64);
-            rank += other < bound || (other == bound && k < lane);
+        float bound[PER];
+        int rank[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            bound[i] = bounds[((int64_t)g * kSteps + len) * N + i * 64 + lane];
+            rank[i] = 0;
         }
-        const float med = __shfl(bound, __ffsll((long long)__ballot(rank == kSamples / 2)) - 1, 64);
-        const float q84 = __shfl(bound, __ffsll((long long)__ballot(rank == 54)) - 1, 64);
-        const int slices = (nk * len) / kSteps;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+#pragma unroll 8
+            for (int k = 0; k < kSamples; ++k) {
+                const float other = __shfl(bound[j], k, 64);
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    rank[i] += other < bound[i] || (other == bound[i] && (j < i || (j == i && k < lane)));
+            }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {          // (the ranks are a permutation: one lane each)
+            if (rank[i] == N * 16 / 100)
+                rank16[len] = bound[i];
+            if (rank[i] == N / 2)
+                rank50[len] = bound[i];
+            if (rank[i] == N * 84 / 100 + 1)
+                rank84[len] = bound[i];
+        }
+        __builtin_amdgcn_wave_barrier();
         if (lane == 0)
-            enough[len] = med + 4.0f * (q84 - med) < thr_floor - 1e-3f && slices >= 2 && 4 * slices <= 3 * nk;
+            reach[len] = rank50[len] + 4.0f * fmaxf(0.5f * (rank84[len] - rank16[len]), 0.85f * (rank84[len] - rank50[len]));
+    }
+    if (threadIdx.x == 0)
+        best = nk;
+    __syncthreads();
+    for (int slices = 2 + threadIdx.x; 4 * slices <= 3 * nk; slices += 1024) {
+        // between two lengths the reach is taken as a straight line
+        const int len = slices * kSteps / nk, rest = slices * kSteps % nk;
+        const float r0 = reach[len], r1 = reach[min(len + 1, kSteps - 1)];
+        if (r0 + (r1 - r0) * ((float)rest / (float)nk) < thr_floor - 1e-3f)
+            atomicMin(&best, slices);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int best = nk;
-        for (int len = kSteps - 1; len >= 1; --len)
-            if (enough[len])
-                best = (nk * len) / kSteps;
+    if (threadIdx.x == 0)
         early_nk[g] = best;
-    }
 }
 
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor)
 {
     float *bounds = reinterpret_cast<float *>(w.active);      // (free until the first assignment step; l_stride >= 256 is room enough)
-    const unsigned grid = (unsigned)pool.G * kSamples / 4;
+    const bool twice = w.l_stride >= 512;
+    const int n_samples = twice ? 2 * kSamples : kSamples;
+    const unsigned grid = (unsigned)pool.G * n_samples / 4;
     if (pool.dtype == KVFUSE_BF16)
-        sample_bounds_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, bounds);
+        sample_bounds_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, n_samples, bounds);
     else
-        sample_bounds_kernel<float><<<grid, 256, 0, s>>>((const float *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, bounds);
-    choose_early_kernel<<<pool.G, 1024, 0, s>>>(bounds, pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64, thr_floor, w.early_nk_mem);
+        sample_bounds_kernel<float><<<grid, 256, 0, s>>>((const float *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, n_samples, bounds);
+    const int nk = pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64;
+    if (twice)
+        choose_early_kernel<2><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem);
+    else
+        choose_early_kernel<1><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem);
 }
 
 // The pairs that the tests left open, 16 lanes per pair: the rest of the product, and the pair's entry in its column's
@@ -168,17 +201,20 @@ __global__ __launch_bounds__(256) void finish_pairs_kernel(PoolDesc pool, WorkDe
     const int sub = threadIdx.x & 15;
     for (int q = (blockIdx.x * 256 + threadIdx.x) >> 4; q < n; q += gridDim.x * 16) {
         const int4 rec = w.pairs[q];
+        if (rec.x < 0)
+            continue;
         const int g = rec.x / w.r_stride;
+        const bool from_start = rec.y < 0;           // (kPairWhole)
         const int64_t pa = (int64_t)g * pool.P + rec.z, pb = (int64_t)g * pool.P + rec.w;
         const float ia = pool.inv_norm_k[pa], ib = pool.inv_norm_k[pb];
-        float dot = product_from<T>((const T *)pool.k + pa * pool.r, (const T *)pool.k + pb * pool.r, 4 * w.early_nk[g],
+        float dot = product_from<T>((const T *)pool.k + pa * pool.r, (const T *)pool.k + pb * pool.r, from_start ? 0 : 4 * w.early_nk[g],
                                     pool.r / Elem<T>::PER16, sub, 16);
 #pragma unroll
         for (int off = 8; off >= 1; off >>= 1)
             dot += __shfl_xor(dot, off, 64);
-        const float cs = (w.pair_head[q] + dot) * ia * ib;
+        const float cs = (from_start ? dot : w.pair_head[q] + dot) * ia * ib;
         if (sub == 0 && cs > thr_floor)
-            emit_candidate(w.cand_cnt, w.cand_idx, w.cand_val, rec.x, w.cand_cap, rec.y, cs);
+            emit_candidate(w.cand_cnt, w.cand_idx, w.cand_val, rec.x, w.cand_cap, rec.y & ~kPairWhole, cs);
     }
 }
 

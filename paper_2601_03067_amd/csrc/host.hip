@@ -282,6 +282,12 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.pair_head = nullptr;
     w.n_pairs = nullptr;
     w.pair_cap = 0;
+    w.open_cnt = cv.take<int32_t>((size_t)G);
+    w.panel_on = nullptr;
+    w.panel_on_mem = cv.take<int32_t>((size_t)G);
+    w.panel_total = cv.take<int32_t>(kMaxHeights);
+    w.panel_rows = nullptr;
+    w.panel_items = nullptr;
     w.group_enable = nullptr;
     w.leaf_src = cv.take<int32_t>((size_t)std::max(n, 1));
     w.rem_k = nullptr;
@@ -298,6 +304,34 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
         w.dyn_items = cv.take<int4>((size_t)G * items);
         w.dyn_base = cv.take<int32_t>((size_t)G * w.dyn_stride);
         w.dyn_count = cv.take<int32_t>((size_t)G);
+    }
+    size_t panel_items = 0;
+    for (HostHeight &h : hs) {
+        // Panel kernel: items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
+        // to 8, while there are fewer than eight a compute unit.
+        h.dev.panel_run = h.dev.panel_items = 0;
+        if (!h.big)
+            continue;
+        auto count = [&](int run) {
+            int64_t c = 0;
+            for (size_t k = 0; k < h.l_cap.size(); ++k)
+                c += (int64_t)((h.r_cap[k] + kPanelCols - 1) / kPanelCols) *
+                     (((h.l_cap[k] + kPanelRows - 1) / kPanelRows + run - 1) / run);
+            return c;
+        };
+        int run = kPanelRun;
+        while (run > 8 && (int64_t)G * count(run) < 2048)
+            run /= 2;
+        const int64_t items = count(run);
+        if (!launch_fits(items * G + 256, 512))
+            continue;
+        h.dev.panel_run = run;
+        h.dev.panel_items = (int32_t)items;
+        panel_items = std::max(panel_items, (size_t)items * (size_t)G);
+    }
+    if (panel_items > 0) {
+        w.panel_rows = cv.take<u32x4>(2 * L);
+        w.panel_items = cv.take<int4>(panel_items);
     }
     for (HostHeight &h : hs) {
         const size_t nn = h.l_off.size();
@@ -677,6 +711,9 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     for (int hgt = 0; hgt < nh; ++hgt) {
         const HeightDesc &d = p.heights[hgt].dev;
         w.n_pairs = w.n_pairs_all + hgt;
+        w.panel_on = early && panel_fits(p.pool) && d.panel_run > 0 ? w.panel_on_mem : nullptr;
+        if (w.panel_on)
+            launch_similarity_panel(c->stream, p.pool, w, d, hgt > 0 ? p.heights[hgt - 1].dev : HeightDesc{}, hgt, floor_f);
         launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);
         if (early)
             launch_finish_pairs(c->stream, p.pool, w, floor_f);

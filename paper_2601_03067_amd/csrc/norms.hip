@@ -244,7 +244,10 @@ __global__ __launch_bounds__(256) void tree_clear_kernel(TableDesc tab, WorkDesc
         w.n_active[i] = 0;
         w.n_refine[i] = 0;
         w.n_pairs_all[i] = 0;
+        w.panel_total[i] = 0;
     }
+    if (i < w.G)
+        w.open_cnt[i] = 0;
 }
 
 // Thread i: reference count of table entry i and the leaf-set position i (leaf_sets_kernel).  Caller errors are counted

@@ -72,9 +72,8 @@ struct EarlyArgs {
     float *pair_head;
     int32_t *n_pairs;
     int32_t pair_cap;
+    int32_t *open_cnt;
 };
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <typename T> struct MmaV;
 template <> struct MmaV<bf16_t> {
@@ -789,8 +788,10 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     // loads then run ahead into the next row tile as they always do.
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                     __syncthreads();
-                    if (tid == 0)
+                    if (tid == 0) {
                         lds_ncand = n_kept;
+                        atomicAdd(&early.open_cnt[g], LIMIT + 1);
+                    }
                     whole = true;
                     n_slices = nk_full;
                     --rt;
@@ -835,8 +836,10 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
         }
         if constexpr (EARLY) {
             __syncthreads();
-            if (tid == 0 && lds_npairs > 0)
+            if (tid == 0 && lds_npairs > 0) {
                 lds_pair0 = atomicAdd(early.n_pairs, lds_npairs);
+                atomicAdd(&early.open_cnt[g], lds_npairs);
+            }
             __syncthreads();
             if (lds_npairs > 0) {
                 const int first = lds_pair0;
@@ -935,6 +938,11 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     __shared__ int64_t lds4[4];
     const int g = blockIdx.x, tid = threadIdx.x;
     int32_t *base = w.dyn_base + (int64_t)g * w.dyn_stride;
+    if (w.panel_on && w.panel_on[g]) {        // this group's share of the height is the panel kernel's
+        if (tid == 0)
+            w.dyn_count[g] = 0;
+        return;
+    }
     int64_t run = 0;
     for (int k0 = 0; k0 < h.n_nodes; k0 += 256) {
         const int k = k0 + tid;
@@ -1010,7 +1018,7 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     A.thr_floor = thr_floor;
     A.total_s = h.total_s;
     const unsigned grid = (unsigned)(((total + 31) / 32) * 32);      // whole quads on every XCD
-    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap};
+    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt};
 #define KVF_SIM_LAUNCH(D, PF, EA)                                                                                          \
     similarity_ring_kernel<T, BIG, D, PF, EA><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
         A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_count, h.l_off, h.r_off, \
