@@ -70,6 +70,10 @@ struct PrefillArgs {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
+// The tables of a call: nothing writes them while it runs, so that a uniform word of theirs is a scalar load, also behind
+// statements that the compiler takes for writes to memory.
+#define KVF_TABLE __attribute__((address_space(4)))
+
 // One 16-token piece of the context: the words that tables hold of it, as they come from memory.  Nothing is computed from
 // them until they are used, a tile later, so that no wait stands between their loads; where they come from is a choice of
 // addresses and not a branch.
@@ -90,9 +94,9 @@ constexpr int32_t kBefore = -(1 << 30), kNowhere = 1 << 30;
 template <int D>
 struct PWalk {
     const bf16_t *kg, *vg;
-    const int32_t *btg;
-    const float *skg, *svg;
-    const PEntry *eg;
+    const KVF_TABLE int32_t *btg;
+    const KVF_TABLE float *skg, *svg;
+    const KVF_TABLE PEntry *eg;
     int ppb, last_block, n_pre, n_pieces;
     uint32_t inv_hi, inv_lo;                                     // 2^40 / ppb, rounded up
 
@@ -104,13 +108,13 @@ struct PWalk {
         const int64_t x = (int64_t)g * A.n + A.req_start + A.chunk_begin / A.t;
         kg = (const bf16_t *)A.kpool + (int64_t)g * A.P * r;
         vg = (const bf16_t *)A.vpool + (int64_t)g * A.P * r;
-        btg = A.bt + x;                                          // the chunk's first block
-        skg = A.scale_k + x;
-        svg = A.scale_v + x;
+        btg = (const KVF_TABLE int32_t *)(A.bt + x);             // the chunk's first block
+        skg = (const KVF_TABLE float *)(A.scale_k + x);
+        svg = (const KVF_TABLE float *)(A.scale_v + x);
         ppb = A.t / 16;                                          // pieces per block
         inv_hi = (uint32_t)(A.ppb_inv >> 32);
         inv_lo = (uint32_t)A.ppb_inv;
-        eg = A.entries + A.entry_begin[gi];
+        eg = (const KVF_TABLE PEntry *)(A.entries + A.entry_begin[gi]);
         last_block = A.entry_begin[gi + 1] - A.entry_begin[gi] - 1;
         n_pre = (last_block + 1) * ppb;
         n_pieces = n_pre + (pos_last - A.chunk_begin) / 16 + 1;
@@ -145,12 +149,12 @@ struct PWalk {
         const bool pre = p < n_pre;
         const int q = max(min(p, n_pieces - 1) - n_pre, 0);
         // no entries at all: unused words of the plan's own memory
-        const PEntry *en = &eg[max(min(block_of(p), last_block), 0)];
+        const KVF_TABLE PEntry *en = &eg[max(min(block_of(p), last_block), 0)];
         PScales sc;
         sc.inst_cnt = en->inst_cnt; sc.inst_off = en->inst_off;
         sc.first.x = *(pre ? &en->first.x : &skg[block_of(q)]);
         sc.first.y = *(pre ? &en->first.y : &svg[block_of(q)]);
-        sc.second = en->second;
+        sc.second.x = en->second.x; sc.second.y = en->second.y;
         sc.sk_max = en->sk_max; sc.sk_min = en->sk_min;
         sc.tok_base = pre ? kBefore : p < n_pieces ? A.chunk_begin + q * 16 : kNowhere;
         return sc;
@@ -237,8 +241,11 @@ __device__ static __forceinline__ float tile_weights_as(const PrefillArgs &A, co
             float2 next = sc.second;
             for (int q = 1; q < n_inst; ++q) {
                 const float zq = base * next.x, vq = next.y;
-                if (q + 1 < n_inst)
-                    next = A.inst[sc.inst_off + q + 1];
+                if (q + 1 < n_inst) {
+                    const KVF_TABLE float2 *in = (const KVF_TABLE float2 *)A.inst + (sc.inst_off + q + 1);
+                    next.x = in->x;
+                    next.y = in->y;
+                }
 #pragma unroll
                 for (int i = 8 * half; i < 8 * half + 8; ++i) {
                     const float pr = __builtin_amdgcn_exp2f(fmaf(z[i], zq, -m_new));
@@ -275,19 +282,38 @@ __device__ static __forceinline__ void split_weights(const float (&pw)[16], bf16
         }
 }
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
+// 16 bytes per lane from `base` (uniform) + `off` straight into LDS, at `to` (uniform) + 16 lane.  In assembly, because the compiler
+// makes every LDS read wait for all such loads of its own, whichever buffer they are for; who issues one waits for it by hand.  (No
+// register is loaded.  The pause is for scalar registers that a vector instruction has just written, and for m0.)
+__device__ static __forceinline__ void load_to_lds(uint64_t base, uint32_t off, uint32_t to)
+{
+    typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
+    const desc_t desc = {(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(desc), "s"(to) : "memory");
+}
+
+// WAVES: wavefronts of a SIMD that the registers are for, see launch_prefill_attn.
+template <int D, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
 {
     typedef bf16_t T;
     constexpr int KS = D / 16;                 // MFMA steps along the head dimension for the logits
     constexpr int DT = D / 32;                 // 32-row tiles of out^T
-    constexpr int KSTR = D * 2 + 16;           // bytes per token row of the K tile (pad: conflict-free 16-byte row reads)
-    constexpr int VSTR = D * 2 + 64;           // bytes per token row of the V tile (pad: conflict-free transpose reads)
-    constexpr int RCH = D / 8;                 // 16-byte chunks per token row
-    constexpr int LPT = 32 * RCH / 256;        // chunks per thread, per tensor and tile (2 for D = 128, 1 for D = 64)
+    constexpr int ROW = D * 2;                 // bytes of a token row
+    constexpr int RCH = D / 8;                 // 16-byte chunks of a token row
+    constexpr int TILE = 32 * ROW;             // bytes of a tile, per tensor
+    constexpr int NLD = 16 * ROW / 1024;       // 1 KB loads of a 16-token piece
+    constexpr bool ROOMY = WAVES < 3;
+    constexpr int BUFS = ROOMY ? 3 : 2;        // tiles in LDS: one in use, the others on their way
+    constexpr int KQ = ROOMY ? 0 : KS - 4;     // query fragments that live in LDS
 
-    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KSTR];
-    __shared__ __attribute__((aligned(16))) char v_lds[2][32 * VSTR];
+    // K rows, then V rows, of each tile.  The loads write a row's 16-byte chunks end to end, so what padding would do is done by
+    // the order of the chunks: chunk c of row r is at c ^ k_swizzle(r) / c ^ v_swizzle(r) (conflict-free 16-byte row reads of 16
+    // consecutive rows; conflict-free transpose reads of 64 bytes of 4 consecutive rows).
+    __shared__ __attribute__((aligned(1024))) char lds[BUFS][2][TILE];
+    __shared__ __attribute__((aligned(16))) uint4 q_lds[4][KQ > 0 ? KQ : 1][64];
+    auto k_swizzle = [](int r) __attribute__((always_inline)) { return RCH == 16 ? r & 15 : (r >> 1) & 7; };
+    auto v_swizzle = [](int r) __attribute__((always_inline)) { return RCH == 16 ? (r & 3) * 4 : ((r >> 1) & 1) * 4; };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -304,50 +330,42 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
     const bool row_used = wave_live && pos_first + rs <= pos_last && hh < A.rep;
     const int my_pos = wave_live ? min(pos_first + rs, pos_last) : A.q_end - 1;   // unused rows mask like a real one
 
-    uint4 qf[KS];                                     // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row
+    // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row.  Where a third wavefront of the SIMD needs the
+    // registers, all but four of them live in LDS.
+    uint4 qf[KS - KQ];
     {
+        uint4 q[KS];
         const int64_t qi = (int64_t)li * (A.q_end - A.q_begin) + (my_pos - A.q_begin);
         const T *qp = (const T *)A.q + (qi * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + 8 * h2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-            qf[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+            q[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+        sign_queries(q, A.q_sign);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            if (ks < KS - KQ)
+                qf[ks] = q[ks];
+            else
+                q_lds[wave][ks - (KS - KQ)][lane] = q[ks];
     }
 
     const PWalk<D> walk(A, kvh, li, pos_last_wg);
     const int n_tiles = (walk.n_pieces + 1) / 2;
 
-    // global -> registers -> LDS, LPT chunks per thread and tensor: chunk c of a tile = token c / RCH, row chunk c % RCH
-    // two register sets: the tile after next is already on its way while the next one waits to be written to LDS
-    typedef uint32_t chunk_t __attribute__((ext_vector_type(4)));
-    chunk_t kr0[LPT], vr0[LPT], kr1[LPT], vr1[LPT];
-    auto fetch = [&](PRows r0, PRows r1, chunk_t (&kreg)[LPT], chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
-        const int64_t u0 = walk.first_row(A, r0), u1 = walk.first_row(A, r1);
+    // ---- loaders: a wavefront fetches one of a tile's two pieces of one tensor, 16 rows end to end, straight into LDS.  The
+    // piece's address is uniform, so it goes into the descriptor.
+    const int piece = wave & 1, tensor = wave >> 1;
+    const bf16_t *my_pool = tensor ? walk.vg : walk.kg;
+    auto load = [&](int buf, const PRows &rw) __attribute__((always_inline)) {
+        const uint64_t from = (uint64_t)(uintptr_t)(my_pool + walk.first_row(A, rw));
+        const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&lds[buf][tensor][piece * 16 * ROW];
+        int at = lane;
+        asm volatile("" : "+v"(at));
 #pragma unroll
-        for (int u = 0; u < LPT; ++u) {
-            const int c = tid + 256 * u;
-            const bool second = RCH == 16 ? u == 1 : (wave & 2) != 0;          // the chunks of a wavefront lie in one piece
-            const int64_t off = (second ? u1 : u0) + (c % (16 * RCH)) * 8;
-            kreg[u] = *reinterpret_cast<const chunk_t *>(walk.kg + off);
-            vreg[u] = *reinterpret_cast<const chunk_t *>(walk.vg + off);
-        }
-    };
-    // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
-    auto hide = [&](PRows r0, PRows r1, chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < LPT; ++u) {
-            const bool second = RCH == 16 ? u == 1 : (wave & 2) != 0;
-            const int tok_base = second ? r1.tok_base : r0.tok_base;
-            const bool hidden = tok_base + ((tid + 256 * u) / RCH & 15) > pos_last_wg;
-            vreg[u] = hidden ? (chunk_t)(0u) : vreg[u];
-        }
-    };
-    auto stash = [&](int buf, const chunk_t (&kreg)[LPT], const chunk_t (&vreg)[LPT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < LPT; ++u) {
-            const int c = tid + 256 * u;
-            const int tok = c / RCH, rc = c % RCH;
-            *reinterpret_cast<chunk_t *>(&k_lds[buf][tok * KSTR + rc * 16]) = kreg[u];
-            *reinterpret_cast<chunk_t *>(&v_lds[buf][tok * VSTR + rc * 16]) = vreg[u];
+        for (int i = 0; i < NLD; ++i) {
+            const int row = i * (1024 / ROW) + at / RCH;
+            const int c = (at % RCH) ^ (tensor ? v_swizzle(row) : k_swizzle(row));
+            load_to_lds(from, (uint32_t)(row * ROW + c * 16), to + i * 1024);
         }
     };
 
@@ -359,46 +377,78 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
         for (int i = 0; i < 16; ++i)
             o[dt][i] = 0.0f;
 
-    // this lane's addresses inside a tile: K row for the logits, V patch for the transpose reads
-    const int k_off = qrow * KSTR + h2 * 16;
+    // this lane's addresses inside a tile: K row for the logits, V patch (8 bytes of a row) for the transpose reads
+    const int k_off = qrow * ROW + (h2 ^ k_swizzle(qrow)) * 16;
     const int l16 = lane & 15;
-    const int v_off = (4 * h2 + (l16 >> 2)) * VSTR + (16 * ((lane >> 4) & 1) + 4 * (l16 & 3)) * 2;
+    const int v_row = 4 * h2 + (l16 >> 2);
+    const int v_off = v_row * ROW + ((2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1)) ^ v_swizzle(v_row)) * 16 + 8 * (l16 & 1);
 
-    // Bound: the softmax's vector instructions and the matrix instructions of a SIMD's two wavefronts hardly overlap (per tile
-    // 270 of the former, 24 of the latter: 54 and 32 % of the cycles).  2048 queries of a 32768-token prompt, 4 layers of 8 KV
-    // heads, a third of the blocks fused: 7.15 -> 5.70 ms since table words and fragments come ahead of their use and the
-    // maximum is taken before the scales are applied.
+    // Bound: the softmax's vector instructions and the matrix instructions of a SIMD's wavefronts (per tile 270 of the former,
+    // 24 of the latter: 71 and 41 % of the cycles), at a clock of 1.6 GHz, which is what they leave of the power.  2048 queries of a
+    // 32768-token prompt, 4 layers of 8 KV heads, a third of the blocks fused: 7.15 -> 5.70 ms since table words and fragments come
+    // ahead of their use and the maximum is taken before the scales are applied; -> 5.06 ms since the tiles go straight into LDS
+    // and a third wavefront fits a SIMD (54 and 32 % before).
     // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
     // before the first product, the V fragments and the next tiles' table words (which wait on the same counter) before the
     // softmax.  The compiler left to itself reads one fragment, waits, multiplies.
     auto compute = [&](const PScales &s0, const PScales &s1, int buf, auto &&tables) __attribute__((always_inline)) {
-        uint4 ka[KS];
+        // (worked out anew for every tile: kept, the sixteen addresses of a tile would cost the registers of a third wavefront)
+        int k_at = k_off, v_at = v_off;
+        asm volatile("" : "+v"(k_at), "+v"(v_at));
+        const char *kt = &lds[buf][0][0], *vtile = &lds[buf][1][0];
+        uint4 ka[4];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            ka[ks] = *reinterpret_cast<const uint4 *>(&k_lds[buf][k_off + ks * 32]);
+        for (int ks = 0; ks < 4; ++ks)
+            ka[ks] = *reinterpret_cast<const uint4 *>(kt + (k_at ^ (ks * 32)));
         __builtin_amdgcn_sched_barrier(0);
         // ---- logits^T of the tile: 32 tokens x 32 query rows
         floatx16 z;
+        uint4 qa[4];
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             z[i] = 0.0f;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        bf16x4 vt[2][DT][2];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const char *vp = &v_lds[buf][v_off + (16 * jj) * VSTR + dt * 64];
-                vt[jj][dt][0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp));
-                vt[jj][dt][1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp + 8 * VSTR));
+        for (int ks = 0; ks < KS; ++ks) {
+            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks & 3]), __builtin_bit_cast(bf16x8, ks < KS - KQ ? qf[ks < KS - KQ ? ks : 0] : qa[ks & 3]), z, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks + 4 < KS) {
+                ka[ks & 3] = *reinterpret_cast<const uint4 *>(kt + (k_at ^ ((ks + 4) * 32)));
+                if constexpr (KQ > 0)
+                    qa[ks & 3] = q_lds[wave][ks][lane];
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        bf16x4 vt[2][DT][2];
+        auto read_v = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const char *vp = vtile + (v_at ^ (dt * 64)) + 16 * jj * ROW;
+                    vt[jj][dt][0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp));
+                    vt[jj][dt][1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(vp + 8 * ROW));
+                }
+        };
+        if constexpr (ROOMY)
+            read_v();
         tables();
         __builtin_amdgcn_sched_barrier(0);
         float pw[16];
         const float corr = tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!ROOMY)
+            read_v();
+        if (max(s0.tok_base, s1.tok_base) + 15 > pos_last_wg) {
+            // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if ((jj ? s1 : s0).tok_base + 8 * (e >> 2) + 4 * h2 + (e & 3) > pos_last_wg)
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt)
+                            vt[jj][dt][e >> 2][e & 3] = (__bf16)0.0f;
+        }
         if (__builtin_amdgcn_ballot_w64(corr != 1.0f)) {
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
@@ -419,49 +469,29 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillArgs A)
             }
     };
 
-    // The rows of the tiles whose values wait in register set 0 (a), in set 1 (b), of the next fetch (c).
-    PRows a0 = walk.rows(A, 0), a1 = walk.rows(A, 1), b0 = walk.rows(A, 2), b1 = walk.rows(A, 3), c0 = walk.rows(A, 4), c1 = walk.rows(A, 5);
-    PScales sa0 = walk.scales(A, 0), sa1 = walk.scales(A, 1), sb0, sb1;
-    fetch(a0, a1, kr0, vr0);
-    fetch(b0, b1, kr1, vr1);
-    hide(a0, a1, vr0);
-    stash(0, kr0, vr0);
-    sign_queries(qf, A.q_sign);
-    __syncthreads();
-    for (int ti = 0; ti < n_tiles; ti += 2) {
-        // tile ti is in buffer 0, tile ti + 1 in register set 1
-        a0 = c0;
-        a1 = c1;
-        if (ti + 2 < n_tiles)
-            fetch(a0, a1, kr0, vr0);
-        compute(sa0, sa1, 0, [&]() __attribute__((always_inline)) {
-            c0 = walk.rows(A, 2 * (ti + 3));
-            c1 = walk.rows(A, 2 * (ti + 3) + 1);
-            sb0 = walk.scales(A, 2 * (ti + 1));
-            sb1 = walk.scales(A, 2 * (ti + 1) + 1);
+    // The next BUFS - 1 tiles are on their way while one is multiplied; past the last tile the loads go on with the last piece's rows.
+    PRows next = walk.rows(A, 2 * (BUFS - 1) + piece);
+    PScales s0 = walk.scales(A, 0), s1 = walk.scales(A, 1), n0, n1;
+#pragma unroll
+    for (int i = 0; i < BUFS - 1; ++i)
+        load(i, walk.rows(A, 2 * i + piece));
+    int buf = 0, ahead = BUFS - 1;
+    for (int ti = 0; ti < n_tiles; ++ti) {
+        // Tile ti has landed, for every wavefront behind the barrier; and every wavefront is done with tile ti - 1, whose place
+        // the next load takes.
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((BUFS - 2) * NLD) : "memory");
+        load(ahead, next);
+        compute(s0, s1, buf, [&]() __attribute__((always_inline)) {
+            next = walk.rows(A, 2 * (ti + BUFS) + piece);
+            n0 = walk.scales(A, 2 * (ti + 1));
+            n1 = walk.scales(A, 2 * (ti + 1) + 1);
         });
-        if (ti + 1 >= n_tiles)
-            break;
-        hide(b0, b1, vr1);
-        stash(1, kr1, vr1);
-        __syncthreads();
-        // tile ti + 1 is in buffer 1, tile ti + 2 in register set 0
-        b0 = c0;
-        b1 = c1;
-        if (ti + 3 < n_tiles)
-            fetch(b0, b1, kr1, vr1);
-        compute(sb0, sb1, 1, [&]() __attribute__((always_inline)) {
-            c0 = walk.rows(A, 2 * (ti + 4));
-            c1 = walk.rows(A, 2 * (ti + 4) + 1);
-            sa0 = walk.scales(A, 2 * (ti + 2));
-            sa1 = walk.scales(A, 2 * (ti + 2) + 1);
-        });
-        if (ti + 2 < n_tiles) {
-            hide(a0, a1, vr0);
-            stash(0, kr0, vr0);
-        }
-        __syncthreads();
+        s0 = n0;
+        s1 = n1;
+        ahead = buf;
+        buf = buf + 1 == BUFS ? 0 : buf + 1;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may leave while loads are on their way into LDS
     l_run = halves_sum(l_run);
 
     // ---- normalise and store: this lane holds out[row qrow][head element 32 dt + 8 (i / 4) + 4 h2 + i % 4]
@@ -659,6 +689,17 @@ static bool split_pays(int64_t staged_wgs, int64_t split_wgs, int64_t tiles, int
 {
     const int64_t half_rounds = std::max<int64_t>(2, (split_wgs + 255) / 256 * (d == 64 ? 1 : 2));
     return staged_wgs <= kSplitBelow && half_rounds * (42 + 2 * tiles) < 2 * (35 + 10 * tiles);
+}
+
+// Head size 128: whether the staged kernel's registers are for two wavefronts per SIMD (all queries in them, V rows read before the
+// softmax, two tiles on their way) or for three.  Grids of at most two workgroups per compute unit never have a third; and where
+// most of a walk is the chunk itself, so that workgroups differ in length, up to 640 workgroups go to compute units that get free
+// better than three at a time to some of them.  Both measured (us, two / three; 8 KV heads, 4 query heads each, three in ten blocks
+// before the chunk fused away), by workgroups: 304 43.5 / 45.9; 416 118.2 / 116.5; 512 147.1 / 148.3; 552, three quarters of the
+// context before the chunk 658 / 543; 576, all of it in the chunk 169 / 191; 752, likewise 291 / 223; 2048 6515 / 6105.
+static bool roomy_pays(int64_t staged_wgs, int64_t tiles_before, int64_t tiles)
+{
+    return staged_wgs <= (2 * tiles_before < tiles ? 640 : 512);
 }
 
 static int pad_pow2_p(int rep)
@@ -878,10 +919,12 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
             prefill_split_kernel<128><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
         else
             prefill_split_kernel<64><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
-    } else if (pool->d == 128)
-        prefill_attn_kernel<128><<<grid, 256, 0, c->stream>>>(A);
+    } else if (pool->d == 64)
+        prefill_attn_kernel<64, 3><<<grid, 256, 0, c->stream>>>(A);
+    else if (roomy_pays(grid.x * per_layer * layers, stored * (pool->t / 16) / 2, tiles))
+        prefill_attn_kernel<128, 2><<<grid, 256, 0, c->stream>>>(A);
     else
-        prefill_attn_kernel<64><<<grid, 256, 0, c->stream>>>(A);
+        prefill_attn_kernel<128, 3><<<grid, 256, 0, c->stream>>>(A);
     KVF_HIP(c, hipGetLastError());
     return KVFUSE_OK;
 }

@@ -88,3 +88,17 @@ def test_softmax_scale_of_either_sign(case, signed_scales, sm_scale):
     """Logits times a scale that is not positive: the largest ones are then the smallest products (of either sign, with scales
     of either sign); rows that see nothing of a tile are among them.  Logits stay below those of the test above."""
     _compare(case, True, sm_scale=sm_scale, signed_scales=signed_scales)
+
+
+# Grids of the staged kernel beyond two workgroups per compute unit, head size 128, where its registers are for three wavefronts per
+# SIMD; the last one is on the other side of that line.
+STAGED = [(18, 8, 4, 16, 128, 64, 5, 129),       # 720: a workgroup of one position, six rows of the last piece hidden
+          (21, 8, 1, 32, 128, 0, 0, 513),        # 840: nothing before the chunk, both pieces of the last tile
+          (9, 8, 16, 48, 128, 96, 7, 65),        # 648: three pieces per block, two positions per wavefront
+          (18, 8, 4, 16, 128, 16, 1, 100)]       # 576, most of it the chunk itself
+
+
+@pytest.mark.parametrize("reuse", [True, False])
+@pytest.mark.parametrize("case", STAGED, ids=[str(i) for i in range(len(STAGED))])
+def test_large_grids_against_binary64(case, reuse):
+    _compare(case, reuse)
