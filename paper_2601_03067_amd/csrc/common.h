@@ -78,6 +78,9 @@ struct Q8Desc {
 constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
 constexpr int kPanelCols = 512, kPanelRows = 64, kPanelSlices = 11, kPanelRun = 32, kPanelOpen = 1024;
 
+// Tree calls on tiny groups (tiny.hip): most table entries, stored blocks and tree nodes of a group, bytes of a block, groups.
+constexpr int kTinyEntries = 64, kTinyPool = 128, kTinySlots = 256, kTinyBytes = 4096, kTinyGroups = 512;
+
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Group-strided work arrays of a plan (device).
@@ -119,6 +122,9 @@ struct WorkDesc {
     u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand
     int4 *panel_items;       // (group, node, first column, first row)
     int32_t *panel_total;    // [max_heights]
+    // tree calls on tiny groups (tiny.hip); null where the tree is too large for them
+    int4 *tiny_nodes;        // [nodes][2] (l_off, r_off, l_slot, r_slot), (out_slot, ...), height by height
+    int32_t *tiny_ptr;       // [heights + 1] first node of every height
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
     int4 *dyn_items;     // [G][item_cap of the height] node, first column, first row, rows
     int32_t *dyn_base;   // [G][dyn_stride] first item of every node, and the total
@@ -204,6 +210,9 @@ void launch_prefix_tails(hipStream_t s, const PoolDesc &pool, const WorkDesc &w)
 // fp8 screen: the e4m3 copy and its error for all key blocks, and for the targets the merge step of a height rebuilt
 void launch_quantise_all(hipStream_t s, const PoolDesc &pool, const WorkDesc &w);
 void launch_quantise_targets(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, int height);
+// a whole tree call on tiny groups, in one launch; counters[7] of a group: its merge targets
+void launch_tiny_tree(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const int32_t *slot_init, int n_heights,
+                      double thr, double band, float thr_floor, int32_t *free_list, int32_t *n_free, int32_t *n_phys);
 void launch_rewrite(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int32_t *free_list, int32_t *n_free,
                     int32_t *n_phys);
 size_t decode_workspace_bytes(int n_layers, int B, int Hq, int kv_heads, int d, int max_blocks);
@@ -568,6 +577,49 @@ __device__ __forceinline__ uint32_t f64_to_bf16_fast(double x)
     }
     return (b >> 16) + up;
 }
+
+// 16 bytes of pool data from fp64 values, rounded once, and what they then are.
+template <typename T> struct Store16;
+template <> struct Store16<bf16_t> {
+    // Eight fp64 values -> bfloat16, nearest even straight from fp64.  The common case is branch free: round to
+    // binary32 (nearest even), then to bfloat16 (nearest even); the two roundings agree with the direct one unless
+    // the binary32 value sits exactly on a bfloat16 rounding boundary or is zero / subnormal / non-finite.  Those
+    // cases (a few per million elements) send all eight values through the exact integer routine.
+    __device__ static __forceinline__ uint4 pack(const double *u, double *back)
+    {
+        uint32_t h[8];
+        bool special = false;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t b = __float_as_uint((float)u[i]);
+            const uint32_t ex = (b >> 23) & 0xFFu;
+            special |= ex == 0u || ex == 0xFFu || (b & 0xFFFFu) == 0x8000u;
+            h[i] = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
+        }
+        if (special) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                h[i] = f64_to_bf16_rne(u[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            back[i] = (double)__uint_as_float(h[i] << 16);
+        return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+    }
+};
+template <> struct Store16<float> {
+    __device__ static __forceinline__ uint4 pack(const double *u, double *back)
+    {
+        uint32_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = (float)u[i];   // v_cvt_f32_f64: round to nearest even
+            h[i] = __float_as_uint(f);
+            back[i] = (double)f;
+        }
+        return make_uint4(h[0], h[1], h[2], h[3]);
+    }
+};
 
 #endif // __HIPCC__
 

@@ -69,6 +69,24 @@ struct Plan {
                flops >= (pool.dtype == KVFUSE_BF16 ? kEarlyMinFlops : kEarlyMinFlops / 16);
     }
 
+    // The whole tree call in one launch (tiny.hip): the default rule and product on groups that fit it, where a workgroup's walk
+    // through its group's pairs and norms (us: 8 and 0.02 + r / 28000 each) takes less than the launches it spares (10 and 25 a
+    // height).  Both measured (us, launches / one, with some 13 us of copies in both; requests x blocks, bytes of a block, 1 group): 2 x 4,
+    // 4096 51 / 22; 16 x 2, 2048 87 / 47; 4 x 8, 4096 binary32 68 / 41, bfloat16 75 / 65; 6 x 8, 4096 binary32 96 / 64, bfloat16
+    // 100 / 107 (launches); 4 x 16, 2048 68 / 94 (launches).  More workgroups than the chip holds take turns, while the launches share
+    // their groups out better: 512 groups of 4 x 8, 2048 163 / 101, 1024 243 / 196, 2048 400 / 399, 4096 744 / 793; 1024 of 3 x 12,
+    // 4096 405 / 414.
+    bool tiny_pays() const
+    {
+        if (!work.tiny_nodes || work.G > kTinyGroups || pool.P > kTinyPool || pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) > kTinyBytes ||
+            assign_rule != KVFUSE_RULE_ARGMAX || work.q8.k || work.screen_prefix != 0 || work.group_enable)
+            return false;
+        double pairs = pool.P;
+        for (const HostHeight &h : heights)
+            pairs += (double)h.dev.total_s;
+        return 8.0 + pairs * (0.020 + pool.r / 28000.0) < 0.93 * (10.0 + 25.0 * (double)heights.size());
+    }
+
     // The copies are centred only where that pays and fits: not together with the prefix screen (a block's share of the
     // common direction differs between prefix and tail) and not for blocks whose direction kernel would need more than
     // 64 KiB of LDS.
@@ -294,6 +312,12 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.screen_prefix = 0;
     w.q8 = Q8Desc{};
     slot_init = cv.take<int32_t>(n_slots);
+    w.tiny_nodes = nullptr;
+    w.tiny_ptr = nullptr;
+    if (n <= kTinyEntries && n_slots <= kTinySlots) {
+        w.tiny_nodes = cv.take<int4>(2 * (size_t)n_slots);
+        w.tiny_ptr = cv.take<int32_t>(kMaxHeights + 1);
+    }
     {
         size_t items = 1, nodes = 1;
         for (const HostHeight &h : hs) {
@@ -514,6 +538,20 @@ int kvfuse_plan_create(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_ta
             for (int i = 0; i < nd.cap; ++i)
                 leaf_src[(size_t)nd.off + i] = nd.src + i;
     if (e == hipSuccess) e = upload(c->stream, p.work.leaf_src, leaf_src);
+    std::vector<int4> tiny_nodes;
+    std::vector<int32_t> tiny_ptr;
+    if (p.work.tiny_nodes) {
+        for (const HostHeight &h : p.heights) {
+            tiny_ptr.push_back((int32_t)tiny_nodes.size() / 2);
+            for (size_t k = 0; k < h.l_off.size(); ++k) {
+                tiny_nodes.push_back(make_int4(h.l_off[k], h.r_off[k], h.l_slot[k], h.r_slot[k]));
+                tiny_nodes.push_back(make_int4(h.out_slot[k], 0, 0, 0));
+            }
+        }
+        tiny_ptr.push_back((int32_t)tiny_nodes.size() / 2);
+        if (e == hipSuccess) e = upload(c->stream, p.work.tiny_nodes, tiny_nodes);
+        if (e == hipSuccess) e = upload(c->stream, p.work.tiny_ptr, tiny_ptr);
+    }
     for (HostHeight &h : p.heights) {
         const HeightDesc &d = h.dev;
         if (e == hipSuccess) e = upload(c->stream, d.l_off, h.l_off);
@@ -701,30 +739,35 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         w.pairs = w.active;
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
-    KVF_TRY(mark());
-    launch_centre_direction(c->stream, p.pool, w);                      // no-op unless the fp8 copies are centred
-    launch_tree_entries(c->stream, p.pool, w, p.tab, p.slot_init, nh);
-    if (early)
-        launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
-    launch_tree_norms(c->stream, p.pool, w, p.tab);
-    KVF_TRY(mark());
-    for (int hgt = 0; hgt < nh; ++hgt) {
-        const HeightDesc &d = p.heights[hgt].dev;
-        w.n_pairs = w.n_pairs_all + hgt;
-        w.panel_on = early && panel_fits(p.pool) && d.panel_run > 0 ? w.panel_on_mem : nullptr;
-        if (w.panel_on)
-            launch_similarity_panel(c->stream, p.pool, w, d, hgt > 0 ? p.heights[hgt - 1].dev : HeightDesc{}, hgt, floor_f);
-        launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);
+    const bool tiny = !timing && p.tiny_pays();       // (stages are timed where there are stages)
+    if (tiny) {
+        launch_tiny_tree(c->stream, p.pool, p.tab, w, p.slot_init, nh, thr, band, floor_f, free_list, n_free, n_phys);
+    } else {
+        KVF_TRY(mark());
+        launch_centre_direction(c->stream, p.pool, w);                      // no-op unless the fp8 copies are centred
+        launch_tree_entries(c->stream, p.pool, w, p.tab, p.slot_init, nh);
         if (early)
-            launch_finish_pairs(c->stream, p.pool, w, floor_f);
+            launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
+        launch_tree_norms(c->stream, p.pool, w, p.tab);
         KVF_TRY(mark());
-        launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule, hgt + 1 < nh);
-        KVF_TRY(mark());
-        launch_merge(c->stream, p.pool, w, d, hgt);
+        for (int hgt = 0; hgt < nh; ++hgt) {
+            const HeightDesc &d = p.heights[hgt].dev;
+            w.n_pairs = w.n_pairs_all + hgt;
+            w.panel_on = early && panel_fits(p.pool) && d.panel_run > 0 ? w.panel_on_mem : nullptr;
+            if (w.panel_on)
+                launch_similarity_panel(c->stream, p.pool, w, d, hgt > 0 ? p.heights[hgt - 1].dev : HeightDesc{}, hgt, floor_f);
+            launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);
+            if (early)
+                launch_finish_pairs(c->stream, p.pool, w, floor_f);
+            KVF_TRY(mark());
+            launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule, hgt + 1 < nh);
+            KVF_TRY(mark());
+            launch_merge(c->stream, p.pool, w, d, hgt);
+            KVF_TRY(mark());
+        }
+        launch_rewrite(c->stream, p.pool, p.tab, free_list, n_free, n_phys);
         KVF_TRY(mark());
     }
-    launch_rewrite(c->stream, p.pool, p.tab, free_list, n_free, n_phys);
-    KVF_TRY(mark());
     KVF_TRY(hipGetLastError());
     if (!stats)
         return KVFUSE_OK;
@@ -755,8 +798,10 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
     cleanup();
     evs.clear();
     int64_t targets = 0;
-    for (int hgt = 0; hgt < nh; ++hgt)
+    for (int hgt = 0; hgt < nh && !tiny; ++hgt)
         targets += n_act[hgt];
+    for (int g = 0; g < w.G && tiny; ++g)
+        targets += counters[(size_t)g * 8 + 7];
     stats->merge_targets = (int32_t)std::min<int64_t>(targets, INT32_MAX);
     int64_t invalid = 0, shared = 0, out_of_range = 0;
     for (int g = 0; g < w.G; ++g) {

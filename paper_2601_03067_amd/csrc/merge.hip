@@ -13,48 +13,6 @@
 
 namespace kvfuse {
 
-template <typename T> struct Store16;
-template <> struct Store16<bf16_t> {
-    // Eight fp64 values -> bfloat16, nearest even straight from fp64.  The common case is branch free: round to
-    // binary32 (nearest even), then to bfloat16 (nearest even); the two roundings agree with the direct one unless
-    // the binary32 value sits exactly on a bfloat16 rounding boundary or is zero / subnormal / non-finite.  Those
-    // cases (a few per million elements) send all eight values through the exact integer routine.
-    __device__ static __forceinline__ uint4 pack(const double *u, double *back)
-    {
-        uint32_t h[8];
-        bool special = false;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t b = __float_as_uint((float)u[i]);
-            const uint32_t ex = (b >> 23) & 0xFFu;
-            special |= ex == 0u || ex == 0xFFu || (b & 0xFFFFu) == 0x8000u;
-            h[i] = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
-        }
-        if (special) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                h[i] = f64_to_bf16_rne(u[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            back[i] = (double)__uint_as_float(h[i] << 16);
-        return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-    }
-};
-template <> struct Store16<float> {
-    __device__ static __forceinline__ uint4 pack(const double *u, double *back)
-    {
-        uint32_t h[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float f = (float)u[i];   // v_cvt_f32_f64: round to nearest even
-            h[i] = __float_as_uint(f);
-            back[i] = (double)f;
-        }
-        return make_uint4(h[0], h[1], h[2], h[3]);
-    }
-};
-
 __device__ __forceinline__ int find_base(const int32_t *__restrict__ base, int n_nodes, int idx)
 {
     int lo = 0, hi = n_nodes;

@@ -1,0 +1,395 @@
+// A whole tree call (norms, every height's similarity, assignment and merge, table rewrite) on groups of at most 64 table entries, in
+// one launch of a workgroup per group.
+//
+// Everything of such a call is latency: as separate launches it is some nineteen kernels of 2 to 11 us, each waiting for the one
+// before it.  A group is no one else's business, so one workgroup can take it from end to end: sets, norms, assignments and the
+// remap table live in LDS, blocks come from the L2, and the steps of Algorithm 1 are separated by barriers.  With so few pairs there is
+// nothing to screen: every cosine is taken in binary64, by the operations of the re-check (assign.hip) in their order, and
+// merges and norms are summed in the order of the kernels they stand in for, so tables, blocks and norms are the same bits.
+//
+// What it costs now: 3 us of norms, then each height some 10 us, most of it the rows of a column one after the other, their blocks
+// 1 us from the L2.  4 requests of 8 blocks in binary32, 2 groups: the call 57 -> 29 us, with statistics and the restoring of the
+// blocks between calls 125 -> 73 us.
+#include "common.h"
+
+namespace kvfuse {
+
+// Sixteen wavefronts, or eight where a lane's share of a merge takes more than half of sixteen wavefronts' registers.
+template <typename T, int CPL>
+constexpr int kTinyThreads = CPL * Elem<T>::PER16 > 16 ? 512 : 1024;
+
+struct TinyArgs {
+    PoolDesc pool;
+    TableDesc tab;
+    WorkDesc w;
+    const int32_t *slot_init;
+    int32_t n_heights;
+    double thr, band;
+    float thr_floor;
+    int32_t *free_list, *n_free, *n_phys;
+};
+
+// (The orders of summation below are those of block_norms_kernel, cosines_f64_reg and merge_group_kernel.)
+template <typename T, int CPL>
+__global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyArgs A)
+{
+    constexpr int PER = Elem<T>::PER16, KW = CPL * PER == 16 ? 2 : 4;
+    constexpr int NT = kTinyThreads<T, CPL>, NW = NT / 64;
+    constexpr bool PAIR = PER == 4 && CPL == 4;      // a merge that merge_group_kernel gives to two wavefronts: two partial sums
+    __shared__ double nk[kTinyPool], nv[kTinyPool];
+    __shared__ int32_t refs[kTinyPool], remap[kTinyPool];
+    __shared__ int32_t bt[kTinyEntries], ids[kTinyEntries], was[kTinyEntries], assign[kTinyEntries];
+    __shared__ unsigned long long tgt_mask[kTinyEntries];      // merges of a height: members (bits of the right set) of a target ...
+    __shared__ int32_t tgt[kTinyEntries], tgt_right[kTinyEntries];      // ... its place in ids, and the right set's
+    __shared__ int32_t cnt[kTinySlots], counters[8], n_tgt;
+
+    const PoolDesc &pool = A.pool;
+    const TableDesc &tab = A.tab;
+    const WorkDesc &w = A.w;
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = w.n, P = pool.P, chunks = pool.r / PER;
+    const int64_t gp = (int64_t)g * P, gn = (int64_t)g * n;
+    T *const kp = (T *)pool.k + gp * pool.r, *const vp = (T *)pool.v + gp * pool.r;
+    auto chunk_of = [&](int c) __attribute__((always_inline)) { return min(lane + 64 * c, chunks - 1); };
+    auto in_block = [&](int c) __attribute__((always_inline)) { return lane + 64 * c < chunks; };
+    auto rows = [&](const T *pool_g, int b) __attribute__((always_inline)) { return reinterpret_cast<const uint4 *>(pool_g + (int64_t)b * pool.r); };
+
+    // ---- the table: references, leaf sets, caller errors (tree_entries_kernel)
+    for (int p = tid; p < P; p += NT) {
+        refs[p] = 0;
+        remap[p] = -1;
+    }
+    for (int s = tid; s < w.n_slots; s += NT)
+        cnt[s] = A.slot_init[s];
+    if (tid < 8)
+        counters[tid] = 0;
+    if (tid == 0)
+        n_tgt = 0;
+    __syncthreads();
+    if (tid < n) {
+        const int p = tab.bt[gn + tid], src = w.leaf_src[tid];
+        bt[tid] = p;
+        if (p < 0 || p >= P) {
+            atomicAdd(&counters[4], 1);
+        } else {
+            const int before = atomicAdd(&refs[p], 1);
+            if (before > 0)
+                atomicAdd(&counters[5], before == 1 ? 2 : 1);
+        }
+        const int q = src >= 0 ? tab.bt[gn + src] : 0;
+        ids[tid] = min(max(q, 0), P - 1);
+    }
+
+    // ---- norms of all stored blocks, a wavefront per block
+    for (int b = wave; b < 2 * P; b += NW) {
+        const bool is_v = b >= P;
+        const int p = is_v ? b - P : b;
+        const uint4 *src = rows(is_v ? vp : kp, p);
+        uint4 raw[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+            raw[c] = src[chunk_of(c)];
+        double ss = 0.0;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            double x[PER];
+            Elem<T>::widen(raw[c], x);
+            if (in_block(c))
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    ss = fma(x[i], x[i], ss);
+        }
+        const double nrm = sqrt(wave_sum(ss));
+        if (lane == 0) {
+            (is_v ? nv : nk)[p] = nrm;
+            (is_v ? pool.norm_v : pool.norm_k)[gp + p] = nrm;
+            if (!is_v)
+                pool.inv_norm_k[gp + p] = nrm > 0.0 ? (float)(1.0 / nrm) : 0.0f;
+        }
+    }
+    __syncthreads();
+    double orig_k = 0.0, orig_v = 0.0;
+    if (tid < n) {
+        const int p = bt[tid];
+        const bool ok = p >= 0 && p < P;
+        orig_k = ok ? nk[p] : 0.0;
+        orig_v = ok ? nv[p] : 0.0;
+        tab.orig_norm_k[gn + tid] = orig_k;
+        tab.orig_norm_v[gn + tid] = orig_v;
+        if (orig_k != 0.0 && !(orig_k >= 0x1p-40 && orig_k <= 0x1p40))
+            atomicAdd(&counters[6], 1);
+    }
+
+    for (int hgt = 0; hgt < A.n_heights; ++hgt) {
+        const int n0 = w.tiny_ptr[hgt], n1 = w.tiny_ptr[hgt + 1];
+        // ---- similarity and assignment, a wavefront per right block
+        for (int k = n0, j = wave; k < n1; ++k) {
+            const int4 nd = w.tiny_nodes[2 * k];            // left and right offset, left and right slot
+            const int ml = cnt[nd.z], mr = cnt[nd.w];
+            for (; j < mr; j += NW) {
+                const int b = __builtin_amdgcn_readfirstlane(ids[nd.y + j]);
+                const double nb = nk[b];
+                uint4 braw[CPL];
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+                    braw[c] = rows(kp, b)[chunk_of(c)];
+                double bv = -INFINITY, mine = -INFINITY;     // the largest cosine, its row; the cosine of row `lane`
+                int bi = -1;
+                for (int i0 = 0; i0 < ml; i0 += KW) {
+                    int a[KW];
+                    uint4 araw[KW][CPL];
+#pragma unroll
+                    for (int q = 0; q < KW; ++q) {
+                        a[q] = __builtin_amdgcn_readfirstlane(ids[nd.x + min(i0 + q, ml - 1)]);
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c)
+                            araw[q][c] = rows(kp, a[q])[chunk_of(c)];
+                    }
+                    double dot[KW];
+#pragma unroll
+                    for (int q = 0; q < KW; ++q)
+                        dot[q] = 0.0;
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        if (in_block(c)) {
+                            double y[PER];
+                            Elem<T>::widen(braw[c], y);
+#pragma unroll
+                            for (int q = 0; q < KW; ++q) {
+                                double x[PER];
+                                Elem<T>::widen(araw[q][c], x);
+#pragma unroll
+                                for (int i = 0; i < PER; ++i)
+                                    dot[q] = fma(x[i], y[i], dot[q]);
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < KW; ++q) {
+                        const double na = nk[a[q]], d = wave_sum(dot[q]);
+                        const double cs = na == 0.0 || nb == 0.0 ? 0.0 : d / (na * nb);
+                        if (i0 + q < ml) {
+                            mine = lane == i0 + q ? cs : mine;
+                            if (cs > bv) {                   // ascending rows: the lowest of equal ones
+                                bv = cs;
+                                bi = i0 + q;
+                            }
+                        }
+                    }
+                }
+                // what the screen in binary32 would have sent to the re-check: counted, as there
+                const float val = (float)mine;
+                const bool listed = lane < ml && val > A.thr_floor;
+                float top = listed ? val : -INFINITY;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1)
+                    top = fmaxf(top, __shfl_xor(top, off, 64));
+                const int n_listed = __popcll(__ballot(listed));
+                const int contenders = __popcll(__ballot(listed && (double)val >= (double)top - 2.0 * A.band));
+                if (lane == 0) {
+                    assign[nd.y + j] = bv > A.thr ? bi : -1;
+                    if (n_listed > w.cand_cap || (n_listed > 0 && !(contenders == 1 && (double)top > A.thr + 2.0 * A.band))) {
+                        atomicAdd(&counters[2], 1);
+                        if (fabs(bv - A.thr) <= A.band)
+                            atomicAdd(&counters[1], 1);
+                        if (n_listed > w.cand_cap)
+                            atomicAdd(&counters[3], 1);
+                    }
+                }
+            }
+            j -= mr;
+        }
+        __syncthreads();
+        // ---- targets and their members, evicted blocks, surviving sets: a wavefront per node, a lane per block
+        for (int k = n0 + wave; k < n1; k += NW) {
+            const int4 nd = w.tiny_nodes[2 * k];
+            const int out_slot = w.tiny_nodes[2 * k + 1].x;
+            const int ml = cnt[nd.z], mr = cnt[nd.w];
+            int id = -1, a = -1;
+            if (lane < mr) {
+                id = ids[nd.y + lane];
+                a = assign[nd.y + lane];
+                was[nd.y + lane] = id;
+            }
+            unsigned long long members = 0;
+            for (int i = 0; i < ml; ++i) {
+                const unsigned long long m = __ballot(a == i);
+                members = lane == i ? m : members;
+            }
+            const unsigned long long targets = __ballot(members != 0), kept = __ballot(lane < mr && a < 0);
+            const unsigned long long below = (1ull << lane) - 1ull;
+            int base = 0;
+            if (lane == 0 && targets)
+                base = atomicAdd(&n_tgt, __popcll(targets));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (members) {
+                const int s = base + __popcll(targets & below);
+                tgt[s] = nd.x + lane;
+                tgt_right[s] = nd.y;
+                tgt_mask[s] = members;
+            }
+            if (a >= 0)
+                remap[id] = ids[nd.x + a];
+            __builtin_amdgcn_wave_barrier();
+            if (lane < mr && a < 0)
+                ids[nd.x + ml + __popcll(kept & below)] = id;
+            if (lane == 0) {
+                cnt[out_slot] = ml + __popcll(kept);
+                atomicAdd(&counters[0], mr - __popcll(kept));
+                atomicAdd(&counters[7], __popcll(targets));
+            }
+        }
+        __syncthreads();
+        // ---- merge, a wavefront per target and tensor
+        const int items = 2 * n_tgt;
+        for (int it = wave; it < items; it += NW) {
+            const int t = it >> 1;
+            const bool is_v = it & 1;
+            T *const pool_g = is_v ? vp : kp;
+            const double *norm = is_v ? nv : nk;
+            const int a = __builtin_amdgcn_readfirstlane(ids[tgt[t]]);
+            double acc[CPL][PER];
+            {
+                const double na = norm[a], ia = na == 0.0 ? 0.0 : 1.0 / na;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    Elem<T>::widen(rows(pool_g, a)[chunk_of(c)], acc[c]);
+#pragma unroll
+                    for (int e = 0; e < PER; ++e)
+                        acc[c][e] = in_block(c) ? acc[c][e] * ia : 0.0;
+                }
+            }
+            for (unsigned long long m = tgt_mask[t]; m; m &= m - 1) {
+                const int b = __builtin_amdgcn_readfirstlane(was[tgt_right[t] + __builtin_ctzll(m)]);
+                const double nb = norm[b], ib = nb == 0.0 ? 0.0 : 1.0 / nb;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    double y[PER];
+                    Elem<T>::widen(rows(pool_g, b)[chunk_of(c)], y);
+#pragma unroll
+                    for (int e = 0; e < PER; ++e)
+                        acc[c][e] = in_block(c) ? fma(y[e], ib, acc[c][e]) : 0.0;
+                }
+            }
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    double &s = PAIR && (c & 1) ? s1 : s0;
+                    s = fma(acc[c][e], acc[c][e], s);
+                }
+            const double len = sqrt(PAIR ? wave_sum(s0) + wave_sum(s1) : wave_sum(s0));
+            const double il = len == 0.0 ? 0.0 : 1.0 / len;
+            uint4 *dst = reinterpret_cast<uint4 *>(pool_g + (int64_t)a * pool.r);
+            s0 = s1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                double u[PER], back[PER];
+#pragma unroll
+                for (int e = 0; e < PER; ++e)
+                    u[e] = acc[c][e] * il;
+                const uint4 packed = Store16<T>::pack(u, back);
+                if (in_block(c)) {
+                    dst[lane + 64 * c] = packed;
+#pragma unroll
+                    for (int e = 0; e < PER; ++e) {
+                        double &s = PAIR && (c & 1) ? s1 : s0;
+                        s = fma(back[e], back[e], s);
+                    }
+                }
+            }
+            const double nrm = sqrt(PAIR ? wave_sum(s0) + wave_sum(s1) : wave_sum(s0));
+            if (lane == 0) {                  // (nobody else reads this block or its norm before the barrier)
+                (is_v ? nv : nk)[a] = nrm;
+                (is_v ? pool.norm_v : pool.norm_k)[gp + a] = nrm;
+                if (!is_v)
+                    pool.inv_norm_k[gp + a] = nrm > 0.0 ? (float)(1.0 / nrm) : 0.0f;
+            }
+        }
+        __syncthreads();
+        if (tid == 0)
+            n_tgt = 0;
+        // (the next height's first atomics on it are behind the barrier after its assignments)
+    }
+
+    // ---- rewrite
+    for (int p = tid; p < P; p += NT)
+        refs[p] = 0;
+    __syncthreads();
+    int p = -1;
+    if (tid < n) {
+        p = bt[tid];
+        if (p < 0 || p >= P) {
+            p = -1;
+        } else {
+            for (int hop = 0; hop < 64; ++hop) {
+                const int q = remap[p];
+                if (q < 0 || q >= P || q == p)
+                    break;
+                p = q;
+            }
+            tab.bt[gn + tid] = p;
+            atomicAdd(&refs[p], 1);
+        }
+    }
+    __syncthreads();
+    if (tid < n) {
+        float sk = 0.0f, sv = 0.0f;
+        if (p >= 0) {
+            const double mk = nk[p], mv = nv[p];
+            const bool own = refs[p] <= 1;
+            sk = own ? 1.0f : mk == 0.0 ? 0.0f : (float)(orig_k / mk);
+            sv = own ? 1.0f : mv == 0.0 ? 0.0f : (float)(orig_v / mv);
+        }
+        tab.scale_k[gn + tid] = sk;
+        tab.scale_v[gn + tid] = sv;
+    }
+    for (int q = tid; q < P; q += NT) {
+        tab.refcount[gp + q] = refs[q];
+        tab.remap[gp + q] = remap[q];
+    }
+    for (int s = tid; s < w.n_slots; s += NT)
+        w.set_cnt[(int64_t)g * w.n_slots + s] = cnt[s];
+    if (tid < 8)
+        w.counters[(int64_t)g * 8 + tid] = counters[tid];
+    if (wave == 0) {
+        int freed = 0, live = 0;
+        for (int q0 = 0; q0 < P; q0 += 64) {
+            const int q = q0 + lane;
+            const bool is_free = q < P && remap[q] >= 0;
+            const unsigned long long m = __ballot(is_free);
+            if (is_free && A.free_list)
+                A.free_list[gp + freed + __popcll(m & ((1ull << lane) - 1ull))] = q;
+            freed += __popcll(m);
+            live += __popcll(__ballot(q < P && refs[q] > 0));
+        }
+        if (lane == 0) {
+            if (A.n_free)
+                A.n_free[g] = freed;
+            if (A.n_phys)
+                A.n_phys[g] = live;
+        }
+    }
+}
+
+void launch_tiny_tree(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const int32_t *slot_init, int n_heights,
+                      double thr, double band, float thr_floor, int32_t *free_list, int32_t *n_free, int32_t *n_phys)
+{
+    const TinyArgs A{pool, tab, w, slot_init, n_heights, thr, band, thr_floor, free_list, n_free, n_phys};
+    const int cpl = (pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 16 + 63) / 64;
+#define KVF_TINY(T)                                                               \
+    do {                                                                          \
+        if (cpl <= 1) tiny_tree_kernel<T, 1><<<pool.G, kTinyThreads<T, 1>, 0, s>>>(A);      \
+        else if (cpl <= 2) tiny_tree_kernel<T, 2><<<pool.G, kTinyThreads<T, 2>, 0, s>>>(A); \
+        else tiny_tree_kernel<T, 4><<<pool.G, kTinyThreads<T, 4>, 0, s>>>(A);               \
+    } while (0)
+    if (pool.dtype == KVFUSE_BF16)
+        KVF_TINY(bf16_t);
+    else
+        KVF_TINY(float);
+#undef KVF_TINY
+}
+
+}  // namespace kvfuse
