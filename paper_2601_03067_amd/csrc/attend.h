@@ -1,5 +1,9 @@
 // What the paged and the shared-block decode kernels share.  One step of decode attention over bfloat16 blocks: 32 tokens (two
-// 16-token pieces) against 16 query rows, both products on the matrix cores and no LDS.
+// 16-token pieces) against 16 query rows, both products on the matrix cores.
+//   loads   every load of a wavefront covers rows end to end.  The keys' fragments (16 rows, 16 bytes out of each quarter) would take
+//           four times as many cache lines per load, and the vector cache's turns over them were what bounded blocks that come out
+//           of the caches; a turn through LDS puts them in place (us, without / with: 8 heads per KV head, 256 x 4096 tokens,
+//           16 groups 720 / 561; 48 ragged requests, 8 groups 153 / 141; shared blocks, 64 x 2048 tokens, 64 groups 254 / 238).
 //   logits  two 16 tokens x 16 rows groups: lane (row = lane & 15, kg = lane >> 4) ends up with the tokens 4 kg .. + 3 of
 //           both pieces, which are the 8 summation indices of the same lane in the second product.
 //   P.V     out^T (16 head elements x 16 rows) += V^T P^T, once per column c of the lane's slice: lane (n = lane & 15, kg)
@@ -59,6 +63,33 @@ struct Attend32 {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             o[c] = attend_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // A lane's part of a piece of keys, as it is loaded: 16 bytes each of rows 64 / CH apart, CH lanes to a row, end to end.
+    static constexpr int CH = D / 8, K_STEP = 512;      // elements from one of its loads to the next
+    static __device__ __forceinline__ int k_source(int lane) { return lane * 8; }
+
+    // ... and turned by way of LDS (the wavefront's own K_LDS bytes) into the fragments that the product takes: token lane & 15, the
+    // quarter kg of its row.  Rows are 16 bytes further apart than they are long, so that neither side meets in a bank.
+    static constexpr int K_PITCH = 2 * D + 16, K_LDS = 32 * K_PITCH;
+    static __device__ __forceinline__ void turn(char *mem, int lane, uint4 (&k0)[NF], uint4 (&k1)[NF])
+    {
+        char *to = mem + lane / CH * K_PITCH + lane % CH * 16;
+        const char *from = mem + (lane & 15) * K_PITCH + (lane >> 4) * (D / 2);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            *reinterpret_cast<uint4 *>(to + f * (64 / CH) * K_PITCH) = k0[f];
+            *reinterpret_cast<uint4 *>(to + (f * (64 / CH) + 16) * K_PITCH) = k1[f];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            k0[f] = *reinterpret_cast<const uint4 *>(from + f * 16);
+            k1[f] = *reinterpret_cast<const uint4 *>(from + 16 * K_PITCH + f * 16);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 
     // k0, k1: K fragments of the two pieces; vr: V rows, [4 piece + i] = token 4 kg + i.  Tokens 4 kg + i with i < left are

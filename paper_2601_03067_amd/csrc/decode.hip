@@ -265,9 +265,9 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
 // Error against binary64, relative in the 2-norm, this kernel / the vector-ALU kernel it replaced: 1.55e-7 / 1.77e-7 (one
 // request of 1000 tokens, d = 128), 1.91e-7 / 2.41e-7 (48 ragged requests), 1.64e-7 / 2.29e-7 (256 requests of 4096 tokens).
 //
-// Bound: HBM for blocks read once (64 x 2048 tokens, 64 groups: 5.35 TB/s of distinct bytes, 541 -> 505 us); blocks that many
-// requests share come out of the caches, where the vector ALU was the limit (8 heads per KV head, 256 x 4096 tokens, 16
-// groups: 893 -> 716 us, 12 TB/s of rows read).  Three wavefronts per SIMD hold 16 KiB each in flight.
+// Bound: HBM for blocks read once (64 x 2048 tokens, 64 groups: 5.6 TB/s of distinct bytes, 541 -> 480 us); blocks that many
+// requests share come out of the caches, where first the vector ALU and then the keys' loads were the limit (8 heads per KV head,
+// 256 x 4096 tokens, 16 groups: 893 -> 561 us, 15 TB/s of rows read).  Three wavefronts per SIMD hold 16 KiB each in flight.
 // NW: wavefronts of a workgroup, as many as the longest split has steps of 32 tokens, up to four: idle ones would keep others off
 // the chip (512 requests, 64 groups, four / NW wavefronts: 16 tokens, one head 158 / 56 us, four 175 / 69; 64 tokens 214 / 197
 // and 234 / 211).  The pieces fall to the same wavefronts whatever NW.
@@ -277,7 +277,10 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
     constexpr int NF = Attend32<D>::NF, NC = Attend32<D>::NC;
     typedef typename Attend32<D>::vrow_t vrow_t;
 
-    extern __shared__ __attribute__((aligned(16))) float w_o[];      // [wave][rep_pad][D]
+    // a wavefront's keys on their way to fragments; at the end its sums, [rep_pad][D]
+    constexpr int KEYS = Attend32<D>::K_LDS;
+    static_assert(KEYS >= 16 * D * (int)sizeof(float), "sums of a wavefront fit where its keys were");
+    __shared__ __attribute__((aligned(16))) char keys[NW][KEYS];
     __shared__ float w_m[NW][16], w_l[NW][16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
     const float *svg = A.scale_v + (int64_t)g * A.n;
 
     const int head = lane & 15, kg = lane >> 4;                         // also: token of a K row / column slice of a V row
-    const int k_off = head * D + kg * (D / 4);
+    const int k_off = head * D + kg * (D / 4), k_src = Attend32<D>::k_source(lane);
     const int v_off = 4 * kg * D + head * NC;
 
     uint4 qf[NF];
@@ -349,8 +352,8 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
         vrow_t vr[8];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            k0[f] = reinterpret_cast<const uint4 *>(kg_ + off0 + k_off)[f];
-            k1[f] = reinterpret_cast<const uint4 *>(kg_ + off1 + k_off)[f];
+            k0[f] = *reinterpret_cast<const uint4 *>(kg_ + off0 + k_src + f * Attend32<D>::K_STEP);
+            k1[f] = *reinterpret_cast<const uint4 *>(kg_ + off1 + k_src + f * Attend32<D>::K_STEP);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -361,6 +364,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
         }
         __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
         const int left0 = ctx - 16 * p - 4 * kg;
+        Attend32<D>::turn(keys[wave], lane, k0, k1);
         st.step(qf, k0, k1, vr, s0, s1, two && 16 * (p + 2) <= ctx, left0, two ? left0 - 16 : 0);
     }
 
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
 
     // ---- publish the wavefront's state, merge them
     if (head < A.rep)
-        st.store(w_o + ((int64_t)wave * A.rep_pad + head) * D, kg);
+        st.store(reinterpret_cast<float *>(keys[wave]) + head * D, kg);
     if (kg == 0) {
         w_m[wave][head] = st.m;
         w_l[wave][head] = st.l;
@@ -417,7 +421,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
         for (int wv = 0; wv < NW; ++wv) {
             const float f = w_m[wv][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(w_m[wv][h] - M);
             L += w_l[wv][h] * f;
-            O += w_o[(wv * A.rep_pad + h) * D + e] * f;
+            O += reinterpret_cast<const float *>(keys[wv])[h * D + e] * f;
         }
         if (A.nsplit == 1) {
             A.out[(((int64_t)li * A.B + b) * A.Hq + (int64_t)kvh * A.rep + h) * D + e] = L > 0.0f ? O / L : 0.0f;
@@ -542,14 +546,13 @@ static void launch_decode_t(hipStream_t s, const DecodeArgs &A, int n_layers)
     const bool mma = bf16 && !ah;
     if constexpr (bf16)
         if (mma) {
-            const size_t wave_lds = (size_t)A.rep_pad * D * sizeof(float);
             const int64_t pieces = (int64_t)A.blocks_per_split * (A.t / 16);          // of the longest split
             if (pieces <= 2)
-                decode_bf16_kernel<D, 1><<<grid, 64, wave_lds, s>>>(A);
+                decode_bf16_kernel<D, 1><<<grid, 64, 0, s>>>(A);
             else if (pieces <= 4)
-                decode_bf16_kernel<D, 2><<<grid, 128, 2 * wave_lds, s>>>(A);
+                decode_bf16_kernel<D, 2><<<grid, 128, 0, s>>>(A);
             else
-                decode_bf16_kernel<D, 4><<<grid, 256, 4 * wave_lds, s>>>(A);
+                decode_bf16_kernel<D, 4><<<grid, 256, 0, s>>>(A);
         }
 #define KVF_DEC(R)                                                         \
     do {                                                                   \

@@ -290,7 +290,10 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArg
     typedef typename Attend32<D>::vrow_t vrow_t;
 
     __shared__ float w_m[NW][16], w_l[NW][16];
-    __shared__ __attribute__((aligned(16))) float w_o[NW][16][D];
+    // a wavefront's keys on their way to fragments; at the end its sums, [16][D]
+    constexpr int KEYS = Attend32<D>::K_LDS;
+    static_assert(KEYS >= 16 * D * (int)sizeof(float), "sums of a wavefront fit where its keys were");
+    __shared__ __attribute__((aligned(16))) char keys[NW][KEYS];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArg
     const bool row_used = rs_raw < nreq && hh < A.rep;
     const int rs = row_used ? rs_raw : 0;
     const int my_req = rs == 0 ? item.req[0] : (rs == 1 ? item.req[1] : (rs == 2 ? item.req[2] : item.req[3]));
-    const int k_off = head * D + kg * (D / 4), v_off = 4 * kg * D + head * NC;
+    const int k_src = Attend32<D>::k_source(lane), v_off = 4 * kg * D + head * NC;
 
     uint4 qf[NF];
     {
@@ -353,8 +356,8 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArg
         vrow_t vr[8];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            k0[f] = reinterpret_cast<const uint4 *>(kgrp + off0 + k_off)[f];
-            k1[f] = reinterpret_cast<const uint4 *>(kgrp + off1 + k_off)[f];
+            k0[f] = *reinterpret_cast<const uint4 *>(kgrp + off0 + k_src + f * Attend32<D>::K_STEP);
+            k1[f] = *reinterpret_cast<const uint4 *>(kgrp + off1 + k_src + f * Attend32<D>::K_STEP);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -365,11 +368,12 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArg
         }
         __builtin_amdgcn_sched_barrier(0);                          // all loads of the step are on their way before the first wait
         const AttendScale s0(base, ska, sva), s1(base, skb, svb);
+        Attend32<D>::turn(keys[wave], lane, k0, k1);
         st.step(qf, k0, k1, vr, s0, s1, left0 >= 16 && left1 >= 16, left0 - 4 * kg, left1 - 4 * kg);
     }
 
     if (row_used)
-        st.store(w_o[wave][head], kg);
+        st.store(reinterpret_cast<float *>(keys[wave]) + head * D, kg);
     if (kg == 0) {
         w_m[wave][head] = st.m;
         w_l[wave][head] = st.l;
@@ -390,7 +394,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_items_bf16_kernel(SharedArg
         for (int wv = 0; wv < NW; ++wv) {
             const float f = w_m[wv][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(w_m[wv][h] - M);
             L += w_l[wv][h] * f;
-            O += w_o[wv][h][e] * f;
+            O += reinterpret_cast<const float *>(keys[wv])[h * D + e] * f;
         }
         const int slot = hs == 0 ? item.slot[0] : (hs == 1 ? item.slot[1] : (hs == 2 ? item.slot[2] : item.slot[3]));
         float *pp = A.part + ((int64_t)slot * A.rep_pad + hq) * (D + 2);
