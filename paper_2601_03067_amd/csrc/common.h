@@ -582,29 +582,30 @@ __device__ __forceinline__ uint32_t f64_to_bf16_fast(double x)
 template <typename T> struct Store16;
 template <> struct Store16<bf16_t> {
     // Eight fp64 values -> bfloat16, nearest even straight from fp64.  The common case is branch free: round to
-    // binary32 (nearest even), then to bfloat16 (nearest even); the two roundings agree with the direct one unless
+    // binary32 (nearest even), then, two at a time, to bfloat16 (nearest even); the two roundings agree with the direct one unless
     // the binary32 value sits exactly on a bfloat16 rounding boundary or is zero / subnormal / non-finite.  Those
     // cases (a few per million elements) send all eight values through the exact integer routine.
     __device__ static __forceinline__ uint4 pack(const double *u, double *back)
     {
-        uint32_t h[8];
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        uint32_t w[4];
         bool special = false;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t b = __float_as_uint((float)u[i]);
-            const uint32_t ex = (b >> 23) & 0xFFu;
-            special |= ex == 0u || ex == 0xFFu || (b & 0xFFFFu) == 0x8000u;
-            h[i] = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
+        for (int i = 0; i < 4; ++i) {
+            const f32x2 f = {(float)u[2 * i], (float)u[2 * i + 1]};
+            special |= !__builtin_isnormal(f[0]) || (uint16_t)__float_as_uint(f[0]) == 0x8000u;
+            special |= !__builtin_isnormal(f[1]) || (uint16_t)__float_as_uint(f[1]) == 0x8000u;
+            w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));      // one instruction, nearest even
         }
         if (special) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                h[i] = f64_to_bf16_rne(u[i]);
+            for (int i = 0; i < 4; ++i)
+                w[i] = f64_to_bf16_rne(u[2 * i]) | f64_to_bf16_rne(u[2 * i + 1]) << 16;
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            back[i] = (double)__uint_as_float(h[i] << 16);
-        return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+        const uint4 out = make_uint4(w[0], w[1], w[2], w[3]);
+        Elem<bf16_t>::widen(out, back);
+        return out;
     }
 };
 template <> struct Store16<float> {

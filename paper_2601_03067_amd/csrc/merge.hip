@@ -9,6 +9,12 @@
 // Blocks too long for two wavefronts' registers take the workgroup-per-target kernel.
 // Unit vectors are formed by multiplying with the fp64 reciprocal of the norm (within one fp64 ulp of a
 // division); the result is rounded once, from fp64, to the pool dtype.
+//
+// What bounds it: memory, 5.1 TB/s of reads and writes of scattered 4 and 8 KiB blocks, once the vector ALU has less than half of the
+// cycles (61 - 73 % before: a conversion in integer steps, masks for blocks that end within a lane's pieces, a second member that was
+// not there; and members past the second one after the other, each behind its place and its norm).  All heights of a call (ms, before /
+// now): 256 requests of 128 popular blocks of 8 KiB, 16 groups 4.04 / 3.60; 2048 blocks, 256 groups, with fp8 copies 1.53 / 1.20; 64
+// requests of 128 blocks, 256 groups, one or two members each 4.71 / 4.66.
 #include "common.h"
 
 namespace kvfuse {
@@ -26,6 +32,8 @@ __device__ __forceinline__ int find_base(const int32_t *__restrict__ base, int n
     return lo;
 }
 
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+
 // GW wavefronts per (target, tensor) item, 4 / GW items per workgroup; CPT = 16-byte chunks per thread.  With GW = 1
 // there are no barriers at all; with GW = 2 each thread holds half as much and more items are in flight per CU.
 // Q8 (fp8 screen on): the rebuilt key block's one-byte copy and its error are written here as well, from the rounded
@@ -39,34 +47,27 @@ __global__ __launch_bounds__(256, 3) void merge_group_kernel(PoolDesc pool, Work
     __shared__ double red[GPW][GW];
     const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / GT);     // wave-uniform
     const int tg = threadIdx.x % GT;
-    const int wv = tg >> 6;
+    const int wv = tg >> 6, lane = threadIdx.x & 63;
     const int chunks = pool.r / PER;
     const int n_items = 2 * w.n_active[height];
     const int stride = gridDim.x * GPW;
     const int n_iter = (n_items + stride - 1) / stride;      // same for every thread of the workgroup (barriers below)
     // the record of the next item is fetched while the current one is being worked on
-    int4 nrec0 = make_int4(0, 0, 0, 0), nrec1 = make_int4(0, 0, 0, 0);
-    {
-        const int it = blockIdx.x * GPW + grp;
-        if (it < n_items) {
-            nrec0 = w.active[2 * (int64_t)(it >> 1)];
-            nrec1 = w.active[2 * (int64_t)(it >> 1) + 1];
-        }
-    }
+    // (an item belongs to whole wavefronts: by scalar loads, which leave their registers to the blocks)
+    const __attribute__((address_space(4))) i32x8 *recs = (const __attribute__((address_space(4))) i32x8 *)(uintptr_t)w.active;
+    i32x8 nrec = {0, 0, 0, 0, 0, 0, 0, 0};
+    if ((int)blockIdx.x * GPW + grp < n_items)
+        nrec = recs[(blockIdx.x * GPW + grp) >> 1];
     for (int k = 0; k < n_iter; ++k) {
         const int it = k * stride + blockIdx.x * GPW + grp;
         const bool live = it < n_items;
         const int kv = it & 1;
-        // an item belongs to whole wavefronts, so its record is the same in every lane: keep it in scalar registers
-        const int g = __builtin_amdgcn_readfirstlane(nrec0.x);
-        const int a = __builtin_amdgcn_readfirstlane(nrec0.y);
-        const int cnt = live ? __builtin_amdgcn_readfirstlane(nrec0.z) : 0;
-        const int32_t *members = w.seg_members + __builtin_amdgcn_readfirstlane(nrec0.w);
-        const int m1 = __builtin_amdgcn_readfirstlane(nrec1.x), m2 = __builtin_amdgcn_readfirstlane(nrec1.y);
+        const int g = nrec[0], a = nrec[1], cnt = live ? nrec[2] : 0, m1 = nrec[4], m2 = nrec[5];
+        const int32_t *members = w.seg_members + nrec[3];
         T *pool_g = (T *)(kv ? pool.v : pool.k) + (int64_t)g * pool.P * pool.r;
         double *norm_g = (kv ? pool.norm_v : pool.norm_k) + (int64_t)g * pool.P;
 
-        // the target and the first two members are fetched together; further members (rare) follow one by one.
+        // the target and the first two members are fetched together; further members follow, two on their way at a time.
         // Loads are unconditional (a lane past the end of the block re-reads its last chunk, an item past the end of
         // the list reads block 0) and the surplus is masked afterwards: no divergent control flow around memory.
         const int b1 = cnt > 0 ? m1 : a;
@@ -85,40 +86,67 @@ __global__ __launch_bounds__(256, 3) void merge_group_kernel(PoolDesc pool, Work
         const double na = norm_g[a], n1 = norm_g[b1], n2 = norm_g[b2];
         {
             const int nit = it + stride;
-            if (nit < n_items) {
-                nrec0 = w.active[2 * (int64_t)(nit >> 1)];
-                nrec1 = w.active[2 * (int64_t)(nit >> 1) + 1];
-            }
+            if (nit < n_items)
+                nrec = recs[nit >> 1];
         }
         const double ia = na == 0.0 ? 0.0 : 1.0 / na;
         const double i1 = (cnt > 0 && n1 != 0.0) ? 1.0 / n1 : 0.0;
         const double i2 = (cnt > 1 && n2 != 0.0) ? 1.0 / n2 : 0.0;
         double acc[CPT][PER];
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            double ya[PER], y1[PER], y2[PER];
-            Elem<T>::widen(xa[c], ya);
-            Elem<T>::widen(x1[c], y1);
-            Elem<T>::widen(x2[c], y2);
-            const bool in = live && tg + GT * c < chunks;
-#pragma unroll
-            for (int e = 0; e < PER; ++e)
-                acc[c][e] = in ? fma(y2[e], i2, fma(y1[e], i1, ya[e] * ia)) : 0.0;
-        }
-        for (int m = 2; m < cnt; ++m) {
-            const int b = members[m];
-            const double nb = norm_g[b];
-            const double ib = nb == 0.0 ? 0.0 : 1.0 / nb;
-            const uint4 *sb = reinterpret_cast<const uint4 *>(pool_g + (int64_t)b * pool.r);
+        auto add = [&](const uint4 (&x)[CPT], double ib) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const int ch = tg + GT * c;
                 double y[PER];
-                Elem<T>::widen(ch < chunks ? sb[ch] : make_uint4(0, 0, 0, 0), y);
+                Elem<T>::widen(x[c], y);
 #pragma unroll
                 for (int e = 0; e < PER; ++e)
                     acc[c][e] = fma(y[e], ib, acc[c][e]);
             }
+        };
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            Elem<T>::widen(xa[c], acc[c]);
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                acc[c][e] *= ia;
+        }
+        add(x1, i1);
+        if (cnt > 1)
+            add(x2, i2);
+        for (int m0 = 2; m0 < cnt; m0 += 64) {
+            const int n = min(cnt - m0, 64);
+            const int mine = members[m0 + min(lane, n - 1)];      // a lane each: all places and norms in two round trips
+            const double nm = norm_g[mine];
+            const double im = nm == 0.0 ? 0.0 : 1.0 / nm;
+            auto fetch = [&](uint4 (&x)[CPT], int m) __attribute__((always_inline)) {
+                const uint4 *sb = reinterpret_cast<const uint4 *>(pool_g + (int64_t)__builtin_amdgcn_readlane(mine, m) * pool.r);
+#pragma unroll
+                for (int c = 0; c < CPT; ++c)
+                    x[c] = sb[min(tg + GT * c, chunks - 1)];
+            };
+            auto inverse = [&](int m) __attribute__((always_inline)) {
+                return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(im), m),
+                                        __builtin_amdgcn_readlane(__double2loint(im), m));
+            };
+            fetch(x1, 0);
+            if (n > 1)
+                fetch(x2, 1);
+            for (int m = 0; m < n; m += 2) {
+                add(x1, inverse(m));
+                if (m + 2 < n)
+                    fetch(x1, m + 2);
+                if (m + 1 < n)
+                    add(x2, inverse(m + 1));
+                if (m + 3 < n)
+                    fetch(x2, m + 3);
+            }
+        }
+        if (chunks != GT * CPT) {       // what lanes past the end of the block have read again
+#pragma unroll
+            for (int c = 0; c < CPT; ++c)
+#pragma unroll
+                for (int e = 0; e < PER; ++e)
+                    acc[c][e] = tg + GT * c < chunks ? acc[c][e] : 0.0;
         }
         double ss = 0.0;
 #pragma unroll
@@ -160,7 +188,7 @@ __global__ __launch_bounds__(256, 3) void merge_group_kernel(PoolDesc pool, Work
 #pragma unroll
                 for (int e = 0; e < PER; ++e)
                     ss2 = fma(back[e], back[e], ss2);
-                if (want_tail && ch >= prefix_chunks) {
+                if (want_tail && kv == 0 && ch >= prefix_chunks) {
 #pragma unroll
                     for (int e = 0; e < PER; ++e)
                         ss2t = fma(back[e], back[e], ss2t);
