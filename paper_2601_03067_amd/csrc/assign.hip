@@ -56,85 +56,91 @@ __device__ __forceinline__ double cosine_f64(const T *__restrict__ pool_g, int r
     return (na == 0.0 || nb == 0.0) ? 0.0 : dot / (na * nb);
 }
 
-// The same cosine with the right block already in registers (raw 16-byte chunks, chunk c of this lane = chunk
-// lane + 64 * c of the block): the re-check evaluates many left rows against one right block, and re-reading that
-// block for every row doubled the traffic through L2.  Same order of operations as cosine_f64, so the two give
-// bit-identical results.
-template <typename T, int CPL>
-__device__ __forceinline__ double cosine_f64_reg(const T *__restrict__ pool_g, int r, const double *__restrict__ norm_g,
-                                                 int a, const uint4 *braw, double nb, int lane)
+// A stored block as a buffer: a row that is the same in every lane takes no vector registers for its address, and what lies past the
+// end of the block reads as zero.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(const T *pool_g, int r, int row)
 {
-    const double na = norm_g[a];
-    const uint4 *pa = reinterpret_cast<const uint4 *>(pool_g + (int64_t)a * r);
-    const int chunks = r / Elem<T>::PER16;
-    uint4 araw[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c)
-        araw[c] = pa[min(lane + 64 * c, chunks - 1)];
-    double dot = 0.0;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        if (lane + 64 * c < chunks) {
-            double x[Elem<T>::PER16], y[Elem<T>::PER16];
-            Elem<T>::widen(araw[c], x);
-            Elem<T>::widen(braw[c], y);
-#pragma unroll
-            for (int i = 0; i < Elem<T>::PER16; ++i)
-                dot = fma(x[i], y[i], dot);
-        }
-    }
-    dot = wave_sum(dot);
-    return (na == 0.0 || nb == 0.0) ? 0.0 : dot / (na * nb);
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(pool_g + (int64_t)row * r), 0, r * (int)sizeof(T), 0x00020000);
+}
+__device__ __forceinline__ uint4 block_piece(__amdgpu_buffer_rsrc_t rsrc, int lane, int c)
+{
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, c * 1024, 0));
 }
 
-// KW such cosines side by side (rows a[0 .. n), n the same in every lane): the blocks of all rows are on their way
-// together and the chains of fused multiply-adds are independent of each other, where one row after the other left a
-// wavefront waiting on one load and one chain at a time.  Each cosine is built by the operations of cosine_f64_reg in
-// their order, so the values are bit-identical to it.
-template <typename T, int CPL, int KW>
-__device__ __forceinline__ void cosines_f64_reg(const T *__restrict__ pool_g, int r, const double *__restrict__ norm_g,
-                                                const int (&a)[KW], int n, const uint4 *braw, double nb, int lane, double (&cs)[KW])
+// Dot products of N left rows with the right block in registers, N * AHEAD pieces of 1 KiB on their way at a time.  Each is built
+// by the operations of cosine_f64 in their order.
+template <typename T, int CPL, int N>
+__device__ __forceinline__ void dots_f64_reg(const T *__restrict__ pool_g, int r, const int *a, const uint4 *braw, int lane, double *dot)
 {
-    const int chunks = r / Elem<T>::PER16;
-    uint4 araw[KW][CPL];
-    double na[KW], dot[KW];
+    constexpr int PER = Elem<T>::PER16, AHEAD = CPL < 8 / N ? CPL : 8 / N;
+    __amdgpu_buffer_rsrc_t rsrc[N];
+    uint4 araw[N][AHEAD];
 #pragma unroll
-    for (int k = 0; k < KW; ++k) {
+    for (int k = 0; k < N; ++k) {
         dot[k] = 0.0;
-        na[k] = 0.0;
-        if (k < n) {
-            na[k] = norm_g[a[k]];
-            const uint4 *pa = reinterpret_cast<const uint4 *>(pool_g + (int64_t)a[k] * r);
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
-                araw[k][c] = pa[min(lane + 64 * c, chunks - 1)];
-        }
+        rsrc[k] = block_rsrc(pool_g, r, a[k]);
     }
+#pragma unroll
+    for (int c = 0; c < AHEAD; ++c)
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            araw[k][c] = block_piece(rsrc[k], lane, c);
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-        if (lane + 64 * c < chunks) {
-            double y[Elem<T>::PER16];
-            Elem<T>::widen(braw[c], y);
+        __builtin_amdgcn_sched_barrier(0);       // (or all loads move up here, and the registers for them cost half the wavefronts)
+        // (widened here and not once for all rounds, which would take four times the registers)
+        uint4 b = braw[c];
+        asm volatile("" : "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w));
+        double y[PER];
+        Elem<T>::widen(b, y);
 #pragma unroll
-            for (int k = 0; k < KW; ++k) {
-                if (k < n) {
-                    double x[Elem<T>::PER16];
-                    Elem<T>::widen(araw[k][c], x);
+        for (int k = 0; k < N; ++k) {
+            double x[PER];
+            Elem<T>::widen(araw[k][c % AHEAD], x);
 #pragma unroll
-                    for (int i = 0; i < Elem<T>::PER16; ++i)
-                        dot[k] = fma(x[i], y[i], dot[k]);
-                }
-            }
+            for (int i = 0; i < PER; ++i)
+                dot[k] = fma(x[i], y[i], dot[k]);
         }
+        if (c + AHEAD < CPL)
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                araw[k][c % AHEAD] = block_piece(rsrc[k], lane, c + AHEAD);
     }
+}
+
+// KW such cosines side by side (rows a[0 .. n), n >= 1 and the rows the same in every lane): the blocks of all rows are on their
+// way together and the chains of fused multiply-adds are independent of each other, where one row after the other left a
+// wavefront waiting on one load and one chain at a time.
+template <typename T, int CPL, int KW>
+__device__ __forceinline__ void cosines_f64_reg(const T *__restrict__ pool_g, int r, const double *__restrict__ norm_g,
+                                                const int (&rows)[KW], int n, const uint4 *braw, double nb, int lane, double (&cs)[KW])
+{
+    static_assert(KW == 4);
+    int a[KW];
+    double dot[KW];
+    const int mine = wave_sum4_of(lane);          // the row whose cosine this lane forms
+    int row = 0;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
-        cs[k] = 0.0;
-        if (k < n) {
-            dot[k] = wave_sum(dot[k]);
-            cs[k] = (na[k] == 0.0 || nb == 0.0) ? 0.0 : dot[k] / (na[k] * nb);
-        }
+        a[k] = __builtin_amdgcn_readfirstlane(rows[k < n ? k : 0]);
+        row = mine == k ? a[k] : row;
+        dot[k] = 0.0;
     }
+    const double na = norm_g[row];
+    if (n > 3)
+        dots_f64_reg<T, CPL, 4>(pool_g, r, a, braw, lane, dot);
+    else if (n == 3)
+        dots_f64_reg<T, CPL, 3>(pool_g, r, a, braw, lane, dot);
+    else if (n == 2)
+        dots_f64_reg<T, CPL, 2>(pool_g, r, a, braw, lane, dot);
+    else
+        dots_f64_reg<T, CPL, 1>(pool_g, r, a, braw, lane, dot);
+    const double sum = wave_sum4(dot[0], dot[1], dot[2], dot[3]);
+    const double c = (na == 0.0 || nb == 0.0) ? 0.0 : sum / (na * nb);
+#pragma unroll
+    for (int k = 0; k < KW; ++k)
+        cs[k] = read_lane(c, wave_sum4_lane(k));
 }
 
 __global__ void assign_reset_kernel(WorkDesc w, int height)
@@ -290,45 +296,49 @@ __global__ __launch_bounds__(256) void assign_screen_kernel(WorkDesc w, HeightDe
 // overflowed), strict '>' against thr, lowest row on exact ties.
 // CPL = 16-byte chunks of a block per lane when the right block is kept in registers (blocks up to 8 KiB), 0 = blocks
 // too long for that: both operands are streamed.
+//
+// What bounds it: where columns have many contenders, blocks that miss L2 (6.2 TB/s at the first height of 256 requests of 128
+// popular blocks, 16 groups), and at the upper heights the latency of a column's rounds.  Rows in pieces of 1 KiB, the right block
+// widened where it is used and rows addressed by scalars leave three wavefronts a SIMD instead of one, the four sums of a round
+// share their exchanges and one division, and the list is dealt out by XCD.  All heights of that call 3.08 -> 2.32 ms (1.31 -> 1.06
+// at the first).
 template <typename T, int CPL>
-__global__ __launch_bounds__(256) void assign_refine_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, int height, double thr,
+__global__ __launch_bounds__(256, 3) void assign_refine_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, int height, double thr,
                                                             double band, int rule, int bound)
 {
-    constexpr int KW = CPL >= 8 ? 2 : 4;       // left rows multiplied side by side (cosines_f64_reg); two for the longest blocks, whose registers are full
+    constexpr int KW = 4;       // left rows multiplied side by side (cosines_f64_reg)
     const int lane = threadIdx.x & 63;
     const int n_items = w.n_refine[height];
-    const int n_waves = gridDim.x * 4;
-    for (int it = blockIdx.x * 4 + (threadIdx.x >> 6); it < n_items; it += n_waves) {
+    // An XCD's workgroups (every eighth) take one part of the list, side by side: columns next to each other belong to one node, and
+    // its left blocks then come out of that XCD's L2.
+    const int parts = min(8, (int)gridDim.x), part = blockIdx.x % parts;
+    const int part_len = (n_items + parts - 1) / parts, part_end = min(n_items, (part + 1) * part_len);
+    const int n_waves = ((int)gridDim.x - part + parts - 1) / parts * 4;
+    for (int it = part * part_len + (int)(blockIdx.x / parts) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); it < part_end; it += n_waves) {
         const int2 item = reinterpret_cast<const int2 *>(w.refine)[it];
         if (item.x < 0)         // settled by assign_q8_fill_kernel
             continue;
-        const int64_t cidx = item.x;
-        const int node = item.y;
+        const int64_t cidx = __builtin_amdgcn_readfirstlane(item.x);
+        const int node = __builtin_amdgcn_readfirstlane(item.y);
         const int g = (int)(cidx / w.r_stride);
         const int c = (int)(cidx - (int64_t)g * w.r_stride);
         const int j = c - h.r_base[node];
         const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[node]];
         const int32_t *l_ids = w.set_ids + (int64_t)g * w.n + h.l_off[node];
-        const int b = w.set_ids[(int64_t)g * w.n + h.r_off[node] + j];
+        const int b = __builtin_amdgcn_readfirstlane(w.set_ids[(int64_t)g * w.n + h.r_off[node] + j]);
         const T *pool_g = (const T *)pool.k + (int64_t)g * pool.P * pool.r;
         const double *norm_g = pool.norm_k + (int64_t)g * pool.P;
         const int cnt = w.cand_cnt[cidx];
         uint4 braw[CPL > 0 ? CPL : 1];
         double nb = 0.0;
         if constexpr (CPL > 0) {
-            const uint4 *pb = reinterpret_cast<const uint4 *>(pool_g + (int64_t)b * pool.r);
-            const int chunks = pool.r / Elem<T>::PER16;
+            const __amdgpu_buffer_rsrc_t rsrc = block_rsrc(pool_g, pool.r, b);
 #pragma unroll
             for (int q = 0; q < CPL; ++q)
-                braw[q] = pb[min(lane + 64 * q, chunks - 1)];
+                braw[q] = block_piece(rsrc, lane, q);
             nb = norm_g[b];
         }
-        auto cosine = [&](int a) __attribute__((always_inline)) {
-            if constexpr (CPL > 0)
-                return cosine_f64_reg<T, CPL>(pool_g, pool.r, norm_g, a, braw, nb, lane);
-            else
-                return cosine_f64<T>(pool_g, pool.r, norm_g, a, b, lane);
-        };
+        auto cosine = [&](int a) __attribute__((always_inline)) { return cosine_f64<T>(pool_g, pool.r, norm_g, a, b, lane); };
         // radius of a listed value around the cosine: band, or (fp8 screen) band + the two copies' errors; per lane, for
         // the candidate that lane holds
         auto radius = [&](int row) __attribute__((always_inline)) {
@@ -855,10 +865,10 @@ void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, co
         unsigned rgrid = 0;
         const int cpl = (pool.r / (pool.dtype == KVFUSE_BF16 ? 8 : 4) + 63) / 64;     // 16-byte chunks per lane
         // a persistent grid: exactly as many workgroups as the GPU holds at once (a workgroup that had to wait for a
-        // free slot would start its share of the list when the others are nearly done)
+        // free slot would start its share of the list when the others are nearly done); as many for each XCD
 #define KVF_REFINE(T, C)                                                                                         \
     do {                                                                                                         \
-        rgrid = (unsigned)std::min<int64_t>((cols + 3) / 4, resident_workgroups(assign_refine_kernel<T, C>));    \
+        rgrid = (unsigned)std::min<int64_t>((cols + 31) / 32 * 8, resident_workgroups(assign_refine_kernel<T, C>));  \
         assign_refine_kernel<T, C><<<rgrid, 256, 0, s>>>(pool, w, h, height, thr, band, rule, bound);                   \
     } while (0)
         if (pool.dtype == KVFUSE_BF16) {

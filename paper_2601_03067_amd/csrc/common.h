@@ -296,6 +296,35 @@ __device__ __forceinline__ double wave_sum(double x)
     return add_lane_xor<1>(x);
 }
 
+// Four such sums for little more than one: after the first exchange a half wavefront holds each of two values, after the second a
+// row of 16 lanes each of four; from there on all go the same way.  The same sums in the same order as wave_sum.  Value k is then in the
+// lanes of row wave_sum4_lane(k) / 16.
+template <int OFF>
+__device__ __forceinline__ double fold_lanes(double a, double b)
+{
+    static_assert(OFF == 32 || OFF == 16);
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    const uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32), yl = (uint32_t)y, yh = (uint32_t)(y >> 32);
+    const auto l = OFF == 32 ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false) : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = OFF == 32 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false) : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    return __longlong_as_double((int64_t)((uint64_t)h[0] << 32 | l[0])) + __longlong_as_double((int64_t)((uint64_t)h[1] << 32 | l[1]));
+}
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d)
+{
+    double x = fold_lanes<16>(fold_lanes<32>(a, b), fold_lanes<32>(c, d));
+    x = add_lane_xor<8>(x);
+    x = add_lane_xor<4>(x);
+    x = add_lane_xor<2>(x);
+    return add_lane_xor<1>(x);
+}
+constexpr int wave_sum4_lane(int k) { return (k & 1) * 32 + (k >> 1) * 16; }
+__device__ __forceinline__ int wave_sum4_of(int lane) { return lane >> 5 | (lane >> 3 & 2); }
+
+__device__ __forceinline__ double read_lane(double x, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
 // Sum over a 256-thread workgroup in a fixed order (wave butterflies, then waves 0..3 left to right).
 __device__ __forceinline__ double block_sum_256(double x, double *lds4)
 {

@@ -124,19 +124,15 @@ __global__ __launch_bounds__(256, 3) void merge_group_kernel(PoolDesc pool, Work
                 for (int c = 0; c < CPT; ++c)
                     x[c] = sb[min(tg + GT * c, chunks - 1)];
             };
-            auto inverse = [&](int m) __attribute__((always_inline)) {
-                return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(im), m),
-                                        __builtin_amdgcn_readlane(__double2loint(im), m));
-            };
             fetch(x1, 0);
             if (n > 1)
                 fetch(x2, 1);
             for (int m = 0; m < n; m += 2) {
-                add(x1, inverse(m));
+                add(x1, read_lane(im, m));
                 if (m + 2 < n)
                     fetch(x1, m + 2);
                 if (m + 1 < n)
-                    add(x2, inverse(m + 1));
+                    add(x2, read_lane(im, m + 1));
                 if (m + 3 < n)
                     fetch(x2, m + 3);
             }
