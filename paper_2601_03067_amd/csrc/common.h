@@ -123,7 +123,7 @@ struct WorkDesc {
     int4 *panel_items;       // (group, node, first column, first row)
     int32_t *panel_total;    // [max_heights]
     // tree calls on tiny groups (tiny.hip); null where the tree is too large for them
-    int4 *tiny_nodes;        // [nodes][2] (l_off, r_off, l_slot, r_slot), (out_slot, ...), height by height
+    int4 *tiny_nodes;        // [nodes][2] (l_off, r_off, l_slot, r_slot), (out_slot, r_base, ...), height by height
     int32_t *tiny_ptr;       // [heights + 1] first node of every height
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
     int4 *dyn_items;     // [G][item_cap of the height] node, first column, first row, rows

@@ -545,7 +545,7 @@ int kvfuse_plan_create(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_ta
             tiny_ptr.push_back((int32_t)tiny_nodes.size() / 2);
             for (size_t k = 0; k < h.l_off.size(); ++k) {
                 tiny_nodes.push_back(make_int4(h.l_off[k], h.r_off[k], h.l_slot[k], h.r_slot[k]));
-                tiny_nodes.push_back(make_int4(h.out_slot[k], 0, 0, 0));
+                tiny_nodes.push_back(make_int4(h.out_slot[k], h.r_base[k], 0, 0));
             }
         }
         tiny_ptr.push_back((int32_t)tiny_nodes.size() / 2);

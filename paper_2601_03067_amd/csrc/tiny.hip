@@ -66,6 +66,13 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         counters[tid] = 0;
     if (tid == 0)
         n_tgt = 0;
+    // What single steps behind the call read and this kernel has no other use for: no open column, no target waits for a merge.
+    for (int c = tid; c < w.r_stride; c += NT) {
+        w.best_packed[(int64_t)g * w.r_stride + c] = 0ull;
+        w.cand_cnt[(int64_t)g * w.r_stride + c] = 0;
+    }
+    if (g == 0 && tid < A.n_heights)
+        w.n_active[tid] = w.n_refine[tid] = w.n_pairs_all[tid] = 0;
     __syncthreads();
     if (tid < n) {
         const int p = tab.bt[gn + tid], src = w.leaf_src[tid];
@@ -126,6 +133,7 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         // ---- similarity and assignment, a wavefront per right block
         for (int k = n0, j = wave; k < n1; ++k) {
             const int4 nd = w.tiny_nodes[2 * k];            // left and right offset, left and right slot
+            const int64_t col0 = (int64_t)g * w.r_stride + w.tiny_nodes[2 * k + 1].y;
             const int ml = cnt[nd.z], mr = cnt[nd.w];
             for (; j < mr; j += NW) {
                 const int b = __builtin_amdgcn_readfirstlane(ids[nd.y + j]);
@@ -187,8 +195,17 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                     top = fmaxf(top, __shfl_xor(top, off, 64));
                 const int n_listed = __popcll(__ballot(listed));
                 const int contenders = __popcll(__ballot(listed && (double)val >= (double)top - 2.0 * A.band));
+                if (hgt + 1 == A.n_heights) {                // the last height's lists stay, as they do launch by launch
+                    const int slot = __popcll(__ballot(listed) & ((1ull << lane) - 1ull));
+                    if (listed && slot < w.cand_cap) {
+                        w.cand_idx[(col0 + j) * w.cand_cap + slot] = lane;
+                        w.cand_val[(col0 + j) * w.cand_cap + slot] = val;
+                    }
+                    if (lane == 0)
+                        w.cand_cnt[col0 + j] = n_listed;
+                }
                 if (lane == 0) {
-                    assign[nd.y + j] = bv > A.thr ? bi : -1;
+                    assign[nd.y + j] = w.assign[col0 + j] = bv > A.thr ? bi : -1;
                     if (n_listed > w.cand_cap || (n_listed > 0 && !(contenders == 1 && (double)top > A.thr + 2.0 * A.band))) {
                         atomicAdd(&counters[2], 1);
                         if (fabs(bv - A.thr) <= A.band)
@@ -352,6 +369,8 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
     }
     for (int s = tid; s < w.n_slots; s += NT)
         w.set_cnt[(int64_t)g * w.n_slots + s] = cnt[s];
+    if (tid < n)
+        w.set_ids[gn + tid] = ids[tid];
     if (tid < 8)
         w.counters[(int64_t)g * 8 + tid] = counters[tid];
     if (wave == 0) {

@@ -55,6 +55,37 @@ def _inputs(rec, spare):
     return mat
 
 
+def _left_behind(plan):
+    """What the view of the last height promises after a call: sets, assignments, candidate counts, the diagnostic's zeros"""
+    kb = gu.load_binding()
+    c, v = plan.cache, plan.view(plan.n_heights - 1)
+    get = lambda ptr, shape, dtype: kb.device_array(ptr, int(np.prod(shape)), dtype, DEV).reshape(shape)
+    out = {"set_ids": get(v.set_ids, (c.G, c.n), np.int32), "set_cnt": get(v.set_cnt, (c.G, v.n_slots), np.int32),
+           "cand_cnt": get(v.cand_cnt, (c.G, v.r_stride), np.int32), "best_packed": get(v.best_packed, (c.G, v.r_stride), np.uint64)}
+    assign = get(v.assign, (c.G, v.r_stride), np.int32)
+    r_slot, r_base = get(v.r_slot, (v.n_nodes,), np.int32), get(v.r_base, (v.n_nodes,), np.int32)
+    out["assign"] = [assign[g, b:b + out["set_cnt"][g, s]].tolist() for g in range(c.G) for s, b in zip(r_slot, r_base)]
+    return out
+
+
+def _steps_behind(ctx, plan, thr):
+    """The single steps of the last height once more, on what the call left"""
+    kb = gu.load_binding()
+    c, last = plan.cache, plan.n_heights - 1
+    dense = torch.full((c.G, max(int(plan.view(last).total_s), 1)), -2.0, device=DEV)
+    kb.similarity(ctx, plan, last, thr, dense_s=dense)
+    kb.assign(ctx, plan, last, thr)
+    left = _left_behind(plan)
+    kb.merge(ctx, plan, last)
+    torch.cuda.synchronize()
+    return dense, left
+
+
+def _same(left, want):
+    for name in want:
+        assert left[name] == want[name] if name == "assign" else np.array_equal(left[name], want[name]), name
+
+
 @pytest.mark.parametrize("case", CASES, ids=[str(i) for i in range(len(CASES))])
 def test_tree_matches_oracle(oracle, case):
     counts, t, d, dtype, bases, groups, spare = case
@@ -72,11 +103,23 @@ def test_tree_matches_oracle(oracle, case):
     again = {"K": torch.from_numpy(np.stack(host[0]).view(np.int16 if dtype == torch.bfloat16 else np.float32)).to(DEV).view(dtype),
              "V": torch.from_numpy(np.stack(host[1]).view(np.int16 if dtype == torch.bfloat16 else np.float32)).to(DEV).view(dtype),
              "bt": torch.from_numpy(np.stack(host[2])).to(DEV)}
-    other, _, st, _ = gu.gpu_fuse(rec, again, timing=True)
+    other, staged, st, ctx2 = gu.gpu_fuse(rec, again, timing=True)
+    assert st.ms_norms > 0 and st.ms_rewrite > 0 and stats.ms_total == 0
     for name in ("K", "V", "bt", "scale_k", "scale_v", "norm_k", "norm_v", "orig_norm_k", "orig_norm_v", "refcount", "remap", "n_free", "n_phys"):
         assert torch.equal(getattr(cache, name), getattr(other, name)), name
     for name in ("fused", "near_threshold", "refined", "cand_overflow", "merge_targets", "physical_blocks"):
         assert getattr(stats, name) == getattr(st, name), name
+    if plan.n_heights:
+        _same(_left_behind(plan), _left_behind(staged))
+        print("single steps behind the call", flush=True)
+        kb, before = gu.load_binding(), cache.K.clone()
+        kb.merge(ctx, plan, plan.n_heights - 1)                         # no target waits for it
+        assert torch.equal(cache.K, before)
+        (dense, left), (dense2, want) = _steps_behind(ctx, plan, rec.thr), _steps_behind(ctx2, staged, rec.thr)
+        assert torch.equal(dense, dense2)
+        for name in ("set_ids", "set_cnt", "assign"):
+            assert left[name] == want[name] if name == "assign" else np.array_equal(left[name], want[name]), name
+        assert torch.equal(cache.K, other.K) and torch.equal(cache.V, other.V)
 
 
 @pytest.mark.parametrize("fault,text", [("outside", "outside"), ("shared", "not injective"), ("range", "norm")])
