@@ -289,7 +289,7 @@ __device__ static __forceinline__ void load_to_lds(uint64_t base, uint32_t off, 
 {
     typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
     const desc_t desc = {(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(desc), "s"(to) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(desc), "s"(to) : "memory", "m0");
 }
 
 // WAVES: wavefronts of a SIMD that the registers are for, see launch_prefill_attn.
