@@ -162,8 +162,8 @@ struct PWalk {
 };
 
 // The running maximum is taken before the softmax scale is applied, which must not turn it round: logits of a negative scale
-// are those of its size and the queries' opposites.  (Called once the first loads of the context are on their way, so that
-// they do not wait for the queries: 46.7 -> 45.7 us for 200 queries of 4296 tokens.)
+// are those of its size and the queries' opposites.  (In the split kernel once the context's first table words are asked for, so
+// that they do not wait for the queries: 46.7 -> 45.7 us for 200 queries of 4296 tokens.)
 template <int KS>
 __device__ static __forceinline__ void sign_queries(uint4 (&qf)[KS], uint32_t sign)
 {
@@ -292,7 +292,7 @@ __device__ static __forceinline__ void load_to_lds(uint64_t base, uint32_t off, 
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(desc), "s"(to) : "memory", "m0");
 }
 
-// WAVES: wavefronts of a SIMD that the registers are for, see launch_prefill_attn.
+// WAVES: wavefronts of a SIMD that the registers are for, see roomy_pays.
 template <int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
 {
@@ -332,14 +332,16 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
 
     // B operand of step ks: head elements 16 ks + 8 h2 .. + 7 of the row.  Where a third wavefront of the SIMD needs the
     // registers, all but four of them live in LDS.
-    uint4 qf[KS - KQ];
+    uint4 qf[KS - KQ], q[KS];
     {
-        uint4 q[KS];
         const int64_t qi = (int64_t)li * (A.q_end - A.q_begin) + (my_pos - A.q_begin);
         const T *qp = (const T *)A.q + (qi * A.Hq + (int64_t)kvh * A.rep + (row_used ? hh : 0)) * D + 8 * h2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             q[ks] = row_used ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+    }
+
+    auto place_queries = [&]() __attribute__((always_inline)) {
         sign_queries(q, A.q_sign);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -347,7 +349,9 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
                 qf[ks] = q[ks];
             else
                 q_lds[wave][ks - (KS - KQ)][lane] = q[ks];
-    }
+    };
+    if constexpr (!ROOMY)
+        place_queries();
 
     const PWalk<D> walk(A, kvh, li, pos_last_wg);
     const int n_tiles = (walk.n_pieces + 1) / 2;
@@ -356,8 +360,8 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
     // piece's address is uniform, so it goes into the descriptor.
     const int piece = wave & 1, tensor = wave >> 1;
     const bf16_t *my_pool = tensor ? walk.vg : walk.kg;
-    auto load = [&](int buf, const PRows &rw) __attribute__((always_inline)) {
-        const uint64_t from = (uint64_t)(uintptr_t)(my_pool + walk.first_row(A, rw));
+    auto address_of = [&](const PRows &rw) __attribute__((always_inline)) { return (uint64_t)(uintptr_t)(my_pool + walk.first_row(A, rw)); };
+    auto load = [&](int buf, uint64_t from) __attribute__((always_inline)) {
         const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&lds[buf][tensor][piece * 16 * ROW];
         int at = lane;
         asm volatile("" : "+v"(at));
@@ -469,18 +473,34 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
             }
     };
 
-    // The next BUFS - 1 tiles are on their way while one is multiplied; past the last tile the loads go on with the last piece's rows.
+    // The next BUFS - 1 tiles are on their way while one is multiplied.  Where the registers are for three wavefronts a SIMD, the loads go
+    // on past the last tile with the last piece's rows: a look at the tile's number costs long walks more (2048 queries of 32768
+    // tokens, 4 layers: 5.27 against 5.13 - 5.21 ms) than such loads do.  The roomier kernel, whose grids are small and walks can be a
+    // few tiles, neither waits for two tiles that nobody needs nor, before its first loads, for the queries (65 queries of
+    // 109 tokens, 21 layers of 8 KV heads, 2 query heads each: 19.0 -> 17.1 us).
     PRows next = walk.rows(A, 2 * (BUFS - 1) + piece);
     PScales s0 = walk.scales(A, 0), s1 = walk.scales(A, 1), n0, n1;
+    uint64_t first[BUFS - 1];
 #pragma unroll
     for (int i = 0; i < BUFS - 1; ++i)
-        load(i, walk.rows(A, 2 * i + piece));
+        first[i] = address_of(walk.rows(A, 2 * i + piece));
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (ROOMY)
+        place_queries();
+#pragma unroll
+    for (int i = 0; i < BUFS - 1; ++i)
+        if (!ROOMY || i < n_tiles)
+            load(i, first[i]);
     int buf = 0, ahead = BUFS - 1;
     for (int ti = 0; ti < n_tiles; ++ti) {
         // Tile ti has landed, for every wavefront behind the barrier; and every wavefront is done with tile ti - 1, whose place
         // the next load takes.
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((BUFS - 2) * NLD) : "memory");
-        load(ahead, next);
+        if (ROOMY && ti + 1 == n_tiles)
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((BUFS - 2) * NLD) : "memory");
+        if (!ROOMY || ti + BUFS - 1 < n_tiles)
+            load(ahead, address_of(next));
         compute(s0, s1, buf, [&]() __attribute__((always_inline)) {
             next = walk.rows(A, 2 * (ti + BUFS) + piece);
             n0 = walk.scales(A, 2 * (ti + 1));
@@ -491,7 +511,8 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
         ahead = buf;
         buf = buf + 1 == BUFS ? 0 : buf + 1;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may leave while loads are on their way into LDS
+    if constexpr (!ROOMY)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may leave while loads are on their way into LDS
     l_run = halves_sum(l_run);
 
     // ---- normalise and store: this lane holds out[row qrow][head element 32 dt + 8 (i / 4) + 4 h2 + i % 4]

@@ -102,3 +102,18 @@ STAGED = [(18, 8, 4, 16, 128, 64, 5, 129),       # 720: a workgroup of one posit
 @pytest.mark.parametrize("case", STAGED, ids=[str(i) for i in range(len(STAGED))])
 def test_large_grids_against_binary64(case, reuse):
     _compare(case, reuse)
+
+
+# Walks of one to four tiles in the staged kernel with room for two tiles on their way (193 to 512 workgroups): fewer than are asked for
+# before the first is multiplied, as many, one and two more.
+SHORT = [(28, 8, 4, 16, 128, 0, 0, 1),           # 224 workgroups, half a tile
+         (28, 8, 4, 16, 128, 0, 0, 32),          # one
+         (28, 8, 4, 16, 128, 0, 9, 33),          # 448; one and a half, two of the last piece's rows hidden
+         (28, 8, 4, 16, 128, 32, 3, 45),         # up to two and a half
+         (21, 8, 2, 16, 128, 0, 44, 65)]         # 336; four, a workgroup of one position
+
+
+@pytest.mark.parametrize("reuse", [True, False])
+@pytest.mark.parametrize("case", SHORT, ids=[str(i) for i in range(len(SHORT))])
+def test_short_walks_against_binary64(case, reuse):
+    _compare(case, reuse)
