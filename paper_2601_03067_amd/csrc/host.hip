@@ -271,6 +271,49 @@ struct Carver {
     }
 };
 
+// The panel kernel's part of a height of big tiles: most stages of an item, or 0 where the ring kernel is the faster one; `items`: most
+// items of a group.  Items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
+// to 8, while there are fewer than eight a compute unit.
+//
+// Which is faster is a matter of how many items there are: a panel's are large (512 columns x 8 to 32 stages), its launches come on
+// top of the ring kernel's (14 us), and the chip's 256 compute units take one workgroup of either at a time.  Times of both as rounds of
+// the largest item that the work makes, in us at a head of 8 slices, from heights of one node and of four and sixteen equal ones, of 256
+// to 16384 blocks in each set, 1 to 256 groups, heads of 4, 6 and 10 slices (209 heights): ring item 8.4 + 7.94 a tile, panel item
+// 14.5 + 3.31 a stage (three quarters of that where it has no more than half its columns).  The rule's choice is slower than the other
+// by 6 % at most, by 0.1 % on average; the panel kernel everywhere is up to twice as slow.  Some of them, ring / panel, 4 KiB blocks,
+// 10 slices: 1024 x 1024 blocks in 16 groups 37 / 72, 64 groups 91 / 84, 256 groups 310 / 256; 4096 x 4096 in 8 groups 110 / 120, 128
+// groups 1480 / 1162; four nodes of 256 x 256 in 256 groups 122 / 160.
+static int panel_run(const HostHeight &h, int G, int64_t &items)
+{
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const size_t nodes = h.l_cap.size();
+    auto count = [&](int64_t run) {
+        int64_t c = 0;
+        for (size_t k = 0; k < nodes; ++k)
+            c += up(h.r_cap[k], kPanelCols) * up(up(h.l_cap[k], kPanelRows), run);
+        return c;
+    };
+    int run = kPanelRun;
+    while (run > 8 && (int64_t)G * count(run) < 2048)
+        run /= 2;
+    items = count(run);
+    double ring = 0.0, ring_item = 1.0, panel = 0.0, panel_item = 1.0;
+    for (size_t k = 0; k < nodes; ++k) {
+        const int64_t l = h.l_cap[k], r = h.r_cap[k];
+        if (l == 0 || r == 0)
+            continue;
+        const int64_t tiles = up(l, kBigM), rt = std::min<int64_t>(up(tiles, 4), 4);          // as items_of_node cuts them
+        ring += (double)up(r, kBigN) * (8.4 * (double)up(tiles, rt) + 7.94 * (double)tiles);
+        ring_item = std::max(ring_item, 8.4 + 7.94 * (double)rt);
+        const int64_t stages = up(l, kPanelRows), n = up(stages, run), last = r % kPanelCols;
+        const double cols = (double)(r / kPanelCols) + (last == 0 ? 0.0 : last <= kPanelCols / 2 ? 0.75 : 1.0);
+        panel += 14.5 * (double)(n * up(r, kPanelCols)) + 3.31 * (double)stages * cols;
+        panel_item = std::max(panel_item, 14.5 + 3.31 * (double)up(stages, n));
+    }
+    auto rounds = [&](double total, double item) { return item * std::ceil(total * G / 256.0 / item - 1e-9); };
+    return rounds(panel, panel_item) + 14.0 < 0.95 * rounds(ring, ring_item) ? run : 0;
+}
+
 static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, int cand_cap,
                   std::vector<HostHeight> &hs, WorkDesc &w, int32_t *&slot_init)
 {
@@ -331,23 +374,10 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     }
     size_t panel_items = 0;
     for (HostHeight &h : hs) {
-        // Panel kernel: items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
-        // to 8, while there are fewer than eight a compute unit.
         h.dev.panel_run = h.dev.panel_items = 0;
-        if (!h.big)
-            continue;
-        auto count = [&](int run) {
-            int64_t c = 0;
-            for (size_t k = 0; k < h.l_cap.size(); ++k)
-                c += (int64_t)((h.r_cap[k] + kPanelCols - 1) / kPanelCols) *
-                     (((h.l_cap[k] + kPanelRows - 1) / kPanelRows + run - 1) / run);
-            return c;
-        };
-        int run = kPanelRun;
-        while (run > 8 && (int64_t)G * count(run) < 2048)
-            run /= 2;
-        const int64_t items = count(run);
-        if (!launch_fits(items * G + 256, 512))
+        int64_t items = 0;
+        const int run = h.big ? panel_run(h, G, items) : 0;
+        if (run == 0 || !launch_fits(items * G + 256, 512))
             continue;
         h.dev.panel_run = run;
         h.dev.panel_items = (int32_t)items;
@@ -739,6 +769,10 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         w.pairs = w.active;
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
+    // A pair of blocks of evenly spread energy is not ruled out before a share 1 - floor of their elements: no group's head will fit
+    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 13 of 128 slices), and its launches,
+    // 8 us a height, would find nothing to do.
+    const bool panel = early && panel_fits(p.pool) && (1.0f - floor_f) * (float)(p.pool.r * 2 / 64) < (float)kPanelSlices;
     const bool tiny = !timing && p.tiny_pays();       // (stages are timed where there are stages)
     if (tiny) {
         launch_tiny_tree(c->stream, p.pool, p.tab, w, p.slot_init, nh, thr, band, floor_f, free_list, n_free, n_phys);
@@ -753,7 +787,7 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         for (int hgt = 0; hgt < nh; ++hgt) {
             const HeightDesc &d = p.heights[hgt].dev;
             w.n_pairs = w.n_pairs_all + hgt;
-            w.panel_on = early && panel_fits(p.pool) && d.panel_run > 0 ? w.panel_on_mem : nullptr;
+            w.panel_on = panel && d.panel_run > 0 ? w.panel_on_mem : nullptr;
             if (w.panel_on)
                 launch_similarity_panel(c->stream, p.pool, w, d, hgt > 0 ? p.heights[hgt - 1].dev : HeightDesc{}, hgt, floor_f);
             launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);

@@ -938,6 +938,8 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     __shared__ int64_t lds4[4];
     const int g = blockIdx.x, tid = threadIdx.x;
     int32_t *base = w.dyn_base + (int64_t)g * w.dyn_stride;
+    if (w.early_nk && !w.panel_on && tid == 0)      // (a height of the panel kernel has begun with that: panel_items_kernel)
+        w.open_cnt[g] = 0;
     if (w.panel_on && w.panel_on[g]) {        // this group's share of the height is the panel kernel's
         if (tid == 0)
             w.dyn_count[g] = 0;
