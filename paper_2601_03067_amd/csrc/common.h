@@ -56,6 +56,7 @@ struct HeightDesc {
     int32_t max_cap;                  // largest left or right set of a node
     bool use_big_tiles;
     int32_t panel_run, panel_items;   // panel kernel (panel.hip): most 64-row stages of an item, 0 = not for this height; most items of a group
+    int32_t panel_from;               // ... shortest head from which it is faster on blocks that have little to do with each other
     int64_t total_s;
 };
 
@@ -77,6 +78,7 @@ struct Q8Desc {
 // registers; and the share of pairs (one in so many) left open at the height before up to which a group takes it.
 constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
 constexpr int kPanelCols = 512, kPanelRows = 64, kPanelSlices = 11, kPanelRun = 32, kPanelOpen = 1024;
+constexpr int kWholeTile = 128;       // open pairs of a panel item beyond which the ring kernel is taken to have multiplied a tile whole
 
 // Tree calls on tiny groups (tiny.hip): most table entries, stored blocks and tree nodes of a group, bytes of a block, groups.
 constexpr int kTinyEntries = 64, kTinyPool = 128, kTinySlots = 256, kTinyBytes = 4096, kTinyGroups = 512;
@@ -116,7 +118,7 @@ struct WorkDesc {
     float *pair_head;        // [pair_cap] ... and their product so far
     int32_t *n_pairs;        // counter of the current height
     int32_t pair_cap;
-    int32_t *open_cnt;       // [G] pairs that the current height's tests left open
+    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; whether tiles were multiplied whole for them
     // panel kernel (panel.hip); panel_on null = not at this height
     int32_t *panel_on, *panel_on_mem;       // [G]
     u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand
@@ -193,13 +195,12 @@ void launch_tree_norms(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
 void launch_centre_direction(hipStream_t s, const PoolDesc &pool, const WorkDesc &w);
 void launch_leaf_sets(hipStream_t s, const WorkDesc &w, const TableDesc &tab, int P, const int32_t *slot_init, const double *norm_k);
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
-                       float *dense_s, bool cleared = false);
+                       float *dense_s, bool cleared = false, const HeightDesc *prev = nullptr, int height = 0);
 // early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
 // bfloat16, and a group's keys within the 32-bit offsets of buffer loads
 static inline bool panel_fits(const PoolDesc &pool) { return pool.dtype == KVFUSE_BF16 && (int64_t)pool.P * pool.r * 2 <= 0xFFFFFFFFll; }
-void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, const HeightDesc &prev, int height,
-                             float thr_floor);
+void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor);
 void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
 void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height);
 void launch_assign(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, const WorkDesc &w, const HeightDesc &h,
@@ -605,6 +606,16 @@ __device__ __forceinline__ uint32_t f64_to_bf16_fast(double x)
         up = (b >> 15) & 1u;
     }
     return (b >> 16) + up;
+}
+
+// The arguments of a kernel whose only one is an Args, read from memory again: what only its end needs would otherwise sit in scalar
+// registers, and spilled from there in vector registers, throughout.
+template <typename Args>
+__device__ __forceinline__ const Args &kernel_args_again()
+{
+    uint64_t p = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Args *)(const __attribute__((address_space(4))) Args *)p;
 }
 
 // 16 bytes of pool data from fp64 values, rounded once, and what they then are.

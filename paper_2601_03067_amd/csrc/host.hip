@@ -271,47 +271,49 @@ struct Carver {
     }
 };
 
-// The panel kernel's part of a height of big tiles: most stages of an item, or 0 where the ring kernel is the faster one; `items`: most
-// items of a group.  Items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
-// to 8, while there are fewer than eight a compute unit.
-//
-// Which is faster is a matter of how many items there are: a panel's are large (512 columns x 8 to 32 stages), its launches come on
-// top of the ring kernel's (14 us), and the chip's 256 compute units take one workgroup of either at a time.  Times of both as rounds of
-// the largest item that the work makes, in us at a head of 8 slices, from heights of one node and of four and sixteen equal ones, of 256
-// to 16384 blocks in each set, 1 to 256 groups, heads of 4, 6 and 10 slices (209 heights): ring item 8.4 + 7.94 a tile, panel item
-// 14.5 + 3.31 a stage (three quarters of that where it has no more than half its columns).  The rule's choice is slower than the other
-// by 6 % at most, by 0.1 % on average; the panel kernel everywhere is up to twice as slow.  Some of them, ring / panel, 4 KiB blocks,
-// 10 slices: 1024 x 1024 blocks in 16 groups 37 / 72, 64 groups 91 / 84, 256 groups 310 / 256; 4096 x 4096 in 8 groups 110 / 120, 128
-// groups 1480 / 1162; four nodes of 256 x 256 in 256 groups 122 / 160.
-static int panel_run(const HostHeight &h, int G, int64_t &items)
+// Items of a group for the panel kernel at a height of big tiles, runs of left blocks of at most `run` stages.
+static int64_t panel_items(const HostHeight &h, int64_t run)
+{
+    int64_t c = 0;
+    for (size_t k = 0; k < h.l_cap.size(); ++k)
+        c += (int64_t)((h.r_cap[k] + kPanelCols - 1) / kPanelCols) * (((h.l_cap[k] + kPanelRows - 1) / kPanelRows + run - 1) / run);
+    return c;
+}
+
+// The shortest head, in slices, from which the panel kernel is the faster one at a height of big tiles, on blocks that have little to do
+// with each other (on others, see panel_items_of_group); longer than any it takes if there is none.  It is a matter of how many items
+// there are: a panel's are large (512 columns x 8 to 32 stages), it takes 14 us more beside the ring kernel's launches, and the chip's
+// 256 compute units hold one workgroup of either at a time; and a ring item spends the more on its products the longer the head is.
+// Times of both as rounds of the largest item that the work makes, in us: ring item 6 + 0.3 s and 2.1 + 0.73 s a tile, panel item 14.5 and
+// 0.55 + 0.345 s a stage (three quarters of that where it has no more than half its columns).  Over heights of one node and of four and
+// sixteen equal ones, 256 to 16384 blocks in each set, 1 to 256 groups, heads of 4, 6 and 10 slices (209 of them, both kernels timed) the
+// choice costs 0.5 % on average; the panel kernel everywhere costs up to 88 %.  The line is drawn 5 % to the panel kernel's side: what
+// pairs stay open cost it less (228 requests of 61 blocks, 12 groups, the last height: 398 us ring, 359 panel).  Some of the 209, us
+// of the whole step, ring / panel, 4 KiB blocks, 10 slices: 1024 x 1024 blocks in 16 groups 36 / 68, 64 groups 91 / 81, 256 groups 309 /
+// 252; 4096 x 4096 in 8 groups 112 / 116, 128 groups 1479 / 1173; four nodes of 256 x 256 in 256 groups 119 / 157.
+static int panel_from(const HostHeight &h, int G, int run)
 {
     auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-    const size_t nodes = h.l_cap.size();
-    auto count = [&](int64_t run) {
-        int64_t c = 0;
-        for (size_t k = 0; k < nodes; ++k)
-            c += up(h.r_cap[k], kPanelCols) * up(up(h.l_cap[k], kPanelRows), run);
-        return c;
-    };
-    int run = kPanelRun;
-    while (run > 8 && (int64_t)G * count(run) < 2048)
-        run /= 2;
-    items = count(run);
-    double ring = 0.0, ring_item = 1.0, panel = 0.0, panel_item = 1.0;
-    for (size_t k = 0; k < nodes; ++k) {
-        const int64_t l = h.l_cap[k], r = h.r_cap[k];
-        if (l == 0 || r == 0)
-            continue;
-        const int64_t tiles = up(l, kBigM), rt = std::min<int64_t>(up(tiles, 4), 4);          // as items_of_node cuts them
-        ring += (double)up(r, kBigN) * (8.4 * (double)up(tiles, rt) + 7.94 * (double)tiles);
-        ring_item = std::max(ring_item, 8.4 + 7.94 * (double)rt);
-        const int64_t stages = up(l, kPanelRows), n = up(stages, run), last = r % kPanelCols;
-        const double cols = (double)(r / kPanelCols) + (last == 0 ? 0.0 : last <= kPanelCols / 2 ? 0.75 : 1.0);
-        panel += 14.5 * (double)(n * up(r, kPanelCols)) + 3.31 * (double)stages * cols;
-        panel_item = std::max(panel_item, 14.5 + 3.31 * (double)up(stages, n));
-    }
     auto rounds = [&](double total, double item) { return item * std::ceil(total * G / 256.0 / item - 1e-9); };
-    return rounds(panel, panel_item) + 14.0 < 0.95 * rounds(ring, ring_item) ? run : 0;
+    for (int s = 2; s <= kPanelSlices; ++s) {
+        const double first = 6.0 + 0.3 * s, tile = 2.1 + 0.73 * s, stage = 0.55 + 0.345 * s;
+        double ring = 0.0, ring_item = 1.0, panel = 0.0, panel_item = 1.0;
+        for (size_t k = 0; k < h.l_cap.size(); ++k) {
+            const int64_t l = h.l_cap[k], r = h.r_cap[k];
+            if (l == 0 || r == 0)
+                continue;
+            const int64_t tiles = up(l, kBigM), rt = std::min<int64_t>(up(tiles, 4), 4);          // as items_of_node cuts them
+            ring += (double)up(r, kBigN) * (first * (double)up(tiles, rt) + tile * (double)tiles);
+            ring_item = std::max(ring_item, first + tile * (double)rt);
+            const int64_t stages = up(l, kPanelRows), n = up(stages, run), last = r % kPanelCols;
+            const double cols = (double)(r / kPanelCols) + (last == 0 ? 0.0 : last <= kPanelCols / 2 ? 0.75 : 1.0);
+            panel += 14.5 * (double)(n * up(r, kPanelCols)) + stage * (double)stages * cols;
+            panel_item = std::max(panel_item, 14.5 + stage * (double)up(stages, n));
+        }
+        if (rounds(panel, panel_item) + 14.0 < 1.05 * rounds(ring, ring_item))
+            return s;
+    }
+    return kPanelSlices + 1;
 }
 
 static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, int cand_cap,
@@ -344,6 +346,7 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.n_pairs = nullptr;
     w.pair_cap = 0;
     w.open_cnt = cv.take<int32_t>((size_t)G);
+    w.whole = cv.take<int32_t>((size_t)G);
     w.panel_on = nullptr;
     w.panel_on_mem = cv.take<int32_t>((size_t)G);
     w.panel_total = cv.take<int32_t>(kMaxHeights);
@@ -372,20 +375,28 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
         w.dyn_base = cv.take<int32_t>((size_t)G * w.dyn_stride);
         w.dyn_count = cv.take<int32_t>((size_t)G);
     }
-    size_t panel_items = 0;
+    size_t panel_room = 0;
     for (HostHeight &h : hs) {
+        // Panel kernel: items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
+        // to 8, while there are fewer than eight a compute unit.
         h.dev.panel_run = h.dev.panel_items = 0;
-        int64_t items = 0;
-        const int run = h.big ? panel_run(h, G, items) : 0;
-        if (run == 0 || !launch_fits(items * G + 256, 512))
+        h.dev.panel_from = 0;
+        if (!h.big)
+            continue;
+        int run = kPanelRun;
+        while (run > 8 && (int64_t)G * panel_items(h, run) < 2048)
+            run /= 2;
+        const int64_t items = panel_items(h, run);
+        if (!launch_fits(items * G + 256, 512))
             continue;
         h.dev.panel_run = run;
         h.dev.panel_items = (int32_t)items;
-        panel_items = std::max(panel_items, (size_t)items * (size_t)G);
+        h.dev.panel_from = panel_from(h, G, run);
+        panel_room = std::max(panel_room, (size_t)items * (size_t)G);
     }
-    if (panel_items > 0) {
+    if (panel_room > 0) {
         w.panel_rows = cv.take<u32x4>(2 * L);
-        w.panel_items = cv.take<int4>(panel_items);
+        w.panel_items = cv.take<int4>(panel_room);
     }
     for (HostHeight &h : hs) {
         const size_t nn = h.l_off.size();
@@ -770,8 +781,8 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
     // A pair of blocks of evenly spread energy is not ruled out before a share 1 - floor of their elements: no group's head will fit
-    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 13 of 128 slices), and its launches,
-    // 8 us a height, would find nothing to do.
+    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 13 of 128 slices), and its launch
+    // would find nothing to do.
     const bool panel = early && panel_fits(p.pool) && (1.0f - floor_f) * (float)(p.pool.r * 2 / 64) < (float)kPanelSlices;
     const bool tiny = !timing && p.tiny_pays();       // (stages are timed where there are stages)
     if (tiny) {
@@ -788,9 +799,7 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
             const HeightDesc &d = p.heights[hgt].dev;
             w.n_pairs = w.n_pairs_all + hgt;
             w.panel_on = panel && d.panel_run > 0 ? w.panel_on_mem : nullptr;
-            if (w.panel_on)
-                launch_similarity_panel(c->stream, p.pool, w, d, hgt > 0 ? p.heights[hgt - 1].dev : HeightDesc{}, hgt, floor_f);
-            launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true);
+            launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true, hgt > 0 ? &p.heights[hgt - 1].dev : nullptr, hgt);
             if (early)
                 launch_finish_pairs(c->stream, p.pool, w, floor_f);
             KVF_TRY(mark());

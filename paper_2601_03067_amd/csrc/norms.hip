@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256) void tree_clear_kernel(TableDesc tab, WorkDesc
         w.panel_total[i] = 0;
     }
     if (i < w.G)
-        w.open_cnt[i] = 0;
+        w.open_cnt[i] = w.whole[i] = 0;
 }
 
 // Thread i: reference count of table entry i and the leaf-set position i (leaf_sets_kernel).  Caller errors are counted

@@ -18,7 +18,7 @@
 // barrier (10 % slower: two round trips to LDS per 32 rows); fragments waited for where they are read (58 % busy).
 #include <type_traits>
 
-#include "common.h"
+#include "items.h"
 
 namespace kvfuse {
 
@@ -30,18 +30,6 @@ __device__ __forceinline__ floatx16 panel_mma(const u32x4 a, const u32x4 b, floa
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// A binary32 number as three bfloat16 parts (upper halves of what is left): exact.
-struct Parts {
-    uint32_t h, m, l;      // in the upper halves
-    __device__ __forceinline__ explicit Parts(float x)
-    {
-        h = __float_as_uint(x) & 0xFFFF0000u;
-        x -= __uint_as_float(h);
-        m = __float_as_uint(x) & 0xFFFF0000u;
-        x -= __uint_as_float(m);
-        l = __float_as_uint(x) & 0xFFFF0000u;
-    }
-};
 // body(0), ..., body(N - 1) with the index a constant from the start: register arrays that loops index before they are unrolled
 // would live in scratch memory.
 template <int N, typename F>
@@ -58,135 +46,6 @@ __device__ __forceinline__ void landed_regs(u32x4 &a, u32x4 &b, u32x4 &c, u32x4 
 
 __device__ __forceinline__ u32x4 lds_read(const char *at) { return *reinterpret_cast<const u32x4 *>(at); }
 
-__device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi) { return (lo >> 16) | hi; }
-
-// Fragments of the MFMA that starts a product.  The 16 summation indices hold, for each of the two terms, the six products of
-// parts that reach 2^-24 of the term: h h, h m, m h, m m, h l, l h.
-__device__ __forceinline__ u32x4 panel_left(float x, float y, int half)
-{
-    const Parts p(x), q(y);
-    return half == 0 ? u32x4{pair16(p.h, p.h), pair16(p.m, p.m), pair16(p.h, p.l), pair16(q.h, q.h)}
-                     : u32x4{pair16(q.m, q.m), pair16(q.h, q.l), 0u, 0u};
-}
-__device__ __forceinline__ u32x4 panel_right(float x, float y, int half)
-{
-    const Parts p(x), q(y);
-    return half == 0 ? u32x4{pair16(p.h, p.m), pair16(p.h, p.m), pair16(p.l, p.h), pair16(q.h, q.m)}
-                     : u32x4{pair16(q.h, q.m), pair16(q.l, q.h), 0u, 0u};
-}
-
-// The two factors of a block: its norm (1 for a zero block, whose products then stay below the floor), and its tail's length.  The
-// left norm carries - floor, lowered by 4e-6 of itself: the roundings of the MFMAs (a few 2^-24 of floor |a| |b|) then only leave
-// more pairs open, which finish_pairs_kernel tests whole.
-__device__ __forceinline__ float panel_norm(const PoolDesc &pool, int64_t b)
-{
-    const float norm = (float)pool.norm_k[b];
-    return norm == 0.0f ? 1.0f : norm;
-}
-__device__ __forceinline__ float panel_floor(float thr_floor) { return -thr_floor * (1.0f - 4e-6f); }
-
-// The left blocks' operands, one thread per block of a left set.
-__global__ __launch_bounds__(256) void panel_rows_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, float thr_floor)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)w.G * h.total_l_cap)
-        return;
-    const int g = (int)(i / h.total_l_cap);
-    const int c = (int)(i - (int64_t)g * h.total_l_cap);
-    if (!w.panel_on[g])
-        return;
-    int lo = 0, hi = h.n_nodes;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (h.l_base[mid] <= c)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    const int row = c - h.l_base[lo];
-    if (row >= w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[lo]])
-        return;
-    const int64_t b = (int64_t)g * pool.P + w.set_ids[(int64_t)g * w.n + h.l_off[lo] + row];
-    const float norm = panel_norm(pool, b);
-    u32x4 *out = w.panel_rows + ((int64_t)g * w.l_stride + c) * 2;
-    out[0] = panel_left(panel_floor(thr_floor) * norm, w.rem_k[b] * norm, 0);
-    out[1] = panel_left(panel_floor(thr_floor) * norm, w.rem_k[b] * norm, 1);
-}
-
-// Rows of a node's items: whole stages, at most `run`, the same number for all but the last.
-__device__ __forceinline__ int panel_rows_per_item(int ml, int run)
-{
-    const int stages = (ml + kPanelRows - 1) / kPanelRows;
-    const int n = max((stages + run - 1) / run, 1);
-    return max((stages + n - 1) / n, 1) * kPanelRows;
-}
-
-// One workgroup per group: whether it takes this kernel at this height, and if so its work items, behind those of the groups
-// that came first.  An item is (group, node, panel of 512 right blocks, run of left blocks); consecutive items of a node share
-// the run, so that the workgroups an XCD holds at a time read the same left rows.
-__global__ __launch_bounds__(256) void panel_items_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int height)
-{
-    __shared__ int64_t lds4[4];
-    __shared__ int node0[256], node_cp[256], node_rows[256];
-    __shared__ int first;
-    const int g = blockIdx.x, tid = threadIdx.x;
-    // pairs that the tests of the height before left open, against the pairs there were
-    double pairs = 0.0;
-    __shared__ double red[4];
-    for (int k = tid; k < prev.n_nodes; k += 256)
-        pairs += (double)w.set_cnt[(int64_t)g * w.n_slots + prev.l_slot[k]] * (double)w.set_cnt[(int64_t)g * w.n_slots + prev.r_slot[k]];
-    pairs = block_sum_256(pairs, red);
-    const bool on = w.early_nk[g] <= kPanelSlices && (!w.group_enable || w.group_enable[g]) &&
-                    (double)w.open_cnt[g] * kPanelOpen <= pairs;
-    auto items_of = [&](int k, int &n_cp, int &rows) {
-        const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
-        n_cp = (mr + kPanelCols - 1) / kPanelCols;
-        rows = panel_rows_per_item(ml, h.panel_run);
-        return n_cp * ((ml + rows - 1) / rows);
-    };
-    int64_t total = 0;
-    if (on) {
-        int64_t mine = 0;
-        for (int k = tid; k < h.n_nodes; k += 256) {
-            int n_cp, rows;
-            mine += items_of(k, n_cp, rows);
-        }
-        (void)block_exscan<256>(mine, lds4, total);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        first = total > 0 ? atomicAdd(&w.panel_total[height], (int)total) : 0;
-        w.panel_on[g] = on;
-        w.open_cnt[g] = 0;
-    }
-    __syncthreads();
-    int run = first;
-    for (int k0 = 0; on && k0 < h.n_nodes; k0 += 256) {
-        int n_cp = 1, rows = 0;
-        const int64_t c = k0 + tid < h.n_nodes ? items_of(k0 + tid, n_cp, rows) : 0;
-        int64_t sum;
-        const int64_t pre = block_exscan<256>(c, lds4, sum);
-        node0[tid] = (int)pre;
-        node_cp[tid] = n_cp;
-        node_rows[tid] = rows;
-        __syncthreads();
-        for (int i = tid; i < (int)sum; i += 256) {
-            int lo = 0, hi = 256;            // the last node whose first item is not behind i (empty ones share their successor's)
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (node0[mid] <= i)
-                    lo = mid;
-                else
-                    hi = mid;
-            }
-            const int q = i - node0[lo];
-            w.panel_items[run + i] = make_int4(g, k0 + lo, (q % node_cp[lo]) * kPanelCols, q / node_cp[lo] * node_rows[lo]);
-        }
-        run += (int)sum;
-        __syncthreads();
-    }
-}
-
 struct PanelArgs {
     PoolDesc pool;
     WorkDesc w;
@@ -194,15 +53,6 @@ struct PanelArgs {
     int32_t height;
     float thr_floor;
 };
-
-// The kernel's arguments read from memory again: what only the end of an item needs would otherwise sit in scalar registers, and
-// spilled from there in vector registers, throughout.
-__device__ __forceinline__ const PanelArgs &panel_args_again()
-{
-    uint64_t p = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const PanelArgs *)(const __attribute__((address_space(4))) PanelArgs *)p;
-}
 
 __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args)
 {
@@ -391,7 +241,7 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
 
         // ---- the list's pairs go out to the pair list; what does not fit there is finished here, a wavefront per pair
         __syncthreads();
-        const PanelArgs &again = panel_args_again();
+        const PanelArgs &again = kernel_args_again<PanelArgs>();
         const PoolDesc &pool = again.pool;
         const WorkDesc &w = again.w;
         const HeightDesc &h = again.h;
@@ -402,6 +252,8 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
         if (tid == 0 && n > 0) {
             lds_first = atomicAdd(w.n_pairs, n);
             atomicAdd(&w.open_cnt[g], n);
+            if (n > kWholeTile)
+                w.whole[g] = 1;
         }
         __syncthreads();
         const int first = n > 0 ? lds_first : 0;
@@ -475,8 +327,10 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
                             emit_candidate(w.cand_cnt, w.cand_idx, w.cand_val, cbase + col, w.cand_cap, row0 + row, cs);
                     }
                 }
-                if (lane == 0)
+                if (lane == 0) {
                     atomicAdd(&w.open_cnt[g], DENSE + 1);
+                    w.whole[g] = 1;
+                }
             }
         }
         break;
@@ -484,12 +338,8 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
 }
 
 // The panel kernel's share of a height's similarity step; the ring kernel takes the groups that are not panel_on.
-void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, const HeightDesc &prev, int height,
-                             float thr_floor)
+void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor)
 {
-    panel_items_kernel<<<w.G, 256, 0, s>>>(w, h, prev, height);
-    const int64_t rows = (int64_t)w.G * h.total_l_cap;
-    panel_rows_kernel<<<(unsigned)((rows + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor);
     const int64_t items = ((int64_t)w.G * h.panel_items + 255) / 256 * 256;
     similarity_panel_kernel<<<(unsigned)items, 512, 0, s>>>(PanelArgs{pool, w, h, height, thr_floor});
 }

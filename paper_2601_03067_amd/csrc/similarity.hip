@@ -42,7 +42,7 @@
 // the iteration the same ring gave it one to two.
 #include <type_traits>
 
-#include "common.h"
+#include "items.h"
 
 namespace kvfuse {
 
@@ -72,7 +72,7 @@ struct EarlyArgs {
     float *pair_head;
     int32_t *n_pairs;
     int32_t pair_cap;
-    int32_t *open_cnt;
+    int32_t *open_cnt, *whole;
 };
 
 template <typename T> struct MmaV;
@@ -791,6 +791,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     if (tid == 0) {
                         lds_ncand = n_kept;
                         atomicAdd(&early.open_cnt[g], LIMIT + 1);
+                        early.whole[g] = 1;
                     }
                     whole = true;
                     n_slices = nk_full;
@@ -922,25 +923,17 @@ __global__ void similarity_clear_kernel(unsigned long long *__restrict__ best_pa
 // time are then one patch (or what is left of a node and the start of the next): they start together, do equal work,
 // and share 8 panels and at most 4 row chunks in that XCD's L2.  Laid out from the capacities instead, a third of the
 // items of an upper height had nothing to do, ended at once and let the patches of an XCD drift apart.
-__device__ __forceinline__ int items_of_node(int ml, int mr, int bm, int bn, int &n_cp, int &rt, int &n_rc)
-{
-    n_cp = (mr + bn - 1) / bn;
-    const int n_rtile = (ml + bm - 1) / bm;
-    rt = min((n_rtile + 3) / 4, 4);
-
-    n_rc = rt > 0 ? (n_rtile + rt - 1) / rt : 0;
-    return n_cp * n_rc;
-}
-
-// First item of every node of a group (exclusive scan over the nodes) and the group's number of items.
-__global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
+// First item of every node of a group (exclusive scan over the nodes) and the group's number of items; or the group's items for the
+// panel kernel.  What the tests of this height leave open is counted from here on.
+__global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int height, int bm, int bn)
 {
     __shared__ int64_t lds4[4];
     const int g = blockIdx.x, tid = threadIdx.x;
     int32_t *base = w.dyn_base + (int64_t)g * w.dyn_stride;
-    if (w.early_nk && !w.panel_on && tid == 0)      // (a height of the panel kernel has begun with that: panel_items_kernel)
-        w.open_cnt[g] = 0;
-    if (w.panel_on && w.panel_on[g]) {        // this group's share of the height is the panel kernel's
+    const bool panel = w.panel_on && panel_items_of_group(w, h, prev, height, g);
+    if (w.early_nk && tid == 0)
+        w.open_cnt[g] = w.whole[g] = 0;
+    if (panel) {                                // this group's share of the height is the panel kernel's
         if (tid == 0)
             w.dyn_count[g] = 0;
         return;
@@ -967,10 +960,13 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     }
 }
 
-// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is.
-__global__ __launch_bounds__(256) void items_fill_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
+// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is; and one per left block for
+// the panel kernel's operands.
+__global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, float thr_floor, int bm, int bn)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (w.panel_on)
+        panel_row(pool, w, h, thr_floor, i);
     if (i >= (int64_t)w.G * h.item_cap)
         return;
     const int g = (int)(i / h.item_cap);
@@ -1000,15 +996,19 @@ __global__ __launch_bounds__(256) void items_fill_kernel(WorkDesc w, HeightDesc 
 }
 
 template <typename T, bool BIG>
-static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor, float *dense_s)
+static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor, float *dense_s,
+                        const HeightDesc *prev, int height)
 {
     const int64_t total = (int64_t)w.G * h.item_cap;
     if (total <= 0)
         return;
     {
         const int bm = BIG ? 256 : 128;
-        items_count_kernel<<<w.G, 256, 0, s>>>(w, h, bm, bm);
-        items_fill_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(w, h, bm, bm);
+        const int64_t rows = w.panel_on ? (int64_t)w.G * h.total_l_cap : 0;
+        items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
+        items_fill_kernel<<<(unsigned)((std::max(total, rows) + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor, bm, bm);
+        if (w.panel_on)
+            launch_similarity_panel(s, pool, w, h, height, thr_floor);
     }
     SimArgs A;
     A.G = w.G; A.n = w.n; A.n_slots = w.n_slots; A.r_stride = w.r_stride; A.cand_cap = w.cand_cap; A.P = pool.P;
@@ -1020,7 +1020,7 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     A.thr_floor = thr_floor;
     A.total_s = h.total_s;
     const unsigned grid = (unsigned)(((total + 31) / 32) * 32);      // whole quads on every XCD
-    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt};
+    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt, w.whole};
 #define KVF_SIM_LAUNCH(D, PF, EA)                                                                                          \
     similarity_ring_kernel<T, BIG, D, PF, EA><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
         A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_count, h.l_off, h.r_off, \
@@ -1145,7 +1145,7 @@ static void launch_small(hipStream_t s, const PoolDesc &pool, const WorkDesc &w,
 }
 
 void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor,
-                       float *dense_s, bool cleared)
+                       float *dense_s, bool cleared, const HeightDesc *prev, int height)
 {
     const int64_t cols = (int64_t)w.G * w.r_stride;
     if (cols > 0 && !cleared)
@@ -1159,19 +1159,19 @@ void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
             launch_small<float>(s, pool, w, h, thr_floor);
     } else if (w.q8.k) {
         if (big)
-            launch_ring<fp8_t, true>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<fp8_t, true>(s, pool, w, h, thr_floor, dense_s, prev, height);
         else
-            launch_ring<fp8_t, false>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<fp8_t, false>(s, pool, w, h, thr_floor, dense_s, prev, height);
     } else if (pool.dtype == KVFUSE_BF16) {
         if (big)
-            launch_ring<bf16_t, true>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<bf16_t, true>(s, pool, w, h, thr_floor, dense_s, prev, height);
         else
-            launch_ring<bf16_t, false>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<bf16_t, false>(s, pool, w, h, thr_floor, dense_s, prev, height);
     } else {
         if (big)
-            launch_ring<float, true>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<float, true>(s, pool, w, h, thr_floor, dense_s, prev, height);
         else
-            launch_ring<float, false>(s, pool, w, h, thr_floor, dense_s);
+            launch_ring<float, false>(s, pool, w, h, thr_floor, dense_s, prev, height);
     }
 }
 

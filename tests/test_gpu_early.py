@@ -24,7 +24,7 @@ def _case(which):
         return wl.llama8b_bff(n_req=6, tokens=16 * 220, layers=20, kv_heads=2, prefix_tokens=16 * 5, near_pool=60, **bff), 2.35, 64
     if which == "dense":                                     # most tiles hold more related pairs than are finished one by one
         return wl.zipf_bff(n_req=8, tokens=32 * 150, layers=12, kv_heads=2, pool=150, t=32, d=64, thr=0.9), 0.0, 64
-    if which == "pair_list_full":                            # 2.4 open pairs per left block; the list holds 1.6
+    if which == "pair_list_full":                            # 2.4 open pairs per left block, the list holds 1.6: in the panel kernel
         return wl.llama8b_bff(n_req=2, tokens=16 * 1300, layers=8, kv_heads=2, prefix_tokens=0, near_pool=560, near_frac=1.0, **bff), 0.0, 64
     if which == "pair_list_full_long":                       # the same behind a test that comes too late for the panel kernel: in the ring kernel
         return wl.llama8b_bff(n_req=2, tokens=16 * 1300, layers=8, kv_heads=2, prefix_tokens=0, near_pool=560, near_frac=1.0, **bff), 1.3, 64
