@@ -42,6 +42,9 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
     __shared__ unsigned long long tgt_mask[kTinyEntries];      // merges of a height: members (bits of the right set) of a target ...
     __shared__ int32_t tgt[kTinyEntries], tgt_right[kTinyEntries];      // ... its place in ids, and the right set's
     __shared__ int32_t cnt[kTinySlots], counters[8], n_tgt;
+    // by column, as the work arrays have them at the end: assignments, and the last height's cosines above the screen's floor
+    __shared__ int32_t col_assign[kTinyEntries], col_cnt[kTinyEntries];
+    __shared__ float col_val[kTinyEntries][kTinyEntries];
 
     const PoolDesc &pool = A.pool;
     const TableDesc &tab = A.tab;
@@ -66,13 +69,10 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         counters[tid] = 0;
     if (tid == 0)
         n_tgt = 0;
-    // What single steps behind the call read and this kernel has no other use for: no open column, no target waits for a merge.
-    for (int c = tid; c < w.r_stride; c += NT) {
-        w.best_packed[(int64_t)g * w.r_stride + c] = 0ull;
-        w.cand_cnt[(int64_t)g * w.r_stride + c] = 0;
+    if (tid < w.r_stride) {
+        col_assign[tid] = -1;
+        col_cnt[tid] = 0;
     }
-    if (g == 0 && tid < A.n_heights)
-        w.n_active[tid] = w.n_refine[tid] = w.n_pairs_all[tid] = 0;
     __syncthreads();
     if (tid < n) {
         const int p = tab.bt[gn + tid], src = w.leaf_src[tid];
@@ -133,7 +133,7 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         // ---- similarity and assignment, a wavefront per right block
         for (int k = n0, j = wave; k < n1; ++k) {
             const int4 nd = w.tiny_nodes[2 * k];            // left and right offset, left and right slot
-            const int64_t col0 = (int64_t)g * w.r_stride + w.tiny_nodes[2 * k + 1].y;
+            const int col0 = w.tiny_nodes[2 * k + 1].y;
             const int ml = cnt[nd.z], mr = cnt[nd.w];
             for (; j < mr; j += NW) {
                 const int b = __builtin_amdgcn_readfirstlane(ids[nd.y + j]);
@@ -195,17 +195,11 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                     top = fmaxf(top, __shfl_xor(top, off, 64));
                 const int n_listed = __popcll(__ballot(listed));
                 const int contenders = __popcll(__ballot(listed && (double)val >= (double)top - 2.0 * A.band));
-                if (hgt + 1 == A.n_heights) {                // the last height's lists stay, as they do launch by launch
-                    const int slot = __popcll(__ballot(listed) & ((1ull << lane) - 1ull));
-                    if (listed && slot < w.cand_cap) {
-                        w.cand_idx[(col0 + j) * w.cand_cap + slot] = lane;
-                        w.cand_val[(col0 + j) * w.cand_cap + slot] = val;
-                    }
-                    if (lane == 0)
-                        w.cand_cnt[col0 + j] = n_listed;
-                }
+                if (hgt + 1 == A.n_heights)
+                    col_val[col0 + j][lane] = listed ? val : -INFINITY;
                 if (lane == 0) {
-                    assign[nd.y + j] = w.assign[col0 + j] = bv > A.thr ? bi : -1;
+                    assign[nd.y + j] = col_assign[col0 + j] = bv > A.thr ? bi : -1;
+                    col_cnt[col0 + j] = hgt + 1 == A.n_heights ? n_listed : 0;
                     if (n_listed > w.cand_cap || (n_listed > 0 && !(contenders == 1 && (double)top > A.thr + 2.0 * A.band))) {
                         atomicAdd(&counters[2], 1);
                         if (fabs(bv - A.thr) <= A.band)
@@ -332,6 +326,9 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
     }
 
     // ---- rewrite
+    const TinyArgs &again = kernel_args_again<TinyArgs>();
+    const TableDesc &tab_end = again.tab;
+    const WorkDesc &w_end = again.w;
     for (int p = tid; p < P; p += NT)
         refs[p] = 0;
     __syncthreads();
@@ -347,7 +344,7 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                     break;
                 p = q;
             }
-            tab.bt[gn + tid] = p;
+            tab_end.bt[gn + tid] = p;
             atomicAdd(&refs[p], 1);
         }
     }
@@ -360,35 +357,58 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
             sk = own ? 1.0f : mk == 0.0 ? 0.0f : (float)(orig_k / mk);
             sv = own ? 1.0f : mv == 0.0 ? 0.0f : (float)(orig_v / mv);
         }
-        tab.scale_k[gn + tid] = sk;
-        tab.scale_v[gn + tid] = sv;
+        tab_end.scale_k[gn + tid] = sk;
+        tab_end.scale_v[gn + tid] = sv;
     }
     for (int q = tid; q < P; q += NT) {
-        tab.refcount[gp + q] = refs[q];
-        tab.remap[gp + q] = remap[q];
+        tab_end.refcount[gp + q] = refs[q];
+        tab_end.remap[gp + q] = remap[q];
     }
-    for (int s = tid; s < w.n_slots; s += NT)
-        w.set_cnt[(int64_t)g * w.n_slots + s] = cnt[s];
-    if (tid < n)
-        w.set_ids[gn + tid] = ids[tid];
+    for (int s = tid; s < w_end.n_slots; s += NT)
+        w_end.set_cnt[(int64_t)g * w_end.n_slots + s] = cnt[s];
+    // What the plan's view shows and single steps behind the call go by: sets, columns with the last height's candidates, and lists
+    // that hold nothing to do.  (Stored here, where no barrier waits for it, by the last wavefronts first: the first one has the free
+    // list to write.)
+    const int back = NT - 1 - tid;
+    if (back < n)
+        w_end.set_ids[gn + back] = ids[back];
+    if (back < w_end.r_stride) {
+        const int64_t at = (int64_t)g * w_end.r_stride + back;
+        w_end.assign[at] = col_assign[back];
+        w_end.cand_cnt[at] = col_cnt[back];
+        w_end.best_packed[at] = 0ull;
+    }
+    for (int c = NW - 1 - wave; c < w_end.r_stride; c += NW)
+        if (col_cnt[c] > 0) {
+            const float val = col_val[c][lane];
+            const unsigned long long listed = __ballot(val > -INFINITY);
+            const int slot = __popcll(listed & ((1ull << lane) - 1ull));
+            if (val > -INFINITY && slot < w_end.cand_cap) {
+                const int64_t at = ((int64_t)g * w_end.r_stride + c) * w_end.cand_cap + slot;
+                w_end.cand_idx[at] = lane;
+                w_end.cand_val[at] = val;
+            }
+        }
+    if (g == 0 && back < again.n_heights)
+        w_end.n_active[back] = w_end.n_refine[back] = w_end.n_pairs_all[back] = 0;
     if (tid < 8)
-        w.counters[(int64_t)g * 8 + tid] = counters[tid];
+        w_end.counters[(int64_t)g * 8 + tid] = counters[tid];
     if (wave == 0) {
         int freed = 0, live = 0;
         for (int q0 = 0; q0 < P; q0 += 64) {
             const int q = q0 + lane;
             const bool is_free = q < P && remap[q] >= 0;
             const unsigned long long m = __ballot(is_free);
-            if (is_free && A.free_list)
-                A.free_list[gp + freed + __popcll(m & ((1ull << lane) - 1ull))] = q;
+            if (is_free && again.free_list)
+                again.free_list[gp + freed + __popcll(m & ((1ull << lane) - 1ull))] = q;
             freed += __popcll(m);
             live += __popcll(__ballot(q < P && refs[q] > 0));
         }
         if (lane == 0) {
-            if (A.n_free)
-                A.n_free[g] = freed;
-            if (A.n_phys)
-                A.n_phys[g] = live;
+            if (again.n_free)
+                again.n_free[g] = freed;
+            if (again.n_phys)
+                again.n_phys[g] = live;
         }
     }
 }
