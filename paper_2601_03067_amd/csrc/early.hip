@@ -34,8 +34,8 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x)
 }
 
 // One wavefront per (group, sampled pair): the pair's bound after every length considered, in binary32 (the result only
-// steers how much work the product does).  Reads half a megabyte per group, HBM-bound for many groups (134 MB for 256 groups
-// of 4 KiB blocks, 33 us) and a few microseconds for few.  (One workgroup per group, the first form of this, took 95 us for
+// steers how much work the product does).  Reads half a megabyte per group of 4 KiB blocks, twice that where there is room for 128
+// pairs: HBM-bound for many groups (268 MB for 256 of them, 73 us; 64 pairs 33 us) and a few microseconds for few.  (One workgroup per group, the first form of this, took 95 us for
 // 256 groups and 174 us for 16 groups of 8 KiB blocks.)
 template <typename T>
 __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict__ kpool, const int32_t *__restrict__ bt, int G, int P, int n,
@@ -113,50 +113,54 @@ __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict_
         bounds[((int64_t)g * kSteps + len) * n_samples + s] = bound;
 }
 
-// One workgroup per group: for every length the bounds of all pairs are ranked; with their median m and the 16th and 84th
+// One workgroup per group: for every length, of the bounds of all pairs, with their median m and the 16th and 84th
 // percentiles, m + 4 s estimates what one unrelated pair in 30 000 reaches, about two of a 256 x 256 tile.  The
 // shortest length for which that stays below the candidate floor is taken.  Ranks instead of moments because a few per cent
 // of the pairs may be related ones; s is half the distance of the two percentiles (which varies less from sample to sample than
 // either's distance from the median), but not much less than the upper one's, where the bounds are skewed.
 // PER: sampled pairs per lane.  One pair and the upper percentile alone: 10, 12 or 14 slices of 64 for groups of one kind, 55 of 256
 // of them 12 or more.
+//
+// The three order statistics of a length are found bit by bit, by counting what lies below: every pair's rank against every other
+// took 30 us at two pairs a lane (11 at one), these counts take 14.
+__device__ __forceinline__ uint32_t ordered_bits(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+
 template <int PER>
 __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
                                                             int32_t *__restrict__ early_nk)
 {
     constexpr int N = PER * kSamples;
-    __shared__ float reach[kSteps], rank16[kSteps], rank50[kSteps], rank84[kSteps];
+    __shared__ float reach[kSteps];
     __shared__ int best;
     const int g = blockIdx.x, lane = threadIdx.x & 63;
     for (int len = threadIdx.x >> 6; len < kSteps; len += 16) {
-        float bound[PER];
-        int rank[PER];
+        uint32_t bound[PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            bound[i] = bounds[((int64_t)g * kSteps + len) * N + i * 64 + lane];
-            rank[i] = 0;
-        }
+        for (int i = 0; i < PER; ++i)
+            bound[i] = ordered_bits(bounds[((int64_t)g * kSteps + len) * N + i * 64 + lane]);
+        constexpr int rank[3] = {N * 16 / 100, N / 2, N * 84 / 100 + 1};
+        uint32_t at[3] = {0u, 0u, 0u};           // the largest number that at most so many bounds lie below: the one of that rank
+#pragma unroll 4
+        for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1)
 #pragma unroll
-        for (int j = 0; j < PER; ++j)
-#pragma unroll 8
-            for (int k = 0; k < kSamples; ++k) {
-                const float other = __shfl(bound[j], k, 64);
+            for (int k = 0; k < 3; ++k) {
+                int below = 0;
 #pragma unroll
                 for (int i = 0; i < PER; ++i)
-                    rank[i] += other < bound[i] || (other == bound[i] && (j < i || (j == i && k < lane)));
+                    below += __popcll(__ballot(bound[i] < (at[k] | bit)));
+                if (below <= rank[k])
+                    at[k] |= bit;
             }
+        float value[3];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {          // (the ranks are a permutation: one lane each)
-            if (rank[i] == N * 16 / 100)
-                rank16[len] = bound[i];
-            if (rank[i] == N / 2)
-                rank50[len] = bound[i];
-            if (rank[i] == N * 84 / 100 + 1)
-                rank84[len] = bound[i];
-        }
-        __builtin_amdgcn_wave_barrier();
+        for (int k = 0; k < 3; ++k)
+            value[k] = __uint_as_float(at[k] ^ ((at[k] >> 31) ? 0x80000000u : 0xFFFFFFFFu));
         if (lane == 0)
-            reach[len] = rank50[len] + 4.0f * fmaxf(0.5f * (rank84[len] - rank16[len]), 0.85f * (rank84[len] - rank50[len]));
+            reach[len] = value[1] + 4.0f * fmaxf(0.5f * (value[2] - value[0]), 0.85f * (value[2] - value[1]));
     }
     if (threadIdx.x == 0)
         best = nk;
