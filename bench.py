@@ -885,7 +885,8 @@ def main():
         "fp8_screen": fp8_screen,
         "graph_replay": graph_replay,
         "norms": {"ms": stage["norms"], "GBps": logi_bytes / (stage["norms"] * 1e-3) / 1e9},
-        "roofline": {"kernel": "similarity_ring_kernel (256 x 256 tile instance on the upper heights, 128 x 128 on the lowest)",
+        "roofline": {"kernel": ("similarity_ring_kernel (128 x 128 tiles on the lowest height, 256 x 256 above) and, where the product "
+                                "stops early, similarity_panel_kernel (the heights whose items fill the chip)"),
                      "bound": "mfma", "achieved": sim_tflops, "peak": peak,
                      "unit": "TFLOP/s", "frac": sim_tflops / peak, "traffic": traffic,
                      "frac_of_measured_mfma_rate": (sim_tflops / probes["mfma_bf16_random_operands_TFLOPs"]

@@ -209,7 +209,9 @@ int kvfuse_rewrite_block_table(kvfuse_ctx *ctx, const kvfuse_pool *pool, const k
 /* a1 .. a5 over all heights of the plan.  The similarity step may stop the product of a tile of pairs early, where a
  * bound on the rest already rules them out (tables, fused blocks and counters are those of the full product); table.refcount
  * serves as scratch memory until the rewrite counts references anew.  If stats is not NULL the call synchronises the stream at the end
- * and fills it; want_timing additionally brackets the stages with HIP events on the stream.  With stats the call
+ * and fills it; want_timing additionally brackets the stages with HIP events on the stream (a call on groups so small that
+ * all of it is one launch has no stages: timed, it is made stage by stage, with the same results, and its times are those of
+ * that, which the untimed call does not take).  With stats the call
  * also reports caller errors found on the device: ids outside [0, P), a table that shares blocks on entry
  * (fused before, or a prefix cache), and key blocks whose norm is not finite or, unless zero, outside [2^-40, 2^40]
  * (the similarity screen multiplies stored values in binary32; products of such blocks leave its range and a pair

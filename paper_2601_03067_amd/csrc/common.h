@@ -285,8 +285,8 @@ __device__ __forceinline__ double add_lane_xor(double x)
 }
 
 // Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane gets the result.  Six exchanges through LDS are a serial chain
-// that bounds the kernels of small calls; these exchanges are the same sums in the same order (4 requests of 8
-// blocks, binary32, 2 groups, with the restoring of the blocks: 128 -> 117 us; 256 requests of 128 blocks, most of them popular, 16 groups: 18.8 -> 18.5 ms).
+// that bounds the kernels of small calls; these exchanges are the same sums in the same order (256 requests of 128 blocks, most of
+// them popular, 16 groups: 18.8 -> 18.5 ms).
 __device__ __forceinline__ double wave_sum(double x)
 {
     x = add_lane_xor<32>(x);

@@ -113,6 +113,13 @@ __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict_
         bounds[((int64_t)g * kSteps + len) * n_samples + s] = bound;
 }
 
+// Numbers that are in the order of the floats.
+__device__ __forceinline__ uint32_t ordered_bits(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+
 // One workgroup per group: for every length, of the bounds of all pairs, with their median m and the 16th and 84th
 // percentiles, m + 4 s estimates what one unrelated pair in 30 000 reaches, about two of a 256 x 256 tile.  The
 // shortest length for which that stays below the candidate floor is taken.  Ranks instead of moments because a few per cent
@@ -123,12 +130,6 @@ __global__ __launch_bounds__(256) void sample_bounds_kernel(const T *__restrict_
 //
 // The three order statistics of a length are found bit by bit, by counting what lies below: every pair's rank against every other
 // took 30 us at two pairs a lane (11 at one), these counts take 14.
-__device__ __forceinline__ uint32_t ordered_bits(float x)
-{
-    const uint32_t b = __float_as_uint(x);
-    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-}
-
 template <int PER>
 __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
                                                             int32_t *__restrict__ early_nk)

@@ -75,7 +75,8 @@ struct Plan {
     // 4096 51 / 22; 16 x 2, 2048 87 / 47; 4 x 8, 4096 binary32 68 / 41, bfloat16 75 / 65; 6 x 8, 4096 binary32 96 / 64, bfloat16
     // 100 / 107 (launches); 4 x 16, 2048 68 / 94 (launches).  More workgroups than the chip holds take turns, while the launches share
     // their groups out better: 512 groups of 4 x 8, 2048 163 / 101, 1024 243 / 196, 2048 400 / 399, 4096 744 / 793; 1024 of 3 x 12,
-    // 4096 405 / 414.
+    // 4096 405 / 414.  Blocks of 4096 bytes in bfloat16, whose workgroups the chip holds one to a compute unit (with the restoring of
+    // the blocks between calls): 4 x 8 in 256 groups 135 / 93, 257 146 / 137, 512 159 / 141; 8 x 4 in 257 171 / 149, 512 212 / 163.
     bool tiny_pays() const
     {
         if (!work.tiny_nodes || work.G > kTinyGroups || pool.P > kTinyPool || pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) > kTinyBytes ||

@@ -9,9 +9,9 @@
 // is of rank two in (a, b): its right side is subtracted by the MFMA that starts a product (the two terms, each factor as three
 // bfloat16 parts: panel_left, panel_right), so that all that is left to do with an accumulator is to look at its sign.
 //
-// What bounds it: the MFMA units, busy 65 % of the cycles at the largest heights, at a clock that follows the power they take (1.8
-// to 2.0 GHz); the rest is the step from one 64-row stage to the next, where all wavefronts meet.  The ring kernel
-// (similarity.hip) has them busy 44 % there: it spends 14 000 of the 24 000 cycles of a 256 x 256 tile on the tests and on the way
+// What bounds it: the MFMA units, busy 65 % of the cycles at the largest heights, at a clock of 1.8 to 1.9 GHz
+// (profiles/cases_kernels.md); the rest is the step from one 64-row stage to the next, where all wavefronts meet.  The ring kernel
+// (similarity.hip) had them busy 43 % there: it spends 14 000 of the 24 000 cycles of a 256 x 256 tile on the tests and on the way
 // from tile to tile.  Similarity of the largest node of 512 ragged requests (8 groups, some 45 000 blocks in each set): 14.2 -> 9.4 ms;
 // the whole fusion of these 43.8 -> 32.5 ms, of 64 requests x 128 blocks in 256 groups (sets of 256 blocks and more) 19.9 -> 18.9 ms.
 // Tried and dropped: each wavefront at its own pace, with counts in LDS of what has landed and what is done instead of the

@@ -387,11 +387,10 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
     const int v_row = 4 * h2 + (l16 >> 2);
     const int v_off = v_row * ROW + ((2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1)) ^ v_swizzle(v_row)) * 16 + 8 * (l16 & 1);
 
-    // Bound: the softmax's vector instructions and the matrix instructions of a SIMD's wavefronts (per tile 270 of the former,
-    // 24 of the latter: 71 and 41 % of the cycles), at a clock of 1.6 GHz, which is what they leave of the power.  2048 queries of a
-    // 32768-token prompt, 4 layers of 8 KV heads, a third of the blocks fused: 7.15 -> 5.70 ms since table words and fragments come
-    // ahead of their use and the maximum is taken before the scales are applied; -> 5.06 ms since the tiles go straight into LDS
-    // and a third wavefront fits a SIMD (54 and 32 % before).
+    // Bound: the softmax's vector instructions, and the matrix instructions of a SIMD's other wavefronts beside them (per tile 270 of
+    // the former, 24 of the latter).  2048 queries of a 32768-token prompt, 4 layers of 8 KV heads, a third of the blocks fused:
+    // 7.15 -> 5.6 ms since table words and fragments come ahead of their use and the maximum is taken before the scales are
+    // applied; -> 5.2 ms since the tiles go straight into LDS and a third wavefront fits a SIMD.
     // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
     // before the first product, the V fragments and the next tiles' table words (which wait on the same counter) before the
     // softmax.  The compiler left to itself reads one fragment, waits, multiplies.

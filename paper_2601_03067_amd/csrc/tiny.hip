@@ -7,9 +7,9 @@
 // nothing to screen: every cosine is taken in binary64, by the operations of the re-check (assign.hip) in their order, and
 // merges and norms are summed in the order of the kernels they stand in for, so tables, blocks and norms are the same bits.
 //
-// What it costs now: 3 us of norms, then each height some 10 us, most of it the rows of a column one after the other, their blocks
-// 1 us from the L2.  4 requests of 8 blocks in binary32, 2 groups: the call 57 -> 29 us, with statistics and the restoring of the
-// blocks between calls 125 -> 73 us.
+// What it costs now: norms, then height by height the rows of a column one after the other, their blocks 1 us from the L2.  4 requests
+// of 8 blocks in binary32, 2 groups: one launch of 40 us (profiles/cases_kernels.md); with statistics and the restoring of the
+// blocks between calls 134 -> 72 us.
 #include "common.h"
 
 namespace kvfuse {
