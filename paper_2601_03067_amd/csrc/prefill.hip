@@ -36,6 +36,7 @@
 #include <algorithm>
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 namespace kvfuse {
@@ -44,12 +45,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A distinct stored block of the part before the chunk.  Its first two scale pairs stand beside it, so that most tiles need
 // one read of the table; the others are at inst_off + 2 ...
-struct PEntry {          // 48 bytes
-    int32_t phys, inst_off, inst_cnt, pad;
+struct PEntry {          // 48 bytes; what a tile's weights need is one load of its first 32
     float2 first, second;
     float sk_max, sk_min;            // over the instances
-    float pad2[2];
+    int32_t inst_off, inst_cnt;
+    int32_t phys, pad[3];
 };
+static_assert(sizeof(PEntry) == 48, "read word by word");
 
 struct PrefillArgs {
     const void *kpool, *vpool;
@@ -159,7 +161,35 @@ struct PWalk {
         sc.tok_base = pre ? kBefore : p < n_pieces ? A.chunk_begin + q * 16 : kNowhere;
         return sc;
     }
+
+    // the same of a piece before the chunk
+    __device__ __forceinline__ PRows rows_before(int p) const
+    {
+        const int b = block_of(p);
+        return PRows{eg[b].phys, p - b * ppb, kBefore};
+    }
+    __device__ __forceinline__ PScales scales_before(int p) const
+    {
+        typedef uint32_t words_t __attribute__((ext_vector_type(8), aligned(16)));
+        const words_t w = *(const KVF_TABLE words_t *)&eg[block_of(p)];
+        return PScales{(int32_t)w[7], (int32_t)w[6], make_float2(__uint_as_float(w[0]), __uint_as_float(w[1])),
+                       make_float2(__uint_as_float(w[2]), __uint_as_float(w[3])), __uint_as_float(w[4]), __uint_as_float(w[5]), kBefore};
+    }
 };
+
+// A uniform factor of vector instructions, in a vector register: gfx950 issues an fp32 multiplication, addition or fused one (and
+// and, xor) whose operands are all vector registers at twice the rate of one with a scalar register among them (measured 1.05
+// against 1.97 ns a wavefront and SIMD; so are shifts, maxima, v_perm and conversions, an exponential 3.4).
+__device__ static __forceinline__ float vector_register(float x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+__device__ static __forceinline__ uint32_t vector_register(uint32_t x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
 
 // The running maximum is taken before the softmax scale is applied, which must not turn it round: logits of a negative scale
 // are those of its size and the queries' opposites.  (In the split kernel once the context's first table words are asked for, so
@@ -228,7 +258,7 @@ __device__ static __forceinline__ float tile_weights_as(const PrefillArgs &A, co
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         const PScales &sc = half ? s1 : s0;
-        const float zs = base * sc.first.x, sv = sc.first.y;
+        const float zs = base * sc.first.x, sv = vector_register(sc.first.y);
 #pragma unroll
         for (int i = 8 * half; i < 8 * half + 8; ++i) {
             const float e = __builtin_amdgcn_exp2f(fmaf(z[i], zs, -m_new));
@@ -240,7 +270,7 @@ __device__ static __forceinline__ float tile_weights_as(const PrefillArgs &A, co
         if (n_inst > 1) {                // before the chunk, and visible to every query
             float2 next = sc.second;
             for (int q = 1; q < n_inst; ++q) {
-                const float zq = base * next.x, vq = next.y;
+                const float zq = base * next.x, vq = vector_register(next.y);
                 if (q + 1 < n_inst) {
                     const KVF_TABLE float2 *in = (const KVF_TABLE float2 *)A.inst + (sc.inst_off + q + 1);
                     next.x = in->x;
@@ -268,28 +298,46 @@ __device__ static __forceinline__ float tile_weights(const PrefillArgs &A, const
 }
 
 // The weights as B operands: the 8 values of MFMA jj are accumulators 8 jj .. 8 jj + 7, as a bfloat16 head (nearest) plus
-// the bfloat16 of what is left.
+// the bfloat16 of what is left.  Two values at a time: one conversion each for both heads and both rests.  (Left to itself the
+// compiler converts every head twice, once to subtract it.)
 __device__ static __forceinline__ void split_weights(const float (&pw)[16], bf16x8 (&p_hi)[2], bf16x8 (&p_lo)[2])
 {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t upper = vector_register(0xFFFF0000u);
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj)
+    for (int jj = 0; jj < 2; ++jj) {
+        uint32_t hi[4], lo[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float w = pw[8 * jj + e];
-            const __bf16 hb = (__bf16)w;
-            p_hi[jj][e] = hb;
-            p_lo[jj][e] = (__bf16)(w - (float)hb);
+        for (int e = 0; e < 4; ++e) {
+            const float a = pw[8 * jj + 2 * e], b = pw[8 * jj + 2 * e + 1];
+            hi[e] = vector_register(__builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b}));
+            lo[e] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(a - __uint_as_float(hi[e] << 16)), (__bf16)(b - __uint_as_float(hi[e] & upper))});
         }
+        p_hi[jj] = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+        p_lo[jj] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+    }
 }
 
-// 16 bytes per lane from `base` (uniform) + `off` straight into LDS, at `to` (uniform) + 16 lane.  In assembly, because the compiler
-// makes every LDS read wait for all such loads of its own, whichever buffer they are for; who issues one waits for it by hand.  (No
-// register is loaded.  The pause is for scalar registers that a vector instruction has just written, and for m0.)
-__device__ static __forceinline__ void load_to_lds(uint64_t base, uint32_t off, uint32_t to)
+// N times 1 KB from `base` (uniform), 16 bytes per lane from off[i] + 1024 i, straight into LDS, end to end from `to` (uniform): the
+// instruction's offset counts on either side.  In assembly, because the compiler makes every LDS read wait for all such loads of its
+// own, whichever buffer they are for; who issues one waits for it by hand.  (No register is loaded.  The pause is for scalar registers that
+// a vector instruction has just written, and for m0.)
+template <int N>
+__device__ static __forceinline__ void load_to_lds(uint64_t base, const uint32_t (&off)[N], uint32_t to)
 {
     typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
     const desc_t desc = {(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(desc), "s"(to) : "memory", "m0");
+    static_assert(N == 2 || N == 4, "16 rows of 128 or 256 bytes");
+    if constexpr (N == 4)
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 4\n\t"
+                     "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds" ::"v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(desc), "s"(to) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 4\n\t"
+                     "buffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds" ::"v"(off[0]), "v"(off[1]), "s"(desc), "s"(to) : "memory", "m0");
 }
 
 // WAVES: wavefronts of a SIMD that the registers are for, see roomy_pays.
@@ -361,16 +409,19 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
     const int piece = wave & 1, tensor = wave >> 1;
     const bf16_t *my_pool = tensor ? walk.vg : walk.kg;
     auto address_of = [&](const PRows &rw) __attribute__((always_inline)) { return (uint64_t)(uintptr_t)(my_pool + walk.first_row(A, rw)); };
+    // This lane's 16 bytes of each of the piece's 1 KB loads.  The swizzles of a load's rows are those of the first one's, but for bit 2 and
+    // up of a K chunk, which is flipped by the load's number: what is to be added is 1024 i, and the load's own offset does that.
+    const uint32_t ld_row = lane / RCH, ld_flip = tensor ? 0 : 64;
+    const uint32_t ld_off = ld_row * ROW + ((lane % RCH) ^ (tensor ? v_swizzle(ld_row) : k_swizzle(ld_row))) * 16;
     auto load = [&](int buf, uint64_t from) __attribute__((always_inline)) {
         const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&lds[buf][tensor][piece * 16 * ROW];
-        int at = lane;
-        asm volatile("" : "+v"(at));
+        uint32_t off[NLD];
+        off[0] = ld_off;
+        asm volatile("" : "+v"(off[0]));         // (the others are worked out anew for every tile: kept, they would cost registers)
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int row = i * (1024 / ROW) + at / RCH;
-            const int c = (at % RCH) ^ (tensor ? v_swizzle(row) : k_swizzle(row));
-            load_to_lds(from, (uint32_t)(row * ROW + c * 16), to + i * 1024);
-        }
+        for (int i = 1; i < NLD; ++i)
+            off[i] = off[0] ^ (ld_flip * i);
+        load_to_lds(from, off, to);
     };
 
     float m_run = -INFINITY, l_run = 0.0f;       // running maximum in base-2 units, running sum
@@ -394,7 +445,7 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
     // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
     // before the first product, the V fragments and the next tiles' table words (which wait on the same counter) before the
     // softmax.  The compiler left to itself reads one fragment, waits, multiplies.
-    auto compute = [&](const PScales &s0, const PScales &s1, int buf, auto &&tables) __attribute__((always_inline)) {
+    auto compute = [&](auto before, const PScales &s0, const PScales &s1, int buf, auto &&tables) __attribute__((always_inline)) {
         // (worked out anew for every tile: kept, the sixteen addresses of a tile would cost the registers of a third wavefront)
         int k_at = k_off, v_at = v_off;
         asm volatile("" : "+v"(k_at), "+v"(v_at));
@@ -437,11 +488,12 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
         tables();
         __builtin_amdgcn_sched_barrier(0);
         float pw[16];
-        const float corr = tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+        const float corr = before ? tile_weights_as<false>(A, s0, s1, z, h2, my_pos, m_run, l_run, pw)
+                                  : tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!ROOMY)
             read_v();
-        if (max(s0.tok_base, s1.tok_base) + 15 > pos_last_wg) {
+        if (!before && max(s0.tok_base, s1.tok_base) + 15 > pos_last_wg) {
             // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
@@ -491,25 +543,33 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
         if (!ROOMY || i < n_tiles)
             load(i, first[i]);
     int buf = 0, ahead = BUFS - 1;
-    for (int ti = 0; ti < n_tiles; ++ti) {
+    auto tile = [&](auto before, int ti) __attribute__((always_inline)) {
         // Tile ti has landed, for every wavefront behind the barrier; and every wavefront is done with tile ti - 1, whose place
         // the next load takes.
-        if (ROOMY && ti + 1 == n_tiles)
+        if (!before && ROOMY && ti + 1 == n_tiles)
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         else
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((BUFS - 2) * NLD) : "memory");
-        if (!ROOMY || ti + BUFS - 1 < n_tiles)
+        if (before || !ROOMY || ti + BUFS - 1 < n_tiles)
             load(ahead, address_of(next));
-        compute(s0, s1, buf, [&]() __attribute__((always_inline)) {
-            next = walk.rows(A, 2 * (ti + BUFS) + piece);
-            n0 = walk.scales(A, 2 * (ti + 1));
-            n1 = walk.scales(A, 2 * (ti + 1) + 1);
+        compute(before, s0, s1, buf, [&]() __attribute__((always_inline)) {
+            next = before ? walk.rows_before(2 * (ti + BUFS) + piece) : walk.rows(A, 2 * (ti + BUFS) + piece);
+            n0 = before ? walk.scales_before(2 * (ti + 1)) : walk.scales(A, 2 * (ti + 1));
+            n1 = before ? walk.scales_before(2 * (ti + 1) + 1) : walk.scales(A, 2 * (ti + 1) + 1);
         });
         s0 = n0;
         s1 = n1;
         ahead = buf;
         buf = buf + 1 == BUFS ? 0 : buf + 1;
-    }
+    };
+    // The tiles that lie before the chunk with all that is fetched meanwhile, which is most of a long walk, need no choice between entries
+    // and table, and no masks.
+    const int n_before = min(walk.n_pre / 2 - BUFS, n_tiles);
+    int ti = 0;
+    for (; ti < n_before; ++ti)
+        tile(std::true_type{}, ti);
+    for (; ti < n_tiles; ++ti)
+        tile(std::false_type{}, ti);
     if constexpr (!ROOMY)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may leave while loads are on their way into LDS
     l_run = halves_sum(l_run);
@@ -829,8 +889,7 @@ int kvfuse_prefill_plan_build(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kv
             en.phys = b[order[s].second];
             en.inst_off = (int32_t)pl->inst.size();
             en.inst_cnt = (int32_t)(e - s);
-            en.pad = 0;
-            en.pad2[0] = en.pad2[1] = 0.0f;
+            en.pad[0] = en.pad[1] = en.pad[2] = 0;
             for (size_t k = s; k < e; ++k) {
                 const float2 pair = make_float2(sk[(size_t)gi * nb_pre + order[k].second], sv[(size_t)gi * nb_pre + order[k].second]);
                 pl->inst.push_back(pair);
