@@ -128,9 +128,10 @@ struct WorkDesc {
     int4 *tiny_nodes;        // [nodes][2] (l_off, r_off, l_slot, r_slot), (out_slot, r_base, ...), height by height
     int32_t *tiny_ptr;       // [heights + 1] first node of every height
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
-    int4 *dyn_items;     // [G][item_cap of the height] node, first column, first row, rows
-    int32_t *dyn_base;   // [G][dyn_stride] first item of every node, and the total
-    int32_t *dyn_count;  // [G]
+    int4 *dyn_items;     // [G * item_cap of the height] node, first column, first row | row tiles, group: nodes' first items from the front, others from the end
+    int2 *dyn_base;      // [G][dyn_stride] first item of every node, such nodes before it
+    int4 *dyn_count;     // [G] items, nodes whose first items stand apart, most row tiles of an item
+    int32_t *dyn_total;  // [2] nodes' first items, others
     int32_t dyn_stride;
     Q8Desc q8;           // fp8 screen: the one-byte copies of the key blocks and what goes with them; q8.k null = off
 };

@@ -371,10 +371,11 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
             items = std::max(items, (size_t)h.item_cap);
             nodes = std::max(nodes, h.l_off.size());
         }
-        w.dyn_stride = (int32_t)(nodes + 1);
+        w.dyn_stride = (int32_t)nodes;
         w.dyn_items = cv.take<int4>((size_t)G * items);
-        w.dyn_base = cv.take<int32_t>((size_t)G * w.dyn_stride);
-        w.dyn_count = cv.take<int32_t>((size_t)G);
+        w.dyn_base = cv.take<int2>((size_t)G * w.dyn_stride);
+        w.dyn_count = cv.take<int4>((size_t)G);
+        w.dyn_total = cv.take<int32_t>(2);
     }
     size_t panel_room = 0;
     for (HostHeight &h : hs) {

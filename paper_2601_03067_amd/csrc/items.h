@@ -5,11 +5,11 @@
 
 namespace kvfuse {
 
-__device__ __forceinline__ int items_of_node(int ml, int mr, int bm, int bn, int &n_cp, int &rt, int &n_rc)
+__device__ __forceinline__ int items_of_node(int ml, int mr, int bm, int bn, int most, int &n_cp, int &rt, int &n_rc)
 {
     n_cp = (mr + bn - 1) / bn;
     const int n_rtile = (ml + bm - 1) / bm;
-    rt = min((n_rtile + 3) / 4, 4);
+    rt = min((n_rtile + 3) / 4, most);
 
     n_rc = rt > 0 ? (n_rtile + rt - 1) / rt : 0;
     return n_cp * n_rc;

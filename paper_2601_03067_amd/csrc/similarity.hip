@@ -105,6 +105,8 @@ __device__ __forceinline__ floatx16 mma_q8(const u32x4 al, const u32x4 ah, const
 }
 
 constexpr int kRingRowTiles = 4;   // most row tiles of one work item (the host's tile table keeps to it)
+constexpr int64_t kFewItems = 8192;   // room for items up to which one workgroup lays them out
+constexpr int kRowAlign = 128;     // every item's first row is a multiple of it
 
 // BIG: 256 x 256 tile, 8 wavefronts of 64 x 128, one workgroup per compute unit.  Otherwise 128 x 128, 4 wavefronts
 // of 64 x 64 and a 64 KB ring, two workgroups per compute unit: for nodes whose sets are smaller than a big tile.
@@ -128,12 +130,12 @@ constexpr int kRingRowTiles = 4;   // most row tiles of one work item (the host'
 template <typename T, bool BIG, bool DENSE, bool PREFIX, bool EARLY>
 __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_kernel(
     SimArgs A, const char *__restrict__ kpool, const float *__restrict__ inv_norm, const int32_t *__restrict__ set_ids,
-    const int32_t *__restrict__ set_cnt, const int4 *__restrict__ dyn_items, const int32_t *__restrict__ dyn_count,
+    const int32_t *__restrict__ set_cnt, const int4 *__restrict__ dyn_items, const int32_t *__restrict__ dyn_total,
     const int32_t *__restrict__ l_off,
     const int32_t *__restrict__ r_off, const int32_t *__restrict__ l_slot, const int32_t *__restrict__ r_slot,
     const int32_t *__restrict__ r_base, const int32_t *__restrict__ r_cap, const int64_t *__restrict__ s_base,
     unsigned long long *__restrict__ best_packed, int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand_idx,
-    float *__restrict__ cand_val, float *__restrict__ dense_s, const uint8_t *__restrict__ group_enable,
+    float *__restrict__ cand_val, float *__restrict__ dense_s,
     const float *__restrict__ rem, const Q8Desc q8, const EarlyArgs early)
 {
     static_assert(!(DENSE && (PREFIX || EARLY)) && !(PREFIX && EARLY), "the dense matrix is the full-length product");
@@ -186,30 +188,31 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     __shared__ int lds_cand_col[MAXC];
     __shared__ float lds_cand_val[MAXC];
 
-    // Each XCD walks a contiguous range of items.  Within it the four items of every quad are rotated by a number that
+    // Each XCD walks an eighth of the nodes' first items, then an eighth of the others, either in a row (items_fill_kernel).  Within
+    // them the four items of every quad are rotated by a number that
     // changes from quad to quad: the workgroups of an XCD are handed to its four shader engines in turn, in order, and items
     // come in patterns of four and eight (the tiles of a node), so without this the long tiles of every node land on the same
     // engine while the others wait (nodes of 2 x 2 tiles, one of them run to its full length: 1236 us, rotated 654 us).
-    const int per_xcd = gridDim.x >> 3;
-    const int seat = blockIdx.x >> 3, quad = seat >> 2;
-    const long long v = (long long)(blockIdx.x & 7) * per_xcd + (quad << 2) + ((seat + quad + (quad >> 2) + (quad >> 4)) & 3);
-    if (v >= (long long)A.G * A.n_items)
+    const int n_first = dyn_total[0], n_rest = dyn_total[1];
+    const int first_seats = (n_first + 7) >> 3, rest_seats = (n_rest + 7) >> 3;
+    int seat = blockIdx.x >> 3;
+    const bool is_first = seat < first_seats;
+    seat -= is_first ? 0 : first_seats;
+    const int seats = is_first ? first_seats : rest_seats, quad = seat >> 2;
+    if ((quad << 2) + 4 <= seats)
+        seat = (quad << 2) + ((seat + quad + (quad >> 2) + (quad >> 4)) & 3);
+    const int v = (int)(blockIdx.x & 7) * seats + seat;
+    if (seat >= seats || v >= (is_first ? n_first : n_rest))
         return;
-    const int g = (int)(v / A.n_items);
-    if (group_enable && !group_enable[g])      // a switched-off group keeps empty candidate lists: nothing fuses
-        return;
-    const int item = (int)(v - (long long)g * A.n_items);
-    if (item >= dyn_count[g])
-        return;
-    const int4 it_rec = dyn_items[(int64_t)g * A.n_items + item];
-    const int node = it_rec.x;
+    const int4 it_rec = dyn_items[is_first ? (int64_t)v : (int64_t)A.G * A.n_items - 1 - v];
+    const int node = it_rec.x, g = it_rec.w;
     const int col0 = it_rec.y;
-    const int row0 = it_rec.z;
+    const int row0 = it_rec.z & ~(kRowAlign - 1);
     const int ml = set_cnt[(int64_t)g * A.n_slots + l_slot[node]];
     const int mr = set_cnt[(int64_t)g * A.n_slots + r_slot[node]];
     if (col0 >= mr || row0 >= ml)
         return;
-    const int row_end = min(ml, row0 + min(it_rec.w, RT * BM));
+    const int row_end = min(ml, row0 + min(it_rec.z & (kRowAlign - 1), RT) * BM);
     const int32_t *__restrict__ l_ids = set_ids + (int64_t)g * A.n + l_off[node];
     const int32_t *__restrict__ r_ids = set_ids + (int64_t)g * A.n + r_off[node];
     const int64_t cbase = (int64_t)g * A.r_stride + r_base[node];
@@ -918,81 +921,198 @@ __global__ void similarity_clear_kernel(unsigned long long *__restrict__ best_pa
 
 // The work items of a height, laid out from the sizes the sets have NOW (they shrink as blocks fuse; the plan only knows
 // their capacities).  An item covers one panel of BN right blocks x up to 4 row tiles of BM left blocks of a node: a node
-// with c panels and a row tiles is cut into row chunks of rt = min(ceil(a / 4), 4) tiles, and its items are ordered in
+// with c panels and a row tiles is cut into row chunks of rt = min(ceil(a / 4), 4) tiles (or fewer, see items_count_kernel), and its items are ordered in
 // patches of 8 panels x all row chunks, row chunk by row chunk within a patch.  The 32 workgroups that an XCD runs at a
 // time are then one patch (or what is left of a node and the start of the next): they start together, do equal work,
 // and share 8 panels and at most 4 row chunks in that XCD's L2.  Laid out from the capacities instead, a third of the
 // items of an upper height had nothing to do, ended at once and let the patches of an XCD drift apart.
-// First item of every node of a group (exclusive scan over the nodes) and the group's number of items; or the group's items for the
-// panel kernel.  What the tests of this height leave open is counted from here on.
+//
+// The items of all groups stand in two lists, one after the other without gaps, the nodes' first items from the front of the room and
+// the others from its end, and each XCD takes an eighth of either.  A node's first tile holds the blocks that come first in
+// both sets, which repeat most where blocks repeat by popularity, so that it is the one that runs on to its full length;
+// started last, it would keep the height waiting (256 requests of popular blocks, 16 groups: 100 of 350 us).  Before, every group
+// had its own room, of the size that the plan knows: the workgroups of what is left of it, which have nothing to do, are handed out in order and had
+// to wait for compute units that were busy with the items before them, so that a group's items started when those of the group before
+// were done, and an XCD without a share in the occupied part of the rooms did nothing.  Heights 4 to 8 of those requests: 453, 386, 471, 581,
+// 659 -> 423, 310, 284, 295, 342 us, with fewer row tiles per item (items_count_kernel).
+
+// First item of every node of a group (exclusive scan over the nodes), how many nodes before it have any, and the group's number of
+// either; or the group's items for the panel kernel.  What the tests of this height leave open is counted from here on.
 __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int height, int bm, int bn)
 {
     __shared__ int64_t lds4[4];
     const int g = blockIdx.x, tid = threadIdx.x;
-    int32_t *base = w.dyn_base + (int64_t)g * w.dyn_stride;
+    int2 *base = w.dyn_base + (int64_t)g * w.dyn_stride;
     const bool panel = w.panel_on && panel_items_of_group(w, h, prev, height, g);
     if (w.early_nk && tid == 0)
         w.open_cnt[g] = w.whole[g] = 0;
-    if (panel) {                                // this group's share of the height is the panel kernel's
-        if (tid == 0)
-            w.dyn_count[g] = 0;
+    if (panel || (w.group_enable && !w.group_enable[g])) {      // this group's share of the height is the panel kernel's; or a
+        if (tid == 0)                                           // switched-off group, which keeps empty candidate lists: nothing fuses
+            w.dyn_count[g] = make_int4(0, 0, 1, 0);
         return;
     }
-    int64_t run = 0;
+    // Most row tiles of an item: as many as leave every compute unit 16 items (of all groups, taken to be like this one), one to
+    // four.  Long items cost less on the way from one to the next, but the height ends with the last of them: 256 requests of popular blocks,
+    // 16 groups, heights 6 to 8 of 9 to 12 tiles a compute unit 349, 443, 546 us with four, 347, 325, 308 with two, 280, 290, 332 with one.
+    int most = kRingRowTiles;
+    if (h.max_cap > 4 * bm) {                   // (up to four row tiles are items of one anyway)
+        int64_t tiles = 0, all;
+        for (int k = tid; k < h.n_nodes; k += 256) {
+            const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
+            tiles += (int64_t)((ml + bm - 1) / bm) * ((mr + bn - 1) / bn);
+        }
+        (void)block_exscan<256>(tiles, lds4, all);
+        if (all <= h.item_cap)                  // (there is room for the plan's bound on items of four, or for single tiles)
+            most = (int)min(max(all * w.G / (16 * 256), (int64_t)1), (int64_t)kRingRowTiles);
+    }
+    int64_t run = 0;                            // items in the lower half, nodes that have any in the upper one
     for (int k0 = 0; k0 < h.n_nodes; k0 += 256) {
         const int k = k0 + tid;
         int c = 0;
         if (k < h.n_nodes) {
             int n_cp, rt, n_rc;
             c = items_of_node(w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]], bm, bn,
-                              n_cp, rt, n_rc);
+                              most, n_cp, rt, n_rc);
         }
         int64_t total;
-        const int64_t pre = block_exscan<256>((int64_t)c, lds4, total);
+        const int64_t pre = run + block_exscan<256>((int64_t)c | (int64_t)(w.early_nk && c > 0) << 32, lds4, total);
         if (k < h.n_nodes)
-            base[k] = (int)min(run + pre, (int64_t)h.item_cap);
+            base[k] = make_int2(min((int)pre, h.item_cap), (int)(pre >> 32));
         run += total;
         __syncthreads();
     }
-    if (tid == 0) {
-        base[h.n_nodes] = (int)min(run, (int64_t)h.item_cap);
-        w.dyn_count[g] = (int)min(run, (int64_t)h.item_cap);      // (never more than the room: see the plan's bound)
-    }
+    if (tid == 0)
+        w.dyn_count[g] = make_int4(min((int)run, h.item_cap), (int)(run >> 32), most, 0);      // (never more than the room: see the plan's bound)
+}
+
+// Item `local` of a node: which panel and row chunk of the node it is.
+__device__ __forceinline__ int4 item_of_node(int local, int n_cp, int rt, int n_rc, int bm, int bn, int node, int g)
+{
+    const int patch = local / (8 * n_rc);
+    const int within = local - patch * 8 * n_rc;
+    const int np = min(8, n_cp - 8 * patch);
+    const int rc = within / np;
+    const int cp = 8 * patch + within - rc * np;
+    return make_int4(node, cp * bn, rc * rt * bm | rt, g);
 }
 
 // One thread per item slot: which node it falls into, and which panel and row chunk of that node it is; and one per left block for
 // the panel kernel's operands.
 __global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, float thr_floor, int bm, int bn)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    __shared__ int64_t lds4[4], before[256];
+    const int tid = threadIdx.x;
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + tid, n_slots = (int64_t)w.G * h.item_cap;
     if (w.panel_on)
         panel_row(pool, w, h, thr_floor, i);
-    if (i >= (int64_t)w.G * h.item_cap)
+    if (i0 >= n_slots)
+        return;
+    // what the groups before have, for each of the (at most 256) groups that these slots belong to: nodes' first items in the lower half,
+    // others in the upper one
+    auto counts = [&](int g) { const int4 c = w.dyn_count[g]; return (int64_t)c.y | (int64_t)(c.x - c.y) << 32; };
+    const int g0 = (int)(i0 / h.item_cap), g1 = (int)(min(i0 + 255, n_slots - 1) / h.item_cap);
+    int64_t sum = 0;
+    if (g0 > 0) {
+        int64_t mine = 0;
+        for (int g = tid; g < g0; g += 256)
+            mine += counts(g);
+        (void)block_exscan<256>(mine, lds4, sum);
+    }
+    if (g1 - g0 > 4) {
+        int64_t all;
+        before[tid] = block_exscan<256>(g0 + tid <= g1 ? counts(g0 + tid) : 0, lds4, all);
+        __syncthreads();
+    }
+    if (i >= n_slots)
         return;
     const int g = (int)(i / h.item_cap);
     const int item = (int)(i - (int64_t)g * h.item_cap);
-    if (item >= w.dyn_count[g])
+    int64_t at = sum;
+    if (g1 - g0 > 4)
+        at += before[g - g0];
+    else
+        for (int q = g0; q < g; ++q)
+            at += counts(q);
+    if (i == n_slots - 1) {
+        const int64_t all = at + counts(g);
+        w.dyn_total[0] = (int32_t)all;
+        w.dyn_total[1] = (int32_t)(all >> 32);
+    }
+    const int4 count = w.dyn_count[g];
+    if (item >= count.x)
         return;
-    const int32_t *base = w.dyn_base + (int64_t)g * w.dyn_stride;
+    const int2 *base = w.dyn_base + (int64_t)g * w.dyn_stride;
     int lo = 0, hi = h.n_nodes;             // the last node whose first item is <= item (empty nodes share a first item
     while (hi - lo > 1) {                   // with their successor and are skipped by taking the last)
         const int mid = (lo + hi) >> 1;
-        if (base[mid] <= item)
+        if (base[mid].x <= item)
             lo = mid;
         else
             hi = mid;
     }
     const int k = lo;
     int n_cp, rt, n_rc;
-    (void)items_of_node(w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]], bm, bn, n_cp,
-                        rt, n_rc);
-    const int local = item - base[k];
-    const int patch = local / (8 * n_rc);
-    const int within = local - patch * 8 * n_rc;
-    const int np = min(8, n_cp - 8 * patch);
-    const int rc = within / np;
-    const int cp = 8 * patch + within - rc * np;
-    w.dyn_items[(int64_t)g * h.item_cap + item] = make_int4(k, cp * bn, rc * rt * bm, rt * bm);
+    (void)items_of_node(w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]], bm, bn, count.z,
+                        n_cp, rt, n_rc);
+    const int2 own = base[k];
+    const int local = item - own.x;
+    const int64_t slot = !w.early_nk  ? n_slots - 1 - ((at >> 32) + item)
+                         : local == 0 ? (int64_t)((int32_t)at + own.y)
+                                      : n_slots - 1 - ((at >> 32) + item - own.y - 1);
+    w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, k, g);
+}
+
+// Both for few nodes and items, by one workgroup: a launch less (an ordinary height of a small call is some 8 launches of 5 us).
+__global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
+{
+    __shared__ int64_t lds16[16];
+    __shared__ int2 base[1024], sizes[1024];
+    const int tid = threadIdx.x, n = w.G * h.n_nodes;            // thread i: node i % n_nodes of group i / n_nodes
+    const int64_t n_slots = (int64_t)w.G * h.item_cap;
+    if (w.early_nk && tid < w.G)
+        w.open_cnt[tid] = w.whole[tid] = 0;
+    int ml = 0, mr = 0;
+    if (tid < n) {
+        const int g = tid / h.n_nodes, k = tid - g * h.n_nodes;
+        if (!w.group_enable || w.group_enable[g]) {
+            ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]];
+            mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
+        }
+    }
+    int most = kRingRowTiles;
+    if (h.max_cap > 4 * bm) {
+        int64_t tiles;
+        (void)block_exscan<1024>((int64_t)((ml + bm - 1) / bm) * ((mr + bn - 1) / bn), lds16, tiles);
+        if (tiles <= n_slots)
+            most = (int)min(max(tiles / (16 * 256), (int64_t)1), (int64_t)kRingRowTiles);
+    }
+    int n_cp, rt, n_rc;
+    const int c = items_of_node(ml, mr, bm, bn, most, n_cp, rt, n_rc);
+    int64_t total;
+    const int64_t pre = block_exscan<1024>((int64_t)c | (int64_t)(w.early_nk && c > 0) << 32, lds16, total);
+    base[tid] = make_int2((int)pre, (int)(pre >> 32));
+    sizes[tid] = make_int2(ml, mr);
+    const int n_first = (int)(total >> 32), n_items = (int)min((int64_t)(int32_t)total, n_slots);
+    if (tid == 0) {
+        w.dyn_total[0] = n_first;
+        w.dyn_total[1] = n_items - n_first;
+    }
+    __syncthreads();
+    for (int item = tid; item < n_items; item += 1024) {
+        int lo = 0, hi = n;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (base[mid].x <= item)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        const int2 own = base[lo], size = sizes[lo];
+        (void)items_of_node(size.x, size.y, bm, bn, most, n_cp, rt, n_rc);
+        const int g = lo / h.n_nodes, local = item - own.x;
+        const int64_t slot = !w.early_nk ? n_slots - 1 - item : local == 0 ? (int64_t)own.y : n_slots - 1 - (item - own.y - 1);
+        w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, lo - g * h.n_nodes, g);
+    }
 }
 
 template <typename T, bool BIG>
@@ -1005,8 +1125,12 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     {
         const int bm = BIG ? 256 : 128;
         const int64_t rows = w.panel_on ? (int64_t)w.G * h.total_l_cap : 0;
-        items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
-        items_fill_kernel<<<(unsigned)((std::max(total, rows) + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor, bm, bm);
+        if (!w.panel_on && (int64_t)w.G * h.n_nodes <= 1024 && total <= kFewItems) {
+            items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, bm, bm);
+        } else {
+            items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
+            items_fill_kernel<<<(unsigned)((std::max(total, rows) + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor, bm, bm);
+        }
         if (w.panel_on)
             launch_similarity_panel(s, pool, w, h, height, thr_floor);
     }
@@ -1019,13 +1143,13 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     A.nk_screen = (prefix ? w.screen_prefix * (int)sizeof(T) : A.row_bytes) >> 6;
     A.thr_floor = thr_floor;
     A.total_s = h.total_s;
-    const unsigned grid = (unsigned)(((total + 31) / 32) * 32);      // whole quads on every XCD
+    const unsigned grid = (unsigned)(((total + 7) / 8 + 1) * 8);     // the seats of both kinds of items, each rounded up
     const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt, w.whole};
 #define KVF_SIM_LAUNCH(D, PF, EA)                                                                                          \
     similarity_ring_kernel<T, BIG, D, PF, EA><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
-        A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_count, h.l_off, h.r_off, \
+        A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_total, h.l_off, h.r_off, \
         h.l_slot, h.r_slot, h.r_base, h.r_cap, h.s_base, w.best_packed, w.cand_cnt, w.cand_idx, w.cand_val, dense_s,           \
-        w.group_enable, w.rem_k, w.q8, early)
+        w.rem_k, w.q8, early)
     if (dense_s) {
         KVF_SIM_LAUNCH(true, false, false);
     } else if (prefix) {
