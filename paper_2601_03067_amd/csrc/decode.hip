@@ -57,6 +57,18 @@ template <> struct ToF32<float> {
     }
 };
 
+// Division by a number that the host knows, in a few scalar instructions (a workgroup of a short context is done in some 2 us; four
+// ordinary divisions took 8 % of it).  The estimate is the quotient or one less: x / d - x m / 2^32 < x / 2^32.
+struct Divisor {
+    uint32_t d, m;
+    __host__ explicit Divisor(int64_t x = 1) : d((uint32_t)std::max<int64_t>(x, 1)), m(d == 1 ? UINT32_MAX : (uint32_t)((1ull << 32) / d)) {}
+    __device__ __forceinline__ uint32_t of(uint32_t x) const
+    {
+        const uint32_t q = __umulhi(x, m);
+        return q + (x - q * d >= d);
+    }
+};
+
 struct DecodeArgs {
     const void *kpool, *vpool;
     const int32_t *bt;
@@ -68,7 +80,52 @@ struct DecodeArgs {
     int32_t P, n, t, kv_heads, layer_begin, B, Hq, rep, rep_pad, nsplit, blocks_per_split;
     int32_t gstride;   // groups between consecutive layers of the pool and the table: kv_heads, or 1 with all-head blocks
     float sm_scale;
+    bool by_xcd;       // see decode_place
+    uint32_t whole;    // groups in whole eights
+    Divisor per_group, left, requests, heads;
 };
+
+// What this workgroup works on.  Workgroups go to the eight XCDs in turn, and each XCD has an L2 of its own: all that read the
+// blocks of one (layer, KV head) are put on one XCD, eight such groups at a time, requests side by side before the next split of them, so that what
+// requests share is read while it is there.  The second half of the requests takes its splits from the end: else a common
+// prefix, which comes out of L2, and what is each request's own, which does not, would be read one after the other.  The groups
+// that are left, fewer than eight, alternate (a power of two of them then also shares as few XCDs as it can).
+// In the order of the grid several splits scatter a group over all XCDs, and of two splits every other XCD gets the second, which is empty for
+// most of ragged requests.  us, in the order of the grid / like this: 48 ragged requests of 512 to 8192 tokens, 8 groups, 141 / 133;
+// 18 requests of 5797 tokens, 16 groups, 119 / 99; 2 of 27945 tokens, 16 groups, 72.5 / 55.5; binary32, 17 ragged ones up to 3812 tokens, 96 groups
+// of four KV heads a layer, 492 / 399.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
+// 15.9; 494 of 107, 44 groups, 157 / 163), and so do all-head blocks, whose tokens all heads of a layer read (7 requests of 10813 tokens
+// 80 / 82; 139 of 438 20.8 / 18.9), and three, five, six or seven groups, which would not keep to an XCD (three: 38.7 / 40.3).
+// (Fewer than 2^32 workgroups: neither the layers nor the requests' KV heads of a call are more than 65535, and splits are taken where
+// there are fewer than 2048 of both.)
+struct DecodePlace {
+    int split, b, kvh, li;
+};
+__device__ __forceinline__ DecodePlace decode_place(const DecodeArgs &A)
+{
+    const uint32_t heads = (uint32_t)A.kv_heads, requests = (uint32_t)A.B;
+    uint32_t split = blockIdx.x, b, li = blockIdx.z, kvh;
+    if (A.by_xcd) {
+        const uint32_t id = split + (uint32_t)A.nsplit * (blockIdx.y + requests * heads * li), seat = id >> 3;
+        const uint32_t per_group = requests * (uint32_t)A.nsplit, eight = A.per_group.of(seat);
+        uint32_t group = eight * 8 + (id & 7), rest = seat - eight * per_group;
+        if (id >= A.whole * per_group) {
+            const uint32_t at = id - A.whole * per_group;
+            rest = A.left.of(at);
+            group = A.whole + at - rest * A.left.d;
+        }
+        split = A.requests.of(rest);
+        b = rest - split * requests;
+        if (2 * b >= requests)
+            split = (uint32_t)A.nsplit - 1 - split;
+        li = A.heads.of(group);
+        kvh = group - li * heads;
+    } else {
+        b = A.heads.of(blockIdx.y);
+        kvh = blockIdx.y - b * heads;
+    }
+    return {(int)split, (int)b, (int)kvh, (int)li};
+}
 
 // AH = all-head blocks (method section: one vector per block over all KV heads, one table per layer): the pool is
 // [layers][P][t][kv_heads][D], so the tokens of a block lie kv_heads * D elements apart, the KV head selects a
@@ -88,10 +145,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
     __shared__ float w_o[4][REP][D];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int split = blockIdx.x;
-    const int b = blockIdx.y / A.kv_heads;
-    const int kvh = blockIdx.y - b * A.kv_heads;
-    const int li = blockIdx.z;
+    const DecodePlace at = decode_place(A);
+    const int split = at.split, b = at.b, kvh = at.kvh, li = at.li;
     const int g = AH ? A.layer_begin + li : (A.layer_begin + li) * A.kv_heads + kvh;
     const int64_t row = AH ? (int64_t)A.kv_heads * D : (int64_t)D;      // elements from one token of a block to the next
     const int ctx = A.ctx_len[b];
@@ -284,10 +339,8 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
     __shared__ float w_m[NW][16], w_l[NW][16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int split = blockIdx.x;
-    const int b = blockIdx.y / A.kv_heads;
-    const int kvh = blockIdx.y - b * A.kv_heads;
-    const int li = blockIdx.z;
+    const DecodePlace at = decode_place(A);
+    const int split = at.split, b = at.b, kvh = at.kvh, li = at.li;
     const int g = (A.layer_begin + li) * A.kv_heads + kvh;
     const int ctx = A.ctx_len[b];
     const int ppb = A.t >> 4;                                           // 16-token pieces per block
@@ -611,6 +664,14 @@ int launch_decode(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int
         return KVFUSE_ENOMEM;
     if (tuples == 0)
         return KVFUSE_OK;
+    const int64_t groups = (int64_t)n_layers * kv_heads;
+    A.by_xcd = !all_heads && (groups >= 8 || 8 % groups == 0) &&
+               (A.nsplit > 1 || kv_heads % 8 != 0) && (int64_t)max_blocks * pool.t >= 1024;      // (8 KV heads, no splits: the grid's own order)
+    A.whole = (uint32_t)groups & ~7u;
+    A.per_group = Divisor((int64_t)B * A.nsplit);
+    A.left = Divisor((int64_t)n_layers * kv_heads % 8);
+    A.requests = Divisor(B);
+    A.heads = Divisor(kv_heads);
     if (pool.dtype == KVFUSE_BF16) {
         if (head_dim == 128) launch_decode_t<bf16_t, 128>(s, A, n_layers);
         else launch_decode_t<bf16_t, 64>(s, A, n_layers);

@@ -76,6 +76,20 @@ def test_against_binary64(t, d, heads, rep, all_heads):
     assert float(out[:, CONTEXTS.index(0)].abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("layers,heads,requests", [(1, 8, 1), (1, 8, 5), (2, 4, 3), (3, 3, 4), (11, 1, 2), (1, 2, 7), (4, 1, 6), (1, 1, 40),
+                                                   (3, 5, 140)])
+def test_workgroups_dealt_out_to_the_xcds(layers, heads, requests):
+    """Contexts from 1024 tokens on: every (layer, request, KV head, split) is done once, for whole eights of groups, what is left of
+    them, and one split of many requests."""
+    t, d = 16, 64
+    contexts = [1100 - 37 * b % 1090 for b in range(requests)]
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 3 + requests, layers, contexts=contexts)
+    q = torch.randn(layers, requests, heads * 2, d, generator=gen, device=DEV).to(torch.bfloat16)
+    ref = _reference(cache, t, d, heads, q, start, False, contexts)
+    out = _call(kb, cache, heads, q, start, max_blocks, False, contexts)
+    assert float((out - ref).abs().max()) < 1.2e-5                         # the same bound as above
+
+
 def test_rows_past_the_context_and_infinite_values():
     t, d, heads, rep = 32, 128, 2, 4
     kb, cache, start, max_blocks, gen = _setup(t, d, heads, 5)
