@@ -82,18 +82,19 @@ struct DecodeArgs {
     float sm_scale;
     bool by_xcd;       // see decode_place
     uint32_t whole;    // groups in whole eights
-    Divisor per_group, left, requests, heads;
+    Divisor per_group, left, requests, heads, split_tokens;
 };
 
 // What this workgroup works on.  Workgroups go to the eight XCDs in turn, and each XCD has an L2 of its own: all that read the
 // blocks of one (layer, KV head) are put on one XCD, eight such groups at a time, requests side by side before the next split of them, so that what
-// requests share is read while it is there.  The second half of the requests takes its splits from the end: else a common
-// prefix, which comes out of L2, and what is each request's own, which does not, would be read one after the other.  The groups
+// requests share is read while it is there.  The second half of the requests starts at the last split that has tokens: else
+// a common prefix, which comes out of L2, and what is each request's own, which does not, would be read one after the other (20 requests
+// of 1742 tokens, 16 groups, 31.4 / 28.5; from the last split whether it has tokens or not, 17 ragged requests 399 / 389).  The groups
 // that are left, fewer than eight, alternate (a power of two of them then also shares as few XCDs as it can).
 // In the order of the grid several splits scatter a group over all XCDs, and of two splits every other XCD gets the second, which is empty for
 // most of ragged requests.  us, in the order of the grid / like this: 48 ragged requests of 512 to 8192 tokens, 8 groups, 141 / 133;
 // 18 requests of 5797 tokens, 16 groups, 119 / 99; 2 of 27945 tokens, 16 groups, 72.5 / 55.5; binary32, 17 ragged ones up to 3812 tokens, 96 groups
-// of four KV heads a layer, 492 / 399.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
+// of four KV heads a layer, 492 / 389.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
 // 15.9; 494 of 107, 44 groups, 157 / 163), and so do all-head blocks, whose tokens all heads of a layer read (7 requests of 10813 tokens
 // 80 / 82; 139 of 438 20.8 / 18.9), and three, five, six or seven groups, which would not keep to an XCD (three: 38.7 / 40.3).
 // (Fewer than 2^32 workgroups: neither the layers nor the requests' KV heads of a call are more than 65535, and splits are taken where
@@ -116,8 +117,10 @@ __device__ __forceinline__ DecodePlace decode_place(const DecodeArgs &A)
         }
         split = A.requests.of(rest);
         b = rest - split * requests;
-        if (2 * b >= requests)
-            split = (uint32_t)A.nsplit - 1 - split;
+        if (2 * b >= requests) {
+            const uint32_t full = A.split_tokens.of((uint32_t)max(A.ctx_len[b] - 1, 0));         // splits before the last one with tokens
+            split = split > full ? split : full - split;
+        }
         li = A.heads.of(group);
         kvh = group - li * heads;
     } else {
@@ -672,6 +675,7 @@ int launch_decode(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int
     A.left = Divisor((int64_t)n_layers * kv_heads % 8);
     A.requests = Divisor(B);
     A.heads = Divisor(kv_heads);
+    A.split_tokens = Divisor((int64_t)A.blocks_per_split * pool.t);
     if (pool.dtype == KVFUSE_BF16) {
         if (head_dim == 128) launch_decode_t<bf16_t, 128>(s, A, n_layers);
         else launch_decode_t<bf16_t, 64>(s, A, n_layers);
