@@ -365,6 +365,39 @@ __device__ __forceinline__ int64_t block_exscan(int64_t x, int64_t (&waves)[NT /
     return pre + inc - x;
 }
 
+// Division by a number that the host knows, in a few scalar instructions (a workgroup of a short context is done in some 2 us; four
+// ordinary divisions took 8 % of it).  The estimate is the quotient or one less: x / d - x m / 2^32 < x / 2^32.
+struct Divisor {
+    uint32_t d, m;
+    __host__ explicit Divisor(int64_t x = 1) : d((uint32_t)std::max<int64_t>(x, 1)), m(d == 1 ? UINT32_MAX : (uint32_t)((1ull << 32) / d)) {}
+    __device__ __forceinline__ uint32_t of(uint32_t x) const
+    {
+        const uint32_t q = __umulhi(x, m);
+        return q + (x - q * d >= d);
+    }
+};
+
+// Workgroups go to the eight XCDs in turn, and each XCD has an L2 of its own.  Workgroup `id` of groups x per_group: which group it works
+// for and which of the group's workgroups it is, eight groups at a time, each on one XCD; the groups that are left, fewer than eight,
+// alternate.
+struct GroupsByXcd {
+    uint32_t whole;             // groups in whole eights
+    Divisor per_group, left;
+    __host__ GroupsByXcd() : whole(0) {}
+    __host__ GroupsByXcd(int64_t groups, int64_t wgs) : whole((uint32_t)groups & ~7u), per_group(wgs), left(groups % 8) {}
+    __device__ __forceinline__ void place(uint32_t id, uint32_t &group, uint32_t &rest) const
+    {
+        const uint32_t seat = id >> 3, eight = per_group.of(seat);
+        group = eight * 8 + (id & 7);
+        rest = seat - eight * per_group.d;
+        if (id >= whole * per_group.d) {
+            const uint32_t at = id - whole * per_group.d;
+            rest = left.of(at);
+            group = whole + at - rest * left.d;
+        }
+    }
+};
+
 // Prefix screen: share of a block's norm that lies beyond the prefix, from the sum of the tail squares and the norm,
 // rounded up to float with an absolute margin (the similarity kernel multiplies two of these into an upper bound).
 __device__ __forceinline__ float tail_share(double tail_squares, double norm)

@@ -57,18 +57,6 @@ template <> struct ToF32<float> {
     }
 };
 
-// Division by a number that the host knows, in a few scalar instructions (a workgroup of a short context is done in some 2 us; four
-// ordinary divisions took 8 % of it).  The estimate is the quotient or one less: x / d - x m / 2^32 < x / 2^32.
-struct Divisor {
-    uint32_t d, m;
-    __host__ explicit Divisor(int64_t x = 1) : d((uint32_t)std::max<int64_t>(x, 1)), m(d == 1 ? UINT32_MAX : (uint32_t)((1ull << 32) / d)) {}
-    __device__ __forceinline__ uint32_t of(uint32_t x) const
-    {
-        const uint32_t q = __umulhi(x, m);
-        return q + (x - q * d >= d);
-    }
-};
-
 struct DecodeArgs {
     const void *kpool, *vpool;
     const int32_t *bt;
@@ -81,8 +69,8 @@ struct DecodeArgs {
     int32_t gstride;   // groups between consecutive layers of the pool and the table: kv_heads, or 1 with all-head blocks
     float sm_scale;
     bool by_xcd;       // see decode_place
-    uint32_t whole;    // groups in whole eights
-    Divisor per_group, left, requests, heads, split_tokens;
+    GroupsByXcd groups;
+    Divisor requests, heads, split_tokens;
 };
 
 // What this workgroup works on.  Workgroups go to the eight XCDs in turn, and each XCD has an L2 of its own: all that read the
@@ -107,14 +95,8 @@ __device__ __forceinline__ DecodePlace decode_place(const DecodeArgs &A)
     const uint32_t heads = (uint32_t)A.kv_heads, requests = (uint32_t)A.B;
     uint32_t split = blockIdx.x, b, li = blockIdx.z, kvh;
     if (A.by_xcd) {
-        const uint32_t id = split + (uint32_t)A.nsplit * (blockIdx.y + requests * heads * li), seat = id >> 3;
-        const uint32_t per_group = requests * (uint32_t)A.nsplit, eight = A.per_group.of(seat);
-        uint32_t group = eight * 8 + (id & 7), rest = seat - eight * per_group;
-        if (id >= A.whole * per_group) {
-            const uint32_t at = id - A.whole * per_group;
-            rest = A.left.of(at);
-            group = A.whole + at - rest * A.left.d;
-        }
+        uint32_t group, rest;
+        A.groups.place(split + (uint32_t)A.nsplit * (blockIdx.y + requests * heads * li), group, rest);
         split = A.requests.of(rest);
         b = rest - split * requests;
         if (2 * b >= requests) {
@@ -670,9 +652,7 @@ int launch_decode(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int
     const int64_t groups = (int64_t)n_layers * kv_heads;
     A.by_xcd = !all_heads && (groups >= 8 || 8 % groups == 0) &&
                (A.nsplit > 1 || kv_heads % 8 != 0) && (int64_t)max_blocks * pool.t >= 1024;      // (8 KV heads, no splits: the grid's own order)
-    A.whole = (uint32_t)groups & ~7u;
-    A.per_group = Divisor((int64_t)B * A.nsplit);
-    A.left = Divisor((int64_t)n_layers * kv_heads % 8);
+    A.groups = GroupsByXcd(groups, (int64_t)B * A.nsplit);
     A.requests = Divisor(B);
     A.heads = Divisor(kv_heads);
     A.split_tokens = Divisor((int64_t)A.blocks_per_split * pool.t);

@@ -67,7 +67,23 @@ struct PrefillArgs {
     uint64_t ppb_inv;                // 2^40 / pieces per block, rounded up
     float sm_scale;                  // its size; a negative one is turned into the sign of the queries
     uint32_t q_sign;                 // 0, or the sign bits of two bfloat16
+    GroupsByXcd groups;              // (layer, KV head)
+    Divisor heads;
 };
+
+// What this workgroup works on: all that read the keys and values of one (layer, KV head) are put on one XCD (us, by rows of the grid,
+// which scatter them over all eight / like this: 2048 queries of a 32768-token prompt, 4 layers of 8 KV heads, 4541 / 4320; 31 of 7177
+// tokens, 16 layers of 4, 96.7 / 64.0; 10 of 2012 tokens, 31 layers of 4, 31.6 / 25.0).
+struct PrefillPlace {
+    int x, kvh, li;
+};
+__device__ static __forceinline__ PrefillPlace prefill_place(const PrefillArgs &A)
+{
+    uint32_t group, x;
+    A.groups.place(blockIdx.x + A.groups.per_group.d * (blockIdx.y + (uint32_t)A.kv_heads * blockIdx.z), group, x);
+    const uint32_t li = A.heads.of(group);
+    return {(int)x, (int)(group - li * (uint32_t)A.kv_heads), (int)li};
+}
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -365,11 +381,12 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kvh = blockIdx.y, li = blockIdx.z;
+    const PrefillPlace place = prefill_place(A);
+    const int kvh = place.kvh, li = place.li;
 
     // rows of this wavefront: lane & 31 = query row, lane >> 5 = which half of the tokens / head elements it holds
     const int qrow = lane & 31, h2 = lane >> 5;
-    const int wg_first = A.q_begin + (int)blockIdx.x * 4 * A.npw;
+    const int wg_first = A.q_begin + place.x * 4 * A.npw;
     const int pos_last_wg = min(A.q_end - 1, wg_first + 4 * A.npw - 1);
     const int pos_first = wg_first + wave * A.npw;                // may lie past the end: such a wavefront only helps loading
     const bool wave_live = pos_first < A.q_end;
@@ -608,9 +625,10 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kvh = blockIdx.y, li = blockIdx.z;
+    const PrefillPlace place = prefill_place(A);
+    const int kvh = place.kvh, li = place.li;
     const int qrow = lane & 31, h2 = lane >> 5;
-    const int pos_first = A.q_begin + (int)blockIdx.x * A.npw;
+    const int pos_first = A.q_begin + place.x * A.npw;
     const int pos_last = min(A.q_end - 1, pos_first + A.npw - 1);
     const int rs = qrow / A.rep_pad, hh = qrow - rs * A.rep_pad;
     const bool row_used = pos_first + rs <= pos_last && hh < A.rep;
@@ -991,9 +1009,12 @@ int kvfuse_prefill_attn(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_t
     const unsigned heads = (unsigned)plan->kv_heads, layers = (unsigned)plan->n_layers;
     const dim3 grid((unsigned)((nq + per_wg - 1) / per_wg), heads, layers);
     const dim3 sgrid((unsigned)((nq + plan->npw - 1) / plan->npw), heads, layers);
+    A.heads = Divisor(heads);
     const int64_t per_layer = heads, stored = (int64_t)plan->entries.size() / (per_layer * layers);
     const int64_t tiles = (stored * (pool->t / 16) + (plan->q_end - 1 - plan->chunk_begin) / 16 + 2) / 2;
-    if (split_pays(grid.x * per_layer * layers, sgrid.x * per_layer * layers, tiles, pool->d)) {
+    const bool split = split_pays(grid.x * per_layer * layers, sgrid.x * per_layer * layers, tiles, pool->d);
+    A.groups = GroupsByXcd(per_layer * layers, split ? sgrid.x : grid.x);
+    if (split) {
         if (pool->d == 128)
             prefill_split_kernel<128><<<sgrid, 64 * kSplitWaves, 0, c->stream>>>(A);
         else
