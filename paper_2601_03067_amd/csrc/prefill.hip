@@ -657,7 +657,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
     PScales n0 = walk.scales(A, 2 * wave), n1 = walk.scales(A, 2 * wave + 1);
     __builtin_amdgcn_sched_barrier(0);
     sign_queries(qf, A.q_sign);
-    for (int ti = wave; ti < n_tiles; ti += kSplitWaves) {
+    auto tile = [&](auto before, int ti) __attribute__((always_inline)) {
         const int64_t u0 = walk.first_row(A, r0), u1 = walk.first_row(A, r1);
         const PScales s0 = n0, s1 = n1;
         uint4 ka[KS];
@@ -671,10 +671,11 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 vr[jj][e] = *reinterpret_cast<const vrow_t *>(walk.vg + (jj ? u1 : u0) + (8 * (e >> 2) + 4 * h2 + (e & 3)) * D + DT * qrow);
-        r0 = walk.rows(A, 2 * (ti + kSplitWaves));
-        r1 = walk.rows(A, 2 * (ti + kSplitWaves) + 1);
-        n0 = walk.scales(A, 2 * (ti + kSplitWaves));
-        n1 = walk.scales(A, 2 * (ti + kSplitWaves) + 1);
+        const int p = 2 * (ti + kSplitWaves);
+        r0 = before ? walk.rows_before(p) : walk.rows(A, p);
+        r1 = before ? walk.rows_before(p + 1) : walk.rows(A, p + 1);
+        n0 = before ? walk.scales_before(p) : walk.scales(A, p);
+        n1 = before ? walk.scales_before(p + 1) : walk.scales(A, p + 1);
         __builtin_amdgcn_sched_barrier(0);     // all loads of the tile are on their way before the first wait
         floatx16 z;
 #pragma unroll
@@ -684,8 +685,9 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
         for (int ks = 0; ks < KS; ++ks)
             z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), __builtin_bit_cast(bf16x8, qf[ks]), z, 0, 0, 0);
         float pw[16];
-        const float corr = tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
-        if (s0.tok_base >= 0 || s1.tok_base >= 0) {
+        const float corr = before ? tile_weights_as<false>(A, s0, s1, z, h2, my_pos, m_run, l_run, pw)
+                                  : tile_weights(A, s0, s1, z, h2, my_pos, m_run, l_run, pw);
+        if (!before && (s0.tok_base >= 0 || s1.tok_base >= 0)) {
             // values of tokens that no query of this workgroup may see can be anything (tail of the last block): zero
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
@@ -718,7 +720,13 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
                 o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), p_hi[jj], o[dt], 0, 0, 0);
                 o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), p_lo[jj], o[dt], 0, 0, 0);
             }
-    }
+    };
+    // (as in the staged kernel: the tiles that lie before the chunk, with the one whose words are fetched meanwhile, apart)
+    int ti = wave;
+    for (; ti + kSplitWaves < walk.n_pre / 2; ti += kSplitWaves)
+        tile(std::true_type{}, ti);
+    for (; ti < n_tiles; ti += kSplitWaves)
+        tile(std::false_type{}, ti);
 
     l_run = halves_sum(l_run);
     // ---- merge: the upper half of the wavefronts hands its state to the lower half, lane by lane, until one is left
