@@ -7,9 +7,10 @@
 // nothing to screen: every cosine is taken in binary64, by the operations of the re-check (assign.hip) in their order, and
 // merges and norms are summed in the order of the kernels they stand in for, so tables, blocks and norms are the same bits.
 //
-// What it costs now: norms, then height by height the rows of a column one after the other, their blocks 1 us from the L2.  4 requests
-// of 8 blocks in binary32, 2 groups: one launch of 40 us (profiles/cases_kernels.md); with statistics and the restoring of the
-// blocks between calls 134 -> 72 us.
+// What it costs now: vector instructions of the cosines (a row is widened for every column it meets) and, between them, chains through
+// LDS: of 32 us the norms take 2, the cosines 10, sets and merges 14, the rewrite 5.  4 requests of 8 blocks in binary32, 2
+// groups: 40.6 -> 31.9 us since keys stay in LDS, four rows share the exchanges of their sums and a division, and blocks are asked for
+// one ahead; with statistics and the restoring of the blocks between calls 72 -> 66 us (134 launch by launch).
 #include "common.h"
 
 namespace kvfuse {
@@ -17,6 +18,9 @@ namespace kvfuse {
 // Sixteen wavefronts, or eight where a lane's share of a merge takes more than half of sixteen wavefronts' registers.
 template <typename T, int CPL>
 constexpr int kTinyThreads = CPL * Elem<T>::PER16 > 16 ? 512 : 1024;
+
+// Bytes of a group's keys that fit beside the tables (27 KB) in a compute unit's LDS.
+constexpr int64_t kTinyStage = 132 << 10;
 
 struct TinyArgs {
     PoolDesc pool;
@@ -30,10 +34,11 @@ struct TinyArgs {
 };
 
 // (The orders of summation below are those of block_norms_kernel, cosines_f64_reg and merge_group_kernel.)
-template <typename T, int CPL>
+// STAGED: the group's keys stay in LDS from the norm pass on (kTinyStage bytes of it), where a row is a tenth of a trip to the L2 away.
+template <typename T, int CPL, bool STAGED>
 __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyArgs A)
 {
-    constexpr int PER = Elem<T>::PER16, KW = CPL * PER == 16 ? 2 : 4;
+    constexpr int PER = Elem<T>::PER16, KW = !STAGED && CPL * PER == 16 ? 2 : 4;      // left rows side by side
     constexpr int NT = kTinyThreads<T, CPL>, NW = NT / 64;
     constexpr bool PAIR = PER == 4 && CPL == 4;      // a merge that merge_group_kernel gives to two wavefronts: two partial sums
     __shared__ double nk[kTinyPool], nv[kTinyPool];
@@ -45,6 +50,8 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
     // by column, as the work arrays have them at the end: assignments, and the last height's cosines above the screen's floor
     __shared__ int32_t col_assign[kTinyEntries], col_cnt[kTinyEntries];
     __shared__ float col_val[kTinyEntries][kTinyEntries];
+    __shared__ int4 nodes[kTinySlots];               // (a node is two of them, and fewer than half the slots are nodes')
+    extern __shared__ uint4 keys[];                  // STAGED: [P][chunks]
 
     const PoolDesc &pool = A.pool;
     const TableDesc &tab = A.tab;
@@ -56,6 +63,10 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
     T *const kp = (T *)pool.k + gp * pool.r, *const vp = (T *)pool.v + gp * pool.r;
     auto chunk_of = [&](int c) __attribute__((always_inline)) { return min(lane + 64 * c, chunks - 1); };
     auto in_block = [&](int c) __attribute__((always_inline)) { return lane + 64 * c < chunks; };
+    // chunk c of a lane's share of a key block
+    auto key_chunk = [&](int b, int c) __attribute__((always_inline)) {
+        return STAGED ? keys[b * chunks + chunk_of(c)] : reinterpret_cast<const uint4 *>(kp + (int64_t)b * pool.r)[chunk_of(c)];
+    };
     auto rows = [&](const T *pool_g, int b) __attribute__((always_inline)) { return reinterpret_cast<const uint4 *>(pool_g + (int64_t)b * pool.r); };
 
     // ---- the table: references, leaf sets, caller errors (tree_entries_kernel)
@@ -63,8 +74,10 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         refs[p] = 0;
         remap[p] = -1;
     }
-    for (int s = tid; s < w.n_slots; s += NT)
+    for (int s = tid; s < w.n_slots; s += NT) {
         cnt[s] = A.slot_init[s];
+        nodes[s] = w.tiny_nodes[s];
+    }
     if (tid < 8)
         counters[tid] = 0;
     if (tid == 0)
@@ -88,18 +101,30 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         ids[tid] = min(max(q, 0), P - 1);
     }
 
-    // ---- norms of all stored blocks, a wavefront per block
+    // ---- norms of all stored blocks, a wavefront per block, the next one on its way
+    uint4 ahead[CPL];
+    auto fetch = [&](int b) __attribute__((always_inline)) {
+        const uint4 *src = b >= P ? rows(vp, b - P) : rows(kp, b);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+            ahead[c] = src[chunk_of(c)];
+    };
+    if (wave < 2 * P)
+        fetch(wave);
     for (int b = wave; b < 2 * P; b += NW) {
         const bool is_v = b >= P;
         const int p = is_v ? b - P : b;
-        const uint4 *src = rows(is_v ? vp : kp, p);
         uint4 raw[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
-            raw[c] = src[chunk_of(c)];
+            raw[c] = ahead[c];
+        if (b + NW < 2 * P)
+            fetch(b + NW);
         double ss = 0.0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
+            if (STAGED && !is_v && in_block(c))
+                keys[p * chunks + lane + 64 * c] = raw[c];
             double x[PER];
             Elem<T>::widen(raw[c], x);
             if (in_block(c))
@@ -132,8 +157,8 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         const int n0 = w.tiny_ptr[hgt], n1 = w.tiny_ptr[hgt + 1];
         // ---- similarity and assignment, a wavefront per right block
         for (int k = n0, j = wave; k < n1; ++k) {
-            const int4 nd = w.tiny_nodes[2 * k];            // left and right offset, left and right slot
-            const int col0 = w.tiny_nodes[2 * k + 1].y;
+            const int4 nd = nodes[2 * k];                   // left and right offset, left and right slot
+            const int col0 = nodes[2 * k + 1].y;
             const int ml = cnt[nd.z], mr = cnt[nd.w];
             for (; j < mr; j += NW) {
                 const int b = __builtin_amdgcn_readfirstlane(ids[nd.y + j]);
@@ -141,18 +166,19 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                 uint4 braw[CPL];
 #pragma unroll
                 for (int c = 0; c < CPL; ++c)
-                    braw[c] = rows(kp, b)[chunk_of(c)];
+                    braw[c] = key_chunk(b, c);
                 double bv = -INFINITY, mine = -INFINITY;     // the largest cosine, its row; the cosine of row `lane`
                 int bi = -1;
                 for (int i0 = 0; i0 < ml; i0 += KW) {
                     int a[KW];
-                    uint4 araw[KW][CPL];
+                    uint4 araw[KW][STAGED ? 1 : CPL];
 #pragma unroll
                     for (int q = 0; q < KW; ++q) {
                         a[q] = __builtin_amdgcn_readfirstlane(ids[nd.x + min(i0 + q, ml - 1)]);
+                        if constexpr (!STAGED)
 #pragma unroll
-                        for (int c = 0; c < CPL; ++c)
-                            araw[q][c] = rows(kp, a[q])[chunk_of(c)];
+                            for (int c = 0; c < CPL; ++c)
+                                araw[q][c] = key_chunk(a[q], c);
                     }
                     double dot[KW];
 #pragma unroll
@@ -160,23 +186,39 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                         dot[q] = 0.0;
 #pragma unroll
                     for (int c = 0; c < CPL; ++c) {
+                        if constexpr (STAGED)
+#pragma unroll
+                            for (int q = 0; q < KW; ++q)
+                                araw[q][0] = key_chunk(a[q], c);
                         if (in_block(c)) {
                             double y[PER];
                             Elem<T>::widen(braw[c], y);
 #pragma unroll
                             for (int q = 0; q < KW; ++q) {
                                 double x[PER];
-                                Elem<T>::widen(araw[q][c], x);
+                                Elem<T>::widen(araw[q][STAGED ? 0 : c], x);
 #pragma unroll
                                 for (int i = 0; i < PER; ++i)
                                     dot[q] = fma(x[i], y[i], dot[q]);
                             }
                         }
                     }
+                    double all = 0.0;                        // four rows: their sums share exchanges and a division
+                    if constexpr (KW == 4) {
+                        const int row = wave_sum4_of(lane);
+                        const double na = nk[row == 0 ? a[0] : row == 1 ? a[1] : row == 2 ? a[KW - 2] : a[KW - 1]];
+                        const double d = wave_sum4(dot[0], dot[1], dot[KW - 2], dot[KW - 1]);
+                        all = na == 0.0 || nb == 0.0 ? 0.0 : d / (na * nb);
+                    }
 #pragma unroll
                     for (int q = 0; q < KW; ++q) {
-                        const double na = nk[a[q]], d = wave_sum(dot[q]);
-                        const double cs = na == 0.0 || nb == 0.0 ? 0.0 : d / (na * nb);
+                        double cs;
+                        if constexpr (KW == 4) {
+                            cs = read_lane(all, wave_sum4_lane(q));
+                        } else {
+                            const double na = nk[a[q]], d = wave_sum(dot[q]);
+                            cs = na == 0.0 || nb == 0.0 ? 0.0 : d / (na * nb);
+                        }
                         if (i0 + q < ml) {
                             mine = lane == i0 + q ? cs : mine;
                             if (cs > bv) {                   // ascending rows: the lowest of equal ones
@@ -214,8 +256,8 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
         __syncthreads();
         // ---- targets and their members, evicted blocks, surviving sets: a wavefront per node, a lane per block
         for (int k = n0 + wave; k < n1; k += NW) {
-            const int4 nd = w.tiny_nodes[2 * k];
-            const int out_slot = w.tiny_nodes[2 * k + 1].x;
+            const int4 nd = nodes[2 * k];
+            const int out_slot = nodes[2 * k + 1].x;
             const int ml = cnt[nd.z], mr = cnt[nd.w];
             int id = -1, a = -1;
             if (lane < mr) {
@@ -260,24 +302,48 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
             T *const pool_g = is_v ? vp : kp;
             const double *norm = is_v ? nv : nk;
             const int a = __builtin_amdgcn_readfirstlane(ids[tgt[t]]);
+            auto chunk = [&](int b, int c) __attribute__((always_inline)) {
+                return STAGED && !is_v ? key_chunk(b, c) : rows(pool_g, b)[chunk_of(c)];
+            };
+            auto member = [&](unsigned long long m) __attribute__((always_inline)) {
+                return __builtin_amdgcn_readfirstlane(was[tgt_right[t] + __builtin_ctzll(m)]);
+            };
             double acc[CPL][PER];
+            unsigned long long m = tgt_mask[t];      // (a target has a member)
+            uint4 mraw[CPL];
             {
+                uint4 araw[CPL];
+                const int b = member(m);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+                    araw[c] = chunk(a, c);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+                    mraw[c] = chunk(b, c);
                 const double na = norm[a], ia = na == 0.0 ? 0.0 : 1.0 / na;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    Elem<T>::widen(rows(pool_g, a)[chunk_of(c)], acc[c]);
+                    Elem<T>::widen(araw[c], acc[c]);
 #pragma unroll
                     for (int e = 0; e < PER; ++e)
                         acc[c][e] = in_block(c) ? acc[c][e] * ia : 0.0;
                 }
             }
-            for (unsigned long long m = tgt_mask[t]; m; m &= m - 1) {
-                const int b = __builtin_amdgcn_readfirstlane(was[tgt_right[t] + __builtin_ctzll(m)]);
-                const double nb = norm[b], ib = nb == 0.0 ? 0.0 : 1.0 / nb;
+            while (m) {
+                const double nb = norm[member(m)], ib = nb == 0.0 ? 0.0 : 1.0 / nb;
+                m &= m - 1;
+                uint4 braw[CPL];
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+                    braw[c] = mraw[c];
+                if (m)
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c)
+                        mraw[c] = chunk(member(m), c);
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
                     double y[PER];
-                    Elem<T>::widen(rows(pool_g, b)[chunk_of(c)], y);
+                    Elem<T>::widen(braw[c], y);
 #pragma unroll
                     for (int e = 0; e < PER; ++e)
                         acc[c][e] = in_block(c) ? fma(y[e], ib, acc[c][e]) : 0.0;
@@ -304,6 +370,8 @@ __global__ __launch_bounds__((kTinyThreads<T, CPL>)) void tiny_tree_kernel(TinyA
                 const uint4 packed = Store16<T>::pack(u, back);
                 if (in_block(c)) {
                     dst[lane + 64 * c] = packed;
+                    if (STAGED && !is_v)
+                        keys[a * chunks + lane + 64 * c] = packed;
 #pragma unroll
                     for (int e = 0; e < PER; ++e) {
                         double &s = PAIR && (c & 1) ? s1 : s0;
@@ -418,17 +486,25 @@ void launch_tiny_tree(hipStream_t s, const PoolDesc &pool, const TableDesc &tab,
 {
     const TinyArgs A{pool, tab, w, slot_init, n_heights, thr, band, thr_floor, free_list, n_free, n_phys};
     const int cpl = (pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 16 + 63) / 64;
-#define KVF_TINY(T)                                                               \
-    do {                                                                          \
-        if (cpl <= 1) tiny_tree_kernel<T, 1><<<pool.G, kTinyThreads<T, 1>, 0, s>>>(A);      \
-        else if (cpl <= 2) tiny_tree_kernel<T, 2><<<pool.G, kTinyThreads<T, 2>, 0, s>>>(A); \
-        else tiny_tree_kernel<T, 4><<<pool.G, kTinyThreads<T, 4>, 0, s>>>(A);               \
+    const int64_t key_bytes = (int64_t)pool.P * pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4);
+    const bool staged = key_bytes <= kTinyStage;
+#define KVF_TINY_CPL(T, CPL)                                                                                \
+    do {                                                                                                    \
+        if (staged) tiny_tree_kernel<T, CPL, true><<<pool.G, kTinyThreads<T, CPL>, (unsigned)key_bytes, s>>>(A); \
+        else tiny_tree_kernel<T, CPL, false><<<pool.G, kTinyThreads<T, CPL>, 0, s>>>(A);                    \
+    } while (0)
+#define KVF_TINY(T)                            \
+    do {                                       \
+        if (cpl <= 1) KVF_TINY_CPL(T, 1);      \
+        else if (cpl <= 2) KVF_TINY_CPL(T, 2); \
+        else KVF_TINY_CPL(T, 4);               \
     } while (0)
     if (pool.dtype == KVFUSE_BF16)
         KVF_TINY(bf16_t);
     else
         KVF_TINY(float);
 #undef KVF_TINY
+#undef KVF_TINY_CPL
 }
 
 }  // namespace kvfuse

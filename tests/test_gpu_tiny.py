@@ -34,7 +34,11 @@ CASES = [([1, 1], 16, 64, torch.bfloat16, 1, 1, 0),                      # one p
          ([1] * 64, 4, 64, torch.float32, 7, 2, 64),                     # the most entries, six heights, up to ten members a target
          ([2] * 9 + [12], 16, 64, torch.bfloat16, 1, 300, 0),            # one target takes everything
          ([4, 8, 3], 16, 64, torch.float32, 0, 1, 0),                    # nothing fuses
-         ([5], 16, 64, torch.bfloat16, 2, 1, 4)]                         # no height
+         ([5], 16, 64, torch.bfloat16, 2, 1, 4),                         # no height
+         ([8, 8, 8, 9], 16, 64, torch.float32, 9, 2, 0),                 # the most keys of 4096 bytes that stay in LDS ...
+         ([8, 8, 8, 9], 16, 64, torch.float32, 9, 2, 1),                 # ... and one more
+         ([11, 9, 13], 16, 128, torch.bfloat16, 7, 2, 0),                # the same in bfloat16
+         ([11, 9, 13], 16, 128, torch.bfloat16, 7, 2, 1)]
 
 
 def _inputs(rec, spare):
