@@ -455,10 +455,13 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
     const int v_row = 4 * h2 + (l16 >> 2);
     const int v_off = v_row * ROW + ((2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1)) ^ v_swizzle(v_row)) * 16 + 8 * (l16 & 1);
 
-    // Bound: the softmax's vector instructions, and the matrix instructions of a SIMD's other wavefronts beside them (per tile 270 of
-    // the former, 24 of the latter).  2048 queries of a 32768-token prompt, 4 layers of 8 KV heads, a third of the blocks fused:
+    // Bound: the softmax's vector instructions beside the matrix instructions of a SIMD's other wavefronts (per tile some 220 of
+    // the former, 24 of the latter; vector ALU busy 75 %, matrix units 51 %), at the clock that the board's power leaves for
+    // both (1.7 GHz at 1325 of 1400 W).  2048 queries of a 32768-token prompt, 4 layers of 8 KV heads, a third of the blocks fused:
     // 7.15 -> 5.6 ms since table words and fragments come ahead of their use and the maximum is taken before the scales are
-    // applied; -> 5.2 ms since the tiles go straight into LDS and a third wavefront fits a SIMD.
+    // applied; -> 5.2 ms since the tiles go straight into LDS and a third wavefront fits a SIMD; -> 4.5 ms since a tile takes 80 vector
+    // instructions less (addresses of its loads, the weights' halves, uniform factors in vector registers) and the tiles before the
+    // chunk have a loop of their own; -> 4.3 ms since a context's readers share an XCD.
     // Everything of a tile that waits for LDS is asked for at once, a product or a softmax ahead of its use: the K fragments
     // before the first product, the V fragments and the next tiles' table words (which wait on the same counter) before the
     // softmax.  The compiler left to itself reads one fragment, waits, multiplies.
@@ -609,7 +612,8 @@ __global__ __launch_bounds__(256, WAVES) void prefill_attn_kernel(PrefillArgs A)
 // by tile.  Every wavefront fetches its own tiles straight into registers and needs no one else until the sums are merged
 // through LDS at the end: no barriers, no staging, so eight tiles are in flight per workgroup.  The staged kernel shares
 // every tile among 4 x 32 rows instead, which is the better trade once its own grid fills the chip.  Bound: latency of a tile
-// (table words, rows, two products, one after the other); 200 queries of 4296 tokens, 8 KV heads: 252 -> 47 us.
+// (table words, rows, two products, one after the other; some 650 instructions, of which a wavefront issues one in seven
+// cycles); 200 queries of 4296 tokens, 8 KV heads: 252 -> 45 us.
 //   V^T fragment dt of a lane (m = lane & 31): element dt of the DT consecutive head elements DT m .. that it loads of its 8
 //   tokens, one v_perm per two values; the tokens are those whose weights the lane already holds.
 constexpr int kSplitWaves = 8;
@@ -787,6 +791,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void prefill_split_kernel(Pref
 //     512   28.1 / 14.5  30.1 / 26.7  31.2 / 38.1  34.2 / 51.5    23.9 / 18.1
 //    1024   45.2 / 17.7  51.4 / 32.3  52.1 / 47.9  53.3 / 62.9    43.7 / 24.4
 //    4096    178 / 46     178 / 87     168 / 120    182 / 165      155 / 62
+// (Both kernels have become 2 to 15 % faster since, which leaves the line where it is.)
 // (Without the second condition 96 queries over 112 tokens, 16 layers of one KV head, took 23.4 us where the staged kernel
 // takes 13.5.)
 constexpr int64_t kSplitBelow = 192;
