@@ -118,7 +118,7 @@ struct WorkDesc {
     float *pair_head;        // [pair_cap] ... and their product so far
     int32_t *n_pairs;        // counter of the current height
     int32_t pair_cap;
-    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; whether tiles were multiplied whole for them
+    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that were multiplied whole for them
     // panel kernel (panel.hip); panel_on null = not at this height
     int32_t *panel_on, *panel_on_mem;       // [G]
     u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand
@@ -130,7 +130,7 @@ struct WorkDesc {
     // similarity work items of the current height, built on the device from the sets' sizes (similarity.hip):
     int4 *dyn_items;     // [G * item_cap of the height] node, first column, first row | row tiles, group: nodes' first items from the front, others from the end
     int2 *dyn_base;      // [G][dyn_stride] first item of every node, such nodes before it
-    int4 *dyn_count;     // [G] items, nodes whose first items stand apart, most row tiles of an item
+    int4 *dyn_count;     // [G] items, nodes whose first items stand apart, most row tiles of an item, what holds of first items (similarity.hip)
     int32_t *dyn_total;  // [2] nodes' first items, others
     int32_t dyn_stride;
     Q8Desc q8;           // fp8 screen: the one-byte copies of the key blocks and what goes with them; q8.k null = off

@@ -105,8 +105,10 @@ __device__ __forceinline__ floatx16 mma_q8(const u32x4 al, const u32x4 ah, const
 }
 
 constexpr int kRingRowTiles = 4;   // most row tiles of one work item (the host's tile table keeps to it)
-constexpr int64_t kFewItems = 8192;   // room for items up to which one workgroup lays them out
+// Room for items up to which one workgroup lays them out: one a thread, 6 us (two launches 11); with several a thread, 10 to 14.
+constexpr int64_t kFewItems = 1024;
 constexpr int kRowAlign = 128;     // every item's first row is a multiple of it
+constexpr int kWholeFirst = 64;    // mark, beside an item's row tiles: the first of them is multiplied whole without a test before
 
 // BIG: 256 x 256 tile, 8 wavefronts of 64 x 128, one workgroup per compute unit.  Otherwise 128 x 128, 4 wavefronts
 // of 64 x 64 and a 64 KB ring, two workgroups per compute unit: for nodes whose sets are smaller than a big tile.
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     const int mr = set_cnt[(int64_t)g * A.n_slots + r_slot[node]];
     if (col0 >= mr || row0 >= ml)
         return;
-    const int row_end = min(ml, row0 + min(it_rec.z & (kRowAlign - 1), RT) * BM);
+    const int row_end = min(ml, row0 + min(it_rec.z & (kWholeFirst - 1), RT) * BM);
     const int32_t *__restrict__ l_ids = set_ids + (int64_t)g * A.n + l_off[node];
     const int32_t *__restrict__ r_ids = set_ids + (int64_t)g * A.n + r_off[node];
     const int64_t cbase = (int64_t)g * A.r_stride + r_base[node];
@@ -446,7 +448,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     // slices with its own counters.  Past the last slice of the last row tile both keep loading rows that exist (the
     // ids of the last row tile, the panel from its start), and those loads are only waited for, never read.
     int pf_kt_a = 0, pf_rt_a = 0, pf_kt_b = 0;
-    int lim_a = nk, lim_b = nk;          // (a tile that runs on to its full length moves these while it does)
+    bool guessed = EARLY && (it_rec.z & kWholeFirst) && nk != nk_full;
+    int lim_a = guessed ? nk_full : nk, lim_b = lim_a;     // (a tile that runs on to its full length moves these while it does)
 #define KVF_DMA_ADVANCE_A()                                                                                        \
     do {                                                                                                           \
         pa0 += 64; pa1 += 64;                                                                                      \
@@ -594,8 +597,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
     // group's test, and for a tile that the test does not settle a second pass over all of them.  (Going on from the
     // accumulators of the first pass would save a sixth of such a tile, but makes them live across the look and the two
     // K loops, which the register allocator answers with a second copy: 420 spilled registers.)
-    int it = 0, rt = 0, n_slices = nk;
-    bool whole = !EARLY || nk == nk_full;       // this pass ends with whole products
+    int it = 0, rt = 0, n_slices = guessed ? nk_full : nk;
+    bool whole = !EARLY || nk == nk_full || guessed;       // this pass ends with whole products
     for (;;) {
         const bool act_m1 = row_end - (row0 + rt * BM) > MT_STRIDE;
         // The fragments of the next row tile's first slice are on their way when the last slice is done.  They are waited for
@@ -780,8 +783,15 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 if (whole) {                         // the list may have run over: the surplus went out directly
                     __syncthreads();
                     n_kept = min(n_now, MAXC);
-                    if (tid == 0)
+                    if (tid == 0) {
                         lds_ncand = n_kept;
+                        if (guessed) {           // what its test would have left open, about
+                            atomicAdd(&early.open_cnt[g], min(n_now, LIMIT + 1));
+                            if (n_now > LIMIT)
+                                atomicAdd(&early.whole[g], 1);
+                        }
+                    }
+                    guessed = false;
                     whole = false;
                     n_slices = nk;
                 } else if (n_now <= MAXC && n_now - n_kept <= LIMIT) {
@@ -794,7 +804,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     if (tid == 0) {
                         lds_ncand = n_kept;
                         atomicAdd(&early.open_cnt[g], LIMIT + 1);
-                        early.whole[g] = 1;
+                        atomicAdd(&early.whole[g], 1);
                     }
                     whole = true;
                     n_slices = nk_full;
@@ -927,14 +937,27 @@ __global__ void similarity_clear_kernel(unsigned long long *__restrict__ best_pa
 // and share 8 panels and at most 4 row chunks in that XCD's L2.  Laid out from the capacities instead, a third of the
 // items of an upper height had nothing to do, ended at once and let the patches of an XCD drift apart.
 //
-// The items of all groups stand in two lists, one after the other without gaps, the nodes' first items from the front of the room and
-// the others from its end, and each XCD takes an eighth of either.  A node's first tile holds the blocks that come first in
-// both sets, which repeat most where blocks repeat by popularity, so that it is the one that runs on to its full length;
-// started last, it would keep the height waiting (256 requests of popular blocks, 16 groups: 100 of 350 us).  Before, every group
-// had its own room, of the size that the plan knows: the workgroups of what is left of it, which have nothing to do, are handed out in order and had
-// to wait for compute units that were busy with the items before them, so that a group's items started when those of the group before
-// were done, and an XCD without a share in the occupied part of the rooms did nothing.  Heights 4 to 8 of those requests: 453, 386, 471, 581,
-// 659 -> 423, 310, 284, 295, 342 us, with fewer row tiles per item (items_count_kernel).
+// The items of all groups stand in two lists without gaps, from the front of the room the first items of the nodes of groups that
+// multiplied tiles whole at the height before, from its end all others, and each XCD takes an eighth of either.  A node's first tile
+// holds the blocks that come first in both sets, which repeat most where blocks repeat by popularity, so that it is the one that runs
+// on to its full length; started last, it would keep the height waiting (256 requests of popular blocks, 16 groups: 100 of 350 us).
+// Before, every group had its own room, of the size that the plan knows: the workgroups of what is left of it, which have nothing to
+// do, are handed out in order and had to wait for compute units that were busy with the items before them, so that a group's items
+// started when those of the group before were done, and an XCD without a share in the occupied part of the rooms did nothing.
+// Heights 4 to 8 of those requests: 453, 386, 471, 581, 659 -> 423, 310, 284, 295, 342 us, with fewer row tiles per item
+// (items_count_kernel).
+
+// What the height before says of a node's first tile.  If any tile was multiplied whole there, first items stand apart and start first;
+// if one in every node was, on average, the first tile is likely to end up whole again, and its head is multiplied once, without
+// the test, instead of twice (256 requests of popular blocks, heights 2 to 4: 795, 690, 423 -> 726, 617, 384 us).
+constexpr int kFirstApart = 1, kFirstWhole = 2;
+__device__ __forceinline__ int first_items(const WorkDesc &w, const HeightDesc &prev, int g)
+{
+    if (!w.early_nk || prev.n_nodes == 0)
+        return 0;
+    const int whole = w.whole[g];
+    return (whole > 0 ? kFirstApart : 0) | (whole >= prev.n_nodes ? kFirstWhole : 0);
+}
 
 // First item of every node of a group (exclusive scan over the nodes), how many nodes before it have any, and the group's number of
 // either; or the group's items for the panel kernel.  What the tests of this height leave open is counted from here on.
@@ -944,6 +967,8 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     const int g = blockIdx.x, tid = threadIdx.x;
     int2 *base = w.dyn_base + (int64_t)g * w.dyn_stride;
     const bool panel = w.panel_on && panel_items_of_group(w, h, prev, height, g);
+    const int firsts = first_items(w, prev, g);
+    __syncthreads();
     if (w.early_nk && tid == 0)
         w.open_cnt[g] = w.whole[g] = 0;
     if (panel || (w.group_enable && !w.group_enable[g])) {      // this group's share of the height is the panel kernel's; or a
@@ -975,25 +1000,25 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
                               most, n_cp, rt, n_rc);
         }
         int64_t total;
-        const int64_t pre = run + block_exscan<256>((int64_t)c | (int64_t)(w.early_nk && c > 0) << 32, lds4, total);
+        const int64_t pre = run + block_exscan<256>((int64_t)c | (int64_t)((firsts & kFirstApart) && c > 0) << 32, lds4, total);
         if (k < h.n_nodes)
             base[k] = make_int2(min((int)pre, h.item_cap), (int)(pre >> 32));
         run += total;
         __syncthreads();
     }
     if (tid == 0)
-        w.dyn_count[g] = make_int4(min((int)run, h.item_cap), (int)(run >> 32), most, 0);      // (never more than the room: see the plan's bound)
+        w.dyn_count[g] = make_int4(min((int)run, h.item_cap), (int)(run >> 32), most, firsts);      // (never more than the room: see the plan's bound)
 }
 
 // Item `local` of a node: which panel and row chunk of the node it is.
-__device__ __forceinline__ int4 item_of_node(int local, int n_cp, int rt, int n_rc, int bm, int bn, int node, int g)
+__device__ __forceinline__ int4 item_of_node(int local, int n_cp, int rt, int n_rc, int bm, int bn, int node, int g, bool whole_first)
 {
     const int patch = local / (8 * n_rc);
     const int within = local - patch * 8 * n_rc;
     const int np = min(8, n_cp - 8 * patch);
     const int rc = within / np;
     const int cp = 8 * patch + within - rc * np;
-    return make_int4(node, cp * bn, rc * rt * bm | rt, g);
+    return make_int4(node, cp * bn, rc * rt * bm | rt | (local == 0 && whole_first ? kWholeFirst : 0), g);
 }
 
 // One thread per item slot: which node it falls into, and which panel and row chunk of that node it is; and one per left block for
@@ -1056,19 +1081,22 @@ __global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc
                         n_cp, rt, n_rc);
     const int2 own = base[k];
     const int local = item - own.x;
-    const int64_t slot = !w.early_nk  ? n_slots - 1 - ((at >> 32) + item)
-                         : local == 0 ? (int64_t)((int32_t)at + own.y)
-                                      : n_slots - 1 - ((at >> 32) + item - own.y - 1);
-    w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, k, g);
+    const int apart = count.w & kFirstApart;          // (else own.y is 0)
+    const int64_t slot = apart && local == 0 ? (int64_t)((int32_t)at + own.y) : n_slots - 1 - ((at >> 32) + item - own.y - apart);
+    w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, k, g, (count.w & kFirstWhole) != 0);
 }
 
-// Both for few nodes and items, by one workgroup: a launch less (an ordinary height of a small call is some 8 launches of 5 us).
-__global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
+// Both for few nodes and items, by one workgroup: a launch less (a height of a small call is some 8 launches of 5 us).
+__global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int bm, int bn)
 {
     __shared__ int64_t lds16[16];
     __shared__ int2 base[1024], sizes[1024];
+    __shared__ uint8_t firsts[1024];                             // by group
     const int tid = threadIdx.x, n = w.G * h.n_nodes;            // thread i: node i % n_nodes of group i / n_nodes
     const int64_t n_slots = (int64_t)w.G * h.item_cap;
+    if (tid < w.G)
+        firsts[tid] = (uint8_t)first_items(w, prev, tid);
+    __syncthreads();
     if (w.early_nk && tid < w.G)
         w.open_cnt[tid] = w.whole[tid] = 0;
     int ml = 0, mr = 0;
@@ -1089,7 +1117,7 @@ __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDe
     int n_cp, rt, n_rc;
     const int c = items_of_node(ml, mr, bm, bn, most, n_cp, rt, n_rc);
     int64_t total;
-    const int64_t pre = block_exscan<1024>((int64_t)c | (int64_t)(w.early_nk && c > 0) << 32, lds16, total);
+    const int64_t pre = block_exscan<1024>((int64_t)c | (int64_t)(c > 0 && (firsts[tid / h.n_nodes] & kFirstApart)) << 32, lds16, total);
     base[tid] = make_int2((int)pre, (int)(pre >> 32));
     sizes[tid] = make_int2(ml, mr);
     const int n_first = (int)(total >> 32), n_items = (int)min((int64_t)(int32_t)total, n_slots);
@@ -1109,9 +1137,10 @@ __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDe
         }
         const int2 own = base[lo], size = sizes[lo];
         (void)items_of_node(size.x, size.y, bm, bn, most, n_cp, rt, n_rc);
-        const int g = lo / h.n_nodes, local = item - own.x;
-        const int64_t slot = !w.early_nk ? n_slots - 1 - item : local == 0 ? (int64_t)own.y : n_slots - 1 - (item - own.y - 1);
-        w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, lo - g * h.n_nodes, g);
+        const int g = lo / h.n_nodes, local = item - own.x, apart = firsts[g] & kFirstApart;
+        // (own.y: first items before, of all groups; this node's own stands before its others)
+        const int64_t slot = apart && local == 0 ? (int64_t)own.y : n_slots - 1 - (item - own.y - apart);
+        w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, lo - g * h.n_nodes, g, (firsts[g] & kFirstWhole) != 0);
     }
 }
 
@@ -1126,7 +1155,7 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
         const int bm = BIG ? 256 : 128;
         const int64_t rows = w.panel_on ? (int64_t)w.G * h.total_l_cap : 0;
         if (!w.panel_on && (int64_t)w.G * h.n_nodes <= 1024 && total <= kFewItems) {
-            items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, bm, bm);
+            items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, bm, bm);
         } else {
             items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
             items_fill_kernel<<<(unsigned)((std::max(total, rows) + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor, bm, bm);

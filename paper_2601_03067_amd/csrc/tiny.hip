@@ -487,7 +487,7 @@ void launch_tiny_tree(hipStream_t s, const PoolDesc &pool, const TableDesc &tab,
     const TinyArgs A{pool, tab, w, slot_init, n_heights, thr, band, thr_floor, free_list, n_free, n_phys};
     const int cpl = (pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 16 + 63) / 64;
     const int64_t key_bytes = (int64_t)pool.P * pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4);
-    const bool staged = key_bytes <= kTinyStage;
+    const bool staged = key_bytes <= kTinyStage && n_heights > 0;
 #define KVF_TINY_CPL(T, CPL)                                                                                \
     do {                                                                                                    \
         if (staged) tiny_tree_kernel<T, CPL, true><<<pool.G, kTinyThreads<T, CPL>, (unsigned)key_bytes, s>>>(A); \

@@ -60,3 +60,34 @@ def test_tree_matches_oracle(oracle, groups, units, count, copies, off):
     fused = kb.group_counters(ctx, plan)[:, 0]
     assert np.all(fused[on == 0] == 0)
     assert n == 2 or min(int(fused[g]) for g in pick if on[g]) > 0
+
+
+@pytest.mark.parametrize("shared", [0, 300])
+def test_first_tiles_expected_whole(oracle, shared):
+    """Four requests, the first two and the last two copies of each other: a tile of every node runs to its full length at the first height,
+    so that the second height's first tiles are multiplied whole at once, with nothing in them (shared = 0) or copies (300).  Keys
+    with a common direction, whose heads are too long for the panel kernel."""
+    kb = gu.load_binding()
+    groups, count = 60, np.full(4, 300, np.int32)
+    base = np.arange(300)
+    src = np.concatenate([base, base, base + 300 - shared, base + 300 - shared]).astype(np.int64)
+    start = np.arange(4, dtype=np.int32) * 300
+    rec = wl.Recipe("whole first", 13, groups, 1, 1, 16, 64, torch.bfloat16, 0.9, src, np.full(1200, 0.03, np.float32), 600, start, count,
+                    count * 16, start, count, np.arange(5, dtype=np.int32))
+    print("whole first", shared, flush=True)
+    mat = wl.materialise(rec, DEV, phys_perm=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7)
+    for g in range(groups):
+        mat["K"][g] = (mat["K"][g].float() + 1.3 * torch.randn(rec.r, generator=gen, device=DEV)).to(rec.dtype)
+    pick = [0, groups - 1]
+    host = ([wl.to_numpy_pool(mat["K"][g]) for g in pick], [wl.to_numpy_pool(mat["V"][g]) for g in pick],
+            [mat["bt"][g].cpu().numpy().copy() for g in pick])
+    cache, plan, stats, ctx = gu.gpu_fuse(rec, mat, cand_cap=64)
+    res = gu.oracle_fuse(oracle, rec, host)
+    gu.check_ambiguity(res, rec.name)
+    for r, g in zip(res, pick):
+        gu.compare_group(r, cache, g, False, rec.name)
+    slices, open_pairs, room = kb.early_counts(ctx, plan)
+    assert room > 0 and np.all((slices > 11) & (slices < 32))                 # tests there are, and not the panel kernel's
+    assert stats.fused == groups * (600 + shared)
