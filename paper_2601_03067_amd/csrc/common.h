@@ -370,9 +370,9 @@ __device__ __forceinline__ int64_t block_exscan(int64_t x, int64_t (&waves)[NT /
 struct Divisor {
     uint32_t d, m;
     __host__ explicit Divisor(int64_t x = 1) : d((uint32_t)std::max<int64_t>(x, 1)), m(d == 1 ? UINT32_MAX : (uint32_t)((1ull << 32) / d)) {}
-    __device__ __forceinline__ uint32_t of(uint32_t x) const
+    __host__ __device__ __forceinline__ uint32_t of(uint32_t x) const
     {
-        const uint32_t q = __umulhi(x, m);
+        const uint32_t q = (uint32_t)((uint64_t)x * m >> 32);
         return q + (x - q * d >= d);
     }
 };
@@ -385,7 +385,7 @@ struct GroupsByXcd {
     Divisor per_group, left;
     __host__ GroupsByXcd() : whole(0) {}
     __host__ GroupsByXcd(int64_t groups, int64_t wgs) : whole((uint32_t)groups & ~7u), per_group(wgs), left(groups % 8) {}
-    __device__ __forceinline__ void place(uint32_t id, uint32_t &group, uint32_t &rest) const
+    __host__ __device__ __forceinline__ void place(uint32_t id, uint32_t &group, uint32_t &rest) const
     {
         const uint32_t seat = id >> 3, eight = per_group.of(seat);
         group = eight * 8 + (id & 7);

@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "attend.h"
+#include "decode_order.h"
 
 namespace kvfuse {
 
@@ -68,49 +69,8 @@ struct DecodeArgs {
     int32_t P, n, t, kv_heads, layer_begin, B, Hq, rep, rep_pad, nsplit, blocks_per_split;
     int32_t gstride;   // groups between consecutive layers of the pool and the table: kv_heads, or 1 with all-head blocks
     float sm_scale;
-    bool by_xcd;       // see decode_place
-    GroupsByXcd groups;
-    Divisor requests, heads, split_tokens;
+    DecodeOrder order;
 };
-
-// What this workgroup works on.  Workgroups go to the eight XCDs in turn, and each XCD has an L2 of its own: all that read the
-// blocks of one (layer, KV head) are put on one XCD, eight such groups at a time, requests side by side before the next split of them, so that what
-// requests share is read while it is there.  The second half of the requests starts at the last split that has tokens: else
-// a common prefix, which comes out of L2, and what is each request's own, which does not, would be read one after the other (20 requests
-// of 1742 tokens, 16 groups, 31.4 / 28.5; from the last split whether it has tokens or not, 17 ragged requests 399 / 389).  The groups
-// that are left, fewer than eight, alternate (a power of two of them then also shares as few XCDs as it can).
-// In the order of the grid several splits scatter a group over all XCDs, and of two splits every other XCD gets the second, which is empty for
-// most of ragged requests.  us, in the order of the grid / like this: 48 ragged requests of 512 to 8192 tokens, 8 groups, 141 / 133;
-// 18 requests of 5797 tokens, 16 groups, 119 / 99; 2 of 27945 tokens, 16 groups, 72.5 / 55.5; binary32, 17 ragged ones up to 3812 tokens, 96 groups
-// of four KV heads a layer, 492 / 389.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
-// 15.9; 494 of 107, 44 groups, 157 / 163), and so do all-head blocks, whose tokens all heads of a layer read (7 requests of 10813 tokens
-// 80 / 82; 139 of 438 20.8 / 18.9), and three, five, six or seven groups, which would not keep to an XCD (three: 38.7 / 40.3).
-// (Fewer than 2^32 workgroups: neither the layers nor the requests' KV heads of a call are more than 65535, and splits are taken where
-// there are fewer than 2048 of both.)
-struct DecodePlace {
-    int split, b, kvh, li;
-};
-__device__ __forceinline__ DecodePlace decode_place(const DecodeArgs &A)
-{
-    const uint32_t heads = (uint32_t)A.kv_heads, requests = (uint32_t)A.B;
-    uint32_t split = blockIdx.x, b, li = blockIdx.z, kvh;
-    if (A.by_xcd) {
-        uint32_t group, rest;
-        A.groups.place(split + (uint32_t)A.nsplit * (blockIdx.y + requests * heads * li), group, rest);
-        split = A.requests.of(rest);
-        b = rest - split * requests;
-        if (2 * b >= requests) {
-            const uint32_t full = A.split_tokens.of((uint32_t)max(A.ctx_len[b] - 1, 0));         // splits before the last one with tokens
-            split = split > full ? split : full - split;
-        }
-        li = A.heads.of(group);
-        kvh = group - li * heads;
-    } else {
-        b = A.heads.of(blockIdx.y);
-        kvh = blockIdx.y - b * heads;
-    }
-    return {(int)split, (int)b, (int)kvh, (int)li};
-}
 
 // AH = all-head blocks (method section: one vector per block over all KV heads, one table per layer): the pool is
 // [layers][P][t][kv_heads][D], so the tokens of a block lie kv_heads * D elements apart, the KV head selects a
@@ -130,7 +90,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs A)
     __shared__ float w_o[4][REP][D];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const DecodePlace at = decode_place(A);
+    const DecodeOrder::Place at = A.order.place(blockIdx.x, blockIdx.y, blockIdx.z, A.ctx_len);
     const int split = at.split, b = at.b, kvh = at.kvh, li = at.li;
     const int g = AH ? A.layer_begin + li : (A.layer_begin + li) * A.kv_heads + kvh;
     const int64_t row = AH ? (int64_t)A.kv_heads * D : (int64_t)D;      // elements from one token of a block to the next
@@ -324,7 +284,7 @@ __global__ __launch_bounds__(64 * NW, 3) void decode_bf16_kernel(DecodeArgs A)
     __shared__ float w_m[NW][16], w_l[NW][16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const DecodePlace at = decode_place(A);
+    const DecodeOrder::Place at = A.order.place(blockIdx.x, blockIdx.y, blockIdx.z, A.ctx_len);
     const int split = at.split, b = at.b, kvh = at.kvh, li = at.li;
     const int g = (A.layer_begin + li) * A.kv_heads + kvh;
     const int ctx = A.ctx_len[b];
@@ -650,12 +610,13 @@ int launch_decode(hipStream_t s, const PoolDesc &pool, const TableDesc &tab, int
     if (tuples == 0)
         return KVFUSE_OK;
     const int64_t groups = (int64_t)n_layers * kv_heads;
-    A.by_xcd = !all_heads && (groups >= 8 || 8 % groups == 0) &&
-               (A.nsplit > 1 || kv_heads % 8 != 0) && (int64_t)max_blocks * pool.t >= 1024;      // (8 KV heads, no splits: the grid's own order)
-    A.groups = GroupsByXcd(groups, (int64_t)B * A.nsplit);
-    A.requests = Divisor(B);
-    A.heads = Divisor(kv_heads);
-    A.split_tokens = Divisor((int64_t)A.blocks_per_split * pool.t);
+    A.order.by_xcd = !all_heads && (groups >= 8 || 8 % groups == 0) &&
+                     (A.nsplit > 1 || kv_heads % 8 != 0) && (int64_t)max_blocks * pool.t >= 1024;      // (8 KV heads, no splits: the grid's own order)
+    A.order.nsplit = (uint32_t)A.nsplit;
+    A.order.groups = GroupsByXcd(groups, (int64_t)B * A.nsplit);
+    A.order.requests = Divisor(B);
+    A.order.heads = Divisor(kv_heads);
+    A.order.split_tokens = Divisor((int64_t)A.blocks_per_split * pool.t);
     if (pool.dtype == KVFUSE_BF16) {
         if (head_dim == 128) launch_decode_t<bf16_t, 128>(s, A, n_layers);
         else launch_decode_t<bf16_t, 64>(s, A, n_layers);

@@ -90,6 +90,26 @@ def test_workgroups_dealt_out_to_the_xcds(layers, heads, requests):
     assert float((out - ref).abs().max()) < 1.2e-5                         # the same bound as above
 
 
+@pytest.mark.parametrize("layers,heads,requests", [(1, 8, 5), (2, 4, 260)])
+def test_a_length_beyond_max_blocks_stays_inside(layers, heads, requests):
+    """Lengths on the device that have outgrown max_blocks (several splits, and one): nothing behind the workspace is written, and the
+    requests that max_blocks covers are what they are without the others."""
+    t, d = 16, 64
+    contexts = [1100 - 37 * b % 1090 for b in range(requests)]
+    contexts[requests // 2] = contexts[-1] = 2500
+    kb, cache, start, _, gen = _setup(t, d, heads, 17, layers, contexts=contexts)
+    max_blocks = (1100 + t - 1) // t
+    q = torch.randn(layers, requests, heads * 2, d, generator=gen, device=DEV).to(torch.bfloat16)
+    nbytes = kb.decode_workspace_bytes(layers, requests, heads * 2, heads, d, max_blocks)
+    ws = torch.full((nbytes + (1 << 20),), 0xA5, dtype=torch.uint8, device=DEV)
+    rs, cl = torch.from_numpy(start).to(DEV), torch.tensor(contexts, dtype=torch.int32, device=DEV)
+    out = kb.paged_decode_attn(kb.Context(DEV), cache, heads, q, rs, cl, max_blocks, workspace=ws)
+    assert bool((ws[nbytes:] == 0xA5).all())
+    covered = [b for b in range(requests) if contexts[b] <= 1100]
+    ref = _reference(cache, t, d, heads, q, start, False, contexts)
+    assert float((out.cpu().double() - ref)[:, covered].abs().max()) < 1.2e-5  # the bound of test_against_binary64
+
+
 def test_rows_past_the_context_and_infinite_values():
     t, d, heads, rep = 32, 128, 2, 4
     kb, cache, start, max_blocks, gen = _setup(t, d, heads, 5)
