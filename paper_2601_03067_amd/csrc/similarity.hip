@@ -945,7 +945,7 @@ __global__ void similarity_clear_kernel(unsigned long long *__restrict__ best_pa
 // do, are handed out in order and had to wait for compute units that were busy with the items before them, so that a group's items
 // started when those of the group before were done, and an XCD without a share in the occupied part of the rooms did nothing.
 // Heights 4 to 8 of those requests: 453, 386, 471, 581, 659 -> 423, 310, 284, 295, 342 us, with fewer row tiles per item
-// (items_count_kernel).
+// (items_count_kernel).  Of more groups than kSumGroups each has its own room again.
 
 // What the height before says of a node's first tile.  If any tile was multiplied whole there, first items stand apart and start first;
 // if one in every node was, on average, the first tile is likely to end up whole again, and its head is multiplied once, without
@@ -959,6 +959,12 @@ __device__ __forceinline__ int first_items(const WorkDesc &w, const HeightDesc &
     return (whole > 0 ? kFirstApart : 0) | (whole >= prev.n_nodes ? kFirstWhole : 0);
 }
 
+// Groups up to which items stand without gaps: every workgroup of items_fill_kernel sums up what the groups before its own have, which grows
+// with the square of the groups.  Of more groups each has room of its own in the second list, and what is left of it holds items of nothing:
+// so many fill the chip in any order.  Whole tree calls on sets of 2 x 40 blocks of 128 bytes, us, summed up / with rooms: 2000 groups 212 / 211, 20 000
+// 1727 / 1710, 400 000 33 640 / 33 190.  (An atomic per group instead, on one counter, 11 ns each: 37 700.)
+constexpr int kSumGroups = 4096;
+
 // First item of every node of a group (exclusive scan over the nodes), how many nodes before it have any, and the group's number of
 // either; or the group's items for the panel kernel.  What the tests of this height leave open is counted from here on.
 __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int height, int bm, int bn)
@@ -966,8 +972,11 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     __shared__ int64_t lds4[4];
     const int g = blockIdx.x, tid = threadIdx.x;
     int2 *base = w.dyn_base + (int64_t)g * w.dyn_stride;
+    auto sizes = [&](int k) {
+        return k < h.n_nodes ? make_int2(w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]]) : make_int2(0, 0);
+    };
+    const int firsts = first_items(w, prev, g) & (w.G > kSumGroups ? ~kFirstApart : ~0);       // (asked for before the panel's sums)
     const bool panel = w.panel_on && panel_items_of_group(w, h, prev, height, g);
-    const int firsts = first_items(w, prev, g);
     __syncthreads();
     if (w.early_nk && tid == 0)
         w.open_cnt[g] = w.whole[g] = 0;
@@ -976,6 +985,7 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
             w.dyn_count[g] = make_int4(0, 0, 1, 0);
         return;
     }
+    const int2 own = sizes(tid);
     // Most row tiles of an item: as many as leave every compute unit 16 items (of all groups, taken to be like this one), one to
     // four.  Long items cost less on the way from one to the next, but the height ends with the last of them: 256 requests of popular blocks,
     // 16 groups, heights 6 to 8 of 9 to 12 tiles a compute unit 349, 443, 546 us with four, 347, 325, 308 with two, 280, 290, 332 with one.
@@ -983,8 +993,8 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     if (h.max_cap > 4 * bm) {                   // (up to four row tiles are items of one anyway)
         int64_t tiles = 0, all;
         for (int k = tid; k < h.n_nodes; k += 256) {
-            const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
-            tiles += (int64_t)((ml + bm - 1) / bm) * ((mr + bn - 1) / bn);
+            const int2 m = k == tid ? own : sizes(k);
+            tiles += (int64_t)((m.x + bm - 1) / bm) * ((m.y + bn - 1) / bn);
         }
         (void)block_exscan<256>(tiles, lds4, all);
         if (all <= h.item_cap)                  // (there is room for the plan's bound on items of four, or for single tiles)
@@ -993,12 +1003,9 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     int64_t run = 0;                            // items in the lower half, nodes that have any in the upper one
     for (int k0 = 0; k0 < h.n_nodes; k0 += 256) {
         const int k = k0 + tid;
-        int c = 0;
-        if (k < h.n_nodes) {
-            int n_cp, rt, n_rc;
-            c = items_of_node(w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]], bm, bn,
-                              most, n_cp, rt, n_rc);
-        }
+        const int2 m = k0 == 0 ? own : sizes(k);
+        int n_cp, rt, n_rc;
+        const int c = items_of_node(m.x, m.y, bm, bn, most, n_cp, rt, n_rc);
         int64_t total;
         const int64_t pre = run + block_exscan<256>((int64_t)c | (int64_t)((firsts & kFirstApart) && c > 0) << 32, lds4, total);
         if (k < h.n_nodes)
@@ -1032,40 +1039,52 @@ __global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc
         panel_row(pool, w, h, thr_floor, i);
     if (i0 >= n_slots)
         return;
-    // what the groups before have, for each of the (at most 256) groups that these slots belong to: nodes' first items in the lower half,
-    // others in the upper one
-    auto counts = [&](int g) { const int4 c = w.dyn_count[g]; return (int64_t)c.y | (int64_t)(c.x - c.y) << 32; };
-    const int g0 = (int)(i0 / h.item_cap), g1 = (int)(min(i0 + 255, n_slots - 1) / h.item_cap);
-    int64_t sum = 0;
-    if (g0 > 0) {
-        int64_t mine = 0;
-        for (int g = tid; g < g0; g += 256)
-            mine += counts(g);
-        (void)block_exscan<256>(mine, lds4, sum);
-    }
-    if (g1 - g0 > 4) {
-        int64_t all;
-        before[tid] = block_exscan<256>(g0 + tid <= g1 ? counts(g0 + tid) : 0, lds4, all);
-        __syncthreads();
+    const int g = (int)(i / h.item_cap);
+    const int item = (int)(i - (int64_t)g * h.item_cap);
+    int64_t at;                                  // where the group begins in either list: nodes' first items in the lower half, others in the upper one
+    if (w.G > kSumGroups) {
+        at = (int64_t)g * h.item_cap << 32;
+        if (i == n_slots - 1) {
+            w.dyn_total[0] = 0;
+            w.dyn_total[1] = (int32_t)n_slots;
+        }
+    } else {
+        // what the groups before have, for each of the (at most 256) groups that these slots belong to
+        auto counts = [&](int q) { const int4 c = w.dyn_count[q]; return (int64_t)c.y | (int64_t)(c.x - c.y) << 32; };
+        const int g0 = (int)(i0 / h.item_cap), g1 = (int)(min(i0 + 255, n_slots - 1) / h.item_cap);
+        at = 0;
+        if (g0 > 0) {
+            int64_t mine = 0;
+            for (int q = tid; q < g0; q += 256)
+                mine += counts(q);
+            (void)block_exscan<256>(mine, lds4, at);
+        }
+        if (g1 - g0 > 4) {
+            int64_t all;
+            before[tid] = block_exscan<256>(g0 + tid <= g1 ? counts(g0 + tid) : 0, lds4, all);
+            __syncthreads();
+        }
+        if (i < n_slots) {
+            if (g1 - g0 > 4)
+                at += before[g - g0];
+            else
+                for (int q = g0; q < g; ++q)
+                    at += counts(q);
+            if (i == n_slots - 1) {
+                const int64_t all = at + counts(g);
+                w.dyn_total[0] = (int32_t)all;
+                w.dyn_total[1] = (int32_t)(all >> 32);
+            }
+        }
     }
     if (i >= n_slots)
         return;
-    const int g = (int)(i / h.item_cap);
-    const int item = (int)(i - (int64_t)g * h.item_cap);
-    int64_t at = sum;
-    if (g1 - g0 > 4)
-        at += before[g - g0];
-    else
-        for (int q = g0; q < g; ++q)
-            at += counts(q);
-    if (i == n_slots - 1) {
-        const int64_t all = at + counts(g);
-        w.dyn_total[0] = (int32_t)all;
-        w.dyn_total[1] = (int32_t)(all >> 32);
-    }
     const int4 count = w.dyn_count[g];
-    if (item >= count.x)
+    if (item >= count.x) {
+        if (w.G > kSumGroups)
+            w.dyn_items[n_slots - 1 - i] = make_int4(0, INT32_MAX, 0, g);
         return;
+    }
     const int2 *base = w.dyn_base + (int64_t)g * w.dyn_stride;
     int lo = 0, hi = h.n_nodes;             // the last node whose first item is <= item (empty nodes share a first item
     while (hi - lo > 1) {                   // with their successor and are skipped by taking the last)

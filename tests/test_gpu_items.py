@@ -20,6 +20,8 @@ CASES = [(1, 2, 1, 0, 0),          # a tile of one pair
          (300, 2, 40, 7, 7),       # slots of many groups per workgroup
          (1030, 2, 34, 9, 0),      # more nodes than one workgroup takes
          (40, 9, 300, 11, 3),      # several heights, two launches at the first
+         (4096, 3, 140, 9, 5),     # items of all groups without gaps, for the last time ...
+         (4097, 3, 140, 9, 5),     # ... and every group with room of its own: four items of a node, none of a switched-off group
          (2, 2, 4200, 60, 0)]      # room for more items than one workgroup lays out; single tiles, 34 rows of them
 
 
