@@ -1105,7 +1105,7 @@ __global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc
     w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, k, g, (count.w & kFirstWhole) != 0);
 }
 
-// Both for few nodes and items, by one workgroup: a launch less (a height of a small call is some 8 launches of 5 us).
+// Both for few nodes and items, a thread each (kFewItems), by one workgroup: a launch less (a height of a small call is some 8 launches of 5 us).
 __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDesc h, HeightDesc prev, int bm, int bn)
 {
     __shared__ int64_t lds16[16];
@@ -1130,8 +1130,8 @@ __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDe
     if (h.max_cap > 4 * bm) {
         int64_t tiles;
         (void)block_exscan<1024>((int64_t)((ml + bm - 1) / bm) * ((mr + bn - 1) / bn), lds16, tiles);
-        if (tiles <= n_slots)
-            most = (int)min(max(tiles / (16 * 256), (int64_t)1), (int64_t)kRingRowTiles);
+        if (tiles <= n_slots)                    // (as in items_count_kernel: fewer than 16 items a compute unit)
+            most = 1;
     }
     int n_cp, rt, n_rc;
     const int c = items_of_node(ml, mr, bm, bn, most, n_cp, rt, n_rc);
@@ -1145,20 +1145,20 @@ __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDe
         w.dyn_total[1] = n_items - n_first;
     }
     __syncthreads();
-    for (int item = tid; item < n_items; item += 1024) {
+    if (tid < n_items) {
         int lo = 0, hi = n;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (base[mid].x <= item)
+            if (base[mid].x <= tid)
                 lo = mid;
             else
                 hi = mid;
         }
         const int2 own = base[lo], size = sizes[lo];
         (void)items_of_node(size.x, size.y, bm, bn, most, n_cp, rt, n_rc);
-        const int g = lo / h.n_nodes, local = item - own.x, apart = firsts[g] & kFirstApart;
+        const int g = lo / h.n_nodes, local = tid - own.x, apart = firsts[g] & kFirstApart;
         // (own.y: first items before, of all groups; this node's own stands before its others)
-        const int64_t slot = apart && local == 0 ? (int64_t)own.y : n_slots - 1 - (item - own.y - apart);
+        const int64_t slot = apart && local == 0 ? (int64_t)own.y : n_slots - 1 - (tid - own.y - apart);
         w.dyn_items[slot] = item_of_node(local, n_cp, rt, n_rc, bm, bn, lo - g * h.n_nodes, g, (firsts[g] & kFirstWhole) != 0);
     }
 }
