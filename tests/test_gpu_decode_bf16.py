@@ -14,15 +14,15 @@ DEV = "cuda:0"
 CONTEXTS = [0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 127, 128, 129, 255, 300, 1000]
 
 
-def _setup(t, d, heads, seed, layers=2, all_heads=False, contexts=CONTEXTS):
+def _setup(t, d, heads, seed, layers=2, all_heads=False, contexts=CONTEXTS, dtype=torch.bfloat16):
     from paper_2601_03067_amd import binding as kb
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
     blocks = [(c + t - 1) // t for c in contexts]
     n, groups, width = sum(blocks), layers * (1 if all_heads else heads), d * (heads if all_heads else 1)
     P = n + 3
-    K = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(torch.bfloat16)
-    V = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(torch.bfloat16)
+    K = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(dtype)
+    V = torch.randn(groups, P, t * width, generator=gen, device=DEV).to(dtype)
     bt = torch.randint(0, P, (groups, n), generator=gen, device=DEV, dtype=torch.int32)       # shared blocks among them
     cache = kb.Cache(K, V, bt, t, width)
     cache.scale_k.copy_(0.5 + torch.rand(groups, n, generator=gen, device=DEV))
@@ -76,15 +76,16 @@ def test_against_binary64(t, d, heads, rep, all_heads):
     assert float(out[:, CONTEXTS.index(0)].abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("dtype,t", [(torch.bfloat16, 16), (torch.float32, 16), (torch.bfloat16, 32)])
 @pytest.mark.parametrize("layers,heads,requests", [(1, 8, 1), (1, 8, 5), (2, 4, 3), (3, 3, 4), (11, 1, 2), (1, 2, 7), (4, 1, 6), (1, 1, 40),
-                                                   (3, 5, 140)])
-def test_workgroups_dealt_out_to_the_xcds(layers, heads, requests):
+                                                   (3, 5, 140), (11, 1, 100)])
+def test_workgroups_dealt_out_to_the_xcds(layers, heads, requests, dtype, t):
     """Contexts from 1024 tokens on: every (layer, request, KV head, split) is done once, for whole eights of groups, what is left of
-    them, and one split of many requests."""
-    t, d = 16, 64
+    them, one split of many requests, and two of more than 512 (layer, request, KV head) triples."""
+    d = 64
     contexts = [1100 - 37 * b % 1090 for b in range(requests)]
-    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 3 + requests, layers, contexts=contexts)
-    q = torch.randn(layers, requests, heads * 2, d, generator=gen, device=DEV).to(torch.bfloat16)
+    kb, cache, start, max_blocks, gen = _setup(t, d, heads, 3 + requests, layers, contexts=contexts, dtype=dtype)
+    q = torch.randn(layers, requests, heads * 2, d, generator=gen, device=DEV).to(dtype)
     ref = _reference(cache, t, d, heads, q, start, False, contexts)
     out = _call(kb, cache, heads, q, start, max_blocks, False, contexts)
     assert float((out - ref).abs().max()) < 1.2e-5                         # the same bound as above

@@ -117,3 +117,19 @@ SHORT = [(28, 8, 4, 16, 128, 0, 0, 1),           # 224 workgroups, half a tile
 @pytest.mark.parametrize("case", SHORT, ids=[str(i) for i in range(len(SHORT))])
 def test_short_walks_against_binary64(case, reuse):
     _compare(case, reuse)
+
+
+# Groups of (layer, KV head) in whole eights and some left over, or fewer than eight, dealt out to the XCDs; either kernel
+GROUPS = [(11, 1, 4, 16, 128, 512, 0, 700),      # 242 workgroups of the staged kernel
+          (5, 5, 1, 16, 128, 160, 7, 900),       # 200
+          (13, 1, 4, 16, 64, 96, 0, 600),        # 247
+          (3, 1, 16, 32, 64, 64, 3, 600),        # 225 of three groups
+          (3, 5, 4, 16, 64, 256, 5, 40),         # split
+          (19, 1, 2, 16, 128, 2048, 0, 20),
+          (7, 1, 8, 48, 128, 96, 1, 30)]
+
+
+@pytest.mark.parametrize("reuse", [True, False])
+@pytest.mark.parametrize("case", GROUPS, ids=[str(i) for i in range(len(GROUPS))])
+def test_groups_dealt_out_to_the_xcds(case, reuse):
+    _compare(case, reuse)
