@@ -393,7 +393,7 @@ int kvfuse_predict_compression(const double *rates, int32_t n_layers, double blo
 double kvfuse_threshold_feedback(double thr, double observed_cr, double target_cr, double gain, double lo, double hi);
 
 /* Switch groups off for the following kvfuse_similarity / kvfuse_fuse_tree calls on this plan: enable is a device
- * array [G] of bytes (0 = skip: the group's similarity work items exit at once, its candidate lists stay empty and
+ * array [G] of bytes (0 = skip: the group gets no similarity work items, its candidate lists stay empty and
  * nothing in it fuses; the other steps run and leave the group as it is), or NULL for all groups.  The array is
  * read during those calls and must stay alive; it is also copied to the host here for the statistics (this call
  * waits for the stream). */

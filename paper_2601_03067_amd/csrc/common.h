@@ -118,7 +118,7 @@ struct WorkDesc {
     float *pair_head;        // [pair_cap] ... and their product so far
     int32_t *n_pairs;        // counter of the current height
     int32_t pair_cap;
-    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that were multiplied whole for them
+    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that the ring kernel multiplied whole for them (1 for any number of a height that was the panel kernel's)
     // panel kernel (panel.hip); panel_on null = not at this height
     int32_t *panel_on, *panel_on_mem;       // [G]
     u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand

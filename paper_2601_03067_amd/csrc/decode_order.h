@@ -11,9 +11,10 @@ namespace kvfuse {
 // of 1742 tokens, 16 groups, 31.4 / 28.5; from the last split whether it has tokens or not, 17 ragged requests 399 / 389).  The groups
 // that are left, fewer than eight, alternate (a power of two of them then also shares as few XCDs as it can).
 // In the order of the grid several splits scatter a group over all XCDs, and of two splits every other XCD gets the second, which is empty for
-// most of ragged requests.  us, in the order of the grid / like this: 48 ragged requests of 512 to 8192 tokens, 8 groups, 141 / 133;
+// most of ragged requests.  us, in the order of the grid / like this: 48 ragged requests of 512 to 8192 tokens, 8 groups, 142 / 135;
 // 18 requests of 5797 tokens, 16 groups, 119 / 99; 2 of 27945 tokens, 16 groups, 72.5 / 55.5; binary32, 17 ragged ones up to 3812 tokens, 96 groups
-// of four KV heads a layer, 492 / 389.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
+// of four KV heads a layer, 492 / 389; about the line below, 24 requests of 1024 tokens, 8 groups, 21.4 / 18.4, of 1200 21.3 / 21.4, of 1500
+// 26.9 / 26.4, of 2000 31.6 / 30.4; 11 groups 27.2 / 23.1, 29.5 / 26.9, 34.4 / 31.0, 44.4 / 39.5; one request level.  Contexts below 1024 tokens stay in the grid's order (22 requests of 760 tokens, 4 groups, 15.3 /
 // 15.9; 494 of 107, 44 groups, 157 / 163), and so do all-head blocks, whose tokens all heads of a layer read (7 requests of 10813 tokens
 // 80 / 82; 139 of 438 20.8 / 18.9), and three, five, six or seven groups, which would not keep to an XCD (three: 38.7 / 40.3).
 // (Fewer than 2^32 workgroups: neither the layers nor the requests' KV heads of a call are more than 65535, and splits are taken where

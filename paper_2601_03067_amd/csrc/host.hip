@@ -71,12 +71,14 @@ struct Plan {
 
     // The whole tree call in one launch (tiny.hip): the default rule and product on groups that fit it, where a workgroup's walk
     // through its group's pairs and norms (us: 8 and 0.02 + r / 28000 each) takes less than the launches it spares (10 and 25 a
-    // height).  Both measured (us, launches / one, with some 13 us of copies in both; requests x blocks, bytes of a block, 1 group): 2 x 4,
-    // 4096 51 / 22; 16 x 2, 2048 87 / 47; 4 x 8, 4096 binary32 68 / 41, bfloat16 75 / 65; 6 x 8, 4096 binary32 96 / 64, bfloat16
-    // 100 / 107 (launches); 4 x 16, 2048 68 / 94 (launches).  More workgroups than the chip holds take turns, while the launches share
-    // their groups out better: 512 groups of 4 x 8, 2048 163 / 101, 1024 243 / 196, 2048 400 / 399, 4096 744 / 793; 1024 of 3 x 12,
-    // 4096 405 / 414.  Blocks of 4096 bytes in bfloat16, whose workgroups the chip holds one to a compute unit (with the restoring of
-    // the blocks between calls): 4 x 8 in 256 groups 135 / 93, 257 146 / 137, 512 159 / 141; 8 x 4 in 257 171 / 149, 512 212 / 163.
+    // height).  Both measured (us, launches / one, with some 11 us of copies in both; requests x blocks, bytes of a block, 1 group): 2 x 4,
+    // 4096 bfloat16 59 / 18; 16 x 2, 2048 bfloat16 124 / 45; 4 x 8, 4096 binary32 72 / 34, bfloat16 75 / 54; 6 x 8, 4096 binary32 95 / 64,
+    // bfloat16 88 / 92 (launches); 4 x 16, 2048 bfloat16 62 / 74 (launches); with keys that do not fit LDS beside them 4 x 8, 4096 binary32
+    // 72 / 40, bfloat16 67 / 55; 16 x 2 125 / 49.  The line was drawn before keys stayed in LDS and is on the launches' side by now: 4 x 16, 2048
+    // binary32 62 / 53 and 4 x 12, 4096 binary32 70 / 61 go launch by launch.  More workgroups than the chip holds take turns, while the launches
+    // share their groups out better (with 22 to 117 us of copies): 512 groups of 4 x 8, 2048 144 / 87, 1024 223 / 177, 2048 390 / 348; 1024 of 3 x 12,
+    // 4096 binary32 360 / 318.  Blocks of 4096 bytes in bfloat16: 4 x 8 in 256 groups 148 / 79, 257 157 / 119, 512 215 / 156; 8 x 4 in 257
+    // 218 / 138, 512 303 / 174.
     bool tiny_pays() const
     {
         if (!work.tiny_nodes || work.G > kTinyGroups || pool.P > kTinyPool || pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) > kTinyBytes ||

@@ -1,5 +1,5 @@
 // Work items of a height, laid out on the device from the sizes the sets have now, for the ring kernel (similarity.hip) and the panel
-// kernel (panel.hip): both in the same two launches, since either may have nothing to do at a height and a launch is 5 us.
+// kernel (panel.hip): where a height may be either's, both in the same two launches, since either may have nothing to do and a launch is 5 us.
 #pragma once
 #include "common.h"
 

@@ -253,7 +253,7 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
             lds_first = atomicAdd(w.n_pairs, n);
             atomicAdd(&w.open_cnt[g], n);
             if (n > kWholeTile)
-                w.whole[g] = 1;
+                w.whole[g] = 1;                  // (some: how many, only the ring kernel counts)
         }
         __syncthreads();
         const int first = n > 0 ? lds_first : 0;

@@ -73,7 +73,10 @@ struct PrefillArgs {
 
 // What this workgroup works on: all that read the keys and values of one (layer, KV head) are put on one XCD (us, by rows of the grid,
 // which scatter them over all eight / like this: 2048 queries of a 32768-token prompt, 4 layers of 8 KV heads, 4541 / 4320; 31 of 7177
-// tokens, 16 layers of 4, 96.7 / 64.0; 10 of 2012 tokens, 31 layers of 4, 31.6 / 25.0).
+// tokens, 16 layers of 4, 96.7 / 64.0; 10 of 2012 tokens, 31 layers of 4, 31.6 / 25.0).  Fewer than eight groups, which share the XCDs in
+// turn, gain too, three of them and five to seven among them (2048 queries of 32768 tokens, one to seven groups: 235 / 231, 467 / 449, 698 / 671,
+// 1025 / 777, 1321 / 1030, 1326 / 1034, 1326 / 1087; 200 of 4296 tokens all 1 to 2 % faster, 1000 of 2000 in one and two groups 0.8 % slower,
+// in the others 4 to 17 % faster).
 struct PrefillPlace {
     int x, kvh, li;
 };

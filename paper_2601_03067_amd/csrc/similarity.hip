@@ -105,7 +105,7 @@ __device__ __forceinline__ floatx16 mma_q8(const u32x4 al, const u32x4 ah, const
 }
 
 constexpr int kRingRowTiles = 4;   // most row tiles of one work item (the host's tile table keeps to it)
-// Room for items up to which one workgroup lays them out: one a thread, 6 us (two launches 11); with several a thread, 10 to 14.
+// Room for items up to which one workgroup lays them out: one a thread, 6 to 9 us (two launches 11); with several a thread, 10 to 14.
 constexpr int64_t kFewItems = 1024;
 constexpr int kRowAlign = 128;     // every item's first row is a multiple of it
 constexpr int kWholeFirst = 64;    // mark, beside an item's row tiles: the first of them is multiplied whole without a test before
@@ -949,7 +949,10 @@ __global__ void similarity_clear_kernel(unsigned long long *__restrict__ best_pa
 
 // What the height before says of a node's first tile.  If any tile was multiplied whole there, first items stand apart and start first;
 // if one in every node was, on average, the first tile is likely to end up whole again, and its head is multiplied once, without
-// the test, instead of twice (256 requests of popular blocks, heights 2 to 4: 795, 690, 423 -> 726, 617, 384 us).
+// the test, instead of twice (256 requests of popular blocks, heights 2 to 4: 795, 690, 423 -> 726, 617, 384 us; whole calls: 64 x 4096 tokens of popular
+// 32-token blocks, 4 groups, 2046 -> 1953 us, 64 x 2048 in binary32 4155 -> 3732, 16 x 8192 with a common half at 0.8, 8 groups, 1171 -> 1122; where
+// hardly a tile runs whole, up to 1 % slower: 64 x 2048 tokens, 8 groups, 1088 -> 1099).  A height that was the panel kernel's says only whether there
+// were any, which is a guess for trees of one node there and an order for others.
 constexpr int kFirstApart = 1, kFirstWhole = 2;
 __device__ __forceinline__ int first_items(const WorkDesc &w, const HeightDesc &prev, int g)
 {
@@ -989,6 +992,8 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     // Most row tiles of an item: as many as leave every compute unit 16 items (of all groups, taken to be like this one), one to
     // four.  Long items cost less on the way from one to the next, but the height ends with the last of them: 256 requests of popular blocks,
     // 16 groups, heights 6 to 8 of 9 to 12 tiles a compute unit 349, 443, 546 us with four, 347, 325, 308 with two, 280, 290, 332 with one.
+    // Only where the tiles fit the plan's room, which is for runs of four where nodes have more than sixteen row tiles: large sets that hardly
+    // shrank keep runs of four, however few items they make.
     int most = kRingRowTiles;
     if (h.max_cap > 4 * bm) {                   // (up to four row tiles are items of one anyway)
         int64_t tiles = 0, all;
@@ -997,7 +1002,7 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
             tiles += (int64_t)((m.x + bm - 1) / bm) * ((m.y + bn - 1) / bn);
         }
         (void)block_exscan<256>(tiles, lds4, all);
-        if (all <= h.item_cap)                  // (there is room for the plan's bound on items of four, or for single tiles)
+        if (all <= h.item_cap)
             most = (int)min(max(all * w.G / (16 * 256), (int64_t)1), (int64_t)kRingRowTiles);
     }
     int64_t run = 0;                            // items in the lower half, nodes that have any in the upper one

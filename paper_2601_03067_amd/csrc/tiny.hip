@@ -10,7 +10,7 @@
 // What it costs now: vector instructions of the cosines (a row is widened for every column it meets) and, between them, chains through
 // LDS: of 32 us the norms take 2, the cosines 10, sets and merges 14, the rewrite 5.  4 requests of 8 blocks in binary32, 2
 // groups: 40.6 -> 31.9 us since keys stay in LDS, four rows share the exchanges of their sums and a division, and blocks are asked for
-// one ahead; with statistics and the restoring of the blocks between calls 72 -> 66 us (134 launch by launch).
+// one ahead; with statistics and the restoring of the blocks between calls 71 -> 64 us (134 launch by launch).
 #include "common.h"
 
 namespace kvfuse {
