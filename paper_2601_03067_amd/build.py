@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvfuse.so")
 PROBE_LIB = os.path.join(HERE, "libkvfuse_probe.so")
-SOURCES = ["host.hip", "norms.hip", "similarity.hip", "early.hip", "panel.hip", "tiny.hip", "assign.hip", "merge.hip", "rewrite.hip", "decode.hip", "decode_shared.hip", "prefill.hip", "threshold.hip", "variants.hip"]
+SOURCES = ["host.hip", "norms.hip", "similarity.hip", "early.hip", "heads.hip", "panel.hip", "tiny.hip", "assign.hip", "merge.hip", "rewrite.hip", "decode.hip", "decode_shared.hip", "prefill.hip", "threshold.hip", "variants.hip"]
 PROBE_SOURCES = ["probe.hip"]
 # packed-fp32 instructions are switched off for every device object of this library
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

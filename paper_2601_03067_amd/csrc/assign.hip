@@ -718,6 +718,9 @@ __global__ __launch_bounds__(NT) void assign_finalize_kernel(int P, TableDesc ta
     const int mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[node]];
     int32_t *l_ids = w.set_ids + (int64_t)g * w.n + h.l_off[node];
     int32_t *r_ids = w.set_ids + (int64_t)g * w.n + h.r_off[node];
+    // the blocks' slots among the head copies (heads.hip), where there are any
+    int32_t *l_places = w.heads ? w.set_slot + (int64_t)g * w.n + h.l_off[node] : nullptr;
+    const int32_t *r_places = w.heads ? w.set_slot + (int64_t)g * w.n + h.r_off[node] : nullptr;
     const int32_t *assign = w.assign + (int64_t)g * w.r_stride + h.r_base[node];
     int32_t *members_out = w.seg_members + (int64_t)g * w.r_stride + h.r_base[node];
     int32_t *members = LOCAL ? lds_members : members_out;
@@ -814,7 +817,7 @@ __global__ __launch_bounds__(NT) void assign_finalize_kernel(int P, TableDesc ta
             const int a = l_ids[i];
             int4 *rec = w.active + 2 * (int64_t)seg_slot[i];
             rec[0] = make_int4(g, a, cnt, (int)((int64_t)g * w.r_stride + h.r_base[node] + start));
-            rec[1] = make_int4(members[start], cnt > 1 ? members[start + 1] : a, 0, 0);
+            rec[1] = make_int4(members[start], cnt > 1 ? members[start + 1] : a, l_places ? l_places[i] : 0, 0);
         }
     }
 
@@ -822,18 +825,23 @@ __global__ __launch_bounds__(NT) void assign_finalize_kernel(int P, TableDesc ta
     int kept = 0;
     for (int j0 = 0; j0 < mr; j0 += NT) {
         const int j = j0 + tid;
-        int id = -1, a = -1;
+        int id = -1, a = -1, place = 0;
         if (j < mr) {
             id = r_ids[j];
             a = assign[j];
+            if (r_places)
+                place = r_places[j];
         }
         int64_t total;
         const int64_t pre = block_exscan<NT>((j < mr && a < 0) ? 1 : 0, lds_scan, total);   // barriers inside: all ids are read
         if (j < mr) {
-            if (a >= 0)
+            if (a >= 0) {
                 tab.remap[(int64_t)g * P + id] = l_ids[a];
-            else
+            } else {
                 l_ids[ml + kept + (int)pre] = id;
+                if (l_places)
+                    l_places[ml + kept + (int)pre] = place;
+            }
         }
         kept += (int)total;
         __syncthreads();

@@ -56,7 +56,7 @@ struct HeightDesc {
     int32_t max_cap;                  // largest left or right set of a node
     bool use_big_tiles;
     int32_t panel_run, panel_items;   // panel kernel (panel.hip): most 64-row stages of an item, 0 = not for this height; most items of a group
-    int32_t panel_from;               // ... shortest head from which it is faster on blocks that have little to do with each other
+    bool panel_few;                   // ... so few tiles that the ring kernel is faster on blocks that have little to do with each other
     int64_t total_s;
 };
 
@@ -74,15 +74,17 @@ struct Q8Desc {
     float *err, *scale, *alpha, *dir;
 };
 
-// Panel kernel (panel.hip): right blocks of a panel, left blocks of a stage, 64-byte slices of a right block that fit a wavefront's
-// registers; and the share of pairs (one in so many) left open at the height before up to which a group takes it.
+// Panel kernel (panel.hip): right blocks of a panel, left blocks of a stage, most stages of an item; and the share of pairs (one in so
+// many) left open at the height before up to which a group takes it.  Head copies (heads.hip): most steps of 64 elements, and bytes of a copy.
 constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
-constexpr int kPanelCols = 512, kPanelRows = 64, kPanelSlices = 11, kPanelRun = 32, kPanelOpen = 1024;
+constexpr int kPanelCols = 512, kPanelRows = 64, kPanelRun = 32, kPanelOpen = 1024;
+constexpr int kHeadSteps = 6, kHeadBytes = 320;
 constexpr int kWholeTile = 128;       // open pairs of a panel item beyond which the ring kernel is taken to have multiplied a tile whole
 
 // Tree calls on tiny groups (tiny.hip): most table entries, stored blocks and tree nodes of a group, bytes of a block, groups.
 constexpr int kTinyEntries = 64, kTinyPool = 128, kTinySlots = 256, kTinyBytes = 4096, kTinyGroups = 512;
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Group-strided work arrays of a plan (device).
@@ -100,7 +102,7 @@ struct WorkDesc {
     int32_t *seg_members;// [G][r_stride]
     int4 *active;        // [G * l_stride][2] merge work list, 32 bytes per target: (group, target's physical id,
                          // member count, index of the first member in seg_members), (physical ids of the first
-                         // two members, unused, unused) -- the merge kernel starts its block loads straight from it
+                         // two members, the target's slot among the head copies or 0, unused) -- the merge kernel starts its block loads straight from it
     int32_t *seg_slot;   // [G][l_stride] position of a target in the work list
     int32_t *n_active;   // [max_heights]
     int32_t *refine;     // [G * r_stride][2] columns that need the fp64 re-check: (g * r_stride + c, node)
@@ -121,8 +123,10 @@ struct WorkDesc {
     int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that the ring kernel multiplied whole for them (1 for any number of a height that was the panel kernel's)
     // panel kernel (panel.hip); panel_on null = not at this height
     int32_t *panel_on, *panel_on_mem;       // [G]
-    u32x4 *panel_rows;       // [G][l_stride][2] a left block's share of the test, as an MFMA operand
-    int4 *panel_items;       // (group, node, first column, first row)
+    char *heads, *heads_mem;                // [G][n][kHeadBytes] head copies (heads.hip); null = none
+    int32_t *set_slot;       // [G][n] beside set_ids: a block's slot among the head copies of its group
+    int32_t *head_steps;     // [G] steps of 64 elements that a head has, 0 = the group has no head copies
+    int4 *panel_items;       // [][2] (group, first row and first column of its set lists, rows << 16 | columns), (first column of the height's, first row of the node, head_steps, unused)
     int32_t *panel_total;    // [max_heights]
     // tree calls on tiny groups (tiny.hip); null where the tree is too large for them
     int4 *tiny_nodes;        // [nodes][2] (l_off, r_off, l_slot, r_slot), (out_slot, r_base, ...), height by height
@@ -199,8 +203,10 @@ void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
                        float *dense_s, bool cleared = false, const HeightDesc *prev = nullptr, int height = 0);
 // early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
-// bfloat16, and a group's keys within the 32-bit offsets of buffer loads
-static inline bool panel_fits(const PoolDesc &pool) { return pool.dtype == KVFUSE_BF16 && (int64_t)pool.P * pool.r * 2 <= 0xFFFFFFFFll; }
+// panel kernel and head copies: bfloat16, and a group's copies within the 32-bit offsets of buffer loads
+static inline bool panel_fits(const PoolDesc &pool, const WorkDesc &w) { return w.heads_mem && pool.dtype == KVFUSE_BF16 && (int64_t)w.n * kHeadBytes <= 0xFFFFFFFFll && launch_fits(((int64_t)w.G * w.n + 15) / 16, 256); }
+void launch_heads(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
+void launch_heads_of_targets(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, int height, float thr_floor);
 void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor);
 void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
 void launch_assign_reset(hipStream_t s, const WorkDesc &w, int height);

@@ -130,13 +130,17 @@ __device__ __forceinline__ uint32_t ordered_bits(float x)
 //
 // The three order statistics of a length are found bit by bit, by counting what lies below: every pair's rank against every other
 // took 30 us at two pairs a lane (11 at one), these counts take 14.
+//
+// head_steps (or null): likewise the steps of 64 elements of the head copies (heads.hip), `wide` slices each, whose test is wider by what the copies
+// miss, some 6.5 % of their share of a block; 0 where kHeadSteps of them would not do, or for a group that is switched off.
 template <int PER>
 __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
-                                                            int32_t *__restrict__ early_nk)
+                                                            int32_t *__restrict__ early_nk, int32_t *__restrict__ head_steps, int wide,
+                                                            const uint8_t *__restrict__ group_enable)
 {
     constexpr int N = PER * kSamples;
     __shared__ float reach[kSteps];
-    __shared__ int best;
+    __shared__ int best, best_steps;
     const int g = blockIdx.x, lane = threadIdx.x & 63;
     for (int len = threadIdx.x >> 6; len < kSteps; len += 16) {
         uint32_t bound[PER];
@@ -163,19 +167,29 @@ __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restr
         if (lane == 0)
             reach[len] = value[1] + 4.0f * fmaxf(0.5f * (value[2] - value[0]), 0.85f * (value[2] - value[1]));
     }
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         best = nk;
-    __syncthreads();
-    for (int slices = 2 + threadIdx.x; 4 * slices <= 3 * nk; slices += 1024) {
-        // between two lengths the reach is taken as a straight line
-        const int len = slices * kSteps / nk, rest = slices * kSteps % nk;
-        const float r0 = reach[len], r1 = reach[min(len + 1, kSteps - 1)];
-        if (r0 + (r1 - r0) * ((float)rest / (float)nk) < thr_floor - 1e-3f)
-            atomicMin(&best, slices);
+        best_steps = kHeadSteps + 1;
     }
     __syncthreads();
-    if (threadIdx.x == 0)
+    // between two lengths the reach is taken as a straight line
+    auto reach_at = [&](int slices) {
+        const int len = slices * kSteps / nk, rest = slices * kSteps % nk;
+        const float r0 = reach[len], r1 = reach[min(len + 1, kSteps - 1)];
+        return r0 + (r1 - r0) * ((float)rest / (float)nk);
+    };
+    for (int slices = 2 + threadIdx.x; 4 * slices <= 3 * nk; slices += 1024)
+        if (reach_at(slices) < thr_floor - 1e-3f)
+            atomicMin(&best, slices);
+    const int steps = 1 + threadIdx.x;
+    if (steps <= kHeadSteps && 4 * steps * wide <= 3 * nk && reach_at(steps * wide) + 0.065f * (float)(steps * wide) / (float)nk < thr_floor - 1e-3f)
+        atomicMin(&best_steps, steps);
+    __syncthreads();
+    if (threadIdx.x == 0) {
         early_nk[g] = best;
+        if (head_steps)
+            head_steps[g] = best_steps <= kHeadSteps && (!group_enable || group_enable[g]) ? best_steps : 0;
+    }
 }
 
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor)
@@ -189,10 +203,11 @@ void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w,
     else
         sample_bounds_kernel<float><<<grid, 256, 0, s>>>((const float *)pool.k, tab.bt, pool.G, pool.P, tab.n, pool.r, n_samples, bounds);
     const int nk = pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64;
+    const int wide = pool.dtype == KVFUSE_BF16 ? 2 : 4;
     if (twice)
-        choose_early_kernel<2><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem);
+        choose_early_kernel<2><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, wide, w.group_enable);
     else
-        choose_early_kernel<1><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem);
+        choose_early_kernel<1><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, wide, w.group_enable);
 }
 
 // The pairs that the tests left open, 16 lanes per pair: the rest of the product, and the pair's entry in its column's

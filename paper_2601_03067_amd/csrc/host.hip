@@ -283,40 +283,23 @@ static int64_t panel_items(const HostHeight &h, int64_t run)
     return c;
 }
 
-// The shortest head, in slices, from which the panel kernel is the faster one at a height of big tiles, on blocks that have little to do
-// with each other (on others, see panel_items_of_group); longer than any it takes if there is none.  It is a matter of how many items
-// there are: a panel's are large (512 columns x 8 to 32 stages), it takes 14 us more beside the ring kernel's launches, and the chip's
-// 256 compute units hold one workgroup of either at a time; and a ring item spends the more on its products the longer the head is.
-// Times of both as rounds of the largest item that the work makes, in us: ring item 6 + 0.3 s and 2.1 + 0.73 s a tile, panel item 14.5 and
-// 0.55 + 0.345 s a stage (three quarters of that where it has no more than half its columns).  Over heights of one node and of four and
-// sixteen equal ones, 256 to 16384 blocks in each set, 1 to 256 groups, heads of 4, 6 and 10 slices (209 of them, both kernels timed) the
-// choice costs 0.5 % on average; the panel kernel everywhere costs up to 88 %.  The line is drawn 5 % to the panel kernel's side: what
-// pairs stay open cost it less (228 requests of 61 blocks, 12 groups, the last height: 398 us ring, 359 panel).  Some of the 209, us
-// of the whole step, ring / panel, 4 KiB blocks, 10 slices: 1024 x 1024 blocks in 16 groups 36 / 68, 64 groups 91 / 81, 256 groups 309 /
-// 252; 4096 x 4096 in 8 groups 112 / 116, 128 groups 1479 / 1173; four nodes of 256 x 256 in 256 groups 119 / 157.
-static int panel_from(const HostHeight &h, int G, int run)
+// Whether a height's tiles are so few that the ring kernel, a tile a compute unit side by side, is the faster one on blocks that have little to
+// do with each other (on others, see panel_items_of_group).  Over heights of one node and of four and sixteen equal ones, 256 to 8192 blocks
+// in each set, 1 to 256 groups, heads of 10 to 11 and of 5 slices (190 of them, both kernels timed) the panel kernel is the faster one
+// wherever there is more than one tile for a compute unit, or an item of more than one, us of the whole step, ring / panel: 1024 x 1024
+// blocks of 4 KiB in 32 groups 50 / 40, 64 groups 80 / 49, 256 groups 283 / 103; 4096 x 4096 in 1 group 49 / 31, 8 groups 111 / 54, 256
+// groups 2822 / 833; four nodes of 256 x 256 in 256 groups 111 / 71.  Of one tile each: 1024 x 1024 in 16 groups 32 / 37, sixteen nodes of
+// 512 x 512 in 4 groups 35 / 41, with the shorter heads 26 / 35.
+static bool panel_few(const HostHeight &h, int G)
 {
-    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-    auto rounds = [&](double total, double item) { return item * std::ceil(total * G / 256.0 / item - 1e-9); };
-    for (int s = 2; s <= kPanelSlices; ++s) {
-        const double first = 6.0 + 0.3 * s, tile = 2.1 + 0.73 * s, stage = 0.55 + 0.345 * s;
-        double ring = 0.0, ring_item = 1.0, panel = 0.0, panel_item = 1.0;
-        for (size_t k = 0; k < h.l_cap.size(); ++k) {
-            const int64_t l = h.l_cap[k], r = h.r_cap[k];
-            if (l == 0 || r == 0)
-                continue;
-            const int64_t tiles = up(l, kBigM), rt = std::min<int64_t>(up(tiles, 4), 4);          // as items_of_node cuts them
-            ring += (double)up(r, kBigN) * (first * (double)up(tiles, rt) + tile * (double)tiles);
-            ring_item = std::max(ring_item, first + tile * (double)rt);
-            const int64_t stages = up(l, kPanelRows), n = up(stages, run), last = r % kPanelCols;
-            const double cols = (double)(r / kPanelCols) + (last == 0 ? 0.0 : last <= kPanelCols / 2 ? 0.75 : 1.0);
-            panel += 14.5 * (double)(n * up(r, kPanelCols)) + stage * (double)stages * cols;
-            panel_item = std::max(panel_item, 14.5 + stage * (double)up(stages, n));
-        }
-        if (rounds(panel, panel_item) + 14.0 < 1.05 * rounds(ring, ring_item))
-            return s;
+    int64_t tiles = 0;
+    for (size_t k = 0; k < h.l_cap.size(); ++k) {
+        const int64_t rows = (h.l_cap[k] + kBigM - 1) / kBigM;
+        if (rows > 4 && h.r_cap[k] > 0)          // (items_of_node: two tiles an item)
+            return false;
+        tiles += rows * ((h.r_cap[k] + kBigN - 1) / kBigN);
     }
-    return kPanelSlices + 1;
+    return tiles * G <= 256;
 }
 
 static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, int cand_cap,
@@ -353,7 +336,9 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.panel_on = nullptr;
     w.panel_on_mem = cv.take<int32_t>((size_t)G);
     w.panel_total = cv.take<int32_t>(kMaxHeights);
-    w.panel_rows = nullptr;
+    w.heads = w.heads_mem = nullptr;
+    w.set_slot = nullptr;
+    w.head_steps = nullptr;
     w.panel_items = nullptr;
     w.group_enable = nullptr;
     w.leaf_src = cv.take<int32_t>((size_t)std::max(n, 1));
@@ -381,26 +366,31 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     }
     size_t panel_room = 0;
     for (HostHeight &h : hs) {
-        // Panel kernel: items of up to 32 stages, whose right blocks' loads (5000 cycles) are then 3 % of their time; shorter ones, down
-        // to 8, while there are fewer than eight a compute unit.
+        // Panel kernel: items of up to 32 stages; shorter ones, down to 8, while there are fewer than eight a compute unit, which holds two
+        // at a time, and down to 2 while there is not one for each place: an item takes some 9 us before its first stage and 1.7 to 2.2 us a
+        // stage (512 right blocks x 4096 left ones, 8 groups, the whole step: 64 items of 8 stages 58 us, 256 of 2 33 us).
         h.dev.panel_run = h.dev.panel_items = 0;
-        h.dev.panel_from = 0;
+        h.dev.panel_few = false;
         if (!h.big)
             continue;
         int run = kPanelRun;
         while (run > 8 && (int64_t)G * panel_items(h, run) < 2048)
             run /= 2;
+        while (run > 2 && (int64_t)G * panel_items(h, run) < 512)
+            run /= 2;
         const int64_t items = panel_items(h, run);
-        if (!launch_fits(items * G + 256, 512))
+        if (!launch_fits(items * G + 512, 256))
             continue;
         h.dev.panel_run = run;
         h.dev.panel_items = (int32_t)items;
-        h.dev.panel_from = panel_from(h, G, run);
+        h.dev.panel_few = panel_few(h, G);
         panel_room = std::max(panel_room, (size_t)items * (size_t)G);
     }
     if (panel_room > 0) {
-        w.panel_rows = cv.take<u32x4>(2 * L);
-        w.panel_items = cv.take<int4>(panel_room);
+        w.heads_mem = cv.take<char>((size_t)G * n * kHeadBytes);
+        w.set_slot = cv.take<int32_t>((size_t)G * n);
+        w.head_steps = cv.take<int32_t>((size_t)G);
+        w.panel_items = cv.take<int4>(2 * panel_room);
     }
     for (HostHeight &h : hs) {
         const size_t nn = h.l_off.size();
@@ -785,9 +775,13 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
     // A pair of blocks of evenly spread energy is not ruled out before a share 1 - floor of their elements: no group's head will fit
-    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 13 of 128 slices), and its launch
+    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 418 of 4096 elements), and its launch
     // would find nothing to do.
-    const bool panel = early && panel_fits(p.pool) && (1.0f - floor_f) * (float)(p.pool.r * 2 / 64) < (float)kPanelSlices;
+    const bool panel = early && panel_fits(p.pool, w) && (1.0f - floor_f) * (float)p.pool.r < 64.0f * (float)kHeadSteps;
+    if (panel)
+        w.heads = w.heads_mem;
+    else
+        w.head_steps = nullptr;
     const bool tiny = !timing && p.tiny_pays();       // (stages are timed where there are stages)
     if (tiny) {
         launch_tiny_tree(c->stream, p.pool, p.tab, w, p.slot_init, nh, thr, band, floor_f, free_list, n_free, n_phys);
@@ -798,6 +792,8 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         if (early)
             launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
         launch_tree_norms(c->stream, p.pool, w, p.tab);
+        if (panel)
+            launch_heads(c->stream, p.pool, w, floor_f);
         KVF_TRY(mark());
         for (int hgt = 0; hgt < nh; ++hgt) {
             const HeightDesc &d = p.heights[hgt].dev;
@@ -810,6 +806,8 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
             launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule, hgt + 1 < nh);
             KVF_TRY(mark());
             launch_merge(c->stream, p.pool, w, d, hgt);
+            if (panel && hgt + 1 < nh)
+                launch_heads_of_targets(c->stream, p.pool, w, hgt, floor_f);
             KVF_TRY(mark());
         }
         launch_rewrite(c->stream, p.pool, p.tab, free_list, n_free, n_phys);

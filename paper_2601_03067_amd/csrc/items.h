@@ -15,71 +15,40 @@ __device__ __forceinline__ int items_of_node(int ml, int mr, int bm, int bn, int
     return n_cp * n_rc;
 }
 
-// A binary32 number as three bfloat16 parts (upper halves of what is left): exact.
+// The first two bfloat16 parts of a binary32 number (upper halves of what is left): both of its sign, less than 2^-14 of it is missing.
 struct Parts {
-    uint32_t h, m, l;      // in the upper halves
+    uint32_t h, m;         // in the upper halves
     __device__ __forceinline__ explicit Parts(float x)
     {
         h = __float_as_uint(x) & 0xFFFF0000u;
-        x -= __uint_as_float(h);
-        m = __float_as_uint(x) & 0xFFFF0000u;
-        x -= __uint_as_float(m);
-        l = __float_as_uint(x) & 0xFFFF0000u;
+        m = __float_as_uint(x - __uint_as_float(h)) & 0xFFFF0000u;
     }
 };
 __device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi) { return (lo >> 16) | hi; }
 
-// Fragments of the MFMA that starts a product.  The 16 summation indices hold, for each of the two terms, the six products of
-// parts that reach 2^-24 of the term: h h, h m, m h, m m, h l, l h.
-__device__ __forceinline__ u32x4 panel_left(float x, float y, int half)
+// A bfloat16 number not below x >= 0, in the upper half.
+__device__ __forceinline__ uint32_t up16(float x) { return (__float_as_uint(x) + 0xFFFFu) & 0xFFFF0000u; }
+
+// Operands of the MFMA that starts a product of heads: the test of a pair (heads.hip),
+//     <q_a, q_b> > floor |a| |b| - tail_a tail_b - E_a H_b - H_a E_b,
+// is of rank four in (a, b), and its right side is what the product starts from.  The eight summation indices hold h h, h m, m h of
+// either of the first two terms and the last two rounded up to bfloat16 (they are a hundredth of the first, 2^-7 of which is the rounding).
+// What the three products of parts miss is not negative and at most 3 / 2^14 of the term: the first term's share of it
+// leaves more pairs open, and the tails are lengthened by 2^-13 for the second's.  x: the norm, y: the tail.
+__device__ __forceinline__ u32x2 panel_left(float x, float y, float e, float h, int half)
 {
-    const Parts p(x), q(y);
-    return half == 0 ? u32x4{pair16(p.h, p.h), pair16(p.m, p.m), pair16(p.h, p.l), pair16(q.h, q.h)}
-                     : u32x4{pair16(q.m, q.m), pair16(q.h, q.l), 0u, 0u};
+    const Parts p(x), q(y * (1.0f + 0x1p-13f));
+    return half == 0 ? u32x2{pair16(p.h, p.h), pair16(p.m, q.h)} : u32x2{pair16(q.h, q.m), pair16(up16(e), up16(h))};
 }
-__device__ __forceinline__ u32x4 panel_right(float x, float y, int half)
+__device__ __forceinline__ u32x2 panel_right(float x, float y, float e, float h, int half)
 {
-    const Parts p(x), q(y);
-    return half == 0 ? u32x4{pair16(p.h, p.m), pair16(p.h, p.m), pair16(p.l, p.h), pair16(q.h, q.m)}
-                     : u32x4{pair16(q.h, q.m), pair16(q.l, q.h), 0u, 0u};
+    const Parts p(x), q(y * (1.0f + 0x1p-13f));
+    return half == 0 ? u32x2{pair16(p.h, p.m), pair16(p.h, q.h)} : u32x2{pair16(q.m, q.h), pair16(up16(h), up16(e))};
 }
 
-// The two factors of a block: its norm (1 for a zero block, whose products then stay below the floor), and its tail's length.  The
-// left norm carries - floor, lowered by 4e-6 of itself: the roundings of the MFMAs (a few 2^-24 of floor |a| |b|) then only leave
-// more pairs open, which finish_pairs_kernel tests whole.
-__device__ __forceinline__ float panel_norm(const PoolDesc &pool, int64_t b)
-{
-    const float norm = (float)pool.norm_k[b];
-    return norm == 0.0f ? 1.0f : norm;
-}
-__device__ __forceinline__ float panel_floor(float thr_floor) { return -thr_floor * (1.0f - 4e-6f); }
-
-// The left blocks' operands, one thread per block of a left set: thread i of a launch over [groups][left blocks of the height].
-__device__ __forceinline__ void panel_row(const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, float thr_floor, int64_t i)
-{
-    if (i >= (int64_t)w.G * h.total_l_cap)
-        return;
-    const int g = (int)(i / h.total_l_cap);
-    const int c = (int)(i - (int64_t)g * h.total_l_cap);
-    if (!w.panel_on[g])
-        return;
-    int lo = 0, hi = h.n_nodes;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (h.l_base[mid] <= c)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    const int row = c - h.l_base[lo];
-    if (row >= w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[lo]])
-        return;
-    const int64_t b = (int64_t)g * pool.P + w.set_ids[(int64_t)g * w.n + h.l_off[lo] + row];
-    const float norm = panel_norm(pool, b);
-    u32x4 *out = w.panel_rows + ((int64_t)g * w.l_stride + c) * 2;
-    out[0] = panel_left(panel_floor(thr_floor) * norm, w.rem_k[b] * norm, 0);
-    out[1] = panel_left(panel_floor(thr_floor) * norm, w.rem_k[b] * norm, 1);
-}
+// The left norm carries - floor, lowered by 8e-6 of itself: the roundings of the MFMAs (a few 2^-24 of floor |a| |b|) and of the norms
+// then only leave more pairs open, which finish_pairs_kernel tests whole.
+__device__ __forceinline__ float panel_floor(float thr_floor) { return -thr_floor * (1.0f - 8e-6f); }
 
 // Rows of a node's items: whole stages, at most `run`, the same number for all but the last.
 __device__ __forceinline__ int panel_rows_per_item(int ml, int run)
@@ -92,9 +61,9 @@ __device__ __forceinline__ int panel_rows_per_item(int ml, int run)
 // A workgroup of 256 for group g: whether the panel kernel takes it at this height, and if so its work items, behind those of the groups
 // that came first.  An item is (group, node, panel of 512 right blocks, run of left blocks); consecutive items of a node share
 // the run, so that the workgroups an XCD holds at a time read the same left rows.  The panel kernel takes a group
-//   - whose head fits its registers,
+//   - whose head fits its registers (head_steps),
 //   - whose tests left few pairs open at the height before (of `prev`, which has no nodes before the first height),
-//   - and, where the ring kernel is faster on blocks that have little to do with each other (panel_from, host.hip), only if tiles were
+//   - and, where the ring kernel is faster on blocks that have little to do with each other (panel_few, host.hip), only if tiles were
 //     multiplied whole at the height before, or there was none.  A whole tile takes the ring kernel some 50 us (4 KiB blocks), and a
 //     height of few tiles ends with it: 13 requests of 492 blocks, a quarter of them common, 8 groups, a height 73 us against 60.
 __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const HeightDesc &h, const HeightDesc &prev, int height, int g)
@@ -109,8 +78,8 @@ __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const He
     for (int k = tid; k < prev.n_nodes; k += 256)
         pairs += (double)w.set_cnt[(int64_t)g * w.n_slots + prev.l_slot[k]] * (double)w.set_cnt[(int64_t)g * w.n_slots + prev.r_slot[k]];
     pairs = block_sum_256(pairs, red);
-    const bool on = w.early_nk[g] <= kPanelSlices && (!w.group_enable || w.group_enable[g]) &&
-                    (double)w.open_cnt[g] * kPanelOpen <= pairs && (w.early_nk[g] >= h.panel_from || prev.n_nodes == 0 || w.whole[g]);
+    const bool on = w.head_steps[g] > 0 && (!w.group_enable || w.group_enable[g]) &&
+                    (double)w.open_cnt[g] * kPanelOpen <= pairs && (!h.panel_few || prev.n_nodes == 0 || w.whole[g]);
     auto items_of = [&](int k, int &n_cp, int &rows) {
         const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
         n_cp = (mr + kPanelCols - 1) / kPanelCols;
@@ -152,7 +121,11 @@ __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const He
                     hi = mid;
             }
             const int q = i - node0[lo];
-            w.panel_items[run + i] = make_int4(g, k0 + lo, (q % node_cp[lo]) * kPanelCols, q / node_cp[lo] * node_rows[lo]);
+            const int k = k0 + lo, col = (q % node_cp[lo]) * kPanelCols, row = q / node_cp[lo] * node_rows[lo];
+            const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
+            int4 *out = w.panel_items + 2 * (int64_t)(run + i);
+            out[0] = make_int4(g, h.l_off[k] + row, h.r_off[k] + col, min(ml - row, node_rows[lo]) << 16 | min(mr - col, kPanelCols));
+            out[1] = make_int4(h.r_base[k] + col, row, w.head_steps[g], 0);
         }
         run += (int)sum;
         __syncthreads();

@@ -1,21 +1,22 @@
-// Early rejection at the large heights of a tree call (early.hip): the heads of all pairs of a node's blocks, with the right
-// blocks' heads held in registers.
+// Early rejection at the large heights of a tree call (early.hip): the head copies (heads.hip) of all pairs of a node's blocks, with the
+// right blocks' copies held in registers.
 //
-// The head is short (nk of 64 slices, 10 at thr 0.9), so a wavefront can keep the heads of 64 right blocks in registers,
-// as MFMA operands, and let the left blocks go by: every left fragment is read from LDS once per wavefront and feeds two MFMAs,
-// a left row crosses L2 -> LDS once per 512 right blocks instead of once per 256, no right row does at all, and the
-// workgroup meets at a barrier every 64 left rows instead of every 64-byte slice.  The test of a pair,
-//     <a_head, b_head> > floor |a| |b| - (tail_a |a|) (tail_b |b|),
-// is of rank two in (a, b): its right side is subtracted by the MFMA that starts a product (the two terms, each factor as three
-// bfloat16 parts: panel_left, panel_right), so that all that is left to do with an accumulator is to look at its sign.
+// A copy is short (up to 384 elements of six bits), so a wavefront can keep those of 128 right blocks in registers, as MFMA operands, and
+// let the left blocks go by: every left fragment is read from LDS once per wavefront and feeds four MFMAs, a left row crosses
+// L2 -> LDS once per 512 right blocks, no right row does at all, and the workgroup meets at a barrier every 64 left rows.  The
+// test of a pair is what its product starts from, by one MFMA (items.h), so that all that is left to do with an accumulator is to look at its
+// sign.  A workgroup has four wavefronts and a compute unit holds two, whose barriers, tests and first loads the other one's
+// products cover.
 //
-// What bounds it: the MFMA units, busy 65 % of the cycles at the largest heights, at a clock of 1.8 to 1.9 GHz
-// (profiles/cases_kernels.md); the rest is the step from one 64-row stage to the next, where all wavefronts meet.  The ring kernel
-// (similarity.hip) had them busy 43 % there: it spends 14 000 of the 24 000 cycles of a 256 x 256 tile on the tests and on the way
-// from tile to tile.  Similarity of the largest node of 512 ragged requests (8 groups, some 45 000 blocks in each set): 14.2 -> 9.4 ms;
-// the whole fusion of these 43.8 -> 32.5 ms, of 64 requests x 128 blocks in 256 groups (sets of 256 blocks and more) 19.9 -> 18.9 ms.
-// Tried and dropped: each wavefront at its own pace, with counts in LDS of what has landed and what is done instead of the
-// barrier (10 % slower: two round trips to LDS per 32 rows); fragments waited for where they are read (58 % busy).
+// What bounds it: power.  At the largest heights the MFMA units are busy 67 % of the cycles at 1.65 GHz; the same instructions on the
+// same kind of data do not get beyond 1.4 GHz from registers (5.8 PFLOP/s against 9.9 at 2.4 GHz on zeros).  With heads of bfloat16 from the
+// pool (10 or 11 slices, 22 MFMAs of 32 x 32 x 16 instead of 6 of 32 x 32 x 64 and the test's) the largest node of 512 ragged requests (8
+// groups, some 45 000 blocks in each set) took 9.1 ms, now 3.2; the whole fusion of these 32.2 -> 18.6 ms, of 64 requests x 128 blocks in 256
+// groups 18.8 -> 17.8 ms.
+// Tried and dropped: three stages in LDS instead of two (unchanged); the accumulators looked at two by two with the next rows' products
+// begun behind that, across the barrier (1 % fewer cycles, the same time); loads into LDS between products (registers spill); wavefronts of
+// a workgroup or around products at a higher priority (unchanged); eight wavefronts of 64 right blocks, each at its own pace, with counts
+// in LDS instead of the barrier (10 % slower: two round trips to LDS per 32 rows).
 #include <type_traits>
 
 #include "items.h"
@@ -25,9 +26,31 @@ namespace kvfuse {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ floatx16 test_mma(const u32x2 a, const u32x2 b, floatx16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
+}
+
 __device__ __forceinline__ floatx16 panel_mma(const u32x4 a, const u32x4 b, floatx16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// 64 elements of e2m3 (format 2), 32 of them in a lane's six registers.
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ floatx16 head_mma(const u32x6 a, const u32x6 b, floatx16 c)
+{
+    auto wide = [](const u32x6 x) { return i32x8{(int)x[0], (int)x[1], (int)x[2], (int)x[3], (int)x[4], (int)x[5], 0, 0}; };
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wide(a), wide(b), c, 2, 2, 0, 0, 0, 0);
+}
+// A step's six registers from the three pieces of its pair of steps.
+template <bool HIGH>
+__device__ __forceinline__ u32x6 of_pieces(const u32x4 x, const u32x4 y, const u32x4 z)
+{
+    return HIGH ? u32x6{y[2], y[3], z[0], z[1], z[2], z[3]} : u32x6{x[0], x[1], x[2], x[3], y[0], y[1]};
 }
 
 // body(0), ..., body(N - 1) with the index a constant from the start: register arrays that loops index before they are unrolled
@@ -42,110 +65,108 @@ __device__ __forceinline__ void each(F body)
 }
 
 // Nothing behind this waits for loads into these registers any more.
-__device__ __forceinline__ void landed_regs(u32x4 &a, u32x4 &b, u32x4 &c, u32x4 &d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+__device__ __forceinline__ void landed_regs(u32x6 &a) { asm volatile("" : "+v"(a)); }
 
 __device__ __forceinline__ u32x4 lds_read(const char *at) { return *reinterpret_cast<const u32x4 *>(at); }
+
+// Five loads of 16 bytes a lane into LDS: 64 bytes on in memory, kPanelRows * 64 on in LDS (an instruction's offset counts on either side).  In
+// assembly, because the compiler makes every LDS read wait for all such loads of its own, whichever buffer they are for; who issues
+// them waits for them by hand.  (No register is loaded.  The pause is for scalar registers that a vector instruction has just written, and for m0.)
+__device__ __forceinline__ void stage_to_lds(uint64_t base, uint32_t off, uint32_t to)
+{
+    typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
+    const desc_t desc = {(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
+    static_assert(kPanelRows * 64 - 64 == 4032, "the steps of m0 below");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen lds\n\t"
+                 "s_add_i32 m0, %2, 4032\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen offset:64 lds\n\t"
+                 "s_add_i32 m0, %2, 8064\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen offset:128 lds\n\t"
+                 "s_add_i32 m0, %2, 12096\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen offset:192 lds\n\t"
+                 "s_add_i32 m0, %2, 16128\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen offset:256 lds" ::"v"(off), "s"(desc), "s"(to) : "memory", "m0", "scc");
+}
 
 struct PanelArgs {
     PoolDesc pool;
     WorkDesc w;
-    HeightDesc h;
     int32_t height;
     float thr_floor;
 };
 
-__global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args)
+__global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args)
 {
-    const PoolDesc &pool = args.pool;
     const WorkDesc &w = args.w;
-    const HeightDesc &h = args.h;
-    constexpr int NK = kPanelSlices, SLICE = kPanelRows * 64, MAXC = 2048;
+    constexpr int NC = 4, QUAD = kPanelRows * 64, STAGE = 5 * QUAD, MAXC = 2048;
     constexpr int DENSE = 32;           // open pairs of a wavefront's 32 x 64 from which they are multiplied whole
-    __shared__ __attribute__((aligned(1024))) char stage[2][NK * SLICE];
-    __shared__ __attribute__((aligned(1024))) u32x4 left_fc[2][2][2][32];      // left blocks' fragments of the test: [stage][32 rows][half][row]
+    // Two stages of 64 left rows each, four pieces of 16 bytes of a row side by side, five times (18 of codes, 2 of the test).
+    __shared__ __attribute__((aligned(1024))) char stages[2 * STAGE];
     __shared__ int lds_n, lds_full[2], lds_first;
     __shared__ uint32_t lds_pair[MAXC];         // row of the item << 16 | column of the panel
-    __shared__ __attribute__((aligned(1024))) u32x4 right_fc[8][2][64];        // right blocks': [wavefront][32 columns][lane]
-    __shared__ uint32_t lds_dense[kPanelRun / 2];        // a bit per (stage, 32 rows of it, wavefront)
+    __shared__ __attribute__((aligned(1024))) u32x2 right_fc[4][NC][64];       // right blocks' operands of the test: [wavefront][32 columns][lane]
+    __shared__ uint32_t lds_dense[kPanelRun / 2];        // a bit per (stage, 32 rows of it, 64 columns)
 
     const int total = w.panel_total[args.height];
     const int seat = blockIdx.x >> 3;
-    const int v = (seat >> 5 << 8) + (int)((blockIdx.x & 7) << 5) + (seat & 31);      // the XCDs take 32 consecutive items in turn
+    const int v = (seat >> 6 << 9) + (int)((blockIdx.x & 7) << 6) + (seat & 63);      // the XCDs take 64 consecutive items in turn
     if (v >= total)
         return;
-    const int4 item = w.panel_items[v];
-    const int g = item.x, node = item.y, col0 = item.z, row0 = item.w;
-    const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[node]];
-    const int mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[node]];
-    const int n_rows = min(ml - row0, panel_rows_per_item(ml, h.panel_run));
+    const int4 item = w.panel_items[2 * (int64_t)v], item2 = w.panel_items[2 * (int64_t)v + 1];
+    const int g = item.x, n_rows = item.w >> 16, n_cols = item.w & 0xFFFF, steps = item2.z;
     const int n_stages = (n_rows + kPanelRows - 1) / kPanelRows;
-    const int32_t *__restrict__ l_ids = w.set_ids + (int64_t)g * w.n + h.l_off[node] + row0;
-    const int32_t *__restrict__ r_ids = w.set_ids + (int64_t)g * w.n + h.r_off[node] + col0;
-    const int n_cols = min(mr - col0, kPanelCols);
-    const int nk = w.early_nk[g];
-    const int row_bytes = pool.r * 2;
-    const char *__restrict__ kg = (const char *)pool.k + (int64_t)g * pool.P * row_bytes;
-    const u32x4 *__restrict__ rows = w.panel_rows + ((int64_t)g * w.l_stride + h.l_base[node] + row0) * 2;
+    const int32_t *__restrict__ l_places = w.set_slot + (int64_t)g * w.n + item.y;
+    const int32_t *__restrict__ r_places = w.set_slot + (int64_t)g * w.n + item.z;
+    const char *__restrict__ heads = w.heads + (int64_t)g * w.n * kHeadBytes;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l31 = lane & 31, half = lane >> 5;
 
-    // A panel of more than 256 right blocks: a wavefront per 64 of them.  A narrower one: per 64 blocks two wavefronts, which take
+    // A panel of more than 256 right blocks: a wavefront per 128 of them.  A narrower one: per 128 blocks two wavefronts, which take
     // turns at the left rows.
     const bool wide = n_cols > kPanelCols / 2;
-    const int my_col = (wide ? wave : wave & 3) * 64;
-    const int sub0 = wide ? 0 : wave >> 2, sub_step = wide ? 1 : 2;
+    const int my_col = (wide ? wave : wave & 1) * 128;
+    const int sub0 = wide ? 0 : wave >> 1, sub_step = wide ? 1 : 2;
 
-    // ---- loaders: this lane's row of a stage, and its (swizzled) 16 bytes of every other slice of it.  (Buffer loads, whose
-    // offsets have 32 bits: the compiler counts global loads into LDS among the LDS's own operations, whose order it then takes for
-    // unknown, so that every wait for a fragment would be for all fragments on their way.)
-    const __amdgpu_buffer_rsrc_t pool_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kg, 0, 0xFFFFFFFFu, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rows_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)rows, 0, 0xFFFFFFFFu, 0x00020000);
-    const int ld_row = (wave & 3) * 16 + (lane >> 2);
+    // ---- loaders: this lane's row of a stage, and its (swizzled) piece of every four
+    const uint64_t heads_at = (uint64_t)heads;
+    const uint32_t stage_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)stages) + (uint32_t)wave * 1024u;
+    const int ld_row = wave * 16 + (lane >> 2);
     const uint32_t ld_off = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
-    auto row_at = [&](int t) __attribute__((always_inline)) { return min(t * kPanelRows + ld_row, n_rows - 1); };
-    auto load_stage = [&](int t, int id) __attribute__((always_inline)) {
-        char *dst = stage[t & 1] + (wave >> 2) * SLICE + (wave & 3) * 1024;
-        const uint32_t src = (uint32_t)id * (uint32_t)row_bytes + ld_off;
-        for (int s = wave >> 2; s < nk; s += 2) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(pool_rsrc, (__attribute__((address_space(3))) void *)dst, 16, src, s * 64, 0, 0);
-            dst += 2 * SLICE;
-        }
-        if (wave >= 6) {
-            const int row = min(t * kPanelRows + (wave - 6) * 32 + l31, n_rows - 1);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_rsrc, (__attribute__((address_space(3))) void *)left_fc[t & 1][wave - 6], 16,
-                                                     (uint32_t)(2 * row + half) * 16u, 0, 0, 0);
-        }
-    };
+    auto row_of = [&](int t) __attribute__((always_inline)) { return (uint32_t)l_places[min(t * kPanelRows + ld_row, n_rows - 1)] * (uint32_t)kHeadBytes; };
+    auto load_stage = [&](uint32_t row, uint32_t at) __attribute__((always_inline)) { stage_to_lds(heads_at, row + ld_off, stage_at + at); };
 
     if (tid == 0)
         lds_n = lds_full[0] = lds_full[1] = 0;
     if (tid < kPanelRun / 2)
         lds_dense[tid] = 0;
-    int id = l_ids[row_at(0)];
-    load_stage(0, id);
-    id = l_ids[row_at(1)];
-    const int frag = l31 * 64 + ((half ^ ((l31 >> 2) & 3)) * 16);
+    uint32_t row = row_of(0);
+    load_stage(row, 0);
+    row = row_of(1);
+    const int frag = l31 * 64 + ((half ^ ((l31 >> 2) & 3)) * 16);         // piece 2 m + half: every second m, 32 bytes on; another quad every two
+    const int test_at = 4 * QUAD + ((l31 * 64 + ((l31 >> 2) & 3) * 16) ^ 32) + half * 8;       // piece 18: eight bytes for either half
     // Once through this loop, unless the list of open pairs fills up on the way: then it is emptied, and the right blocks, whose
     // registers that takes, are loaded again.
     for (int t = 0;;) {
-        u32x4 fb[NK][2][2];
-        // (a row has more than NK slices: those past the group's nk are loaded and not used)
-        each<2>([&](auto c) __attribute__((always_inline)) {
+        u32x6 fb[kHeadSteps][NC];
+        each<NC>([&](auto c) __attribute__((always_inline)) {
             const int col = my_col + 32 * c + l31;
-            const int rid = r_ids[min(col, n_cols - 1)];
-            const char *src = kg + ((int64_t)rid * row_bytes + half * 16);
-            each<NK>([&](auto s) __attribute__((always_inline)) {
-                fb[s][0][c] = *reinterpret_cast<const u32x4 *>(src + 64 * s);
-                fb[s][1][c] = *reinterpret_cast<const u32x4 *>(src + 64 * s + 32);
+            const char *src = heads + ((int64_t)r_places[min(col, n_cols - 1)] * kHeadBytes + half * 16);
+            each<kHeadSteps / 2>([&](auto p) __attribute__((always_inline)) {
+                u32x4 x[3];
+                each<3>([&](auto j) __attribute__((always_inline)) { x[j] = *reinterpret_cast<const u32x4 *>(src + (3 * p + j) * 32); });
+                fb[2 * p][c] = of_pieces<false>(x[0], x[1], x[2]);
+                fb[2 * p + 1][c] = of_pieces<true>(x[0], x[1], x[2]);
             });
-            const int64_t b = (int64_t)g * pool.P + rid;
-            const float norm = panel_norm(pool, b);
-            // past the last column: a floor of 16 times the norms, above every cosine (thr_floor > 1/4)
-            right_fc[wave][c][lane] = panel_right(col < n_cols ? norm : 16.0f * norm, col < n_cols ? w.rem_k[b] * norm : 0.0f, half);
+            u32x2 test = *reinterpret_cast<const u32x2 *>(src + 304 - 8 * half);
+            // past the last column: a floor of 2^30 times the left norm, above every product
+            if (col >= n_cols)
+                test = panel_right(0x1p30f, 0.0f, 0.0f, 0.0f, half);
+            right_fc[wave][c][lane] = test;
         });
         // whole before the loop: nothing in it may wait for these loads behind the ones into LDS
-        each<NK>([&](auto s) __attribute__((always_inline)) { landed_regs(fb[s][0][0], fb[s][0][1], fb[s][1][0], fb[s][1][1]); });
+        each<kHeadSteps>([&](auto s) __attribute__((always_inline)) { each<NC>([&](auto c) __attribute__((always_inline)) { landed_regs(fb[s][c]); }); });
 
         for (; t < n_stages; ++t) {
             // this wavefront's loads of stage t have landed; behind the barrier all have, and nobody reads stage t - 1 any more
@@ -154,67 +175,73 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
             if (__builtin_expect(__builtin_amdgcn_readfirstlane(__hip_atomic_load(&lds_full[(t + 1) & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)), 0))
                 break;
             if (t + 1 < n_stages) {
-                load_stage(t + 1, id);
-                id = l_ids[row_at(t + 2)];
+                load_stage(row, (uint32_t)((t + 1) & 1) * STAGE);
+                row = row_of(t + 2);
             }
             if (my_col >= n_cols)
                 continue;
+            const char *stage = stages + (t & 1) * STAGE;
+            // A step's fragment of 32 left rows (at `rows`): pieces 3 p, 3 p + 1 and 3 p + 2 of a pair of steps hold its first 16 bytes, eight
+            // of either step, and the second's last 16.
+            auto fragment = [&](const char *rows, auto s) __attribute__((always_inline)) {
+                constexpr int m = 3 * (s / 2) + 2 * (s & 1), y = 3 * (s / 2) + 1;
+                const u32x4 x4 = lds_read(rows + (m & 1 ? frag ^ 32 : frag) + (m >> 1) * QUAD);
+                const u32x2 x2 = *reinterpret_cast<const u32x2 *>(rows + (y & 1 ? frag ^ 32 : frag) + (y >> 1) * QUAD + 8 * (s & 1));
+                return s & 1 ? u32x6{x2[0], x2[1], x4[0], x4[1], x4[2], x4[3]} : u32x6{x4[0], x4[1], x4[2], x4[3], x2[0], x2[1]};
+            };
+            // Three fragments are on their way or in use at a time: a step's place is asked for anew as soon as its products are issued.
+            u32x6 fa[3];
+            each<3>([&](auto s) __attribute__((always_inline)) { fa[s] = fragment(stage + sub0 * 2048, s); });
 #pragma unroll 1
             for (int sub = sub0; sub < 2; sub += sub_step) {
-                int n_slices = nk;
-                asm volatile("" : "+s"(n_slices));      // (or the comparisons below are kept for the whole loop, in two registers each)
-                const char *at0 = stage[t & 1] + frag + sub * 2048, *at1 = stage[t & 1] + (frag ^ 32) + sub * 2048;
-                // Four fragments are on their way or in use at a time: one is asked for as soon as the products of its place's last one are
-                // issued, the products of three fragments ahead of its own.  (Behind the last slice: whatever is there, not used.)
-                u32x4 fa[4] = {lds_read(at0), lds_read(at1), lds_read(at0 + SLICE), lds_read(at1 + SLICE)};
-                floatx16 acc0, acc1;
+                const char *rows = stage + sub * 2048;
+                int n_steps = steps;
+                asm volatile("" : "+s"(n_steps));      // (or the comparisons below are kept for the whole loop, in two registers each)
+                floatx16 acc[NC];
                 {
-                    const u32x4 fl = left_fc[t & 1][sub][half][l31];
+                    const u32x2 fl = *reinterpret_cast<const u32x2 *>(rows + test_at);
                     floatx16 zero;
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
                         zero[e] = 0.0f;
-                    acc0 = panel_mma(fl, right_fc[wave][0][lane], zero);
-                    acc1 = panel_mma(fl, right_fc[wave][1][lane], zero);
+                    each<NC>([&](auto c) __attribute__((always_inline)) { acc[c] = test_mma(fl, right_fc[wave][c][lane], zero); });
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                each<NK>([&](auto s) __attribute__((always_inline)) {
-                    if (s < n_slices) {
-                        constexpr int i = 2 * (s & 1);
-                        acc0 = panel_mma(fa[i], fb[s][0][0], acc0);
-                        acc1 = panel_mma(fa[i], fb[s][0][1], acc1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (s + 2 < NK)
-                            fa[i] = lds_read(at0 + (s + 2) * SLICE);
-                        __builtin_amdgcn_sched_barrier(0);
-                        acc0 = panel_mma(fa[i + 1], fb[s][1][0], acc0);
-                        acc1 = panel_mma(fa[i + 1], fb[s][1][1], acc1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (s + 2 < NK)
-                            fa[i + 1] = lds_read(at1 + (s + 2) * SLICE);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                each<kHeadSteps>([&](auto s) __attribute__((always_inline)) {
+                    if (s < n_steps)
+                        each<NC>([&](auto c) __attribute__((always_inline)) { acc[c] = head_mma(fa[s % 3], fb[s][c], acc[c]); });
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (s < 3)
+                        fa[s % 3] = fragment(rows, std::integral_constant<int, s + 3>{});
+                    else             // (behind the last rows: whatever is there, not used)
+                        fa[s % 3] = fragment(rows + 2048, std::integral_constant<int, s - 3>{});
+                    __builtin_amdgcn_sched_barrier(0);
                 });
-                float mx0 = -1.0f, mx1 = -1.0f;
+                float mx[NC];
+                each<NC>([&](auto c) __attribute__((always_inline)) {
+                    mx[c] = -1.0f;
 #pragma unroll
-                for (int e = 0; e < 16; e += 2) {
-                    mx0 = fmaxf(fmaxf(acc0[e], acc0[e + 1]), mx0);
-                    mx1 = fmaxf(fmaxf(acc1[e], acc1[e + 1]), mx1);
-                }
-                if (__builtin_expect(__any(fmaxf(mx0, mx1) >= 0.0f), 0)) {
-                    const int r0 = sub * 32 + 4 * half;               // element e: row r0 + 8 (e / 4) + e % 4 of the stage
-                    uint32_t closed = 0;                              // bit 31 - e: acc0[e], bit 15 - e: acc1[e]; their signs
+                    for (int e = 0; e < 16; e += 2)
+                        mx[c] = fmaxf(fmaxf(acc[c][e], acc[c][e + 1]), mx[c]);
+                });
+                if (__builtin_expect(!__any(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])) >= 0.0f), 1))
+                    continue;
+                const int r0 = sub * 32 + 4 * half;               // element e: row r0 + 8 (e / 4) + e % 4 of the stage
+                each<NC / 2>([&](auto cc) __attribute__((always_inline)) {
+                    uint32_t closed = 0;                          // bit 31 - e: the first 32 columns, bit 15 - e: the others; their signs
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
-                        closed = __builtin_amdgcn_alignbit(closed, __float_as_uint(acc0[e]), 31);
+                        closed = __builtin_amdgcn_alignbit(closed, __float_as_uint(acc[2 * cc][e]), 31);
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
-                        closed = __builtin_amdgcn_alignbit(closed, __float_as_uint(acc1[e]), 31);
+                        closed = __builtin_amdgcn_alignbit(closed, __float_as_uint(acc[2 * cc + 1][e]), 31);
                     uint32_t mask = ~closed;
                     int open = 0;
                     unsigned long long lanes;
                     for (uint32_t m = mask; (lanes = __ballot(m != 0)) != 0 && open <= DENSE; m &= m - 1)
                         open += __popcll(lanes);
+                    if (open == 0)
+                        return;
                     if (__builtin_expect(open <= DENSE, 1)) {
                         int k = 0;
                         if (lane == 0) {
@@ -228,14 +255,14 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
                                 const int bit = __builtin_ctz(mask), e = 15 - (bit & 15);
                                 const int slot = k + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0));
                                 lds_pair[slot] = (uint32_t)(t * kPanelRows + r0 + 8 * (e >> 2) + (e & 3)) << 16 |
-                                                 (uint32_t)(my_col + (bit < 16 ? 32 : 0) + l31);
+                                                 (uint32_t)(my_col + 64 * cc + (bit < 16 ? 32 : 0) + l31);
                             }
                             k += __popcll(lanes);
                         }
                     } else if (lane == 0) {
-                        atomicOr(&lds_dense[t >> 1], 1u << ((t & 1) * 16 + sub * 8 + wave));
+                        atomicOr(&lds_dense[t >> 1], 1u << ((t & 1) * 16 + sub * 8 + (my_col >> 6) + cc));
                     }
-                }
+                });
             }
         }
 
@@ -244,9 +271,12 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
         const PanelArgs &again = kernel_args_again<PanelArgs>();
         const PoolDesc &pool = again.pool;
         const WorkDesc &w = again.w;
-        const HeightDesc &h = again.h;
+        const int row_bytes = pool.r * 2, row0 = item2.y;
+        const char *__restrict__ kg = (const char *)pool.k + (int64_t)g * pool.P * row_bytes;
+        const int32_t *__restrict__ l_ids = w.set_ids + (int64_t)g * w.n + item.y;
+        const int32_t *__restrict__ r_ids = w.set_ids + (int64_t)g * w.n + item.z;
         const float thr_floor = again.thr_floor;
-        const int64_t cbase = (int64_t)g * w.r_stride + h.r_base[node] + col0;
+        const int64_t cbase = (int64_t)g * w.r_stride + item2.x;
         const float *__restrict__ inv = pool.inv_norm_k + (int64_t)g * pool.P;
         const int n = lds_n;
         if (tid == 0 && n > 0) {
@@ -257,13 +287,13 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
         }
         __syncthreads();
         const int first = n > 0 ? lds_first : 0;
-        for (int k = tid; k < n; k += 512) {
+        for (int k = tid; k < n; k += 256) {
             const int row = (int)(lds_pair[k] >> 16), col = (int)(lds_pair[k] & 0xFFFFu);
             const bool real = row < n_rows;              // (a row past the end is the last one again)
             if (first + k < w.pair_cap)
                 w.pairs[first + k] = make_int4(real ? (int)(cbase + col) : -1, (row0 + row) | kPairWhole, l_ids[min(row, n_rows - 1)], r_ids[col]);
         }
-        for (int k = max(0, w.pair_cap - first) + wave; k < n; k += 8) {
+        for (int k = max(0, w.pair_cap - first) + wave; k < n; k += 4) {
             const int row = (int)(lds_pair[k] >> 16), col = (int)(lds_pair[k] & 0xFFFFu);
             if (row >= n_rows)
                 continue;
@@ -289,10 +319,10 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
         for (int word = 0; word < (n_stages + 1) / 2; ++word) {
             uint32_t bits = __builtin_amdgcn_readfirstlane(lds_dense[word]);
             for (int i = 0; bits; bits &= bits - 1, ++i) {
-                if ((i & 7) != wave)
+                if ((i & 3) != wave)
                     continue;
                 const int bit = __builtin_ctz(bits);
-                const int r0 = (2 * word + (bit >> 4)) * kPanelRows + ((bit >> 3) & 1) * 32, c0 = (wide ? bit & 7 : bit & 3) * 64;
+                const int r0 = (2 * word + (bit >> 4)) * kPanelRows + ((bit >> 3) & 1) * 32, c0 = (bit & 7) * 64;
                 floatx16 acc0, acc1;
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
@@ -340,8 +370,8 @@ __global__ __launch_bounds__(512, 1) void similarity_panel_kernel(PanelArgs args
 // The panel kernel's share of a height's similarity step; the ring kernel takes the groups that are not panel_on.
 void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor)
 {
-    const int64_t items = ((int64_t)w.G * h.panel_items + 255) / 256 * 256;
-    similarity_panel_kernel<<<(unsigned)items, 512, 0, s>>>(PanelArgs{pool, w, h, height, thr_floor});
+    const int64_t items = ((int64_t)w.G * h.panel_items + 511) / 512 * 512;
+    similarity_panel_kernel<<<(unsigned)items, 256, 0, s>>>(PanelArgs{pool, w, height, thr_floor});
 }
 
 }  // namespace kvfuse

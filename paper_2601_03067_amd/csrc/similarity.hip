@@ -1033,17 +1033,12 @@ __device__ __forceinline__ int4 item_of_node(int local, int n_cp, int rt, int n_
     return make_int4(node, cp * bn, rc * rt * bm | rt | (local == 0 && whole_first ? kWholeFirst : 0), g);
 }
 
-// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is; and one per left block for
-// the panel kernel's operands.
-__global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, float thr_floor, int bm, int bn)
+// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is.
+__global__ __launch_bounds__(256) void items_fill_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
 {
     __shared__ int64_t lds4[4], before[256];
     const int tid = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + tid, n_slots = (int64_t)w.G * h.item_cap;
-    if (w.panel_on)
-        panel_row(pool, w, h, thr_floor, i);
-    if (i0 >= n_slots)
-        return;
     const int g = (int)(i / h.item_cap);
     const int item = (int)(i - (int64_t)g * h.item_cap);
     int64_t at;                                  // where the group begins in either list: nodes' first items in the lower half, others in the upper one
@@ -1177,12 +1172,11 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
         return;
     {
         const int bm = BIG ? 256 : 128;
-        const int64_t rows = w.panel_on ? (int64_t)w.G * h.total_l_cap : 0;
         if (!w.panel_on && (int64_t)w.G * h.n_nodes <= 1024 && total <= kFewItems) {
             items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, bm, bm);
         } else {
             items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
-            items_fill_kernel<<<(unsigned)((std::max(total, rows) + 255) / 256), 256, 0, s>>>(pool, w, h, thr_floor, bm, bm);
+            items_fill_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(w, h, bm, bm);
         }
         if (w.panel_on)
             launch_similarity_panel(s, pool, w, h, height, thr_floor);

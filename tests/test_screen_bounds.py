@@ -8,6 +8,11 @@
                   |cos(a, b) - (<q(a), q(b)> s_a s_b + alpha_a alpha_b)| <= e_a + e_b + e_a e_b,
                   e = |u_c - q s| + 2e-6  (the margin covers the roundings of m and alpha)
 
+and of the one that the head copies of the panel kernel rest on (csrc/heads.hip):
+
+* head copies:    <a, b> <= <q_a, q_b> / (s_a s_b) + E_a H_b + H_a E_b + tail_a tail_b, q = nearest e2m3 value of every element of s x[:p],
+                  s a power of two, E = |x[:p] - q / s|, H = |x[:p]| + 3 E / 2, and with the operands of its test, in bfloat16 parts
+
 The e4m3 values are written out from the format's definition (4 exponent bits, bias 7, 3 mantissa bits, subnormals,
 largest finite value 448) and rounding is done by a nearest-value search, independently of any conversion routine.  The
 inputs include the cases where the bounds are tight or the copies are bad: parallel vectors, vectors whose energy sits
@@ -132,3 +137,55 @@ def test_centred_fp8_copy_bound_holds_for_any_direction(r, direction):
     # the block that IS the direction has nothing left to store: zeros (or rounding dust), error at the margin
     if direction == "one of the blocks":
         assert copies[5][3] < 1e-4 and abs(copies[5][2] - 1.0) < 1e-6
+
+
+def _e2m3_values():
+    v = np.array(sorted({m / 8.0 if e == 0 else (1.0 + m / 8.0) * 2.0 ** (e - 1) for e in range(4) for m in range(8)}))
+    return np.concatenate([-v[::-1], v])
+
+
+def _upper(x, up=False):
+    """The bfloat16 number in a binary32 number's upper half; the next one if there is something behind it and ``up``."""
+    bits = np.float32(x).view(np.uint32)
+    return np.uint32((int(bits) + (0xFFFF if up else 0)) & 0xFFFF0000).view(np.float32)
+
+
+def _parts(x):
+    h = _upper(x)
+    return float(h), float(_upper(np.float32(x) - h))
+
+
+@pytest.mark.parametrize("r", [512, 2048])
+@pytest.mark.parametrize("steps", [1, 4, 6])
+def test_head_copy_bound_holds_also_in_the_operands_of_its_test(r, steps):
+    table = _e2m3_values()
+    assert table.max() == 7.5 and len(table) == 64
+    rng = np.random.default_rng(31 + r + steps)
+    p, floor = 64 * steps, 0.898
+    cases = list(_cases(rng, r))
+    for name, a, b in cases + [(n + ", scaled", a * 2.0 ** 39, b * 2.0 ** -39 / np.sqrt(r)) for n, a, b in cases]:
+        side = []
+        for x in (a, b):
+            norm, head = np.linalg.norm(x), np.linalg.norm(x[:p])
+            most = 20 - int(np.floor(np.log2(norm)))
+            k = most if head == 0.0 else min(int(np.floor(np.log2(2.5 * np.sqrt(p) / head))), most)
+            s = 2.0 ** np.clip(k, -100, 100)
+            q = _nearest(table, s * x[:p])
+            err = np.linalg.norm(s * x[:p] - q)
+            side.append((q, s * norm, s * np.linalg.norm(x[p:]), err, s * head + 1.5 * err, s))
+        (qa, na, ta, ea, ha, sa), (qb, nb, tb, eb, hb, sb) = side
+        dot = float(a @ b) * sa * sb
+        bound = float(qa @ qb) + ea * hb + ha * eb + ta * tb
+        assert dot <= bound + 1e-9 * na * nb, (name, "bound")
+        if name == "unrelated":
+            assert 0.02 * ha < ea < 0.04 * ha               # 3 mantissa bits on elements of 1.25 to 2.5 root mean square
+        # the test as the kernel makes it: three products of parts for norms and tails (lengthened by 2^-13), rounded up for the rest
+        grow = np.float32(1.0 + 2.0 ** -13)
+        (xh, xm), (yh, ym) = _parts(np.float32(floor) * np.float32(1 - 8e-6) * np.float32(na)), _parts(np.float32(ta) * grow)
+        (uh, um), (vh, vm) = _parts(np.float32(nb)), _parts(np.float32(tb) * grow)
+        first = xh * uh + xh * um + xm * uh
+        second = yh * vh + yh * vm + ym * vh
+        rest = float(_upper(ea, True)) * float(_upper(hb, True)) + float(_upper(ha, True)) * float(_upper(eb, True))
+        assert first <= floor * na * nb * (1 - 4e-6) and second >= ta * tb * (1 - 1e-6) and rest >= ea * hb + ha * eb
+        if dot >= floor * na * nb:
+            assert float(qa @ qb) - first + second + rest > 0.0, name          # stays open
