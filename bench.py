@@ -175,14 +175,15 @@ def run_whole_config(args, torch, kb, wl):
 def counted_share(kb, ctx, plan, row_bytes):
     """Share of the full-length product that the roofline counts, for the last tree call on this plan.  A large call without a
     screen tests every tile after so many 64-byte slices of the rows, chosen per group (kvfuse_plan_early_counts): those
-    slices have been multiplied for all pairs.  What tiles that went on to their full length and pairs that were finished one
+    slices have been multiplied for all pairs (by the panel kernel no fewer elements, in copies of six bits each, whose products the
+    peak of bfloat16 does not bound).  What tiles that went on to their full length and pairs that were finished one
     by one add is not counted, so the rate stated is a lower bound of the executed one."""
     slices, _, room = kb.early_counts(ctx, plan)
     return float(slices.mean()) / (row_bytes // 64) if room else 1.0
 
 
 ROOFLINE_NOTE = ("counts the slices of every row that the kernel multiplied before it tested a tile for stopping early; tiles that "
-                 "went on to full length are counted no further.  full_length_equivalent counts whole rows and can exceed the peak")
+                 "went on to full length are counted no further, nor what the panel kernel multiplies beyond them, in six bits an element.  full_length_equivalent counts whole rows and can exceed the peak")
 
 
 def cpu_baseline(wl, reduced=False):

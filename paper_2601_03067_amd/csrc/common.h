@@ -55,7 +55,8 @@ struct HeightDesc {
     int32_t small_tiles;              // most 32 x 32 tiles one node can have
     int32_t max_cap;                  // largest left or right set of a node
     bool use_big_tiles;
-    int32_t panel_run, panel_items;   // panel kernel (panel.hip): most 64-row stages of an item, 0 = not for this height; most items of a group
+    int32_t panel_run[2], panel_items[2];   // panel kernel (panel.hip), for either length of heads: most stages of an item, 0 = not for this height; most items of a group
+    double panel_left;                // ... pairs of this and later heights that it may take, against those of this one, by the sets' capacities
     bool panel_few;                   // ... so few tiles that the ring kernel is faster on blocks that have little to do with each other
     int64_t total_s;
 };
@@ -74,11 +75,25 @@ struct Q8Desc {
     float *err, *scale, *alpha, *dir;
 };
 
-// Panel kernel (panel.hip): right blocks of a panel, left blocks of a stage, most stages of an item; and the share of pairs (one in so
-// many) left open at the height before up to which a group takes it.  Head copies (heads.hip): most steps of 64 elements, and bytes of a copy.
-constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
-constexpr int kPanelCols = 512, kPanelRows = 64, kPanelRun = 32, kPanelOpen = 1024;
-constexpr int kHeadSteps = 6, kHeadBytes = 320;
+// Head copies (heads.hip) and the panel kernel (panel.hip), for heads of up to 384 and of up to 768 elements: most steps of 64 elements and
+// bytes of a copy; right blocks of a panel, left blocks of a stage.  A wavefront holds the copies of a quarter of a panel in registers, and
+// two stages fit half of a compute unit's LDS.
+template <bool LONG>
+struct HeadShape {
+    static constexpr int steps = LONG ? 12 : 6, bytes = LONG ? 640 : 320, cols = LONG ? 256 : 512, rows = LONG ? 32 : 64;
+};
+static inline __host__ __device__ int head_steps_most(int is_long) { return is_long ? HeadShape<true>::steps : HeadShape<false>::steps; }
+static inline __host__ __device__ int head_bytes(int is_long) { return is_long ? HeadShape<true>::bytes : HeadShape<false>::bytes; }
+static inline __host__ __device__ int panel_cols(int is_long) { return is_long ? HeadShape<true>::cols : HeadShape<false>::cols; }
+static inline __host__ __device__ int panel_rows(int is_long) { return is_long ? HeadShape<true>::rows : HeadShape<false>::rows; }
+// Most stages of an item; the share of pairs (one in so many) left open at the height before, and of related ones in tiles that the ring kernel
+// multiplied whole, up to which the panel kernel takes a group; the
+// mark of a pair (in its row) whose product starts at the first element (column -1: no pair).
+// Pairs to a block, of the heights that are left, from which copies pay: making them costs 0.3 ns a block, long ones twice that, and a tile of
+// 256 x 256 pairs some 30 ns less than in the ring kernel, both of the whole chip (one prompt of 16 chunks of 128 blocks at 0.85, 64 groups, 900
+// pairs a block: 1364 us without, 1433 with long copies; 256 requests of popular blocks, at the last height only, 750: 16.35 and 16.7 ms).
+constexpr double kHeadPairs = 512.0;       // (twice that for long ones)
+constexpr int kPanelRun = 32, kPanelOpen = 256, kPanelDense = 4096, kPairWhole = (int)0x80000000;
 constexpr int kWholeTile = 128;       // open pairs of a panel item beyond which the ring kernel is taken to have multiplied a tile whole
 
 // Tree calls on tiny groups (tiny.hip): most table entries, stored blocks and tree nodes of a group, bytes of a block, groups.
@@ -120,12 +135,17 @@ struct WorkDesc {
     float *pair_head;        // [pair_cap] ... and their product so far
     int32_t *n_pairs;        // counter of the current height
     int32_t pair_cap;
-    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that the ring kernel multiplied whole for them (1 for any number of a height that was the panel kernel's)
+    int32_t *open_cnt, *whole;       // [G] pairs that the current height's tests left open; tiles that the ring kernel multiplied whole for them (-1 for any number of a height that was the panel kernel's; before the first height sampled pairs that are related)
+    int32_t *dense_cnt;      // [G] related pairs in the tiles that the ring kernel multiplied whole
     // panel kernel (panel.hip); panel_on null = not at this height
     int32_t *panel_on, *panel_on_mem;       // [G]
-    char *heads, *heads_mem;                // [G][n][kHeadBytes] head copies (heads.hip); null = none
+    char *heads, *heads_mem;                // [G][n][head_bytes] head copies (heads.hip); null = none
+    int32_t long_heads;      // their shape (HeadShape)
     int32_t *set_slot;       // [G][n] beside set_ids: a block's slot among the head copies of its group
-    int32_t *head_steps;     // [G] steps of 64 elements that a head has, 0 = the group has no head copies
+    int32_t *head_steps;     // [G] steps of 64 elements that a head has, 0 = too long for copies
+    int32_t *head_made;      // [G] 1 + the height that the group's copies were made at, 0 = not yet
+    int32_t *new_groups, *n_new;     // groups whose copies are made at this height: [G], and [max_heights] how many
+    const int32_t *pos_leaf, *node_off, *node_parent, *node_height;      // position in a set_ids row -> slot of its leaf or -1 [n]; of every slot [n_slots]
     int4 *panel_items;       // [][2] (group, first row and first column of its set lists, rows << 16 | columns), (first column of the height's, first row of the node, head_steps, unused)
     int32_t *panel_total;    // [max_heights]
     // tree calls on tiny groups (tiny.hip); null where the tree is too large for them
@@ -204,8 +224,10 @@ void launch_similarity(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, c
 // early rejection (early.hip): the number of slices after which each group's tiles are tested; the pairs left open
 void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const TableDesc &tab, float thr_floor);
 // panel kernel and head copies: bfloat16, and a group's copies within the 32-bit offsets of buffer loads
-static inline bool panel_fits(const PoolDesc &pool, const WorkDesc &w) { return w.heads_mem && pool.dtype == KVFUSE_BF16 && (int64_t)w.n * kHeadBytes <= 0xFFFFFFFFll && launch_fits(((int64_t)w.G * w.n + 15) / 16, 256); }
-void launch_heads(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);
+static inline bool panel_fits(const PoolDesc &pool, const WorkDesc &w)
+{
+    return w.heads_mem && pool.dtype == KVFUSE_BF16 && (int64_t)w.n * head_bytes(1) <= 0xFFFFFFFFll && launch_fits(((int64_t)w.G * w.n + 7) / 8, 256);
+}
 void launch_heads_of_targets(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, int height, float thr_floor);
 void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor);
 void launch_finish_pairs(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, float thr_floor);

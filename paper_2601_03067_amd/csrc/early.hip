@@ -132,11 +132,11 @@ __device__ __forceinline__ uint32_t ordered_bits(float x)
 // took 30 us at two pairs a lane (11 at one), these counts take 14.
 //
 // head_steps (or null): likewise the steps of 64 elements of the head copies (heads.hip), `wide` slices each, whose test is wider by what the copies
-// miss, some 6.5 % of their share of a block; 0 where kHeadSteps of them would not do, or for a group that is switched off.
+// miss, some 6.5 % of their share of a block; 0 where `steps_most` of them would not do, or for a group that is switched off.
 template <int PER>
 __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restrict__ bounds, int nk, float thr_floor,
-                                                            int32_t *__restrict__ early_nk, int32_t *__restrict__ head_steps, int wide,
-                                                            const uint8_t *__restrict__ group_enable)
+                                                            int32_t *__restrict__ early_nk, int32_t *__restrict__ head_steps, int steps_most, int wide,
+                                                            const uint8_t *__restrict__ group_enable, int32_t *__restrict__ related)
 {
     constexpr int N = PER * kSamples;
     __shared__ float reach[kSteps];
@@ -164,12 +164,20 @@ __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restr
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             value[k] = __uint_as_float(at[k] ^ ((at[k] >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+        if (len == kSteps - 1) {             // (sampled pairs that are near copies: all but a 32nd of their products is in)
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                n += __popcll(__ballot(bound[i] >= ordered_bits(thr_floor)));
+            if (lane == 0)
+                related[g] = n;
+        }
         if (lane == 0)
             reach[len] = value[1] + 4.0f * fmaxf(0.5f * (value[2] - value[0]), 0.85f * (value[2] - value[1]));
     }
     if (threadIdx.x == 0) {
         best = nk;
-        best_steps = kHeadSteps + 1;
+        best_steps = steps_most + 1;
     }
     __syncthreads();
     // between two lengths the reach is taken as a straight line
@@ -182,13 +190,13 @@ __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restr
         if (reach_at(slices) < thr_floor - 1e-3f)
             atomicMin(&best, slices);
     const int steps = 1 + threadIdx.x;
-    if (steps <= kHeadSteps && 4 * steps * wide <= 3 * nk && reach_at(steps * wide) + 0.065f * (float)(steps * wide) / (float)nk < thr_floor - 1e-3f)
+    if (steps <= steps_most && 4 * steps * wide <= 3 * nk && reach_at(steps * wide) + 0.065f * (float)(steps * wide) / (float)nk < thr_floor - 1e-3f)
         atomicMin(&best_steps, steps);
     __syncthreads();
     if (threadIdx.x == 0) {
         early_nk[g] = best;
         if (head_steps)
-            head_steps[g] = best_steps <= kHeadSteps && (!group_enable || group_enable[g]) ? best_steps : 0;
+            head_steps[g] = best_steps <= steps_most && (!group_enable || group_enable[g]) ? best_steps : 0;
     }
 }
 
@@ -205,9 +213,9 @@ void launch_choose_early(hipStream_t s, const PoolDesc &pool, const WorkDesc &w,
     const int nk = pool.r * (pool.dtype == KVFUSE_BF16 ? 2 : 4) / 64;
     const int wide = pool.dtype == KVFUSE_BF16 ? 2 : 4;
     if (twice)
-        choose_early_kernel<2><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, wide, w.group_enable);
+        choose_early_kernel<2><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, head_steps_most(w.long_heads), wide, w.group_enable, w.whole);
     else
-        choose_early_kernel<1><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, wide, w.group_enable);
+        choose_early_kernel<1><<<pool.G, 1024, 0, s>>>(bounds, nk, thr_floor, w.early_nk_mem, w.head_steps, head_steps_most(w.long_heads), wide, w.group_enable, w.whole);
 }
 
 // The pairs that the tests left open, 16 lanes per pair: the rest of the product, and the pair's entry in its column's

@@ -275,11 +275,12 @@ struct Carver {
 };
 
 // Items of a group for the panel kernel at a height of big tiles, runs of left blocks of at most `run` stages.
-static int64_t panel_items(const HostHeight &h, int64_t run)
+static int64_t panel_items(const HostHeight &h, int64_t run, int is_long)
 {
+    const int cols = panel_cols(is_long), rows = panel_rows(is_long);
     int64_t c = 0;
     for (size_t k = 0; k < h.l_cap.size(); ++k)
-        c += (int64_t)((h.r_cap[k] + kPanelCols - 1) / kPanelCols) * (((h.l_cap[k] + kPanelRows - 1) / kPanelRows + run - 1) / run);
+        c += (int64_t)((h.r_cap[k] + cols - 1) / cols) * (((h.l_cap[k] + rows - 1) / rows + run - 1) / run);
     return c;
 }
 
@@ -333,12 +334,14 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
     w.pair_cap = 0;
     w.open_cnt = cv.take<int32_t>((size_t)G);
     w.whole = cv.take<int32_t>((size_t)G);
+    w.dense_cnt = cv.take<int32_t>((size_t)G);
     w.panel_on = nullptr;
     w.panel_on_mem = cv.take<int32_t>((size_t)G);
     w.panel_total = cv.take<int32_t>(kMaxHeights);
     w.heads = w.heads_mem = nullptr;
-    w.set_slot = nullptr;
-    w.head_steps = nullptr;
+    w.long_heads = 0;
+    w.set_slot = w.head_steps = w.head_made = w.new_groups = w.n_new = nullptr;
+    w.pos_leaf = w.node_off = w.node_parent = w.node_height = nullptr;
     w.panel_items = nullptr;
     w.group_enable = nullptr;
     w.leaf_src = cv.take<int32_t>((size_t)std::max(n, 1));
@@ -369,28 +372,43 @@ static void carve(Carver &cv, int G, int n, int n_slots, int max_r, int max_l, i
         // Panel kernel: items of up to 32 stages; shorter ones, down to 8, while there are fewer than eight a compute unit, which holds two
         // at a time, and down to 2 while there is not one for each place: an item takes some 9 us before its first stage and 1.7 to 2.2 us a
         // stage (512 right blocks x 4096 left ones, 8 groups, the whole step: 64 items of 8 stages 58 us, 256 of 2 33 us).
-        h.dev.panel_run = h.dev.panel_items = 0;
         h.dev.panel_few = false;
-        if (!h.big)
-            continue;
-        int run = kPanelRun;
-        while (run > 8 && (int64_t)G * panel_items(h, run) < 2048)
-            run /= 2;
-        while (run > 2 && (int64_t)G * panel_items(h, run) < 512)
-            run /= 2;
-        const int64_t items = panel_items(h, run);
-        if (!launch_fits(items * G + 512, 256))
-            continue;
-        h.dev.panel_run = run;
-        h.dev.panel_items = (int32_t)items;
-        h.dev.panel_few = panel_few(h, G);
-        panel_room = std::max(panel_room, (size_t)items * (size_t)G);
+        for (int is_long = 0; is_long < 2; ++is_long) {
+            h.dev.panel_run[is_long] = h.dev.panel_items[is_long] = 0;
+            if (!h.big)
+                continue;
+            int run = kPanelRun;
+            while (run > 8 && (int64_t)G * panel_items(h, run, is_long) < 2048)
+                run /= 2;
+            while (run > 2 && (int64_t)G * panel_items(h, run, is_long) < 512)
+                run /= 2;
+            const int64_t items = panel_items(h, run, is_long);
+            if (!launch_fits(items * G + 512, 256))
+                continue;
+            h.dev.panel_run[is_long] = run;
+            h.dev.panel_items[is_long] = (int32_t)items;
+            h.dev.panel_few = panel_few(h, G);
+            panel_room = std::max(panel_room, (size_t)items * (size_t)G);
+        }
     }
     if (panel_room > 0) {
-        w.heads_mem = cv.take<char>((size_t)G * n * kHeadBytes);
+        w.heads_mem = cv.take<char>((size_t)G * n * head_bytes(1));
         w.set_slot = cv.take<int32_t>((size_t)G * n);
         w.head_steps = cv.take<int32_t>((size_t)G);
+        w.head_made = cv.take<int32_t>((size_t)G);
+        w.new_groups = cv.take<int32_t>((size_t)G);
+        w.n_new = cv.take<int32_t>(kMaxHeights);
+        w.pos_leaf = cv.take<int32_t>((size_t)std::max(n, 1));
+        w.node_off = cv.take<int32_t>((size_t)n_slots);
+        w.node_parent = cv.take<int32_t>((size_t)n_slots);
+        w.node_height = cv.take<int32_t>((size_t)n_slots);
         w.panel_items = cv.take<int4>(2 * panel_room);
+    }
+    double left = 0.0;
+    for (auto h = hs.rbegin(); h != hs.rend(); ++h) {
+        const double own = (double)h->s_base.back();
+        left += h->big ? own : 0.0;
+        h->dev.panel_left = own > 0.0 ? left / own : 0.0;
     }
     for (HostHeight &h : hs) {
         const size_t nn = h.l_off.size();
@@ -573,6 +591,26 @@ int kvfuse_plan_create(kvfuse_ctx *ctx, const kvfuse_pool *pool, const kvfuse_ta
             for (int i = 0; i < nd.cap; ++i)
                 leaf_src[(size_t)nd.off + i] = nd.src + i;
     if (e == hipSuccess) e = upload(c->stream, p.work.leaf_src, leaf_src);
+    std::vector<int32_t> pos_leaf, node_off, node_parent, node_height;
+    if (p.work.heads_mem) {
+        pos_leaf.assign((size_t)std::max(table->n, 1), -1);
+        node_parent.assign(n_slots, -1);
+        node_off.assign(n_slots, 0);
+        node_height.assign(n_slots, 0);
+        for (size_t k = 0; k < p.nodes.size(); ++k) {
+            const Node &nd = p.nodes[k];
+            node_off[k] = nd.off;
+            node_height[k] = nd.height;
+            if (nd.left >= 0)
+                node_parent[(size_t)nd.left] = node_parent[(size_t)nd.right] = (int32_t)k;
+            else
+                std::fill_n(pos_leaf.begin() + nd.off, nd.cap, (int32_t)k);
+        }
+        if (e == hipSuccess) e = upload(c->stream, p.work.pos_leaf, pos_leaf);
+        if (e == hipSuccess) e = upload(c->stream, p.work.node_off, node_off);
+        if (e == hipSuccess) e = upload(c->stream, p.work.node_parent, node_parent);
+        if (e == hipSuccess) e = upload(c->stream, p.work.node_height, node_height);
+    }
     std::vector<int4> tiny_nodes;
     std::vector<int32_t> tiny_ptr;
     if (p.work.tiny_nodes) {
@@ -774,10 +812,19 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         w.pairs = w.active;
         w.pair_head = reinterpret_cast<float *>(w.active + w.pair_cap);
     }
-    // A pair of blocks of evenly spread energy is not ruled out before a share 1 - floor of their elements: no group's head will fit
-    // the panel kernel's registers where even that does not (8 KiB blocks at 0.9: 418 of 4096 elements), and its launch
-    // would find nothing to do.
-    const bool panel = early && panel_fits(p.pool, w) && (1.0f - floor_f) * (float)p.pool.r < 64.0f * (float)kHeadSteps;
+    // Unrelated blocks of evenly spread energy are ruled out where a head of a share x of them leaves 0.935 x (what the copies of the
+    // head keep of it) above 1 - floor by five standard deviations of its product: which shape of head copies will do, if any (blocks of
+    // 4 KiB: six steps at 0.9 and above, twelve at 0.8; of 8 KiB: six at 0.95, twelve at 0.9).
+    auto head_does = [&](int steps) {
+        const double x = 64.0 * steps / p.pool.r;
+        return 4 * steps * 64 <= 3 * p.pool.r && 0.935 * x - 5.0 * std::sqrt(x / p.pool.r) > 1.0 - (double)floor_f;
+    };
+    w.long_heads = !head_does(head_steps_most(0));
+    double pairs = 0.0;
+    for (const HostHeight &h : p.heights)
+        pairs += h.dev.panel_run[w.long_heads] > 0 ? (double)h.dev.total_s : 0.0;
+    const bool panel = early && panel_fits(p.pool, w) && (!w.long_heads || head_does(head_steps_most(1))) &&
+                       pairs >= (1 + w.long_heads) * kHeadPairs * (double)w.n;
     if (panel)
         w.heads = w.heads_mem;
     else
@@ -792,13 +839,11 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
         if (early)
             launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
         launch_tree_norms(c->stream, p.pool, w, p.tab);
-        if (panel)
-            launch_heads(c->stream, p.pool, w, floor_f);
         KVF_TRY(mark());
         for (int hgt = 0; hgt < nh; ++hgt) {
             const HeightDesc &d = p.heights[hgt].dev;
             w.n_pairs = w.n_pairs_all + hgt;
-            w.panel_on = panel && d.panel_run > 0 ? w.panel_on_mem : nullptr;
+            w.panel_on = panel && d.panel_run[w.long_heads] > 0 ? w.panel_on_mem : nullptr;
             launch_similarity(c->stream, p.pool, w, d, floor_f, nullptr, true, hgt > 0 ? &p.heights[hgt - 1].dev : nullptr, hgt);
             if (early)
                 launch_finish_pairs(c->stream, p.pool, w, floor_f);
@@ -806,7 +851,8 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
             launch_assign(c->stream, p.pool, p.tab, w, d, hgt, thr, band, p.assign_rule, hgt + 1 < nh);
             KVF_TRY(mark());
             launch_merge(c->stream, p.pool, w, d, hgt);
-            if (panel && hgt + 1 < nh)
+            // (the next height sees to the rewritten blocks' copies, if it may be the panel kernel's)
+            if (panel && hgt + 1 < nh && p.heights[hgt + 1].dev.panel_run[w.long_heads] == 0)
                 launch_heads_of_targets(c->stream, p.pool, w, hgt, floor_f);
             KVF_TRY(mark());
         }

@@ -50,19 +50,24 @@ __device__ __forceinline__ u32x2 panel_right(float x, float y, float e, float h,
 // then only leave more pairs open, which finish_pairs_kernel tests whole.
 __device__ __forceinline__ float panel_floor(float thr_floor) { return -thr_floor * (1.0f - 8e-6f); }
 
-// Rows of a node's items: whole stages, at most `run`, the same number for all but the last.
-__device__ __forceinline__ int panel_rows_per_item(int ml, int run)
+// Rows of a node's items: whole stages of `rows`, at most `run`, the same number for all but the last.
+__device__ __forceinline__ int panel_rows_per_item(int ml, int rows, int run)
 {
-    const int stages = (ml + kPanelRows - 1) / kPanelRows;
+    const int stages = (ml + rows - 1) / rows;
     const int n = max((stages + run - 1) / run, 1);
-    return max((stages + n - 1) / n, 1) * kPanelRows;
+    return max((stages + n - 1) / n, 1) * rows;
 }
 
 // A workgroup of 256 for group g: whether the panel kernel takes it at this height, and if so its work items, behind those of the groups
-// that came first.  An item is (group, node, panel of 512 right blocks, run of left blocks); consecutive items of a node share
+// that came first.  An item is (group, node, panel of right blocks, run of left blocks); consecutive items of a node share
 // the run, so that the workgroups an XCD holds at a time read the same left rows.  The panel kernel takes a group
 //   - whose head fits its registers (head_steps),
-//   - whose tests left few pairs open at the height before (of `prev`, which has no nodes before the first height),
+//   - whose blocks repeat little: few pairs left open by the tests of the height before (`prev`, which has no nodes before the first height)
+//     and hardly any in tiles that the ring kernel multiplied whole there, or at the first height no related pair in the sample
+//     (early.hip).  Of a whole tile, 50 us on one compute unit of 256, every related pair goes to finish_pairs_kernel instead, 1.6 ns
+//     each for blocks of 4 KiB, and a tile without any takes 30 ns (of the chip) less here than there (128 requests of 256 popular blocks
+//     at 0.8, 16 groups, first height: 2600 us in this kernel, 740 in that one);
+//   - that has its head copies, or pairs enough ahead for making them (kHeadPairs);
 //   - and, where the ring kernel is faster on blocks that have little to do with each other (panel_few, host.hip), only if tiles were
 //     multiplied whole at the height before, or there was none.  A whole tile takes the ring kernel some 50 us (4 KiB blocks), and a
 //     height of few tiles ends with it: 13 requests of 492 blocks, a quarter of them common, 8 groups, a height 73 us against 60.
@@ -71,34 +76,54 @@ __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const He
     __shared__ int64_t lds4[4];
     __shared__ int node0[256], node_cp[256], node_rows[256];
     __shared__ int first;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, cols = panel_cols(w.long_heads), stage = panel_rows(w.long_heads), run_most = h.panel_run[w.long_heads];
     // pairs that the tests of the height before left open, against the pairs there were
     double pairs = 0.0;
     __shared__ double red[4];
     for (int k = tid; k < prev.n_nodes; k += 256)
         pairs += (double)w.set_cnt[(int64_t)g * w.n_slots + prev.l_slot[k]] * (double)w.set_cnt[(int64_t)g * w.n_slots + prev.r_slot[k]];
     pairs = block_sum_256(pairs, red);
-    const bool on = w.head_steps[g] > 0 && (!w.group_enable || w.group_enable[g]) &&
-                    (double)w.open_cnt[g] * kPanelOpen <= pairs && (!h.panel_few || prev.n_nodes == 0 || w.whole[g]);
+    bool on = w.head_steps[g] > 0 && (!w.group_enable || w.group_enable[g]) &&
+                    (prev.n_nodes == 0 ? w.whole[g] == 0
+                                       : (double)w.open_cnt[g] * kPanelOpen <= pairs && (double)w.dense_cnt[g] * kPanelDense <= pairs) &&
+                    (!h.panel_few || prev.n_nodes == 0 || w.whole[g]);
     auto items_of = [&](int k, int &n_cp, int &rows) {
         const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
-        n_cp = (mr + kPanelCols - 1) / kPanelCols;
-        rows = panel_rows_per_item(ml, h.panel_run);
+        n_cp = (mr + cols - 1) / cols;
+        rows = panel_rows_per_item(ml, stage, run_most);
         return n_cp * ((ml + rows - 1) / rows);
     };
     int64_t total = 0;
     if (on) {
         int64_t mine = 0;
+        double now = 0.0, blocks = 0.0;
         for (int k = tid; k < h.n_nodes; k += 256) {
             int n_cp, rows;
             mine += items_of(k, n_cp, rows);
+            const double ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
+            now += ml * mr;
+            blocks += ml + mr;
         }
         (void)block_exscan<256>(mine, lds4, total);
+        if (w.head_made[g] == 0) {
+            __syncthreads();
+            now = block_sum_256(now, red);
+            __syncthreads();
+            blocks = block_sum_256(blocks, red);
+            if (now * h.panel_left < (1 + w.long_heads) * kHeadPairs * blocks)
+                on = false;
+        }
     }
+    if (!on)
+        total = 0;
     __syncthreads();
     if (tid == 0) {
         first = total > 0 ? atomicAdd(&w.panel_total[height], (int)total) : 0;
         w.panel_on[g] = on;
+        if (total > 0 && w.head_made[g] == 0) {
+            w.head_made[g] = height + 1;
+            w.new_groups[atomicAdd(&w.n_new[height], 1)] = g;
+        }
     }
     __syncthreads();
     int run = first;
@@ -121,10 +146,10 @@ __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const He
                     hi = mid;
             }
             const int q = i - node0[lo];
-            const int k = k0 + lo, col = (q % node_cp[lo]) * kPanelCols, row = q / node_cp[lo] * node_rows[lo];
+            const int k = k0 + lo, col = (q % node_cp[lo]) * cols, row = q / node_cp[lo] * node_rows[lo];
             const int ml = w.set_cnt[(int64_t)g * w.n_slots + h.l_slot[k]], mr = w.set_cnt[(int64_t)g * w.n_slots + h.r_slot[k]];
             int4 *out = w.panel_items + 2 * (int64_t)(run + i);
-            out[0] = make_int4(g, h.l_off[k] + row, h.r_off[k] + col, min(ml - row, node_rows[lo]) << 16 | min(mr - col, kPanelCols));
+            out[0] = make_int4(g, h.l_off[k] + row, h.r_off[k] + col, min(ml - row, node_rows[lo]) << 16 | min(mr - col, cols));
             out[1] = make_int4(h.r_base[k] + col, row, w.head_steps[g], 0);
         }
         run += (int)sum;

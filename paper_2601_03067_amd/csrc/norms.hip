@@ -245,9 +245,14 @@ __global__ __launch_bounds__(256) void tree_clear_kernel(TableDesc tab, WorkDesc
         w.n_refine[i] = 0;
         w.n_pairs_all[i] = 0;
         w.panel_total[i] = 0;
+        if (w.heads)
+            w.n_new[i] = 0;
     }
-    if (i < w.G)
-        w.open_cnt[i] = w.whole[i] = 0;
+    if (i < w.G) {
+        w.open_cnt[i] = w.whole[i] = w.dense_cnt[i] = 0;
+        if (w.heads)
+            w.head_made[i] = 0;
+    }
 }
 
 // Thread i: reference count of table entry i and the leaf-set position i (leaf_sets_kernel).  Caller errors are counted

@@ -69,24 +69,24 @@ __device__ __forceinline__ void landed_regs(u32x6 &a) { asm volatile("" : "+v"(a
 
 __device__ __forceinline__ u32x4 lds_read(const char *at) { return *reinterpret_cast<const u32x4 *>(at); }
 
-// Five loads of 16 bytes a lane into LDS: 64 bytes on in memory, kPanelRows * 64 on in LDS (an instruction's offset counts on either side).  In
+// Five loads of 16 bytes a lane into LDS: 64 bytes on in memory, QUAD on in LDS (an instruction's offset counts on either side).  In
 // assembly, because the compiler makes every LDS read wait for all such loads of its own, whichever buffer they are for; who issues
 // them waits for them by hand.  (No register is loaded.  The pause is for scalar registers that a vector instruction has just written, and for m0.)
-__device__ __forceinline__ void stage_to_lds(uint64_t base, uint32_t off, uint32_t to)
+template <int QUAD>
+__device__ __forceinline__ void quads_to_lds(uint64_t base, uint32_t off, uint32_t to)
 {
     typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
     const desc_t desc = {(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
-    static_assert(kPanelRows * 64 - 64 == 4032, "the steps of m0 below");
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\t"
                  "buffer_load_dwordx4 %0, %1, 0 offen lds\n\t"
-                 "s_add_i32 m0, %2, 4032\n\ts_nop 0\n\t"
+                 "s_add_i32 m0, %2, %3\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %0, %1, 0 offen offset:64 lds\n\t"
-                 "s_add_i32 m0, %2, 8064\n\ts_nop 0\n\t"
+                 "s_add_i32 m0, %2, 2 * %3\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %0, %1, 0 offen offset:128 lds\n\t"
-                 "s_add_i32 m0, %2, 12096\n\ts_nop 0\n\t"
+                 "s_add_i32 m0, %2, 3 * %3\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %0, %1, 0 offen offset:192 lds\n\t"
-                 "s_add_i32 m0, %2, 16128\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %0, %1, 0 offen offset:256 lds" ::"v"(off), "s"(desc), "s"(to) : "memory", "m0", "scc");
+                 "s_add_i32 m0, %2, 4 * %3\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, 0 offen offset:256 lds" ::"v"(off), "s"(desc), "s"(to), "n"(QUAD - 64) : "memory", "m0", "scc");
 }
 
 struct PanelArgs {
@@ -96,17 +96,25 @@ struct PanelArgs {
     float thr_floor;
 };
 
+template <bool LONG>
 __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args)
 {
+    using S = HeadShape<LONG>;
     const WorkDesc &w = args.w;
-    constexpr int NC = 4, QUAD = kPanelRows * 64, STAGE = 5 * QUAD, MAXC = 2048;
-    constexpr int DENSE = 32;           // open pairs of a wavefront's 32 x 64 from which they are multiplied whole
-    // Two stages of 64 left rows each, four pieces of 16 bytes of a row side by side, five times (18 of codes, 2 of the test).
+    constexpr int STEPS = S::steps, HEAD = S::bytes, ROWS = S::rows, COLS = S::cols, NC = COLS / 128, QUAD = ROWS * 64, STAGE = HEAD / 64 * QUAD;
+    constexpr int MAXC = 2048, TEST = 3 * STEPS / 2;
+    // Open pairs of a wavefront's 32 x 64 from which they are multiplied whole: as many as the list has room for (as one or two wavefronts
+    // walk along a piece's rows alone while the rest of the chip is done: 128 pieces in a height, 120 us with them in the list, 336 without).
+    constexpr int DENSE = LONG ? 256 : 64;
+    // Two stages of left rows, four pieces of 16 bytes of a row side by side, as many times as a copy has four.
     __shared__ __attribute__((aligned(1024))) char stages[2 * STAGE];
     __shared__ int lds_n, lds_full[2], lds_first;
     __shared__ uint32_t lds_pair[MAXC];         // row of the item << 16 | column of the panel
     __shared__ __attribute__((aligned(1024))) u32x2 right_fc[4][NC][64];       // right blocks' operands of the test: [wavefront][32 columns][lane]
-    __shared__ uint32_t lds_dense[kPanelRun / 2];        // a bit per (stage, 32 rows of it, 64 columns)
+    constexpr int DENSE_WORDS = kPanelRun * ROWS / 32 * (COLS / 64) / 32;
+    __shared__ uint32_t lds_dense[DENSE_WORDS];          // a bit per (32 rows, 64 columns)
+
+    static_assert(4 * (ROWS / 32) * (NC / 2) * DENSE <= MAXC / 2, "a stage's pairs fit half the list");
 
     const int total = w.panel_total[args.height];
     const int seat = blockIdx.x >> 3;
@@ -115,58 +123,62 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
         return;
     const int4 item = w.panel_items[2 * (int64_t)v], item2 = w.panel_items[2 * (int64_t)v + 1];
     const int g = item.x, n_rows = item.w >> 16, n_cols = item.w & 0xFFFF, steps = item2.z;
-    const int n_stages = (n_rows + kPanelRows - 1) / kPanelRows;
+    const int n_stages = (n_rows + ROWS - 1) / ROWS;
     const int32_t *__restrict__ l_places = w.set_slot + (int64_t)g * w.n + item.y;
     const int32_t *__restrict__ r_places = w.set_slot + (int64_t)g * w.n + item.z;
-    const char *__restrict__ heads = w.heads + (int64_t)g * w.n * kHeadBytes;
+    const char *__restrict__ heads = w.heads + (int64_t)g * w.n * HEAD;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l31 = lane & 31, half = lane >> 5;
 
-    // A panel of more than 256 right blocks: a wavefront per 128 of them.  A narrower one: per 128 blocks two wavefronts, which take
-    // turns at the left rows.
-    const bool wide = n_cols > kPanelCols / 2;
-    const int my_col = (wide ? wave : wave & 1) * 128;
-    const int sub0 = wide ? 0 : wave >> 1, sub_step = wide ? 1 : 2;
+    // A panel of more than half its right blocks: a wavefront per quarter of them.  A narrower one: per quarter two wavefronts, which take
+    // turns at the left rows, at 32 at a time.
+    const bool wide = n_cols > COLS / 2;
+    const int my_col = (wide ? wave : wave & 1) * (COLS / 4);
+    const int sub0 = wide || ROWS == 32 ? 0 : wave >> 1, sub_step = wide ? 1 : 2;
 
     // ---- loaders: this lane's row of a stage, and its (swizzled) piece of every four
+    // (a wavefront takes 16 rows, or half of their pieces)
+    constexpr int PARTS = 64 / ROWS;
+    const int ld_wave = wave % (ROWS / 16), ld_part = wave / (ROWS / 16);
+    static_assert(PARTS * 320 == HEAD, "five loads of 64 bytes a row for each part");
     const uint64_t heads_at = (uint64_t)heads;
-    const uint32_t stage_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)stages) + (uint32_t)wave * 1024u;
-    const int ld_row = wave * 16 + (lane >> 2);
-    const uint32_t ld_off = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
-    auto row_of = [&](int t) __attribute__((always_inline)) { return (uint32_t)l_places[min(t * kPanelRows + ld_row, n_rows - 1)] * (uint32_t)kHeadBytes; };
-    auto load_stage = [&](uint32_t row, uint32_t at) __attribute__((always_inline)) { stage_to_lds(heads_at, row + ld_off, stage_at + at); };
+    const uint32_t stage_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)stages) + (uint32_t)ld_wave * 1024u + (uint32_t)ld_part * (5u * QUAD);
+    const int ld_row = ld_wave * 16 + (lane >> 2);
+    const uint32_t ld_off = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u + (uint32_t)ld_part * 320u;
+    auto row_of = [&](int t) __attribute__((always_inline)) { return (uint32_t)l_places[min(t * ROWS + ld_row, n_rows - 1)] * (uint32_t)HEAD; };
+    auto load_stage = [&](uint32_t row, uint32_t at) __attribute__((always_inline)) { quads_to_lds<QUAD>(heads_at, row + ld_off, stage_at + at); };
 
     if (tid == 0)
         lds_n = lds_full[0] = lds_full[1] = 0;
-    if (tid < kPanelRun / 2)
+    if (tid < DENSE_WORDS)
         lds_dense[tid] = 0;
     uint32_t row = row_of(0);
     load_stage(row, 0);
     row = row_of(1);
     const int frag = l31 * 64 + ((half ^ ((l31 >> 2) & 3)) * 16);         // piece 2 m + half: every second m, 32 bytes on; another quad every two
-    const int test_at = 4 * QUAD + ((l31 * 64 + ((l31 >> 2) & 3) * 16) ^ 32) + half * 8;       // piece 18: eight bytes for either half
+    const int test_at = (TEST >> 1) * QUAD + ((l31 * 64 + ((l31 >> 2) & 3) * 16) ^ (TEST & 1 ? 32 : 0)) + half * 8;       // the piece behind the codes: eight bytes for either half
     // Once through this loop, unless the list of open pairs fills up on the way: then it is emptied, and the right blocks, whose
     // registers that takes, are loaded again.
     for (int t = 0;;) {
-        u32x6 fb[kHeadSteps][NC];
+        u32x6 fb[STEPS][NC];
         each<NC>([&](auto c) __attribute__((always_inline)) {
             const int col = my_col + 32 * c + l31;
-            const char *src = heads + ((int64_t)r_places[min(col, n_cols - 1)] * kHeadBytes + half * 16);
-            each<kHeadSteps / 2>([&](auto p) __attribute__((always_inline)) {
+            const char *src = heads + ((int64_t)r_places[min(col, n_cols - 1)] * HEAD + half * 16);
+            each<STEPS / 2>([&](auto p) __attribute__((always_inline)) {
                 u32x4 x[3];
                 each<3>([&](auto j) __attribute__((always_inline)) { x[j] = *reinterpret_cast<const u32x4 *>(src + (3 * p + j) * 32); });
                 fb[2 * p][c] = of_pieces<false>(x[0], x[1], x[2]);
                 fb[2 * p + 1][c] = of_pieces<true>(x[0], x[1], x[2]);
             });
-            u32x2 test = *reinterpret_cast<const u32x2 *>(src + 304 - 8 * half);
+            u32x2 test = *reinterpret_cast<const u32x2 *>(src + (2 * TEST + 1) * 16 - 8 * half);
             // past the last column: a floor of 2^30 times the left norm, above every product
             if (col >= n_cols)
                 test = panel_right(0x1p30f, 0.0f, 0.0f, 0.0f, half);
             right_fc[wave][c][lane] = test;
         });
         // whole before the loop: nothing in it may wait for these loads behind the ones into LDS
-        each<kHeadSteps>([&](auto s) __attribute__((always_inline)) { each<NC>([&](auto c) __attribute__((always_inline)) { landed_regs(fb[s][c]); }); });
+        each<STEPS>([&](auto s) __attribute__((always_inline)) { each<NC>([&](auto c) __attribute__((always_inline)) { landed_regs(fb[s][c]); }); });
 
         for (; t < n_stages; ++t) {
             // this wavefront's loads of stage t have landed; behind the barrier all have, and nobody reads stage t - 1 any more
@@ -178,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
                 load_stage(row, (uint32_t)((t + 1) & 1) * STAGE);
                 row = row_of(t + 2);
             }
-            if (my_col >= n_cols)
+            if (my_col >= n_cols || (ROWS == 32 && !wide && (t & 1) != wave >> 1))
                 continue;
             const char *stage = stages + (t & 1) * STAGE;
             // A step's fragment of 32 left rows (at `rows`): pieces 3 p, 3 p + 1 and 3 p + 2 of a pair of steps hold its first 16 bytes, eight
@@ -193,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
             u32x6 fa[3];
             each<3>([&](auto s) __attribute__((always_inline)) { fa[s] = fragment(stage + sub0 * 2048, s); });
 #pragma unroll 1
-            for (int sub = sub0; sub < 2; sub += sub_step) {
+            for (int sub = sub0; sub < ROWS / 32; sub += sub_step) {
                 const char *rows = stage + sub * 2048;
                 int n_steps = steps;
                 asm volatile("" : "+s"(n_steps));      // (or the comparisons below are kept for the whole loop, in two registers each)
@@ -207,24 +219,25 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
                     each<NC>([&](auto c) __attribute__((always_inline)) { acc[c] = test_mma(fl, right_fc[wave][c][lane], zero); });
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                each<kHeadSteps>([&](auto s) __attribute__((always_inline)) {
+                each<STEPS>([&](auto s) __attribute__((always_inline)) {
                     if (s < n_steps)
                         each<NC>([&](auto c) __attribute__((always_inline)) { acc[c] = head_mma(fa[s % 3], fb[s][c], acc[c]); });
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (s < 3)
+                    if constexpr (s + 3 < STEPS)
                         fa[s % 3] = fragment(rows, std::integral_constant<int, s + 3>{});
-                    else             // (behind the last rows: whatever is there, not used)
-                        fa[s % 3] = fragment(rows + 2048, std::integral_constant<int, s - 3>{});
+                    else if constexpr (ROWS > 32)             // (behind the last rows: whatever is there, not used)
+                        fa[s % 3] = fragment(rows + 2048, std::integral_constant<int, s + 3 - STEPS>{});
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                float mx[NC];
+                float mx[NC], most = -1.0f;
                 each<NC>([&](auto c) __attribute__((always_inline)) {
                     mx[c] = -1.0f;
 #pragma unroll
                     for (int e = 0; e < 16; e += 2)
                         mx[c] = fmaxf(fmaxf(acc[c][e], acc[c][e + 1]), mx[c]);
                 });
-                if (__builtin_expect(!__any(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])) >= 0.0f), 1))
+                each<NC>([&](auto c) __attribute__((always_inline)) { most = fmaxf(most, mx[c]); });
+                if (__builtin_expect(!__any(most >= 0.0f), 1))
                     continue;
                 const int r0 = sub * 32 + 4 * half;               // element e: row r0 + 8 (e / 4) + e % 4 of the stage
                 each<NC / 2>([&](auto cc) __attribute__((always_inline)) {
@@ -245,7 +258,7 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
                     if (__builtin_expect(open <= DENSE, 1)) {
                         int k = 0;
                         if (lane == 0) {
-                            k = atomicAdd(&lds_n, open);       // (16 x DENSE a stage at most: never beyond MAXC)
+                            k = atomicAdd(&lds_n, open);       // (MAXC / 2 a stage at most: never beyond MAXC)
                             if (k + open > MAXC / 2)
                                 lds_full[t & 1] = 1;
                         }
@@ -254,13 +267,14 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
                             if (mask) {
                                 const int bit = __builtin_ctz(mask), e = 15 - (bit & 15);
                                 const int slot = k + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0));
-                                lds_pair[slot] = (uint32_t)(t * kPanelRows + r0 + 8 * (e >> 2) + (e & 3)) << 16 |
+                                lds_pair[slot] = (uint32_t)(t * ROWS + r0 + 8 * (e >> 2) + (e & 3)) << 16 |
                                                  (uint32_t)(my_col + 64 * cc + (bit < 16 ? 32 : 0) + l31);
                             }
                             k += __popcll(lanes);
                         }
                     } else if (lane == 0) {
-                        atomicOr(&lds_dense[t >> 1], 1u << ((t & 1) * 16 + sub * 8 + (my_col >> 6) + cc));
+                        const int bit = (t * (ROWS / 32) + sub) * (COLS / 64) + (my_col >> 6) + cc;
+                        atomicOr(&lds_dense[bit >> 5], 1u << (bit & 31));
                     }
                 });
             }
@@ -283,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
             lds_first = atomicAdd(w.n_pairs, n);
             atomicAdd(&w.open_cnt[g], n);
             if (n > kWholeTile)
-                w.whole[g] = 1;                  // (some: how many, only the ring kernel counts)
+                w.whole[g] = -1;                 // (some: how many, only the ring kernel counts)
         }
         __syncthreads();
         const int first = n > 0 ? lds_first : 0;
@@ -316,13 +330,13 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
         }
 
         // ---- pieces of 32 x 64 with many open pairs: whole products, straight from memory, and the candidates at once
-        for (int word = 0; word < (n_stages + 1) / 2; ++word) {
+        for (int word = 0; word < DENSE_WORDS; ++word) {
             uint32_t bits = __builtin_amdgcn_readfirstlane(lds_dense[word]);
             for (int i = 0; bits; bits &= bits - 1, ++i) {
                 if ((i & 3) != wave)
                     continue;
-                const int bit = __builtin_ctz(bits);
-                const int r0 = (2 * word + (bit >> 4)) * kPanelRows + ((bit >> 3) & 1) * 32, c0 = (bit & 7) * 64;
+                const int piece = word * 32 + __builtin_ctz(bits);
+                const int r0 = piece / (COLS / 64) * 32, c0 = piece % (COLS / 64) * 64;
                 floatx16 acc0, acc1;
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
@@ -359,7 +373,7 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
                 }
                 if (lane == 0) {
                     atomicAdd(&w.open_cnt[g], DENSE + 1);
-                    w.whole[g] = 1;
+                    w.whole[g] = -1;
                 }
             }
         }
@@ -370,8 +384,12 @@ __global__ __launch_bounds__(256, 2) void similarity_panel_kernel(PanelArgs args
 // The panel kernel's share of a height's similarity step; the ring kernel takes the groups that are not panel_on.
 void launch_similarity_panel(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, const HeightDesc &h, int height, float thr_floor)
 {
-    const int64_t items = ((int64_t)w.G * h.panel_items + 511) / 512 * 512;
-    similarity_panel_kernel<<<(unsigned)items, 256, 0, s>>>(PanelArgs{pool, w, height, thr_floor});
+    const int64_t items = ((int64_t)w.G * h.panel_items[w.long_heads] + 511) / 512 * 512;
+    const PanelArgs args{pool, w, height, thr_floor};
+    if (w.long_heads)
+        similarity_panel_kernel<true><<<(unsigned)items, 256, 0, s>>>(args);
+    else
+        similarity_panel_kernel<false><<<(unsigned)items, 256, 0, s>>>(args);
 }
 
 }  // namespace kvfuse

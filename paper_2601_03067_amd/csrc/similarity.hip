@@ -42,7 +42,7 @@
 // the iteration the same ring gave it one to two.
 #include <type_traits>
 
-#include "items.h"
+#include "heads.h"
 
 namespace kvfuse {
 
@@ -72,7 +72,7 @@ struct EarlyArgs {
     float *pair_head;
     int32_t *n_pairs;
     int32_t pair_cap;
-    int32_t *open_cnt, *whole;
+    int32_t *open_cnt, *whole, *dense_cnt;
 };
 
 template <typename T> struct MmaV;
@@ -782,15 +782,16 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                 const int n_now = lds_ncand;
                 if (whole) {                         // the list may have run over: the surplus went out directly
                     __syncthreads();
-                    n_kept = min(n_now, MAXC);
                     if (tid == 0) {
-                        lds_ncand = n_kept;
-                        if (guessed) {           // what its test would have left open, about
-                            atomicAdd(&early.open_cnt[g], min(n_now, LIMIT + 1));
-                            if (n_now > LIMIT)
-                                atomicAdd(&early.whole[g], 1);
+                        const int related = n_now - n_kept;          // what its test would have left open, about
+                        atomicAdd(&early.open_cnt[g], related);
+                        if (!guessed || related > LIMIT) {
+                            atomicAdd(&early.whole[g], 1);
+                            atomicAdd(&early.dense_cnt[g], related);
                         }
+                        lds_ncand = min(n_now, MAXC);
                     }
+                    n_kept = min(n_now, MAXC);
                     guessed = false;
                     whole = false;
                     n_slices = nk;
@@ -801,11 +802,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, BIG ? 1 : 2) void similarity_ring_
                     // loads then run ahead into the next row tile as they always do.
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                     __syncthreads();
-                    if (tid == 0) {
+                    if (tid == 0)
                         lds_ncand = n_kept;
-                        atomicAdd(&early.open_cnt[g], LIMIT + 1);
-                        atomicAdd(&early.whole[g], 1);
-                    }
                     whole = true;
                     n_slices = nk_full;
                     --rt;
@@ -958,7 +956,7 @@ __device__ __forceinline__ int first_items(const WorkDesc &w, const HeightDesc &
 {
     if (!w.early_nk || prev.n_nodes == 0)
         return 0;
-    const int whole = w.whole[g];
+    const int whole = abs(w.whole[g]);           // (-1: some, of a height that was the panel kernel's)
     return (whole > 0 ? kFirstApart : 0) | (whole >= prev.n_nodes ? kFirstWhole : 0);
 }
 
@@ -982,7 +980,7 @@ __global__ __launch_bounds__(256) void items_count_kernel(WorkDesc w, HeightDesc
     const bool panel = w.panel_on && panel_items_of_group(w, h, prev, height, g);
     __syncthreads();
     if (w.early_nk && tid == 0)
-        w.open_cnt[g] = w.whole[g] = 0;
+        w.open_cnt[g] = w.whole[g] = w.dense_cnt[g] = 0;
     if (panel || (w.group_enable && !w.group_enable[g])) {      // this group's share of the height is the panel kernel's; or a
         if (tid == 0)                                           // switched-off group, which keeps empty candidate lists: nothing fuses
             w.dyn_count[g] = make_int4(0, 0, 1, 0);
@@ -1033,9 +1031,17 @@ __device__ __forceinline__ int4 item_of_node(int local, int n_cp, int rt, int n_
     return make_int4(node, cp * bn, rc * rt * bm | rt | (local == 0 && whole_first ? kWholeFirst : 0), g);
 }
 
-// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is.
-__global__ __launch_bounds__(256) void items_fill_kernel(WorkDesc w, HeightDesc h, int bm, int bn)
+// One thread per item slot: which node it falls into, and which panel and row chunk of that node it is.  HEADS (1: short, 2: long): the
+// workgroups behind the slots' make the head copies that the panel kernel needs at this height (heads.h), which saves a launch.
+template <int HEADS>
+__global__ __launch_bounds__(256) void items_fill_kernel(PoolDesc pool, WorkDesc w, HeightDesc h, int bm, int bn, int height, float thr_floor, int n_fill)
 {
+    if constexpr (HEADS > 0) {
+        if ((int)blockIdx.x >= n_fill) {
+            heads_of_height<HEADS == 2>(pool, w, height, thr_floor, (int)blockIdx.x - n_fill, (int)gridDim.x - n_fill);
+            return;
+        }
+    }
     __shared__ int64_t lds4[4], before[256];
     const int tid = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + tid, n_slots = (int64_t)w.G * h.item_cap;
@@ -1117,7 +1123,7 @@ __global__ __launch_bounds__(1024) void items_of_few_kernel(WorkDesc w, HeightDe
         firsts[tid] = (uint8_t)first_items(w, prev, tid);
     __syncthreads();
     if (w.early_nk && tid < w.G)
-        w.open_cnt[tid] = w.whole[tid] = 0;
+        w.open_cnt[tid] = w.whole[tid] = w.dense_cnt[tid] = 0;
     int ml = 0, mr = 0;
     if (tid < n) {
         const int g = tid / h.n_nodes, k = tid - g * h.n_nodes;
@@ -1176,7 +1182,13 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
             items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, bm, bm);
         } else {
             items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
-            items_fill_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(w, h, bm, bm);
+            const int n_fill = (int)((total + 255) / 256), n_heads = (int)std::min<int64_t>(((int64_t)w.G * w.n + 15) / 16, 256 * 8);
+            if (!w.panel_on)
+                items_fill_kernel<0><<<(unsigned)n_fill, 256, 0, s>>>(pool, w, h, bm, bm, height, thr_floor, n_fill);
+            else if (w.long_heads)
+                items_fill_kernel<2><<<(unsigned)(n_fill + n_heads), 256, 0, s>>>(pool, w, h, bm, bm, height, thr_floor, n_fill);
+            else
+                items_fill_kernel<1><<<(unsigned)(n_fill + n_heads), 256, 0, s>>>(pool, w, h, bm, bm, height, thr_floor, n_fill);
         }
         if (w.panel_on)
             launch_similarity_panel(s, pool, w, h, height, thr_floor);
@@ -1191,7 +1203,7 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
     A.thr_floor = thr_floor;
     A.total_s = h.total_s;
     const unsigned grid = (unsigned)(((total + 7) / 8 + 1) * 8);     // the seats of both kinds of items, each rounded up
-    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt, w.whole};
+    const EarlyArgs early{w.early_nk, w.pairs, w.pair_head, w.n_pairs, w.pair_cap, w.open_cnt, w.whole, w.dense_cnt};
 #define KVF_SIM_LAUNCH(D, PF, EA)                                                                                          \
     similarity_ring_kernel<T, BIG, D, PF, EA><<<grid, BIG ? 512 : 256, 0, s>>>(                                                             \
         A, kpool, pool.inv_norm_k, w.set_ids, w.set_cnt, w.dyn_items, w.dyn_total, h.l_off, h.r_off, \

@@ -11,10 +11,10 @@ import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-T, D, LEFT, RIGHT, GROUPS = 16, 64, 600, 700, 60          # the smallest trees of this shape that stop products early
+T, D, LEFT, RIGHT, GROUPS = 16, 64, 1100, 1100, 21        # about the smallest trees of this shape that copies are made for
 
 
-def _spoil(K, kind, gen):
+def _spoil(K, kind, gen, thr=0.9):
     """K [n][r] float64, changed in place: blocks 0 .. 39 of the left set and as many of the right one, which are their near copies"""
     n, r = K.shape
     left, right = torch.arange(40, device=K.device), torch.arange(LEFT, LEFT + 40, device=K.device)
@@ -31,8 +31,8 @@ def _spoil(K, kind, gen):
         K[left, 64 * (1 + left % 6)[0]:] = 0.0
     elif kind == "scales":
         scale = torch.exp2(torch.arange(80, device=K.device, dtype=torch.float64).clamp(max=78)[:, None] - 39.0) / r ** 0.5      # norms of 2^-39 to 2^39
-    # near copies at cosines of 0.9 +- 0.02, on both sides of the threshold
-    c = torch.linspace(0.88, 0.92, 40, device=K.device, dtype=torch.float64)[:, None]
+    # near copies at cosines of thr +- 0.02, on both sides of the threshold
+    c = torch.linspace(thr - 0.02, thr + 0.02, 40, device=K.device, dtype=torch.float64)[:, None]
     u = K[left]
     noise -= (noise * u).sum(1, keepdim=True) / (u * u).sum(1, keepdim=True) * u
     if kind == "loud head":
@@ -73,14 +73,15 @@ def test_blocks_with_bad_copies(oracle, kind):
     assert per_group[pick, 0].tolist() == [int(r.stats[1]) for r in res] and 10 <= min(per_group[pick, 0]) and max(per_group[pick, 0]) <= 30
 
 
-@pytest.mark.parametrize("thr", [0.9, 0.95, 0.98])
+@pytest.mark.parametrize("thr", [0.7, 0.8, 0.9, 0.95, 0.98])
 def test_heads_of_every_length(oracle, thr):
-    """Two requests of four chunks: heads of other lengths, and blocks that a merge has rewritten, whose copies are made anew."""
-    groups, count = 40, np.full(8, 300, np.int32)
+    """Two requests of four chunks: heads of other lengths (at 0.7 long copies), made at the first height or a later one, and blocks that
+    a merge has rewritten, whose copies are made anew."""
+    groups, n, count = 12, 8 * 650, np.full(8, 650, np.int32)
     rng = np.random.default_rng(5)
-    src = np.where(rng.random(2400) < 0.3, rng.integers(0, 300, 2400), np.arange(2400) + 300).astype(np.int64)
-    start = np.arange(8, dtype=np.int32) * 300
-    rec = wl.Recipe("heads lengths", 13, groups, 1, 1, T, D, torch.bfloat16, thr, src, np.full(2400, 0.02, np.float32), 2700, start, count, count * T,
+    src = np.where(rng.random(n) < 0.1, rng.integers(0, 650, n), np.arange(n) + 650).astype(np.int64)
+    start = np.arange(8, dtype=np.int32) * 650
+    rec = wl.Recipe("heads lengths", 13, groups, 1, 1, T, D, torch.bfloat16, thr, src, np.full(n, 0.02, np.float32), n + 650, start, count, count * T,
                     start, count, np.array([0, 4, 8], np.int32))
     print("heads at", thr, flush=True)
     mat = wl.materialise(rec, DEV, phys_perm=True)
@@ -92,4 +93,63 @@ def test_heads_of_every_length(oracle, thr):
     gu.check_ambiguity(res, rec.name)
     for r, g in zip(res, pick):
         gu.compare_group(r, cache, g, False, rec.name)
-    assert min(int(r.stats[1]) for r in res) > 300
+    assert min(int(r.stats[1]) for r in res) > 100
+
+
+# left, right, thr, groups: ends of panels (512 and, at 0.7, 256 right blocks), stages (64, 32) and runs, panels of few columns
+SHAPES = [(1100, 1025, 0.9, 22), (1153, 1100, 0.9, 20), (2049, 770, 0.9, 16), (2100, 2049, 0.7, 6), (2113, 2180, 0.7, 6)]
+
+
+@pytest.mark.parametrize("left,right,thr,groups", SHAPES)
+@pytest.mark.parametrize("related", ["few", "diagonal"])
+def test_edges_of_panels(oracle, left, right, thr, groups, related):
+    """Few related pairs, or one for every right block along the diagonal: the list of open pairs then fills up and is emptied on the way."""
+    kb = gu.load_binding()
+    n = left + right
+    rng = np.random.default_rng(n)
+    src = np.full(n, -1, np.int64)
+    src[:left] = np.arange(left)
+    if related == "few":
+        src[left + rng.choice(right, right // 16, replace=False)] = rng.integers(0, left, right // 16)
+    else:
+        src[left:] = np.arange(right) % left
+    start, count = np.array([0, left], np.int32), np.array([left, right], np.int32)
+    rec = wl.Recipe("panel ends", 14, groups, 1, 1, T, D, torch.bfloat16, thr, src, np.where(np.arange(n) >= left, 0.05, 0.0).astype(np.float32), left, start,
+                    count, count * T, start, count, np.arange(3, dtype=np.int32))
+    print("panel ends", left, right, thr, related, flush=True)
+    mat = wl.materialise(rec, DEV, phys_perm=True)
+    for g in range(groups):                                   # zero blocks in both sets
+        mat["K"][g][mat["bt"][g][torch.tensor([3, left - 1, left + 5, n - 1], device=DEV).long()].long()] = 0
+    pick = [0, groups - 1]
+    host = ([wl.to_numpy_pool(mat["K"][g]) for g in pick], [wl.to_numpy_pool(mat["V"][g]) for g in pick],
+            [mat["bt"][g].cpu().numpy().copy() for g in pick])
+    cache, plan, stats, ctx = gu.gpu_fuse(rec, mat, cand_cap=64)
+    res = gu.oracle_fuse(oracle, rec, host)
+    gu.check_ambiguity(res, rec.name)
+    for r, g in zip(res, pick):
+        gu.compare_group(r, cache, g, False, rec.name)
+    _, open_pairs, room = kb.early_counts(ctx, plan)
+    assert room > 0 and open_pairs.sum() >= stats.fused       # (the ring kernel multiplies whole tiles along the diagonal, whose pairs are not left open)
+
+
+def test_height_between_that_is_not_the_panel_kernels(oracle):
+    """The sets of the second height are too unequal for big tiles; what the merges of the first two rewrite has new copies at the third."""
+    kb = gu.load_binding()
+    groups, count = 5, np.array([1100, 1100, 40, 40] * 2, np.int32)
+    n = int(count.sum())
+    start = (np.cumsum(count) - count).astype(np.int32)
+    rng = np.random.default_rng(8)
+    src = np.where(rng.random(n) < 0.08, rng.integers(0, 200, n), np.arange(n) + 200).astype(np.int64)
+    rec = wl.Recipe("panel between", 15, groups, 1, 1, T, D, torch.bfloat16, 0.9, src, np.full(n, 0.1, np.float32), n + 200, start, count, count * T,
+                    start, count, np.arange(9, dtype=np.int32))
+    print("panel between", flush=True)
+    mat = wl.materialise(rec, DEV, phys_perm=True)
+    pick = [0, groups - 1]
+    host = ([wl.to_numpy_pool(mat["K"][g]) for g in pick], [wl.to_numpy_pool(mat["V"][g]) for g in pick],
+            [mat["bt"][g].cpu().numpy().copy() for g in pick])
+    cache, plan, stats, ctx = gu.gpu_fuse(rec, mat, cand_cap=64)
+    res = gu.oracle_fuse(oracle, rec, host)
+    gu.check_ambiguity(res, rec.name)
+    for r, g in zip(res, pick):
+        gu.compare_group(r, cache, g, False, rec.name)
+    assert kb.early_counts(ctx, plan)[2] > 0 and min(int(r.stats[1]) for r in res) > 100
