@@ -129,7 +129,7 @@ __device__ __forceinline__ uint32_t ordered_bits(float x)
 // of them 12 or more.
 //
 // The three order statistics of a length are found bit by bit, by counting what lies below: every pair's rank against every other
-// took 30 us at two pairs a lane (11 at one), these counts take 14.
+// took 30 us at two pairs a lane (11 at one), these counts take 15 over all 32 bits and 12 over 20.
 //
 // head_steps (or null): likewise the steps of 64 elements of the head copies (heads.hip), `wide` slices each, whose test is wider by what the copies
 // miss, some 6.5 % of their share of a block; 0 where `steps_most` of them would not do, or for a group that is switched off.
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(1024) void choose_early_kernel(const float *__restr
         constexpr int rank[3] = {N * 16 / 100, N / 2, N * 84 / 100 + 1};
         uint32_t at[3] = {0u, 0u, 0u};           // the largest number that at most so many bounds lie below: the one of that rank
 #pragma unroll 4
-        for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1)
+        for (uint32_t bit = 0x80000000u; bit >= 0x1000u; bit >>= 1)          // (20 bits are 2^-11 of a bound, below the margin of the choice)
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 int below = 0;

@@ -11,8 +11,11 @@
 //
 // A copy of up to six steps of 64 elements has 320 bytes, one of up to twelve 640 (HeadShape): 18 or 36 pieces of 16 bytes of codes,
 // piece 2 m + h the m-th of what half h of a wavefront multiplies, 48 bytes for every two steps, in the order of an MFMA operand; then the
-// operands of the test (items.h) for the block on the left and on the right, eight bytes for either half.  A copy's place (slot) is its block's first position in the
-// set lists; set_slot follows the block when the lists are compacted.  Blocks that a merge has rewritten get their copy anew.
+// operands of the test (items.h) for the block on the left and on the right, eight bytes for either half.
+//
+// Copies of a group's blocks are made at the first height that the panel kernel takes the group at, of the blocks that are still there; a
+// copy's place (slot) is its block's position in the set lists then, and set_slot follows the block when the lists are compacted.  Blocks that
+// a merge has rewritten get their copy anew.
 #pragma once
 #include "items.h"
 
@@ -121,7 +124,8 @@ __device__ __forceinline__ void heads_of_targets(const PoolDesc &pool, const Wor
 
 // Likewise, before the products of a height: all blocks that are still there, of the groups that have no copies yet, and the targets of the
 // height before of those that have.
-// What bounds it: memory, 768 bytes read and 320 written per block (2.1 million blocks of 4 KiB: 0.55 ms, 4.1 TB/s), or twice that.
+// What bounds it: memory, 768 bytes read and 320 written per block (1.7 million blocks of 4 KiB: 0.5 ms, 3.7 TB/s), or twice that.  One position a
+// wavefront and trip, behind the five loads that find its block, took 0.8 ms.
 template <bool LONG>
 __device__ __forceinline__ void heads_of_height(const PoolDesc &pool, const WorkDesc &w, int height, float thr_floor, int wg, int n_wg)
 {

@@ -840,6 +840,7 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
             launch_choose_early(c->stream, p.pool, w, p.tab, floor_f);
         launch_tree_norms(c->stream, p.pool, w, p.tab);
         KVF_TRY(mark());
+        bool copies = false;                 // there may be some by now
         for (int hgt = 0; hgt < nh; ++hgt) {
             const HeightDesc &d = p.heights[hgt].dev;
             w.n_pairs = w.n_pairs_all + hgt;
@@ -852,7 +853,8 @@ int kvfuse_fuse_tree(kvfuse_ctx *ctx, kvfuse_plan *plan, double thr, double band
             KVF_TRY(mark());
             launch_merge(c->stream, p.pool, w, d, hgt);
             // (the next height sees to the rewritten blocks' copies, if it may be the panel kernel's)
-            if (panel && hgt + 1 < nh && p.heights[hgt + 1].dev.panel_run[w.long_heads] == 0)
+            copies |= panel && d.panel_run[w.long_heads] > 0;
+            if (copies && hgt + 1 < nh && p.heights[hgt + 1].dev.panel_run[w.long_heads] == 0)
                 launch_heads_of_targets(c->stream, p.pool, w, hgt, floor_f);
             KVF_TRY(mark());
         }

@@ -77,13 +77,19 @@ __device__ __forceinline__ bool panel_items_of_group(const WorkDesc &w, const He
     __shared__ int node0[256], node_cp[256], node_rows[256];
     __shared__ int first;
     const int tid = threadIdx.x, cols = panel_cols(w.long_heads), stage = panel_rows(w.long_heads), run_most = h.panel_run[w.long_heads];
+    // (nothing is summed up for a group whose heads are too long, or whose blocks repeat too much whatever the sum)
+    if (w.head_steps[g] == 0 || (prev.n_nodes > 0 && (double)w.dense_cnt[g] * kPanelDense > (double)prev.total_s)) {
+        if (tid == 0)
+            w.panel_on[g] = 0;
+        return false;
+    }
     // pairs that the tests of the height before left open, against the pairs there were
     double pairs = 0.0;
     __shared__ double red[4];
     for (int k = tid; k < prev.n_nodes; k += 256)
         pairs += (double)w.set_cnt[(int64_t)g * w.n_slots + prev.l_slot[k]] * (double)w.set_cnt[(int64_t)g * w.n_slots + prev.r_slot[k]];
     pairs = block_sum_256(pairs, red);
-    bool on = w.head_steps[g] > 0 && (!w.group_enable || w.group_enable[g]) &&
+    bool on = (!w.group_enable || w.group_enable[g]) &&
                     (prev.n_nodes == 0 ? w.whole[g] == 0
                                        : (double)w.open_cnt[g] * kPanelOpen <= pairs && (double)w.dense_cnt[g] * kPanelDense <= pairs) &&
                     (!h.panel_few || prev.n_nodes == 0 || w.whole[g]);

@@ -95,15 +95,29 @@ __global__ __launch_bounds__(256) void block_norms_kernel(const T *__restrict__ 
         // One sum in one order, with or without a tail, so that the norm's bits do not depend on the screens: a lane walks its
         // chunks upwards, and its tail is what the sum gains after the prefix.  The 2^-44 pays for the roundings of both
         // (fewer than 2^9 additions of at most half a unit of 2^-52), upwards, as the bound needs it.
+        // Four pieces are on their way at a time (one, behind whose arithmetic the next was asked for: 2.1 million blocks of 4 KiB, K and V,
+        // 2.98 ms; four 2.85, 6.0 TB/s).
+        constexpr int BATCH = 4;
         double sp = 0.0;
-        for (int c = lane; c < chunks; c += 64) {
-            double x[PER];
-            Elem<T>::widen(src[c], x);
+        for (int c0 = lane; c0 < chunks; c0 += 64 * BATCH) {
+            uint4 raw[BATCH];
 #pragma unroll
-            for (int i = 0; i < PER; ++i)
-                ss = fma(x[i], x[i], ss);
-            if (want_tail)
-                sp = c < prefix_chunks ? ss : sp;
+            for (int q = 0; q < BATCH; ++q)
+                raw[q] = src[min(c0 + 64 * q, chunks - 1)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q) {
+                const int c = c0 + 64 * q;
+                if (c >= chunks)             // (zeros leave the sum as it is)
+                    raw[q] = make_uint4(0u, 0u, 0u, 0u);
+                double x[PER];
+                Elem<T>::widen(raw[q], x);
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    ss = fma(x[i], x[i], ss);
+                if (want_tail)
+                    sp = c < prefix_chunks ? ss : sp;
+            }
         }
         if (want_tail)
             st = ss - sp + ss * 0x1p-44;

@@ -1182,7 +1182,7 @@ static void launch_ring(hipStream_t s, const PoolDesc &pool, const WorkDesc &w, 
             items_of_few_kernel<<<1, 1024, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, bm, bm);
         } else {
             items_count_kernel<<<w.G, 256, 0, s>>>(w, h, prev ? *prev : HeightDesc{}, height, bm, bm);
-            const int n_fill = (int)((total + 255) / 256), n_heads = (int)std::min<int64_t>(((int64_t)w.G * w.n + 15) / 16, 256 * 8);
+            const int n_fill = (int)((total + 255) / 256), n_heads = (int)std::min<int64_t>(((int64_t)w.G * w.n + 15) / 16, 256 * 5);       // (as many as the chip holds)
             if (!w.panel_on)
                 items_fill_kernel<0><<<(unsigned)n_fill, 256, 0, s>>>(pool, w, h, bm, bm, height, thr_floor, n_fill);
             else if (w.long_heads)
