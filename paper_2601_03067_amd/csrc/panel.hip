@@ -8,7 +8,7 @@
 // sign.  A workgroup has four wavefronts and a compute unit holds two, whose barriers, tests and first loads the other one's
 // products cover.
 //
-// What bounds it: power.  At the largest heights the MFMA units are busy 67 % of the cycles at 1.65 GHz; the same instructions on the
+// What bounds it: power.  At the largest heights the MFMA units are busy 64 to 67 % of the cycles at 1.65 to 1.8 GHz; the same instructions on the
 // same kind of data do not get beyond 1.4 GHz from registers (5.8 PFLOP/s against 9.9 at 2.4 GHz on zeros).  With heads of bfloat16 from the
 // pool (10 or 11 slices, 22 MFMAs of 32 x 32 x 16 instead of 6 of 32 x 32 x 64 and the test's) the largest node of 512 ragged requests (8
 // groups, some 45 000 blocks in each set) took 9.1 ms, now 3.2; the whole fusion of these 32.2 -> 18.6 ms, of 64 requests x 128 blocks in 256
