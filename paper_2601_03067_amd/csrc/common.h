@@ -75,7 +75,7 @@ struct Q8Desc {
     float *err, *scale, *alpha, *dir;
 };
 
-// Head copies (heads.hip) and the panel kernel (panel.hip), for heads of up to 384 and of up to 768 elements: most steps of 64 elements and
+// Head copies (heads.h) and the panel kernel (panel.hip), for heads of up to 384 and of up to 768 elements: most steps of 64 elements and
 // bytes of a copy; right blocks of a panel, left blocks of a stage.  A wavefront holds the copies of a quarter of a panel in registers, and
 // two stages fit half of a compute unit's LDS.
 template <bool LONG>
@@ -86,14 +86,14 @@ static inline __host__ __device__ int head_steps_most(int is_long) { return is_l
 static inline __host__ __device__ int head_bytes(int is_long) { return is_long ? HeadShape<true>::bytes : HeadShape<false>::bytes; }
 static inline __host__ __device__ int panel_cols(int is_long) { return is_long ? HeadShape<true>::cols : HeadShape<false>::cols; }
 static inline __host__ __device__ int panel_rows(int is_long) { return is_long ? HeadShape<true>::rows : HeadShape<false>::rows; }
-// Most stages of an item; the share of pairs (one in so many) left open at the height before, and of related ones in tiles that the ring kernel
-// multiplied whole, up to which the panel kernel takes a group; the
-// mark of a pair (in its row) whose product starts at the first element (column -1: no pair).
+// Panel kernel: most stages of an item; the share of pairs (one in so many) left open at the height before, and of related ones in tiles that
+// the ring kernel multiplied whole there, up to which it takes a group.
+constexpr int kPanelRun = 32, kPanelOpen = 256, kPanelDense = 4096;
 // Pairs to a block, of the heights that are left, from which copies pay: making them costs 0.3 ns a block, long ones twice that, and a tile of
 // 256 x 256 pairs some 30 ns less than in the ring kernel, both of the whole chip (one prompt of 16 chunks of 128 blocks at 0.85, 64 groups, 900
 // pairs a block: 1364 us without, 1433 with long copies; 256 requests of popular blocks, at the last height only, 750: 16.35 and 16.7 ms).
 constexpr double kHeadPairs = 512.0;       // (twice that for long ones)
-constexpr int kPanelRun = 32, kPanelOpen = 256, kPanelDense = 4096, kPairWhole = (int)0x80000000;
+constexpr int kPairWhole = (int)0x80000000;       // mark of a pair (in its row) whose product starts at the first element; column -1: no pair
 constexpr int kWholeTile = 128;       // open pairs of a panel item beyond which the ring kernel is taken to have multiplied a tile whole
 
 // Tree calls on tiny groups (tiny.hip): most table entries, stored blocks and tree nodes of a group, bytes of a block, groups.
